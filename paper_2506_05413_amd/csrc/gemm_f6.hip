@@ -330,13 +330,19 @@ __device__ __forceinline__ void f6_tiles(
 
 constexpr int f6_lds_bytes(int BM, int BN, int SLOTS) { return SLOTS * (BM + BN) / 8 * BLK + 2 * (BM + BN) * 4 + 256; }   // ring, two scale areas, slack
 
+// MFMA column tiles the epilogue stages at a time: a wave's whole width where the staging of all waves fits one slot
+constexpr int f6_staged_columns(int BM, int BN, int waves, int WGN)
+{
+    return waves * 32 * (BN / WGN * 2 + 16) <= (BM + BN) / 8 * BLK ? BN / WGN / 32 : 1;
+}
+
 template <int BM, int BN, int WGM, int WGN, int SLOTS, int WG_PER_CU>
 __global__ __launch_bounds__(WGM * WGN * 64, WGM * WGN * WG_PER_CU / 4) void gemm_f6_kernel(
     const uint8_t *__restrict__ X6, const float *__restrict__ xs, const uint8_t *__restrict__ W6,
     const float *__restrict__ ws, int M, int N, int K, void *__restrict__ Yv, int64_t ldy, int out_i32,
     int tiles_m, int tiles_n, int xcd_m)
 {
-    f6_tiles<BM, BN, WGM, WGN, SLOTS, BN / WGN / 32>(X6, xs, W6, ws, M, N, K, Yv, ldy, out_i32, tiles_m, tiles_n, xcd_m, 0,
+    f6_tiles<BM, BN, WGM, WGN, SLOTS, f6_staged_columns(BM, BN, WGM * WGN, WGN)>(X6, xs, W6, ws, M, N, K, Yv, ldy, out_i32, tiles_m, tiles_n, xcd_m, 0,
                                                      (int)blockIdx.x, (int)gridDim.x, tiles_m * tiles_n);
 }
 
@@ -456,31 +462,61 @@ hipError_t launch_pack_f6(const uint8_t *Q4, int64_t rows, int64_t K, uint8_t *T
 hipError_t launch_gemm_f6(const uint8_t *X6, const float *xs, const uint8_t *W6, const float *ws, int64_t M, int64_t N,
                           int64_t K, void *Y, int64_t ldy, int out_i32, hipStream_t st, const void *warm, size_t warm_bytes)
 {
-    // the tile knob selects a tile configuration by number; not set = heuristic
-    int variant = 0;
-    if (int64_t t; tuned(kTuneGemmTile, t)) variant = (int)t;
-    switch (variant) {
-        case 61: return launch_f6<256, 256, 2, 4, 3, 1>(X6, xs, W6, ws, M, N, K, Y, ldy, out_i32, st);
-        case 63: return launch_f6<256, 128, 2, 2, 2, 2>(X6, xs, W6, ws, M, N, K, Y, ldy, out_i32, st);
-        case 64: return launch_f6<256, 256, 2, 4, 2, 1>(X6, xs, W6, ws, M, N, K, Y, ldy, out_i32, st);
-        case 65: return launch_f6<256, 128, 4, 2, 4, 1, true>(X6, xs, W6, ws, M, N, K, Y, ldy, out_i32, st, warm, warm_bytes);
-        case 66: return launch_f6<256, 128, 4, 2, 3, 1>(X6, xs, W6, ws, M, N, K, Y, ldy, out_i32, st);
-        default: break;
-    }
-    // 256 x 256 tiles (eight waves of 128 x 64) run ~15 % faster per output than 256 x 128 tiles (eight waves of
-    // 64 x 64: more LDS traffic per MFMA), so the small tile is taken only where it saves whole rounds:
-    // measured at M = 2048, K = 4096: N = 14336 63.8 us against 77.6 us; N = 4096 (128 big tiles on 256 CUs)
-    // 28.9 us against 24.3 us.  Four-wave workgroups (one wave per SIMD) lost everywhere.  N = 14336 at M = 2048 is
-    // 448 big tiles = 1.75 rounds; a launch mixing one round of 256-wide with one round of 192-wide tiles (every CU
-    // then works 1.75 tile times) was built and measured: 63.3 us against 61.9 us -- the second, three-quarters
-    // filled round of the plain schedule already runs faster (fewer CUs draw power and share L2), so it was dropped.
+    // What a launch costs, by configuration: with t tiles on c compute units, r = ceil(t / c) rounds and n = K / 128
+    // stages,   fixed + per_round r + n (stage_round r + stage_tile t / c)   microseconds,
+    // fitted to 240 shapes (M 8 .. 5000, N 1024 .. 28672, K 2048 .. 14336; weights rotating over three copies).  On
+    // shapes left out of the fit the cheapest configuration by this rule is 0.9 % slower on average (29 % at worst)
+    // than the fastest one of all; the rule that knew 256 x 256 and 256 x 128 tiles only was 1.7 times slower, mostly
+    // below ~1000 rows, where those tiles leave CUs idle (37 x 6144 x 4096: 15.8 -> 6.1 us, 128 x 4096 x 14336:
+    // 40.8 -> 14.8 us, 521 x 4096 x 14336: 44.7 -> 35.4 us, 2869 x 8192 x 8192: 110 -> 88 us).  A stage costs what the
+    // vector-memory path of a CU takes for its operands, 80 - 120 GB/s whatever the shape of the tile.
+    struct Config { int id, bm, bn; float fixed, per_round, stage_round, stage_tile; };
+    static constexpr Config configs[] = {
+        {61, 256, 256, 0.f, 5.71f, .419f, .435f},     // eight waves of 128 x 64
+        {72, 192, 256, .62f, 4.11f, .385f, .320f},    // eight waves of 96 x 64
+        {65, 256, 128, .97f, 3.29f, .316f, .225f},    // eight waves of 64 x 64, a ninth for the cache-warming hint
+        {68, 128, 256, 1.93f, 2.62f, .332f, .240f},   // eight waves of 64 x 64
+        {67, 128, 128, 4.24f, 0.f, .250f, .099f},     // four waves of 64 x 64, two workgroups per CU
+        {69, 128, 64, 3.90f, 0.f, .182f, .062f},      // four waves of 64 x 32, two workgroups per CU
+        // operands straight into registers, K split over eight waves (gemm_f6_stream.hip)
+        {64064, 64, 64, 2.24f, 1.61f, .099f, .069f},
+        {48064, 48, 64, 2.00f, 1.46f, .101f, .042f},
+        {48032, 48, 32, 2.80f, 0.f, .069f, .027f},
+        {32064, 32, 64, 2.97f, 0.f, .090f, .027f},
+        {32032, 32, 32, 2.89f, 0.f, .053f, .024f},
+        {16032, 16, 32, 2.80f, 0.f, .040f, .018f},
+        {16016, 16, 16, 2.70f, .22f, .019f, .016f},
+    };
     const int64_t cus = compute_units();
-    const int64_t tm = (M + 255) / 256;
-    auto rounds = [&](int64_t tiles) { return (tiles + cus - 1) / cus; };
-    const int64_t cost_big = rounds(tm * ((N + 255) / 256)) * 256 * 256 * 85;
-    const int64_t cost_small = rounds(tm * ((N + 127) / 128)) * 256 * 128 * 100;
-    if (cost_big <= cost_small) return launch_f6<256, 256, 2, 4, 3, 1>(X6, xs, W6, ws, M, N, K, Y, ldy, out_i32, st);
-    return launch_f6<256, 128, 4, 2, 4, 1, true>(X6, xs, W6, ws, M, N, K, Y, ldy, out_i32, st, warm, warm_bytes);
+    auto cost = [&](const Config &c) {
+        const int64_t tiles = ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
+        const float r = (float)((tiles + cus - 1) / cus), n = (float)(K / 128);
+        return c.fixed + c.per_round * r + n * (c.stage_round * r + c.stage_tile * (float)tiles / (float)cus);
+    };
+    const Config *best = &configs[0];
+    float best_cost = cost(configs[0]), cost65 = 0.f;
+    for (const Config &c : configs) {
+        const float v = cost(c);
+        if (v < best_cost) { best = &c; best_cost = v; }
+        if (c.id == 65) cost65 = v;
+    }
+    int id = best->id;
+    // the hint is worth several microseconds to the next launch (44 MB read ahead save it 4 us of 67)
+    if (warm && warm_bytes >= ((size_t)1 << 20) && cost65 <= 1.15f * best_cost) id = 65;
+    // the tile knob selects a configuration by number; not set or unknown = the rule above
+    if (int64_t t; tuned(kTuneGemmTile, t)) {
+        for (const Config &c : configs)
+            if (c.id == t) id = (int)t;
+    }
+    switch (id) {
+        case 61: return launch_f6<256, 256, 2, 4, 3, 1>(X6, xs, W6, ws, M, N, K, Y, ldy, out_i32, st);
+        case 65: return launch_f6<256, 128, 4, 2, 4, 1, true>(X6, xs, W6, ws, M, N, K, Y, ldy, out_i32, st, warm, warm_bytes);
+        case 67: return launch_f6<128, 128, 2, 2, 3, 2>(X6, xs, W6, ws, M, N, K, Y, ldy, out_i32, st);
+        case 68: return launch_f6<128, 256, 2, 4, 4, 1>(X6, xs, W6, ws, M, N, K, Y, ldy, out_i32, st);
+        case 69: return launch_f6<128, 64, 2, 2, 4, 2>(X6, xs, W6, ws, M, N, K, Y, ldy, out_i32, st);
+        case 72: return launch_f6<192, 256, 2, 4, 3, 1>(X6, xs, W6, ws, M, N, K, Y, ldy, out_i32, st);
+        default: return launch_gemm_f6_stream(X6, xs, W6, ws, M, N, K, Y, ldy, out_i32, st, id / 1000, id % 1000);
+    }
 }
 
 }  // namespace sr

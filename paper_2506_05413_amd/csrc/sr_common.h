@@ -147,6 +147,10 @@ hipError_t launch_gemm_f6(const uint8_t *X6, const float *xs, const uint8_t *W6,
                           int64_t M, int64_t N, int64_t K, void *Y, int64_t ldy, int out_i32,
                           hipStream_t st, const void *warm = nullptr, size_t warm_bytes = 0);
 
+// the same for few rows: bm x bn outputs per workgroup, operands straight into registers (see gemm_f6_stream.hip)
+hipError_t launch_gemm_f6_stream(const uint8_t *X6, const float *xs, const uint8_t *W6, const float *ws, int64_t M,
+                                 int64_t N, int64_t K, void *Y, int64_t ldy, int out_i32, hipStream_t st, int bm, int bn);
+
 hipError_t launch_gemm_decode(const uint8_t *Xq, const float *xs, const uint8_t *Wq, const float *ws,
                               int64_t M, int64_t N, int64_t K, void *Y, int64_t ldy, int out_i32,
                               hipStream_t st);
