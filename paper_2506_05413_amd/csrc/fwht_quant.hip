@@ -126,6 +126,117 @@ __global__ __launch_bounds__(NT, STREAM ? 2 * NT / 256 : 1) void fwht_quant_kern
 }
 
 // ------------------------------------------------------------------------------------------
+// Clipping-ratio search over a rotated row in LDS (`row`, maximum `amax` > 0), by a workgroup of NT threads:
+//     err_i = sum_j (y_j - Delta_i * code_i(y_j))^2,   Delta_i = grid[i] * amax / 7
+// for every ratio; returns the ratio with the smallest error (first minimum in grid order) to every thread.
+//
+// Bound by vector-ALU issue: what counts is the number and kind of instructions per value and ratio.  On this chip
+// fp32 add / mul / fma with VGPR operands issue in ~2.7 cycles, rint / min / max / med3, conversions, and anything with
+// an SGPR or DPP operand in ~4.6 (measured per instruction).  So
+//  * a LANE owns a ratio (Delta_i, 1/Delta_i in its registers) and the values come by broadcast LDS reads: no scalar
+//    operands, and no reduction over lanes per ratio.  64 / n subsets of lanes take different groups of 8 values
+//    (21 ratios: 3 subsets, 63 lanes at work);
+//  * a value costs five of the cheap instructions: clamp to [0, 1] of (y / Delta + 8) / 15 (the clamp is an output
+//    modifier of the fma), times 15 plus 1.5 * 2^23 (rounds to an integer), minus 1.5 * 2^23 + 8 (the code), residual,
+//    square-accumulate.  The scaling by 15 moves a rounding boundary by less than 1e-6 code units, where both codes
+//    give the same error; the codes themselves are taken from the chosen ratio by the usual quantiser.
+// Eight terms are summed in fp32, those sums in fp64.  4096 x 14336, 21 ratios, whole kernel: 288 -> 190 us (five
+// instructions of 4.6 cycles per value and a six-step lane reduction per ratio before).
+// ------------------------------------------------------------------------------------------
+template <int K, int NT>
+__device__ __forceinline__ float search_ratio(const float *row, const float amax, const float *grid, const int n, const int t)
+{
+    constexpr int NW = NT / 64, G = K / 8, MAX_SUB = NW <= 4 ? 8 : 4;
+    __shared__ double err_w[NW * MAX_SUB][kMaxClipGrid];
+    __shared__ float ratios[kMaxClipGrid];
+    if (t == 0) {
+#pragma unroll
+        for (int i = 0; i < kMaxClipGrid; ++i) ratios[i] = grid[i];
+    }
+    __syncthreads();
+    const int lane = t & 63, subs = 64 / n < MAX_SUB ? 64 / n : MAX_SUB;
+    const int sub = lane / n, i = lane - sub * n;        // lanes of subset `subs` and above idle along with subset 0
+    const int units = NW * subs, unit = (t >> 6) * subs + (sub < subs ? sub : 0);
+    const float d = (ratios[i] * amax) / 7.f, inv15 = 1.f / (15.f * d);
+    constexpr float magic = 12582912.f;                  // 1.5 * 2^23
+    double acc = 0.0;
+    auto add_group = [&](const float4 &a, const float4 &b) {
+        const float y[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+        float u[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) u[e] = __builtin_amdgcn_fmed3f(fmaf(y[e], inv15, 8.f / 15.f), 0.f, 1.f);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) u[e] = fmaf(u[e], 15.f, magic);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) u[e] = fmaf(-d, u[e] - (magic + 8.f), y[e]);
+        float even = 0.f, odd = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; e += 2) {
+            even = fmaf(u[e], u[e], even);
+            odd = fmaf(u[e + 1], u[e + 1], odd);
+        }
+        acc += (double)(even + odd);
+    };
+    auto read = [&](int g, float4 &a, float4 &b) {
+        const float *src = row + pad(8 * g);
+        a = *reinterpret_cast<const float4 *>(src);
+        b = *reinterpret_cast<const float4 *>(src + 4);
+    };
+    float4 a0, b0, a1, b1;
+    int g = unit;                                        // a unit's groups: unit, unit + units, ..
+    read(g < G ? g : 0, a0, b0);
+    for (; g + units < G; g += 2 * units) {              // the group after the one at work is on its way
+        read(g + units, a1, b1);
+        add_group(a0, b0);
+        read(g + 2 * units < G ? g + 2 * units : 0, a0, b0);
+        add_group(a1, b1);
+    }
+    if (g < G) add_group(a0, b0);
+    if (sub < subs) err_w[unit][i] = acc;
+    __syncthreads();
+    if (t < n) {
+        double e = err_w[0][t];
+        for (int u = 1; u < units; ++u) e += err_w[u][t];
+        err_w[0][t] = e;
+    }
+    __syncthreads();
+    double best = err_w[0][0];
+    int best_i = 0;
+    for (int k = 1; k < n; ++k) {                        // every thread takes the same decision
+        const double e = err_w[0][k];
+        if (e < best) { best = e; best_i = k; }
+    }
+    return ratios[best_i];
+}
+
+// The fold of a weight with the search, full transform: one workgroup per output channel.
+template <int K, int NT>
+__global__ __launch_bounds__(NT) void fwht_quant_search_kernel(const __half *__restrict__ X, int64_t ldx,
+                                                               const float *__restrict__ pre, float post_scale,
+                                                               uint8_t *__restrict__ Q, float *__restrict__ scale_out,
+                                                               const RowExtras ex)
+{
+    extern __shared__ float row[];
+    __shared__ float red[NT / 64];
+    const int t = threadIdx.x;
+    const int64_t m = blockIdx.x;
+    const float amax = rotate_row_absmax<K, NT>(X + m * ldx, pre, row, red, t);
+    const float clip = amax != 0.f ? search_ratio<K, NT>(row, amax, ex.grid, ex.n_grid, t) : ex.grid[0];
+    if (ex.ratio_out && t == 0) ex.ratio_out[m] = clip;
+    const float delta = (amax == 0.f) ? 1.f : (clip * amax) / 7.f;
+    const float inv_delta = 1.f / delta;
+    if (t == 0) scale_out[m] = (amax == 0.f) ? 1.f : delta * post_scale;
+    uint32_t *q = reinterpret_cast<uint32_t *>(Q + m * (int64_t)(K / 2));
+    for (int c = t; c < K / 8; c += NT) {
+        const float *src = row + pad(8 * c);
+        const float4 a = *reinterpret_cast<const float4 *>(src);
+        const float4 b = *reinterpret_cast<const float4 *>(src + 4);
+        const float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+        q[c] = quant_pack8(v, inv_delta);
+    }
+}
+
+// ------------------------------------------------------------------------------------------
 // Extended row kernel: the same rotation + quantiser with three optional extras
 //   gate       x = silu(gate) * X in fp32 before smoothing (the down-projection input of the gated
 //              FFN, paper Fig. 2: sigma(gate) (.) up, then 1/s, Hadamard, quantiser)
@@ -147,7 +258,6 @@ __global__ __launch_bounds__(NT) void fwht_quant_ex_kernel(const __half *__restr
 
     extern __shared__ float row[];
     __shared__ float red[NW];
-    __shared__ double err_w[kMaxClipGrid][NW];
 
     const int t = threadIdx.x;
     int64_t m = blockIdx.x;
@@ -224,42 +334,8 @@ __global__ __launch_bounds__(NT) void fwht_quant_ex_kernel(const __half *__restr
 #pragma unroll
     for (int w = 1; w < NW; ++w) amax = fmaxf(amax, red[w]);
 
-    // ---- clipping-ratio search: err_r = sum_j (y_j - Delta_r * code_r(y_j))^2 for every ratio -------
-    if (ex.n_grid > 0 && amax != 0.f) {
-        for (int i = 0; i < ex.n_grid; ++i) {
-            const float d = (ex.grid[i] * amax) / 7.f;
-            const float inv = 1.f / d;
-            double acc = 0.0;
-            for (int c = t; c < K / 8; c += NT) {
-                const float *src = row + pad(8 * c);
-                const float4 a = *reinterpret_cast<const float4 *>(src);
-                const float4 b = *reinterpret_cast<const float4 *>(src + 4);
-                const float y[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-                float part = 0.f;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const float code = fminf(fmaxf(rintf(y[e] * inv), -8.f), 7.f);
-                    const float r = fmaf(-d, code, y[e]);
-                    part = fmaf(r, r, part);
-                }
-                acc += (double)part;
-            }
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off, 64);
-            if ((t & 63) == 0) err_w[i][t >> 6] = acc;
-        }
-        __syncthreads();
-        double best = 0.0;
-        int best_i = 0;
-        for (int i = 0; i < ex.n_grid; ++i) {               // every thread takes the same decision
-            double e = 0.0;
-#pragma unroll
-            for (int w = 0; w < NW; ++w) e += err_w[i][w];
-            if (i == 0 || e < best) { best = e; best_i = i; }
-        }
-        clip = ex.grid[best_i];
-    } else if (ex.n_grid > 0) {
-        clip = ex.grid[0];
+    if constexpr (!F6) {                                 // (the search belongs to the weight fold, which writes nibbles)
+        if (ex.n_grid > 0) clip = amax != 0.f ? search_ratio<K, NT>(row, amax, ex.grid, ex.n_grid, t) : ex.grid[0];
     }
     if (ex.ratio_out && t == 0) ex.ratio_out[m] = clip;
 
@@ -742,6 +818,22 @@ hipError_t launch_one_ex(const void *X, int64_t rows, int64_t ldx, const float *
     constexpr int groups = K / 16;
     constexpr int NT = groups >= 256 ? 256 : (groups >= 128 ? 128 : 64);
     constexpr size_t lds = sizeof(float) * padded_len(K);
+    if constexpr (!F6) {
+        if (ex.n_grid > 0 && !ex.gate && (ex.had_mask == 0xFFFFFFFFu || !is_pow2(K))) {
+            // threads per row as in launch_one (many rows), but never fewer than 256: workgroups of one or two waves
+            // run the search at a third of the speed (2048 x 4096, 21 ratios: 35 us with 256 threads, 95 with 128)
+            constexpr int NTS = K == 8192 ? 512 : (K == 16384 || K == 28672 || K == 32768) ? 1024 : 256;
+            auto kern = fwht_quant_search_kernel<K, NTS>;
+            if (lds > 40 * 1024) {
+                hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
+                                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+                if (e != hipSuccess) return e;
+            }
+            hipLaunchKernelGGL(kern, dim3((unsigned)rows), dim3(NTS), lds, st, static_cast<const __half *>(X), ldx, pre,
+                               post_scale, Q, scale_out, ex);
+            return hipGetLastError();
+        }
+    }
     auto kern = fwht_quant_ex_kernel<K, NT, F6>;
     if (lds > 40 * 1024) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
@@ -868,6 +960,7 @@ hipError_t launch_fwht_quant_ex(const void *X, int64_t rows, int64_t K, int64_t 
         }
 #undef SR_CASE
     }
+    if (f6 && ex.n_grid > 0) return hipErrorInvalidValue;
     if (f6) {
 #define SR_CASE(KK) case KK: return launch_one_ex<KK, true>(X, rows, ldx, pre, clip, post_scale, Q, scale_out, ex, st);
         switch (K) {                                    // K % 128 == 0
