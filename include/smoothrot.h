@@ -298,7 +298,7 @@ SR_API int sr_w4a4_linear_decode(const void *X_f16, int64_t M, int64_t K, int64_
  * matrix instruction reads without any unpacking:
  *
  *   a code matrix [rows, K] (K % 128 == 0; rows padded to a multiple of 8 -- the padding rows may hold
- *   anything: sr_pack_f6_tiles writes zero codes there, sr_fwht_quant_act_f6 leaves them unwritten, and
+ *   anything: sr_pack_f6_tiles and the activation quantisers write zero codes there, and
  *   the GEMM multiplies them but never stores their outputs; every 6-bit pattern is a finite number) is
  *   cut into blocks of 8 rows x 128 codes; block (R, C) is 768 bytes at ((C * rows/8) + R) * 768
  *   (all row blocks of one 128-code chunk are contiguous);
@@ -326,7 +326,7 @@ SR_API int sr_pack_f6_tiles(const uint8_t *Q4, int64_t rows, int64_t K, uint8_t 
  * may differ from the one sr_fwht_quant_act packs where y / Delta sits on a rounding boundary
  * (both are within the rounding freedom of the fp32 rotation).
  *   X6   out, sr_f6_tiles_bytes(M, K) bytes, 16-byte aligned; the rows that pad the last block of
- *        8 are left unwritten (the GEMM never stores their outputs)
+ *        8 get zero codes (the GEMM never stores their outputs)
  *   K    a supported Hadamard order that is a multiple of 128
  */
 SR_API int sr_fwht_quant_act_f6(const void *X_f16, int64_t M, int64_t K, int64_t ldx,

@@ -1,9 +1,10 @@
-"""ctypes binding of libsmoothrot.so -- argument marshalling only.
+"""Binding of libsmoothrot.so -- argument marshalling only.
 
 Function names and argument order follow include/smoothrot.h.  torch supplies
 device memory and the current stream; every step of the computation runs in the
-library's HIP kernels.  There is no fallback: if the shared library is missing
-or a call fails, an exception is raised.
+library's HIP kernels.  The per-token calls marshal their tensors in native code
+(csrc/marshal.cpp), the offline ones through ctypes.  There is no fallback: if a
+shared library is missing or a call fails, an exception is raised.
 """
 from __future__ import annotations
 
@@ -85,12 +86,33 @@ def raw() -> ctypes.CDLL:
     return _lib
 
 
+_native = None
+
+
+def _marshal():
+    """The native marshalling module (loads it, and the library, on first use)."""
+    global _native
+    if _native is None:
+        raw()
+        try:
+            from . import _marshal as module
+        except ImportError as e:
+            raise ImportError("_marshal.so is not built: run `python -m paper_2506_05413_amd.build` "
+                              "(there is no fallback path)") from e
+        _native = module
+    return _native
+
+
 def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
 def _stream():
-    return torch.cuda.current_stream().cuda_stream
+    return (_native or _marshal()).current_stream()
+
+
+def _refused(status: int, where: str):
+    raise SmoothRotError(status, where)
 
 
 def _check(status: int, where: str):
@@ -176,62 +198,26 @@ def sr_fold_smooth_rotate_quant_noalloc(W, act_absmax, alpha: float, w_clip, Wq,
 
 def sr_fwht_quant_act(X, inv_s, clip: float = 0.9, Xq=None, x_scale=None):
     """X fp16 [M, K] -> (Xq uint8 [M, K/2], x_scale fp32 [M])."""
-    _dev(X, torch.float16, "X")
-    M, K = X.shape
-    Xq = torch.empty((M, K // 2), dtype=torch.uint8, device=X.device) if Xq is None else Xq
-    x_scale = torch.empty(M, dtype=torch.float32, device=X.device) if x_scale is None else x_scale
-    ldx = X.stride(0) if M > 1 else K
-    _check(raw().sr_fwht_quant_act(_ptr(X), M, K, ldx, _ptr(inv_s), clip, _ptr(Xq), _ptr(x_scale), _stream()),
-           "sr_fwht_quant_act")
-    return Xq, x_scale
+    out = (_native or _marshal()).fwht_quant_act(X, inv_s, clip, Xq, x_scale)
+    return out if type(out) is tuple else _refused(out, "sr_fwht_quant_act")
 
 
 def sr_w4a4_gemm(Xq, x_scale, Wq, w_scale, out_dtype: int = SR_F16, Y=None, workspace=None):
     """Xq uint8 [M, K/2], Wq uint8 [N, K/2] -> Y [M, N] fp16 (dequantised) or int32 (accumulators)."""
-    _dev(Xq, torch.uint8, "Xq"); _dev(Wq, torch.uint8, "Wq")
-    M, Kb = Xq.shape
-    N = Wq.shape[0]
-    if Wq.shape[1] != Kb:
-        raise ValueError("Xq and Wq disagree on K")
-    if Y is None:
-        Y = torch.empty((M, N), dtype=torch.float16 if out_dtype == SR_F16 else torch.int32, device=Xq.device)
-    ldy = Y.stride(0) if M > 1 else N
-    if workspace is None:
-        need = sr_gemm_workspace_bytes(M, N, 2 * Kb)
-        if need:
-            workspace = torch.empty(need, dtype=torch.uint8, device=Xq.device)
-    _check(raw().sr_w4a4_gemm(_ptr(Xq), _ptr(x_scale), _ptr(Wq), _ptr(w_scale), M, N, 2 * Kb, _ptr(Y), ldy,
-                              out_dtype, _ptr(workspace), 0 if workspace is None else workspace.numel(),
-                              _stream()),
-           "sr_w4a4_gemm")
-    return Y
+    out = (_native or _marshal()).w4a4_gemm(Xq, x_scale, Wq, w_scale, out_dtype, Y, workspace)
+    return _refused(out, "sr_w4a4_gemm") if type(out) is int else out
 
 
 def sr_swiglu_fwht_quant_act(G, U, inv_s, clip: float = 0.9, Xq=None, x_scale=None):
     """G, U fp16 [M, K] -> codes and scales of silu(G) * U (smoothed, rotated, quantised)."""
-    _dev(G, torch.float16, "G"); _dev(U, torch.float16, "U")
-    M, K = U.shape
-    if tuple(G.shape) != (M, K):
-        raise ValueError("G and U must have the same shape")
-    Xq = torch.empty((M, K // 2), dtype=torch.uint8, device=U.device) if Xq is None else Xq
-    x_scale = torch.empty(M, dtype=torch.float32, device=U.device) if x_scale is None else x_scale
-    ldg = G.stride(0) if M > 1 else K
-    ldu = U.stride(0) if M > 1 else K
-    _check(raw().sr_swiglu_fwht_quant_act(_ptr(G), _ptr(U), M, K, ldg, ldu, _ptr(inv_s), clip, _ptr(Xq),
-                                          _ptr(x_scale), _stream()), "sr_swiglu_fwht_quant_act")
-    return Xq, x_scale
+    out = (_native or _marshal()).swiglu_fwht_quant_act(G, U, inv_s, clip, Xq, x_scale, False)
+    return out if type(out) is tuple else _refused(out, "sr_swiglu_fwht_quant_act")
 
 
 def sr_fwht_quant_act_heads(X, n_heads: int, across: bool, inv_s, clip: float = 0.9, Xq=None, x_scale=None):
     """X fp16 [M, K] -> codes and scales after the head-wise Hadamard transform."""
-    _dev(X, torch.float16, "X")
-    M, K = X.shape
-    Xq = torch.empty((M, K // 2), dtype=torch.uint8, device=X.device) if Xq is None else Xq
-    x_scale = torch.empty(M, dtype=torch.float32, device=X.device) if x_scale is None else x_scale
-    ldx = X.stride(0) if M > 1 else K
-    _check(raw().sr_fwht_quant_act_heads(_ptr(X), M, K, ldx, n_heads, int(bool(across)), _ptr(inv_s), clip,
-                                         _ptr(Xq), _ptr(x_scale), _stream()), "sr_fwht_quant_act_heads")
-    return Xq, x_scale
+    out = (_native or _marshal()).fwht_quant_act_heads(X, n_heads, across, inv_s, clip, Xq, x_scale)
+    return out if type(out) is tuple else _refused(out, "sr_fwht_quant_act_heads")
 
 
 def sr_fold_smooth_rotate_quant_ex(W, act_absmax, alpha: float, n_heads: int = 0, across: bool = False,
@@ -257,16 +243,8 @@ def sr_fold_smooth_rotate_quant_ex(W, act_absmax, alpha: float, n_heads: int = 0
 
 def sr_kv_quant_asym(X, group: int = 128, clip: float = 0.95, Q=None, scale=None, zero=None):
     """X fp16 [rows, D] -> (Q uint8 [rows, D/2], scale fp32 [rows, D/group], zero fp32 [rows, D/group])."""
-    _dev(X, torch.float16, "X")
-    rows, D = X.shape
-    ng = max(D // group, 1)
-    Q = torch.empty((rows, D // 2), dtype=torch.uint8, device=X.device) if Q is None else Q
-    scale = torch.empty((rows, ng), dtype=torch.float32, device=X.device) if scale is None else scale
-    zero = torch.empty((rows, ng), dtype=torch.float32, device=X.device) if zero is None else zero
-    ldx = X.stride(0) if rows > 1 else D
-    _check(raw().sr_kv_quant_asym(_ptr(X), rows, D, ldx, group, clip, _ptr(Q), _ptr(scale), _ptr(zero), _stream()),
-           "sr_kv_quant_asym")
-    return Q, scale, zero
+    out = (_native or _marshal()).kv_quant_asym(X, group, clip, Q, scale, zero)
+    return out if type(out) is tuple else _refused(out, "sr_kv_quant_asym")
 
 
 def sr_linear_decode_workspace_bytes(M: int, K: int) -> int:
@@ -278,21 +256,8 @@ def sr_w4a4_linear_decode(X, inv_s, Wq, w_scale, clip: float = 0.9, Y=None, Xq_o
     """X fp16 [M <= 16, K], Wq uint8 [N, K/2] -> Y fp16 [M, N] in one launch (rotate, quantise, multiply).
     workspace: a uint8 device tensor of sr_linear_decode_workspace_bytes(M, K) bytes (reuse it from call to call);
     one is made per call if none is given."""
-    _dev(X, torch.float16, "X"); _dev(Wq, torch.uint8, "Wq")
-    M, K = X.shape
-    N = Wq.shape[0]
-    if Wq.shape[1] * 2 != K:
-        raise ValueError("X and Wq disagree on K")
-    Y = torch.empty((M, N), dtype=torch.float16, device=X.device) if Y is None else Y
-    ldx = X.stride(0) if M > 1 else K
-    ldy = Y.stride(0) if M > 1 else N
-    need = sr_linear_decode_workspace_bytes(M, K)
-    if workspace is None and need:
-        workspace = torch.empty(need, dtype=torch.uint8, device=X.device)
-    _check(raw().sr_w4a4_linear_decode(_ptr(X), M, K, ldx, _ptr(inv_s), clip, _ptr(Wq), _ptr(w_scale), N, _ptr(Y),
-                                       ldy, _ptr(Xq_out), _ptr(x_scale_out), _ptr(workspace),
-                                       0 if workspace is None else workspace.numel(), _stream()), "sr_w4a4_linear_decode")
-    return Y
+    out = (_native or _marshal()).w4a4_linear_decode(X, inv_s, Wq, w_scale, clip, Y, Xq_out, x_scale_out, workspace)
+    return _refused(out, "sr_w4a4_linear_decode") if type(out) is int else out
 
 
 def sr_f6_tiles_bytes(rows: int, K: int) -> int:
@@ -315,22 +280,8 @@ def sr_w4a4_gemm_f6(X6, x_scale, W6, w_scale, M: int, N: int, K: int, out_dtype:
     """X6, W6 = f6 tiles of the codes [M, K] and [N, K] -> Y [M, N] fp16 (dequantised) or int32 (accumulators).
     warm: a contiguous device tensor (the weights of the next linear) to be pulled into the memory-side cache on
     the side where the launch has a wave to spare (sr_w4a4_gemm_f6_warm)."""
-    _dev(X6, torch.uint8, "X6"); _dev(W6, torch.uint8, "W6")
-    if X6.numel() < sr_f6_tiles_bytes(M, K) or W6.numel() < sr_f6_tiles_bytes(N, K):
-        raise ValueError("tile buffers are smaller than sr_f6_tiles_bytes says")
-    if Y is None:
-        Y = torch.empty((M, N), dtype=torch.float16 if out_dtype == SR_F16 else torch.int32, device=X6.device)
-    ldy = Y.stride(0) if M > 1 else N
-    if warm is not None:
-        if not (warm.is_cuda and warm.is_contiguous()):
-            raise ValueError("warm must be a contiguous device tensor")
-        _check(raw().sr_w4a4_gemm_f6_warm(_ptr(X6), _ptr(x_scale), _ptr(W6), _ptr(w_scale), M, N, K, _ptr(Y), ldy,
-                                          out_dtype, _ptr(warm), warm.numel() * warm.element_size(), None, 0, _stream()),
-               "sr_w4a4_gemm_f6_warm")
-        return Y
-    _check(raw().sr_w4a4_gemm_f6(_ptr(X6), _ptr(x_scale), _ptr(W6), _ptr(w_scale), M, N, K, _ptr(Y), ldy,
-                                 out_dtype, None, 0, _stream()), "sr_w4a4_gemm_f6")
-    return Y
+    out = (_native or _marshal()).w4a4_gemm_f6(X6, x_scale, W6, w_scale, M, N, K, out_dtype, Y, warm)
+    return _refused(out, "sr_w4a4_gemm_f6") if type(out) is int else out
 
 
 def sr_w4a4_gemm_f6_warm(X6, x_scale, W6, w_scale, M: int, N: int, K: int, warm, out_dtype: int = SR_F16, Y=None):
@@ -342,22 +293,8 @@ def sr_fwht_quant_act_f6(X, inv_s, clip: float = 0.9, X6=None, x_scale=None, war
     """X fp16 [M, K] -> (X6 uint8 [sr_f6_tiles_bytes(M, K)] f6 tiles of the codes, x_scale fp32 [M]).
     warm: a contiguous device tensor (the weights of the GEMM that follows) to be pulled into the memory-side
     cache on the side (sr_fwht_quant_act_f6_warm)."""
-    _dev(X, torch.float16, "X")
-    M, K = X.shape
-    if X6 is None:
-        X6 = torch.zeros(max(sr_f6_tiles_bytes(M, K), 16), dtype=torch.uint8, device=X.device)
-    x_scale = torch.empty(M, dtype=torch.float32, device=X.device) if x_scale is None else x_scale
-    ldx = X.stride(0) if M > 1 else K
-    if warm is not None:
-        if not (warm.is_cuda and warm.is_contiguous()):
-            raise ValueError("warm must be a contiguous device tensor")
-        _check(raw().sr_fwht_quant_act_f6_warm(_ptr(X), M, K, ldx, _ptr(inv_s), clip, _ptr(X6), _ptr(x_scale),
-                                               _ptr(warm), warm.numel() * warm.element_size(), _stream()),
-               "sr_fwht_quant_act_f6_warm")
-        return X6, x_scale
-    _check(raw().sr_fwht_quant_act_f6(_ptr(X), M, K, ldx, _ptr(inv_s), clip, _ptr(X6), _ptr(x_scale), _stream()),
-           "sr_fwht_quant_act_f6")
-    return X6, x_scale
+    out = (_native or _marshal()).fwht_quant_act_f6(X, inv_s, clip, X6, x_scale, warm)
+    return out if type(out) is tuple else _refused(out, "sr_fwht_quant_act_f6")
 
 
 def sr_fwht_quant_act_f6_warm(X, inv_s, clip: float, next_operand, X6=None, x_scale=None):
@@ -368,18 +305,8 @@ def sr_fwht_quant_act_f6_warm(X, inv_s, clip: float, next_operand, X6=None, x_sc
 
 def sr_swiglu_fwht_quant_act_f6(G, U, inv_s, clip: float = 0.9, X6=None, x_scale=None):
     """G, U fp16 [M, K] -> f6 tiles and scales of silu(G) * U (smoothed, rotated, quantised)."""
-    _dev(G, torch.float16, "G"); _dev(U, torch.float16, "U")
-    M, K = U.shape
-    if tuple(G.shape) != (M, K):
-        raise ValueError("G and U must have the same shape")
-    if X6 is None:
-        X6 = torch.zeros(max(sr_f6_tiles_bytes(M, K), 16), dtype=torch.uint8, device=U.device)
-    x_scale = torch.empty(M, dtype=torch.float32, device=U.device) if x_scale is None else x_scale
-    ldg = G.stride(0) if M > 1 else K
-    ldu = U.stride(0) if M > 1 else K
-    _check(raw().sr_swiglu_fwht_quant_act_f6(_ptr(G), _ptr(U), M, K, ldg, ldu, _ptr(inv_s), clip, _ptr(X6),
-                                             _ptr(x_scale), _stream()), "sr_swiglu_fwht_quant_act_f6")
-    return X6, x_scale
+    out = (_native or _marshal()).swiglu_fwht_quant_act(G, U, inv_s, clip, X6, x_scale, True)
+    return out if type(out) is tuple else _refused(out, "sr_swiglu_fwht_quant_act_f6")
 
 
 def sr_ceiling_hbm_read(src, grid: int, block: int = 256, in_flight: int = 8, nontemporal: bool = True):

@@ -1,4 +1,4 @@
-"""Builds libsmoothrot.so (HIP, gfx950 only) in-tree with hipcc.
+"""Builds libsmoothrot.so (HIP, gfx950 only) with hipcc and _marshal.so (the binding's native half) with g++, in-tree.
 
     python -m paper_2506_05413_amd.build
 """
@@ -7,12 +7,14 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libsmoothrot.so")
+MARSHAL = os.path.join(PKG, "_marshal.so")
 
 SOURCES = ["sr_api.hip", "fwht_quant.hip", "calib_fold.hip", "gemm_prefill.hip", "gemm_f6.hip", "gemm_f6_stream.hip", "gemm_decode.hip", "kv_quant.hip", "linear_decode.hip", "ceilings.hip"]
 
@@ -55,17 +57,46 @@ def _check_asm_loads() -> None:
         raise RuntimeError("inline-assembly load check failed:\n" + r.stdout + r.stderr)
 
 
+def _compile_marshal() -> str:
+    """csrc/marshal.cpp -> object file: host code against the headers of the installed torch and Python."""
+    import torch
+    root = os.path.dirname(torch.__file__)
+    obj = os.path.join(OBJ, "marshal.o")
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-fvisibility=hidden", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI]
+    cmd += [f for d in ("include", "include/torch/csrc/api/include") for f in ("-isystem", os.path.join(root, d))]
+    cmd += ["-isystem", "/opt/rocm/include", "-isystem", sysconfig.get_paths()["include"]]
+    r = subprocess.run(cmd + ["-c", os.path.join(CSRC, "marshal.cpp"), "-o", obj], capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed for marshal.cpp:\n" + r.stderr)
+    return obj
+
+
+def _link_marshal(obj: str) -> None:
+    """_marshal.so; torch's libraries are in the process when it is imported, libsmoothrot.so lies beside it."""
+    import torch
+    libs = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = ["g++", "-shared", "-o", MARSHAL, obj, "-L", PKG, "-lsmoothrot", "-L", libs, "-ltorch_python", "-ltorch_hip", "-ltorch_cpu",
+           "-lc10_hip", "-lc10", "-Wl,-rpath,$ORIGIN"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("link of _marshal.so failed:\n" + r.stderr)
+
+
 def build(verbose: bool = True) -> str:
-    """Compile every HIP source and link the shared library; returns its path."""
+    """Compile every source and link both shared libraries; returns the path of libsmoothrot.so."""
     os.makedirs(OBJ, exist_ok=True)
-    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + 1)) as ex:
+    with ThreadPoolExecutor(max_workers=8) as ex:
+        marshal = ex.submit(_compile_marshal)
         check = ex.submit(_check_asm_loads)
         objs = list(ex.map(_compile, SOURCES))
         check.result()
+        marshal_obj = marshal.result()
     cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("link failed:\n" + r.stderr)
+    _link_marshal(marshal_obj)
     if verbose:
         print("built", LIB)
     return LIB

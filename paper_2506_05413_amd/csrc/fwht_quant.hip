@@ -83,7 +83,10 @@ __global__ __launch_bounds__(NT, STREAM ? 2 * NT / 256 : 1) void fwht_quant_kern
 
     if constexpr (!STREAM) {
         const int64_t m = row_of(blockIdx.x);
-        if (m >= rows) return;                           // F6: the grid is rounded up to a multiple of 64
+        if (m >= rows) {                                 // F6: the grid is rounded up to a multiple of 64
+            if constexpr (F6) zero_f6_padding_row<K, NT>(Q, (rows + 7) >> 3, m, t);
+            return;
+        }
         RowLoad<K, NT> ld;
         row_load<K, NT, false, GATE>(X + m * ldx, pre, t, ld, GATE ? gate + m * ldg : nullptr);
         const float amax = rotate_loaded_row_absmax<K, NT, GATE>(ld, pre, row, red, t, warm_lines_now);
@@ -94,7 +97,15 @@ __global__ __launch_bounds__(NT, STREAM ? 2 * NT / 256 : 1) void fwht_quant_kern
         static_assert(!GATE, "the walking variant takes no gate row");
         const int64_t step = gridDim.x;
         int64_t w = blockIdx.x;
-        while (w < total && row_of(w) >= rows) w += step;
+        // from w on to a row of X; padding rows met on the way get zero codes
+        auto skip_padding = [&](int64_t v) {
+            while (v < total && row_of(v) >= rows) {
+                if constexpr (F6) zero_f6_padding_row<K, NT>(Q, (rows + 7) >> 3, row_of(v), t);
+                v += step;
+            }
+            return v;
+        };
+        w = skip_padding(w);
         if (w >= total) return;
         RowLoad<K, NT> ld;
         {
@@ -104,8 +115,7 @@ __global__ __launch_bounds__(NT, STREAM ? 2 * NT / 256 : 1) void fwht_quant_kern
         bool first = true;
         for (;;) {
             const int64_t m = row_of(w);
-            int64_t wn = w + step;
-            while (wn < total && row_of(wn) >= rows) wn += step;
+            const int64_t wn = skip_padding(w + step);
             const bool more = wn < total;                // uniform over the workgroup
             // the next row is requested as soon as this one has left the registers; the smoothing factors,
             // which come from L2, only after the register-hungry passes
@@ -264,7 +274,10 @@ __global__ __launch_bounds__(NT) void fwht_quant_ex_kernel(const __half *__restr
     if constexpr (F6) {                                  // rows of a tile block from one XCD (see fwht_quant_kernel)
         const int64_t w = blockIdx.x, x8 = w & 7, a = w >> 3;
         m = 64 * (a >> 3) + 8 * x8 + (a & 7);
-        if (m >= rows) return;
+        if (m >= rows) {
+            zero_f6_padding_row<K, NT>(Q, (rows + 7) >> 3, m, t);
+            return;
+        }
     }
     const __half *x = X + m * ldx;
     const __half *gt = ex.gate ? ex.gate + m * ex.ldg : nullptr;
@@ -393,7 +406,10 @@ __global__ __launch_bounds__(256) void fwht4096_wave_kernel(const __half *__rest
     }
     static_assert(!STAGED || (HAS_PRE && !MASKED), "the staged variant is the plain transform with factors");
     if constexpr (!STAGED) {
-        if (m >= rows) return;                           // no barrier below: waves are independent
+        if (m >= rows) {                                 // no barrier below: waves are independent
+            if constexpr (F6) zero_f6_padding_row<K, 64>(Q, (rows + 7) >> 3, m, lane);
+            return;
+        }
     }
     float *buf = smem_rows + wave * ROWF;
     const __half *x = X + m * ldx;
@@ -437,6 +453,7 @@ __global__ __launch_bounds__(256) void fwht4096_wave_kernel(const __half *__rest
         barrier_nofence();                               // every wave holds its factors: the row buffers are free
         if (!active) {
             wait_vmcnt<0>();                             // (its loads read row 0; nothing may be in flight at the end)
+            if constexpr (F6) zero_f6_padding_row<K, 64>(Q, (rows + 7) >> 3, m, lane);
             return;
         }
     } else {
@@ -629,7 +646,10 @@ __global__ __launch_bounds__(256) void fwht4096_wg_kernel(const __half *__restri
         const int64_t w = blockIdx.x, x = w & 7, a = w >> 3;
         m = 8 * (8 * (a >> 3) + x) + (a & 7);
     }
-    if (m >= rows) return;                               // the whole workgroup: no barrier is left behind
+    if (m >= rows) {                                     // the whole workgroup: no barrier is left behind
+        if constexpr (F6) zero_f6_padding_row<K, 256>(Q, (rows + 7) >> 3, m, t);
+        return;
+    }
     const __half *x = X + m * ldx;
 
     // ---- pass 1: index bits 0..5 ------------------------------------------------------------------
@@ -747,10 +767,11 @@ hipError_t launch_row_kernel(const void *X, int64_t rows, int64_t ldx, const flo
         if (int64_t f; tuned(kTuneFwhtStream, f)) stream = resident >= 64 && f != 0;
         if (stream) grid = resident < total ? resident : total;
     }
-    auto kern = stream ? fwht_quant_kernel<K, NT, F6, GATE, (K == 14336 && NT == 256 && !GATE)> : fwht_quant_kernel<K, NT, F6, GATE, false>;
+    constexpr auto walking = fwht_quant_kernel<K, NT, F6, GATE, (K == 14336 && NT == 256 && !GATE)>;
+    constexpr auto one_row = fwht_quant_kernel<K, NT, F6, GATE, false>;
+    auto kern = stream ? walking : one_row;
     if (lds > 48 * 1024) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        hipError_t e = stream ? allow_dynamic_lds<walking>((int)lds) : allow_dynamic_lds<one_row>((int)lds);
         if (e != hipSuccess) return e;
     }
     // the hint is honoured from 256 workgroups on (a launch of a few rows cannot move megabytes on the side)
@@ -823,10 +844,9 @@ hipError_t launch_one_ex(const void *X, int64_t rows, int64_t ldx, const float *
             // threads per row as in launch_one (many rows), but never fewer than 256: workgroups of one or two waves
             // run the search at a third of the speed (2048 x 4096, 21 ratios: 35 us with 256 threads, 95 with 128)
             constexpr int NTS = K == 8192 ? 512 : (K == 16384 || K == 28672 || K == 32768) ? 1024 : 256;
-            auto kern = fwht_quant_search_kernel<K, NTS>;
+            constexpr auto kern = fwht_quant_search_kernel<K, NTS>;
             if (lds > 40 * 1024) {
-                hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+                hipError_t e = allow_dynamic_lds<kern>((int)lds);
                 if (e != hipSuccess) return e;
             }
             hipLaunchKernelGGL(kern, dim3((unsigned)rows), dim3(NTS), lds, st, static_cast<const __half *>(X), ldx, pre,
@@ -834,10 +854,9 @@ hipError_t launch_one_ex(const void *X, int64_t rows, int64_t ldx, const float *
             return hipGetLastError();
         }
     }
-    auto kern = fwht_quant_ex_kernel<K, NT, F6>;
+    constexpr auto kern = fwht_quant_ex_kernel<K, NT, F6>;
     if (lds > 40 * 1024) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        hipError_t e = allow_dynamic_lds<kern>((int)lds);
         if (e != hipSuccess) return e;
     }
     const unsigned grid = F6 ? (unsigned)((rows + 63) / 64 * 64) : (unsigned)rows;
@@ -860,8 +879,8 @@ hipError_t launch_wave4096(const void *X, int64_t rows, int64_t ldx, const float
 {
     constexpr size_t lds = 4 * (4096 + (F6 ? 576 : 64)) * sizeof(float);
     const unsigned blocks = F6 ? (unsigned)((rows + 63) / 64 * 16) : (unsigned)((rows + 3) / 4);
-    auto kern = fwht4096_wave_kernel<HAS_PRE, F6, MASKED, STAGED>;
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    constexpr auto kern = fwht4096_wave_kernel<HAS_PRE, F6, MASKED, STAGED>;
+    hipError_t e = allow_dynamic_lds<kern>((int)lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), lds, st, static_cast<const __half *>(X), ldx, rows, pre, clip,
                        post_scale, Q, scale_out, had_mask, warm_bytes >= 128 ? static_cast<const uint32_t *>(warm) : nullptr,

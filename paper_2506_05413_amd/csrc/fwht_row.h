@@ -274,6 +274,22 @@ __device__ __forceinline__ uint32_t quant_pack8(const float (&y)[8], float inv_d
 // 32 p + 31) and stores its 24 bytes: the first 16 and the last 8 go to different places of the tile block.
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef unsigned int v6u __attribute__((ext_vector_type(6)));
+__device__ __forceinline__ void store_f6_piece(const v6u f, uint8_t *__restrict__ T6, int64_t row_blocks, int64_t m, int p)
+{
+    const int C = p >> 2, t = (p >> 1) & 1, g = p & 1;
+    const int64_t R = m >> 3;
+    const int r = (int)(m & 7), swz = (int)(R & 1);
+    uint8_t *blk = T6 + ((int64_t)C * row_blocks + R) * 768;
+    *reinterpret_cast<uint4 *>(blk + 256 * t + 128 * (g ^ swz) + 16 * r) = make_uint4(f[0], f[1], f[2], f[3]);
+    *reinterpret_cast<uint2 *>(blk + 512 + 128 * (g ^ swz) + 16 * r + 8 * t) = make_uint2(f[4], f[5]);
+}
+// thread t of NT: zero codes into row m if it pads the last block of 8 (rows <= m < 8 row_blocks)
+template <int K, int NT>
+__device__ __forceinline__ void zero_f6_padding_row(uint8_t *__restrict__ T6, int64_t row_blocks, int64_t m, int t)
+{
+    if (m >= 8 * row_blocks) return;
+    for (int p = t; p < K / 32; p += NT) store_f6_piece(v6u{0u, 0u, 0u, 0u, 0u, 0u}, T6, row_blocks, m, p);
+}
 // (inv_lo for the first 16 values, inv_hi for the last 16: callers whose values carry a sign per group of 16
 // pass +-1/Delta; the others the same factor twice)
 __device__ __forceinline__ void quant_store_f6_piece(const float *s32, float inv_lo, float inv_hi, uint8_t *__restrict__ T6,
@@ -289,13 +305,7 @@ __device__ __forceinline__ void quant_store_f6_piece(const float *s32, float inv
         ev[2 * k + 1] = __builtin_amdgcn_fmed3f(q.z * inv_delta, -8.f, 7.f);
         od[2 * k + 1] = __builtin_amdgcn_fmed3f(q.w * inv_delta, -8.f, 7.f);
     }
-    const v6u f = __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(ev, od, 8.f);
-    const int C = p >> 2, t = (p >> 1) & 1, g = p & 1;
-    const int64_t R = m >> 3;
-    const int r = (int)(m & 7), swz = (int)(R & 1);
-    uint8_t *blk = T6 + ((int64_t)C * row_blocks + R) * 768;
-    *reinterpret_cast<uint4 *>(blk + 256 * t + 128 * (g ^ swz) + 16 * r) = make_uint4(f[0], f[1], f[2], f[3]);
-    *reinterpret_cast<uint2 *>(blk + 512 + 128 * (g ^ swz) + 16 * r + 8 * t) = make_uint2(f[4], f[5]);
+    store_f6_piece(__builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(ev, od, 8.f), T6, row_blocks, m, p);
 }
 __device__ __forceinline__ void quant_store_f6_piece(const float *s32, float inv_delta, uint8_t *__restrict__ T6,
                                                      int64_t row_blocks, int64_t m, int p)

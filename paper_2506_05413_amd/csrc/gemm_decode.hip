@@ -447,10 +447,10 @@ template <int SPW, int UPW>
 hipError_t launch_stream(const uint8_t *Xq, const float *xs, const uint8_t *Wq, const float *ws, int64_t M, int64_t N,
                          int64_t K, void *Y, int64_t ldy, int out_i32, int wgx, hipStream_t st)
 {
-    auto kern = gemm_decode_stream_kernel<SPW, UPW>;
+    constexpr auto kern = gemm_decode_stream_kernel<SPW, UPW>;
     constexpr int lds = 16 * ((UPW + 1) / 2) * 64 * 16;               // the waves' accumulators
     // with the 36 KB of static staging buffers the workgroup needs up to 100 KB of LDS
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    hipError_t e = allow_dynamic_lds<kern>(lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3(8 * wgx), dim3(1024), lds, st, Xq, xs, Wq, ws, (int)M, (int)N, (int)K, Y, ldy, out_i32);
     return hipGetLastError();

@@ -364,12 +364,11 @@ hipError_t launch_f6(const uint8_t *X6, const float *xs, const uint8_t *W6, cons
                      int64_t K, void *Y, int64_t ldy, int out_i32, hipStream_t st, const void *warm = nullptr,
                      size_t warm_bytes = 0)
 {
-    auto kern = gemm_f6_kernel<BM, BN, WGM, WGN, SLOTS, WG_PER_CU>;
+    constexpr auto kern = gemm_f6_kernel<BM, BN, WGM, WGN, SLOTS, WG_PER_CU>;
     constexpr int lds = f6_lds_bytes(BM, BN, SLOTS);
     static_assert(lds * WG_PER_CU <= 160 * 1024, "LDS");
     if (lds > 48 * 1024) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        hipError_t e = allow_dynamic_lds<kern>(lds);
         if (e != hipSuccess) return e;
     }
     bool warms = false;
@@ -378,8 +377,7 @@ hipError_t launch_f6(const uint8_t *X6, const float *xs, const uint8_t *W6, cons
         warms = warm && warm_bytes >= 128;
         if (int64_t w; tuned(kTuneGemmWarm, w) && w == 0) warms = false;
         if (warms && lds > 48 * 1024) {
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(gemm_f6_warm_kernel<BM, BN, WGM, WGN, SLOTS>),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+            hipError_t e = allow_dynamic_lds<gemm_f6_warm_kernel<BM, BN, WGM, WGN, SLOTS>>(lds);
             if (e != hipSuccess) return e;
         }
     }

@@ -316,12 +316,11 @@ template <int BM, int BN, int WGM, int WGN, int WG_PER_CU>
 hipError_t launch_tile(const uint8_t *Xq, const float *xs, const uint8_t *Wq, const float *ws, int64_t M, int64_t N,
                        int64_t K, void *Y, int64_t ldy, int out_i32, hipStream_t st)
 {
-    auto kern = gemm_w4a4_kernel<BM, BN, WGM, WGN>;
+    constexpr auto kern = gemm_w4a4_kernel<BM, BN, WGM, WGN>;
     constexpr int lds = 2 * (BM + BN) * ROWB;
     static_assert(lds * WG_PER_CU <= 160 * 1024, "LDS");
     if (lds > 48 * 1024) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        hipError_t e = allow_dynamic_lds<kern>(lds);
         if (e != hipSuccess) return e;
     }
     const int tiles_m = (int)((M + BM - 1) / BM), tiles_n = (int)((N + BN - 1) / BN);

@@ -150,12 +150,11 @@ template <int K, int G>
 hipError_t launch_ld(const void *X, int64_t M, int64_t ldx, const float *pre, float clip, const uint8_t *Wq,
                      const float *ws, int64_t N, void *Y, int64_t ldy, uint8_t *Xq_out, float *xs_out, hipStream_t st)
 {
-    auto kern = linear_decode_kernel<K, G>;
+    constexpr auto kern = linear_decode_kernel<K, G>;
     constexpr int lds = (int)(sizeof(float) * padded_len(K)) + LD_MT * (K / 2);
     static_assert(lds + 64 <= 160 * 1024, "LDS");
     if (lds > 40 * 1024) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        hipError_t e = allow_dynamic_lds<kern>(lds);
         if (e != hipSuccess) return e;
     }
     const unsigned blocks = (unsigned)((N + 8 * G - 1) / (8 * G));

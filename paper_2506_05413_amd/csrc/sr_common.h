@@ -85,6 +85,20 @@ inline int compute_units()
     return n;
 }
 
+// Lets a kernel use `bytes` of dynamic LDS (more than the default limit); asked of the runtime once per kernel and
+// device.  `bytes` is a constant of the kernel.
+template <auto Kernel> inline hipError_t allow_dynamic_lds(int bytes)
+{
+    static std::atomic<uint64_t> done{0};                // bit = device; concurrent first calls ask twice
+    int dev = 0;
+    if (hipError_t e = hipGetDevice(&dev); e != hipSuccess) return e;
+    const uint64_t bit = dev >= 0 && dev < 64 ? 1ull << dev : 0;
+    if (done.load(std::memory_order_relaxed) & bit) return hipSuccess;
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(Kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    if (e == hipSuccess) done.fetch_or(bit, std::memory_order_relaxed);
+    return e;
+}
+
 // ---- launchers (each returns hipGetLastError() of its launches) ------------------
 
 // y = (x * pre) H per row, per-row symmetric INT4, scale_out = delta * post_scale.
