@@ -512,21 +512,49 @@ hipError_t launch_gemm_prefill(const uint8_t *Xq, const float *xs, const uint8_t
                            Xq, xs, Wq, ws, (int)M, (int)N, (int)K, Y, ldy, out_i32, tiles_m, tiles_n);
         return hipGetLastError();
     }
-    // A launch takes about ceil(tiles / slots) rounds of one tile time each (tile time ~ BM * BN): pick the
-    // tile shape with the cheapest schedule; ties go to the larger tile (less L2 traffic, fewer fragment reads).
-    //   256 x 128: eight waves (two per SIMD, so that one can issue MFMAs while the other is held up issuing
-    //              LDS or DMA instructions), 96 KB of LDS, one workgroup per CU
-    //   128 x 128: four waves, 64 KB of LDS, two workgroups per CU
-    if (variant == 14) return launch_tile<128, 128, 2, 2, 2>(Xq, xs, Wq, ws, M, N, K, Y, ldy, out_i32, st);
-    if (variant == 15) return launch_tile<256, 128, 4, 2, 1>(Xq, xs, Wq, ws, M, N, K, Y, ldy, out_i32, st);
-    const int64_t cus = compute_units();
-    auto cost = [&](int64_t bm, int64_t bn) {       // a half-filled last round of 128 x 128 tiles costs about half
-        const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
-        return ((tiles + cus - 1) / cus) * bm * bn;
+    // What a launch costs, by configuration: with t tiles on c compute units, r = ceil(t / c) rounds and n = K / 256
+    // stages,   fixed + per_round r + n (stage_round r + stage_tile t / c)   microseconds,
+    // fitted to 150 shapes (M 17 .. 4900, N 1024 .. 16000, K 2048 .. 14336).  Between the two large tiles the cheaper
+    // schedule of whole rounds decides (ties to the larger tile); another configuration replaces that choice where it is
+    // predicted at least 5 % faster: mostly below 500 rows, where 128 x 128 tiles leave CUs idle (29 x 4096 x 14336
+    // 47.6 -> 12.2 us, 52 x 2208 x 8192 28.7 -> 9.7, 172 x 3968 x 4096 17.3 -> 10.2, 445 x 3088 x 4096 18.3 -> 14.4).
+    struct Config { int id, bm, bn; float fixed, per_round, stage_round, stage_tile; };
+    static constexpr Config configs[] = {
+        {14, 128, 128, 4.86f, .55f, .675f, .153f},    // four waves of 64 x 64, two workgroups per CU
+        {15, 256, 128, 1.62f, 4.18f, .964f, .456f},   // eight waves of 64 x 64: while one wave of a SIMD is held up issuing
+                                                      // LDS or DMA instructions, the other can issue MFMAs
+        {17, 128, 64, 3.62f, .31f, .477f, .128f},     // eight waves of 32 x 32, two workgroups per CU
+        {18, 192, 128, 2.18f, 2.86f, .977f, .328f},   // eight waves of 96 x 32
+        {19, 64, 128, 3.99f, .03f, .527f, .074f},     // eight waves of 32 x 32, two workgroups per CU
+        // operands straight into registers, K split over eight waves (gemm_packed_stream.hip)
+        {64064, 64, 64, 1.26f, 2.32f, .370f, .114f},
+        {48064, 48, 64, 1.25f, 2.22f, .327f, .088f},
+        {48032, 48, 32, 1.26f, 2.57f, .172f, .068f},
+        {32064, 32, 64, 2.62f, 1.99f, .248f, .062f},
+        {32032, 32, 32, 2.71f, .96f, .155f, .038f},
+        {32016, 32, 16, 2.04f, 1.05f, .114f, .021f},
     };
-    if (cost(256, 128) <= cost(128, 128))
-        return launch_tile<256, 128, 4, 2, 1>(Xq, xs, Wq, ws, M, N, K, Y, ldy, out_i32, st);
-    return launch_tile<128, 128, 2, 2, 2>(Xq, xs, Wq, ws, M, N, K, Y, ldy, out_i32, st);
+    const int64_t cus = compute_units();
+    auto tiles = [&](const Config &c) { return ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn); };
+    auto cost = [&](const Config &c) {
+        const float r = (float)((tiles(c) + cus - 1) / cus), n = (float)(K / 256);
+        return c.fixed + c.per_round * r + n * (c.stage_round * r + c.stage_tile * (float)tiles(c) / (float)cus);
+    };
+    auto area = [&](const Config &c) { return (tiles(c) + cus - 1) / cus * c.bm * c.bn; };
+    const Config *best = area(configs[1]) <= area(configs[0]) ? &configs[1] : &configs[0];
+    float best_cost = .95f * cost(*best);
+    for (const Config &c : configs)
+        if (const float v = cost(c); v < best_cost) { best = &c; best_cost = v; }
+    for (const Config &c : configs)
+        if (c.id == variant) best = &c;
+    switch (best->id) {
+        case 14: return launch_tile<128, 128, 2, 2, 2>(Xq, xs, Wq, ws, M, N, K, Y, ldy, out_i32, st);
+        case 15: return launch_tile<256, 128, 4, 2, 1>(Xq, xs, Wq, ws, M, N, K, Y, ldy, out_i32, st);
+        case 17: return launch_tile<128, 64, 4, 2, 2>(Xq, xs, Wq, ws, M, N, K, Y, ldy, out_i32, st);
+        case 18: return launch_tile<192, 128, 2, 4, 1>(Xq, xs, Wq, ws, M, N, K, Y, ldy, out_i32, st);
+        case 19: return launch_tile<64, 128, 2, 4, 2>(Xq, xs, Wq, ws, M, N, K, Y, ldy, out_i32, st);
+        default: return launch_gemm_w4a4_stream(Xq, xs, Wq, ws, M, N, K, Y, ldy, out_i32, st, best->id / 1000, best->id % 1000);
+    }
 }
 
 }  // namespace sr

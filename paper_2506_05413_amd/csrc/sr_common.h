@@ -153,6 +153,11 @@ hipError_t launch_gemm_prefill(const uint8_t *Xq, const float *xs, const uint8_t
                                int64_t M, int64_t N, int64_t K, void *Y, int64_t ldy, int out_i32,
                                hipStream_t st);
 
+// the same for few and medium row counts, K % 256 == 0: bm x bn outputs per workgroup, operands straight into registers
+// (see gemm_packed_stream.hip)
+hipError_t launch_gemm_w4a4_stream(const uint8_t *Xq, const float *xs, const uint8_t *Wq, const float *ws, int64_t M,
+                                   int64_t N, int64_t K, void *Y, int64_t ldy, int out_i32, hipStream_t st, int bm, int bn);
+
 // f6 tiles (see gemm_f6.hip): repacking of canonical INT4 codes, and the GEMM on the FP6 matrix pipe
 hipError_t launch_pack_f6(const uint8_t *Q4, int64_t rows, int64_t K, uint8_t *T6, hipStream_t st);
 // warm / warm_bytes: a region whose 128-byte lines the launch reads on the side where its tile configuration has a

@@ -1,0 +1,34 @@
+"""Every configuration of the packed-nibble GEMM (M > 16) the launch rule can pick, forced where its indexing can go
+wrong: fewer K chunks than waves, K remainders of the wave split, ragged last tiles on both sides, more tiles than
+workgroups, K that only the generic kernel takes.  INT32 accumulators must equal the oracle's bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import smoothrot_oracle as o
+import workloads as wl
+from parity import check_output
+
+pytestmark = pytest.mark.gpu
+
+CONFIGS = [14, 15, 17, 18, 19, 64064, 48064, 48032, 32064, 32032, 32016]
+SHAPES = [(17, 16, 256), (33, 80, 2304), (49, 208, 4352), (65, 48, 768), (200, 1040, 2560), (40, 4112, 4608), (70, 96, 192)]
+
+
+@pytest.mark.parametrize("config", CONFIGS)
+@pytest.mark.parametrize("M,N,K", SHAPES)
+def test_forced_configuration(gpu, tune, config, M, N, K):
+    print("case", config, M, N, K, flush=True)
+    tune(gpu.SR_TUNE_GEMM_TILE, config)
+    cx, cw = wl.random_codes(M + K, M, K), wl.random_codes(N + 3 * K, N, K)
+    Xq, Wq = (torch.from_numpy(o.pack_int4(c)).cuda() for c in (cx, cw))
+    want = o.gemm_i32_c(cx, cw)
+    full = torch.full((M, N + 8), -7, dtype=torch.int32, device="cuda")
+    gpu.sr_w4a4_gemm(Xq, None, Wq, None, gpu.SR_I32, full[:, :N])
+    rng = np.random.default_rng(K)
+    xs, ws = rng.uniform(0.01, 2.0, M).astype(np.float32), rng.uniform(1e-4, 1e-2, N).astype(np.float32)
+    Y = gpu.sr_w4a4_gemm(Xq, torch.from_numpy(xs).cuda(), Wq, torch.from_numpy(ws).cuda())
+    torch.cuda.synchronize()
+    assert bool((full[:, N:] == -7).all())
+    assert np.array_equal(full[:, :N].cpu().numpy().astype(np.int64), want)
+    check_output(Y.cpu().numpy(), o.dequant_out(want, xs.astype(np.float64), ws.astype(np.float64)))
