@@ -32,7 +32,10 @@ __global__ __launch_bounds__(NT, STREAM ? 2 * NT / 256 : 1) void fwht_quant_kern
                                                         const __half *__restrict__ gate, int64_t ldg,
                                                         const uint32_t *__restrict__ warm, int64_t warm_lines)
 {
-    extern __shared__ float row[];
+    // The alignment is part of the layout: without it the row starts where the static LDS of the kernel happens to end
+    // (8 bytes in with two waves), and every 16-byte access splits -- K = 2048, 16384 rows: 44.5 -> 33.7 us, K = 1024,
+    // 4096 rows: 12.5 -> 6.1 us.
+    extern __shared__ __attribute__((aligned(16))) float row[];
     __shared__ float red[NT / 64];
 
     const int t = threadIdx.x;
@@ -226,7 +229,7 @@ __global__ __launch_bounds__(NT) void fwht_quant_search_kernel(const __half *__r
                                                                uint8_t *__restrict__ Q, float *__restrict__ scale_out,
                                                                const RowExtras ex)
 {
-    extern __shared__ float row[];
+    extern __shared__ __attribute__((aligned(16))) float row[];
     __shared__ float red[NT / 64];
     const int t = threadIdx.x;
     const int64_t m = blockIdx.x;
@@ -266,7 +269,7 @@ __global__ __launch_bounds__(NT) void fwht_quant_ex_kernel(const __half *__restr
     constexpr int LOGP = ilog2(P2);
     constexpr int NW = NT / 64;
 
-    extern __shared__ float row[];
+    extern __shared__ __attribute__((aligned(16))) float row[];
     __shared__ float red[NW];
 
     const int t = threadIdx.x;
@@ -841,9 +844,9 @@ hipError_t launch_one_ex(const void *X, int64_t rows, int64_t ldx, const float *
     constexpr size_t lds = sizeof(float) * padded_len(K);
     if constexpr (!F6) {
         if (ex.n_grid > 0 && !ex.gate && (ex.had_mask == 0xFFFFFFFFu || !is_pow2(K))) {
-            // threads per row as in launch_one (many rows), but never fewer than 256: workgroups of one or two waves
-            // run the search at a third of the speed (2048 x 4096, 21 ratios: 35 us with 256 threads, 95 with 128)
-            constexpr int NTS = K == 8192 ? 512 : (K == 16384 || K == 28672 || K == 32768) ? 1024 : 256;
+            // threads per row as in launch_one (many rows); K = 2048 x 4096 channels, 21 ratios: 34 us with 256 threads
+            // against 39 with 128 (1024: 24 against 19 with 64, 512: 17 against 13)
+            constexpr int NTS = K == 8192 ? 512 : (K == 16384 || K == 28672 || K == 32768) ? 1024 : K == 2048 ? 256 : NT;
             constexpr auto kern = fwht_quant_search_kernel<K, NTS>;
             if (lds > 40 * 1024) {
                 hipError_t e = allow_dynamic_lds<kern>((int)lds);
