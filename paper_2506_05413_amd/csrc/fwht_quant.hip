@@ -21,11 +21,8 @@ namespace sr {
 namespace {
 
 // F6: Q receives f6 tiles (operands of the FP6-MFMA GEMM) instead of packed nibbles; K % 128 == 0 then.
-// STREAM: the grid is smaller than the number of rows; a workgroup walks over rows w, w + gridDim.x, .. and
-// fetches its next row while it rotates the current one (gridDim.x % 64 == 0 for F6, so that the row mapping
-// below stays what it is for a grid of one workgroup per row).
-template <int K, int NT, bool F6, bool GATE = false, bool STREAM = false>
-__global__ __launch_bounds__(NT, STREAM ? 2 * NT / 256 : 1) void fwht_quant_kernel(const __half *__restrict__ X, int64_t ldx, int64_t rows,
+template <int K, int NT, bool F6, bool GATE = false>
+__global__ __launch_bounds__(NT) void fwht_quant_kernel(const __half *__restrict__ X, int64_t ldx, int64_t rows,
                                                         const float *__restrict__ pre, float clip,
                                                         float post_scale, uint8_t *__restrict__ Q,
                                                         float *__restrict__ scale_out,
@@ -51,88 +48,38 @@ __global__ __launch_bounds__(NT, STREAM ? 2 * NT / 256 : 1) void fwht_quant_kern
     // F6: the eight rows of a tile block (768 contiguous bytes per 128 codes) should be written from ONE XCD at
     // about the same time, so that its L2 assembles whole lines: workgroups are dealt round-robin to the 8
     // XCDs, so (virtual) workgroup w = 8 a + x (XCD x) takes row r = a % 8 of row block 8 (a / 8) + x.
-    auto row_of = [](int64_t w) -> int64_t {
-        if constexpr (F6) {
-            const int64_t x = w & 7, a = w >> 3;
-            return 64 * (a >> 3) + 8 * x + (a & 7);
-        } else {
-            return w;
-        }
-    };
-    const int64_t total = F6 ? (rows + 63) / 64 * 64 : rows;      // virtual workgroups; F6: some map past the last row
-    auto quantise = [&](int64_t m, float amax) {
-        // Delta = clip * absmax / 7 (1 for an all-zero row), Eq. (1) with the signed range
-        const float delta = (amax == 0.f) ? 1.f : (clip * amax) / 7.f;
-        const float inv_delta = 1.f / delta;
-        if (t == 0) scale_out[m] = (amax == 0.f) ? 1.f : delta * post_scale;
-
-        if constexpr (F6) {
-            // ---- 32 contiguous values -> one 24-byte piece of a tile (the padding of 4 floats per 64 keeps the
-            // 16-byte reads of 16 neighbouring threads on distinct banks) -----------------------------------------
-            const int64_t row_blocks = (rows + 7) >> 3;
-            for (int p = t; p < K / 32; p += NT) quant_store_f6_piece(row + pad(32 * p), inv_delta, Q, row_blocks, m, p);
-        } else {
-            // ---- quantise 8 contiguous values -> one packed dword ---------------------------------------------
-            uint32_t *q = reinterpret_cast<uint32_t *>(Q + m * (int64_t)(K / 2));
-            for (int c = t; c < K / 8; c += NT) {
-                const float *src = row + pad(8 * c);
-                const float4 a = *reinterpret_cast<const float4 *>(src);
-                const float4 b = *reinterpret_cast<const float4 *>(src + 4);
-                const float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-                q[c] = quant_pack8(v, inv_delta);
-            }
-        }
-    };
-
-    if constexpr (!STREAM) {
-        const int64_t m = row_of(blockIdx.x);
-        if (m >= rows) {                                 // F6: the grid is rounded up to a multiple of 64
-            if constexpr (F6) zero_f6_padding_row<K, NT>(Q, (rows + 7) >> 3, m, t);
+    int64_t m = blockIdx.x;
+    if constexpr (F6) {
+        const int64_t w = blockIdx.x, x = w & 7, a = w >> 3;
+        m = 64 * (a >> 3) + 8 * x + (a & 7);
+        if (m >= rows) {                                 // the grid is rounded up to a multiple of 64
+            zero_f6_padding_row<K, NT>(Q, (rows + 7) >> 3, m, t);
             return;
         }
-        RowLoad<K, NT> ld;
-        row_load<K, NT, false, GATE>(X + m * ldx, pre, t, ld, GATE ? gate + m * ldg : nullptr);
-        const float amax = rotate_loaded_row_absmax<K, NT, GATE>(ld, pre, row, red, t, warm_lines_now);
-        quantise(m, amax);
+    }
+    RowLoad<K, NT> ld;
+    row_load<K, NT, false, GATE>(X + m * ldx, pre, t, ld, GATE ? gate + m * ldg : nullptr);
+    const float amax = rotate_loaded_row_absmax<K, NT, GATE>(ld, pre, row, red, t, warm_lines_now);
+
+    // Delta = clip * absmax / 7 (1 for an all-zero row), Eq. (1) with the signed range
+    const float delta = (amax == 0.f) ? 1.f : (clip * amax) / 7.f;
+    const float inv_delta = 1.f / delta;
+    if (t == 0) scale_out[m] = (amax == 0.f) ? 1.f : delta * post_scale;
+
+    if constexpr (F6) {
+        // ---- 32 contiguous values -> one 24-byte piece of a tile (the padding of 4 floats per 64 keeps the
+        // 16-byte reads of 16 neighbouring threads on distinct banks) -----------------------------------------
+        const int64_t row_blocks = (rows + 7) >> 3;
+        for (int p = t; p < K / 32; p += NT) quant_store_f6_piece(row + pad(32 * p), inv_delta, Q, row_blocks, m, p);
     } else {
-        // (not with a gate row: twice the registers in flight; measured 15 - 25 % slower than one row per
-        // workgroup, also with the prefetch moved behind the Paley pass)
-        static_assert(!GATE, "the walking variant takes no gate row");
-        const int64_t step = gridDim.x;
-        int64_t w = blockIdx.x;
-        // from w on to a row of X; padding rows met on the way get zero codes
-        auto skip_padding = [&](int64_t v) {
-            while (v < total && row_of(v) >= rows) {
-                if constexpr (F6) zero_f6_padding_row<K, NT>(Q, (rows + 7) >> 3, row_of(v), t);
-                v += step;
-            }
-            return v;
-        };
-        w = skip_padding(w);
-        if (w >= total) return;
-        RowLoad<K, NT> ld;
-        {
-            const int64_t m = row_of(w);
-            row_load<K, NT, false, GATE>(X + m * ldx, pre, t, ld);
-        }
-        bool first = true;
-        for (;;) {
-            const int64_t m = row_of(w);
-            const int64_t wn = skip_padding(w + step);
-            const bool more = wn < total;                // uniform over the workgroup
-            // the next row is requested as soon as this one has left the registers; the smoothing factors,
-            // which come from L2, only after the register-hungry passes
-            const int64_t mn = more ? row_of(wn) : m;
-            const float amax = rotate_loaded_row_absmax<K, NT, GATE>(ld, pre, row, red, t, [&]() {
-                if (more) row_load<K, NT, false, GATE, 1>(X + mn * ldx, pre, t, ld);
-                if (first) warm_lines_now();
-            });
-            first = false;
-            if (more) row_load<K, NT, false, GATE, 2>(X + mn * ldx, pre, t, ld);
-            quantise(m, amax);
-            if (!more) break;
-            w = wn;
-            __syncthreads();                             // the row buffer is rewritten by the next first pass
+        // ---- quantise 8 contiguous values -> one packed dword ---------------------------------------------
+        uint32_t *q = reinterpret_cast<uint32_t *>(Q + m * (int64_t)(K / 2));
+        for (int c = t; c < K / 8; c += NT) {
+            const float *src = row + pad(8 * c);
+            const float4 a = *reinterpret_cast<const float4 *>(src);
+            const float4 b = *reinterpret_cast<const float4 *>(src + 4);
+            const float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+            q[c] = quant_pack8(v, inv_delta);
         }
     }
     asm volatile("" ::"v"(warm_acc));                    // keeps the warming loads; they returned long ago
@@ -586,195 +533,23 @@ __global__ __launch_bounds__(256) void fwht4096_wave_kernel(const __half *__rest
     asm volatile("" ::"v"(warm_acc));                    // keeps the warming loads; they returned long ago
 }
 
-// ------------------------------------------------------------------------------------------
-// K = 4096, one row per workgroup of four waves, two passes of SIX index bits each: four bits in registers
-// (16 values per thread) and two across neighbouring lanes by DPP.  A single wave of this chip issues a vector
-// instruction every ~5 cycles however independent its instructions are, and two waves per SIMD double that: the
-// wave-per-row kernel above leaves a row's ~1150 instructions to ONE wave (2.5 us after the row has arrived, with
-// two waves per SIMD at 2048 rows), this one to four waves of ~300 each, eight waves per SIMD -- with the same LDS
-// traffic (the row goes through LDS twice), where the general workgroup-per-row kernel needs three passes of four
-// bits and three round trips.
-//
-// Thread t holds x[16 t .. 16 t + 15]: index bits 0..3 in registers, bits 4, 5 in lane bits 0, 1.  A butterfly
-// across lanes is ONE instruction per value, v <- v + c * v[partner] (v_fmac_f32 with a DPP source, c = +1 in
-// the lane whose bit is clear, -1 in the other): the lane with the bit clear gets a + b, the other b - a -- the
-// difference with its sign flipped.  The flip is not undone on the spot: every later step is linear and pairs
-// only lanes with equal flips, so a value simply carries the sign (-1)^(number of set bits among the lane bits
-// used so far); row maxima ignore it, and the quantiser multiplies by 1/Delta anyway, so it multiplies by
-// -1/Delta where the sign is -1 (exact).  Pass 2 reads c + 64 r + 1024 q for r = 0..15 (c = t >> 2: index bits
-// 0..5, q = t & 3: bits 10, 11 in lane bits 0, 1; registers: bits 6..9), all written by threads with lane bits
-// 0, 1 = (t >> 6) & 3 -- one sign per thread from pass 1 -- and writes them back where it read them.
-// LDS layout: element i at i + 4 (i >> 5) + 8 (i >> 10) floats: the 16-byte writes of pass 1, the 4-byte
-// accesses of pass 2 (a half-wave covers eight consecutive c and four q: banks c + 8 q, all 32) and the 16-byte
-// reads of the quantiser are all free of bank conflicts.
-// ------------------------------------------------------------------------------------------
-__device__ __forceinline__ int wg4096_pos(int i) { return i + ((i >> 5) << 2) + ((i >> 10) << 3); }
-constexpr int kWg4096Floats = 4096 + 4 * 128 + 8 * 4;
-
-// v[e] += c * v[e] of the lane with lane bit 0 (QP = 0xB1) or lane bit 1 (QP = 0x4E) flipped, for 16 values.
-// (Inline assembly: the two wait states a DPP read needs after a vector write of the same register are given
-// by the s_nop in front; inside the block no instruction reads what its predecessor wrote.)
-template <int QP>
-__device__ __forceinline__ void lane_butterfly16(float (&v)[16], float c)
-{
-    static_assert(QP == 0xB1 || QP == 0x4E, "quad permutations [1,0,3,2] and [2,3,0,1]");
-#define SR_DPP_FMAC(i) "v_fmac_f32_dpp %" #i ", %" #i ", %16 quad_perm:[%17,%18,%19,%20] row_mask:0xf bank_mask:0xf\n\t"
-    asm("s_nop 1\n\t"
-        SR_DPP_FMAC(0) SR_DPP_FMAC(1) SR_DPP_FMAC(2) SR_DPP_FMAC(3) SR_DPP_FMAC(4) SR_DPP_FMAC(5) SR_DPP_FMAC(6) SR_DPP_FMAC(7)
-        SR_DPP_FMAC(8) SR_DPP_FMAC(9) SR_DPP_FMAC(10) SR_DPP_FMAC(11) SR_DPP_FMAC(12) SR_DPP_FMAC(13) SR_DPP_FMAC(14) SR_DPP_FMAC(15)
-        : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]), "+v"(v[7]),
-          "+v"(v[8]), "+v"(v[9]), "+v"(v[10]), "+v"(v[11]), "+v"(v[12]), "+v"(v[13]), "+v"(v[14]), "+v"(v[15])
-        : "v"(c), "n"(QP & 3), "n"((QP >> 2) & 3), "n"((QP >> 4) & 3), "n"((QP >> 6) & 3));
-#undef SR_DPP_FMAC
-}
-
-// (Measured and dropped: 2, 4 or 8 rows per workgroup, one after the other, all loads issued up front and two LDS
-// buffers taking turns, so that a row would arrive while the one before it is computed -- 9.7 / 10.8 / 13.8 us
-// against 9.0 us at 2048 rows, worse at every row count below 16384.)
-template <bool HAS_PRE, bool F6>
-__global__ __launch_bounds__(256) void fwht4096_wg_kernel(const __half *__restrict__ X, int64_t ldx, int64_t rows,
-                                                          const float *__restrict__ pre, float clip, float post_scale,
-                                                          uint8_t *__restrict__ Q, float *__restrict__ scale_out,
-                                                          const uint32_t *__restrict__ warm, int64_t warm_lines)
-{
-    constexpr int K = 4096;
-    extern __shared__ __attribute__((aligned(16))) float smem_rows[];
-    __shared__ float red[4];
-    float *row = smem_rows;
-    const int t = threadIdx.x, lane = t & 63;
-    int64_t m = blockIdx.x;
-    if constexpr (F6) {
-        // the eight rows of a tile block from the same XCD: workgroup w = 8 a + x (XCD x) takes row a % 8 of
-        // block 8 (a / 8) + x
-        const int64_t w = blockIdx.x, x = w & 7, a = w >> 3;
-        m = 8 * (8 * (a >> 3) + x) + (a & 7);
-    }
-    if (m >= rows) {                                     // the whole workgroup: no barrier is left behind
-        if constexpr (F6) zero_f6_padding_row<K, 256>(Q, (rows + 7) >> 3, m, t);
-        return;
-    }
-    const __half *x = X + m * ldx;
-
-    // ---- pass 1: index bits 0..5 ------------------------------------------------------------------
-    uint4 rx[2];
-    float4 rs[4];
-    rx[0] = *reinterpret_cast<const uint4 *>(x + 16 * t);
-    rx[1] = *reinterpret_cast<const uint4 *>(x + 16 * t + 8);
-    if (HAS_PRE) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) rs[q] = *reinterpret_cast<const float4 *>(pre + 16 * t + 4 * q);
-    }
-    const float c0 = (lane & 1) ? -1.f : 1.f, c1 = (lane & 2) ? -1.f : 1.f;
-    float v[16];
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        union { uint4 u; half2v h[4]; } raw;
-        raw.u = rx[j];
-        if (HAS_PRE) {
-            const float4 s0 = rs[2 * j], s1 = rs[2 * j + 1];
-            pair_level(raw.h[0], s0.x, s0.y, v[8 * j], v[8 * j + 1]);
-            pair_level(raw.h[1], s0.z, s0.w, v[8 * j + 2], v[8 * j + 3]);
-            pair_level(raw.h[2], s1.x, s1.y, v[8 * j + 4], v[8 * j + 5]);
-            pair_level(raw.h[3], s1.z, s1.w, v[8 * j + 6], v[8 * j + 7]);
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) pair_level(raw.h[e], v[8 * j + 2 * e], v[8 * j + 2 * e + 1]);
-        }
-    }
-    butterflies_from<4, 2>(v);
-    lane_butterfly16<0xB1>(v, c0);
-    lane_butterfly16<0x4E>(v, c1);
-    {
-        float *d = row + wg4096_pos(16 * t);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) *reinterpret_cast<float4 *>(d + 4 * q) = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
-    }
-    // (barriers without the fence of __syncthreads: that would also wait for the warming loads below)
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    barrier_nofence();
-    // warming the memory-side cache for the kernel that follows (see fwht4096_wave_kernel): one word of every
-    // 128-byte line of the region, shared among the threads of the launch, ordinary loads, never looked at
-    uint32_t warm_acc = 0;
-    if (warm) {
-        const int64_t nthreads = (int64_t)gridDim.x * 256;
-        for (int64_t l = (int64_t)blockIdx.x * 256 + t; l < warm_lines; l += nthreads) warm_acc ^= warm[l * 32];
-    }
-
-    // ---- pass 2: index bits 6..11 -----------------------------------------------------------------
-    float *col = row + wg4096_pos((t >> 2) + 1024 * (t & 3));
-#pragma unroll
-    for (int r = 0; r < 16; ++r) v[r] = col[72 * r];     // element + 64 r sits 64 r + 4 * 2 r floats further
-    butterflies<4>(v);
-    lane_butterfly16<0xB1>(v, c0);
-    lane_butterfly16<0x4E>(v, c1);
-    float amax = 0.f;
-#pragma unroll
-    for (int r = 0; r < 16; r += 2) amax = fmaxf(fmaxf(amax, fabsf(v[r])), fabsf(v[r + 1]));
-#pragma unroll
-    for (int r = 0; r < 16; ++r) col[72 * r] = v[r];     // the same thread read these: nothing to wait for
-    amax = max_of_wave(amax);
-    if (lane == 0) red[t >> 6] = amax;
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    barrier_nofence();
-    amax = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-    const float delta = (amax == 0.f) ? 1.f : (clip * amax) / 7.f;
-    const float inv_delta = 1.f / delta;
-    if (t == 0) scale_out[m] = (amax == 0.f) ? 1.f : delta * post_scale;
-
-    // ---- quantise.  The 16 values of group g = i >> 4 carry the sign (-1)^(popcount(g & 3) + popcount(g >> 6)):
-    // lane bits 0, 1 of their writer in pass 1 were g & 3, in pass 2 g >> 6.
-    auto signed_inv = [&](int g) { return (__builtin_popcount((g & 3) | ((g >> 6) << 2)) & 1) ? -inv_delta : inv_delta; };
-    if constexpr (F6) {
-        if (t < K / 32) {
-            const float *s32 = row + 36 * t + 8 * (t >> 5);
-            quant_store_f6_piece(s32, signed_inv(2 * t), signed_inv(2 * t + 1), Q, (rows + 7) >> 3, m, t);
-        }
-    } else {
-        const float *s16 = row + wg4096_pos(16 * t);
-        const float sd = signed_inv(t);
-        uint32_t *q = reinterpret_cast<uint32_t *>(Q + m * (int64_t)(K / 2));
-        uint32_t w2[2];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const float4 a = *reinterpret_cast<const float4 *>(s16 + 8 * h);
-            const float4 b = *reinterpret_cast<const float4 *>(s16 + 8 * h + 4);
-            const float y[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-            w2[h] = quant_pack8(y, sd);
-        }
-        *reinterpret_cast<uint2 *>(q + 2 * t) = make_uint2(w2[0], w2[1]);
-    }
-    asm volatile("" ::"v"(warm_acc));                    // keeps the warming loads; they returned long ago
-}
-
 __global__ __launch_bounds__(256) void fill_f32_kernel(float *__restrict__ dst, int64_t n, float value)
 {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i < n) dst[i] = value;
 }
 
-// One workgroup per row -- or, for K = 14336 with 256 threads, no gate row and at least two rounds of rows, as many
-// workgroups as the chip holds at once (the fp32 row in LDS allows two per CU), each walking over rows and
-// fetching its next row while it works on the current one (2048 rows: 36.2 -> 34.4 us, 16384: 264 -> 243 us).
+// One workgroup per row.
 template <int K, int NT, bool F6, bool GATE>
 hipError_t launch_row_kernel(const void *X, int64_t rows, int64_t ldx, const float *pre, float clip, float post_scale,
                              uint8_t *Q, float *scale_out, const __half *gate, int64_t ldg, hipStream_t st,
                              const void *warm = nullptr, size_t warm_bytes = 0)
 {
     constexpr size_t lds = sizeof(float) * padded_len(K);
-    const int64_t total = F6 ? (rows + 63) / 64 * 64 : rows;
-    int64_t grid = total;
-    bool stream = false;
-    if constexpr (K == 14336 && NT == 256 && !GATE) {
-        const int64_t resident = (int64_t)compute_units() * (int64_t)(160 * 1024 / lds) / 64 * 64;
-        stream = resident >= 64 && total >= 2 * resident;
-        if (int64_t f; tuned(kTuneFwhtStream, f)) stream = resident >= 64 && f != 0;
-        if (stream) grid = resident < total ? resident : total;
-    }
-    constexpr auto walking = fwht_quant_kernel<K, NT, F6, GATE, (K == 14336 && NT == 256 && !GATE)>;
-    constexpr auto one_row = fwht_quant_kernel<K, NT, F6, GATE, false>;
-    auto kern = stream ? walking : one_row;
+    const int64_t grid = F6 ? (rows + 63) / 64 * 64 : rows;
+    constexpr auto kern = fwht_quant_kernel<K, NT, F6, GATE>;
     if (lds > 48 * 1024) {
-        hipError_t e = stream ? allow_dynamic_lds<walking>((int)lds) : allow_dynamic_lds<one_row>((int)lds);
+        hipError_t e = allow_dynamic_lds<kern>((int)lds);
         if (e != hipSuccess) return e;
     }
     // the hint is honoured from 256 workgroups on (a launch of a few rows cannot move megabytes on the side)
@@ -793,19 +568,12 @@ hipError_t launch_one(const void *X, int64_t rows, int64_t ldx, const float *pre
     constexpr int groups = K / 16;
     constexpr int NT = NT_FORCE ? NT_FORCE : (groups >= 256 ? 256 : (groups >= 128 ? 128 : 64));
     // Long rows: more threads per row where they pay (measured, one row / 2048 rows, 256 threads against the
-    // choice below).  K = 8192: 5.6 -> 4.1 us / 19.2 -> 16.3 us; 16384: 9.0 -> 6.0 / 46.6 -> 34.4; 28672 (one
-    // workgroup per CU whatever its size): 23.5 -> 9.7 / 257 -> 87; 32768: 24.9 -> 19.9 / 276 -> 222.  K = 14336
-    // and 7168 only while every row still has a CU to itself (14336: 8.0 -> 6.1 us for one row with 1024 threads,
-    // 9.7 -> 7.9 us for 256 rows with 512, but 42 -> 57 us for 2048 rows: two small workgroups per CU overlap
-    // better than one large one).
+    // choice below).  K = 16384: 9.0 -> 6.0 / 46.6 -> 34.4; 28672 (one workgroup per CU whatever its size): 23.5 ->
+    // 9.7 / 257 -> 87; 32768: 24.9 -> 19.9 / 276 -> 222.  K = 7168 only while every row still has a CU to itself (two
+    // small workgroups per CU overlap better than one large one).
     if constexpr (NT_FORCE == 0) {
-        if constexpr (K == 8192) return launch_one<K, F6, 512>(X, rows, ldx, pre, clip, post_scale, Q, scale_out, st);
         if constexpr (K == 16384 || K == 28672 || K == 32768)
             return launch_one<K, F6, 1024>(X, rows, ldx, pre, clip, post_scale, Q, scale_out, st);
-        if constexpr (K == 14336) {
-            if (rows <= 64) return launch_one<K, F6, 1024>(X, rows, ldx, pre, clip, post_scale, Q, scale_out, st);
-            if (rows <= 256) return launch_one<K, F6, 512>(X, rows, ldx, pre, clip, post_scale, Q, scale_out, st);
-        }
         if constexpr (K == 7168) {
             if (rows <= 512) return launch_one<K, F6, 512>(X, rows, ldx, pre, clip, post_scale, Q, scale_out, st);
         }
@@ -821,13 +589,8 @@ hipError_t launch_one_gated(const void *X, int64_t rows, int64_t ldx, const floa
     constexpr int groups = K / 16;
     constexpr int NT = NT_FORCE ? NT_FORCE : (groups >= 256 ? 256 : (groups >= 128 ? 128 : 64));
     if constexpr (NT_FORCE == 0) {                          // threads per row as in launch_one
-        if constexpr (K == 8192) return launch_one_gated<K, F6, 512>(X, rows, ldx, pre, clip, post_scale, Q, scale_out, gate, ldg, st);
         if constexpr (K == 16384 || K == 28672)
             return launch_one_gated<K, F6, 1024>(X, rows, ldx, pre, clip, post_scale, Q, scale_out, gate, ldg, st);
-        if constexpr (K == 14336) {
-            if (rows <= 64) return launch_one_gated<K, F6, 1024>(X, rows, ldx, pre, clip, post_scale, Q, scale_out, gate, ldg, st);
-            if (rows <= 256) return launch_one_gated<K, F6, 512>(X, rows, ldx, pre, clip, post_scale, Q, scale_out, gate, ldg, st);
-        }
         if constexpr (K == 7168) {
             if (rows <= 512) return launch_one_gated<K, F6, 512>(X, rows, ldx, pre, clip, post_scale, Q, scale_out, gate, ldg, st);
         }
@@ -873,7 +636,7 @@ hipError_t launch_one_ex(const void *X, int64_t rows, int64_t ldx, const float *
 // K = 4096: below this many rows the wave-per-row kernel leaves most of the chip idle (4 rows per workgroup)
 // and the workgroup-per-row kernel has the shorter critical path.
 constexpr int64_t kWaveKernelMinRows = 1024;   // measured: 3.3 - 4.8 us against 4.2 - 5.9 us up to 512 rows, equal at 1024
-constexpr int64_t kWgKernelMaxRows = 3072;     // the two-pass workgroup-per-row kernel up to here (see launch_fwht_quant)
+constexpr int64_t kTwoPassMaxRows4096 = 3072;  // the two-pass workgroup-per-row kernel up to here (see launch_fwht_quant)
 
 template <bool HAS_PRE, bool F6, bool MASKED = false, bool STAGED = false>
 hipError_t launch_wave4096(const void *X, int64_t rows, int64_t ldx, const float *pre, float clip, float post_scale,
@@ -891,36 +654,18 @@ hipError_t launch_wave4096(const void *X, int64_t rows, int64_t ldx, const float
     return hipGetLastError();
 }
 
-template <bool HAS_PRE, bool F6>
-hipError_t launch_wg4096(const void *X, int64_t rows, int64_t ldx, const float *pre, float clip, float post_scale,
-                         uint8_t *Q, float *scale_out, hipStream_t st, const void *warm, size_t warm_bytes)
-{
-    constexpr size_t lds = kWg4096Floats * sizeof(float);
-    const unsigned blocks = F6 ? (unsigned)((rows + 63) / 64 * 64) : (unsigned)rows;
-    const bool warms = warm && warm_bytes >= 128 && blocks >= 256;
-    hipLaunchKernelGGL((fwht4096_wg_kernel<HAS_PRE, F6>), dim3(blocks), dim3(256), lds, st, static_cast<const __half *>(X), ldx,
-                       rows, pre, clip, post_scale, Q, scale_out, warms ? static_cast<const uint32_t *>(warm) : nullptr,
-                       (int64_t)(warm_bytes / 128));
-    return hipGetLastError();
-}
-
 hipError_t launch_fwht_quant(const void *X, int64_t rows, int64_t K, int64_t ldx, const float *pre,
                              float clip, float post_scale, uint8_t *Q, float *scale_out, hipStream_t st, bool f6,
                              const void *warm, size_t warm_bytes)
 {
     int pick = 0;
     if (int64_t f; tuned(kTuneFwht4096, f)) pick = (int)f;
-    // K = 4096: a workgroup of four waves per row in two passes of six bits up to kWgKernelMaxRows rows (every row
-    // count measured from 1 to 3072: 3.1 / 3.4 / 4.7 / 6.1 / 9.0 / 12.5 us for 1 / 64 / 512 / 1024 / 2048 / 3072 rows
-    // against 3.5 / 3.7 / 5.3 / 6.8 / 9.5 / 13.4 for the general workgroup-per-row kernel and 4.4 / 5.4 / 6.3 / 7.2 /
-    // 9.4 / 14.0 for a wave per row); a wave per row beyond (16384 rows: 52 against 57 us)
-    const bool wg_ok = !pre || (reinterpret_cast<uintptr_t>(pre) & 15u) == 0;
-    if (K == 4096 && wg_ok && (pick == 5 || (pick == 0 && rows <= kWgKernelMaxRows))) {
-        if (pre) return f6 ? launch_wg4096<true, true>(X, rows, ldx, pre, clip, post_scale, Q, scale_out, st, warm, warm_bytes)
-                           : launch_wg4096<true, false>(X, rows, ldx, pre, clip, post_scale, Q, scale_out, st, warm, warm_bytes);
-        return f6 ? launch_wg4096<false, true>(X, rows, ldx, pre, clip, post_scale, Q, scale_out, st, warm, warm_bytes)
-                  : launch_wg4096<false, false>(X, rows, ldx, pre, clip, post_scale, Q, scale_out, st, warm, warm_bytes);
-    }
+    // One workgroup per row in two passes: at every row count for 2048, 8192 and 14336 (see fwht_two_pass.hip), for 4096
+    // up to kTwoPassMaxRows4096 (every row count measured from 1 to 3072: 3.1 / 3.4 / 4.7 / 6.1 / 9.0 / 12.5 us for 1 /
+    // 64 / 512 / 1024 / 2048 / 3072 rows against 3.5 / 3.7 / 5.3 / 6.8 / 9.5 / 13.4 for the general workgroup-per-row
+    // kernel and 4.4 / 5.4 / 6.3 / 7.2 / 9.4 / 14.0 for a wave per row); a wave per row beyond (16384 rows: 52 against 57 us)
+    if (K == 2048 || K == 8192 || K == 14336 || (K == 4096 && (pick == 5 || (pick == 0 && rows <= kTwoPassMaxRows4096))))
+        return launch_fwht_two_pass(X, rows, K, ldx, pre, clip, post_scale, Q, scale_out, nullptr, 0, st, f6, warm, warm_bytes);
     if (K == 4096 && (pick == 1 || pick == 3 || pick == 4 || (pick == 0 && rows > kWaveKernelMinRows))) {
         constexpr uint32_t all = 0xFFFFFFFFu;
         // factors through LDS (one copy per workgroup) unless the knob asks for per-wave vector loads (4)
@@ -935,18 +680,18 @@ hipError_t launch_fwht_quant(const void *X, int64_t rows, int64_t K, int64_t ldx
     if (f6) {
 #define SR_CASE(KK) case KK: return launch_one<KK, true>(X, rows, ldx, pre, clip, post_scale, Q, scale_out, st, warm, warm_bytes);
         switch (K) {                                    // K % 128 == 0
-            SR_CASE(128) SR_CASE(256) SR_CASE(512) SR_CASE(1024) SR_CASE(2048)
-            SR_CASE(4096) SR_CASE(8192) SR_CASE(16384) SR_CASE(32768)
-            SR_CASE(896) SR_CASE(1792) SR_CASE(3584) SR_CASE(7168) SR_CASE(14336) SR_CASE(28672)
+            SR_CASE(128) SR_CASE(256) SR_CASE(512) SR_CASE(1024)
+            SR_CASE(4096) SR_CASE(16384) SR_CASE(32768)
+            SR_CASE(896) SR_CASE(1792) SR_CASE(3584) SR_CASE(7168) SR_CASE(28672)
             default: return hipErrorInvalidValue;
         }
 #undef SR_CASE
     }
 #define SR_CASE(KK) case KK: return launch_one<KK>(X, rows, ldx, pre, clip, post_scale, Q, scale_out, st);
     switch (K) {
-        SR_CASE(64) SR_CASE(128) SR_CASE(256) SR_CASE(512) SR_CASE(1024) SR_CASE(2048)
-        SR_CASE(4096) SR_CASE(8192) SR_CASE(16384) SR_CASE(32768)
-        SR_CASE(448) SR_CASE(896) SR_CASE(1792) SR_CASE(3584) SR_CASE(7168) SR_CASE(14336) SR_CASE(28672)
+        SR_CASE(64) SR_CASE(128) SR_CASE(256) SR_CASE(512) SR_CASE(1024)
+        SR_CASE(4096) SR_CASE(16384) SR_CASE(32768)
+        SR_CASE(448) SR_CASE(896) SR_CASE(1792) SR_CASE(3584) SR_CASE(7168) SR_CASE(28672)
         default: return hipErrorInvalidValue;
     }
 #undef SR_CASE
@@ -968,16 +713,18 @@ hipError_t launch_fwht_quant_ex(const void *X, int64_t rows, int64_t K, int64_t 
         return f6 ? launch_wave4096<false, true, true>(X, rows, ldx, pre, clip, post_scale, Q, scale_out, st, ex.had_mask)
                   : launch_wave4096<false, false, true>(X, rows, ldx, pre, clip, post_scale, Q, scale_out, st, ex.had_mask);
     }
-    // the gate alone (the FFN down-projection input) goes through the plain kernel: fewer passes over the row
-    // than the general kernel below (K = 14336, 2048 rows: 52 against 68 us)
+    // the gate alone (the FFN down-projection input) goes through the plain kernels: fewer passes over the row
+    // than the general kernel below (K = 14336, 2048 rows: 38 against 68 us)
     if (ex.gate && ex.n_grid == 0 && (ex.had_mask == 0xFFFFFFFFu || !is_pow2(K))) {
 #define SR_CASE(KK)                                                                                                      \
     case KK:                                                                                                             \
         return f6 ? launch_one_gated<KK, true>(X, rows, ldx, pre, clip, post_scale, Q, scale_out, ex.gate, ex.ldg, st)  \
                   : launch_one_gated<KK, false>(X, rows, ldx, pre, clip, post_scale, Q, scale_out, ex.gate, ex.ldg, st);
         switch (K) {                                    // the FFN widths; other K take the general kernel
-            SR_CASE(1024) SR_CASE(2048) SR_CASE(4096) SR_CASE(8192) SR_CASE(16384)
-            SR_CASE(3584) SR_CASE(7168) SR_CASE(14336) SR_CASE(28672)
+            case 2048: case 4096: case 8192: case 14336:
+                return launch_fwht_two_pass(X, rows, K, ldx, pre, clip, post_scale, Q, scale_out, ex.gate, ex.ldg, st, f6, nullptr, 0);
+            SR_CASE(1024) SR_CASE(16384)
+            SR_CASE(3584) SR_CASE(7168) SR_CASE(28672)
             default: break;
         }
 #undef SR_CASE

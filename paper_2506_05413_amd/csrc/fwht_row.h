@@ -329,7 +329,8 @@ struct RowLoad {
 
 // ALWAYS: threads beyond the row load group 0 instead of nothing, so that the loads sit in straight-line code
 // (for a caller that issues further loads behind these and wants the compiler to count them in its waits).
-// PARTS: 1 = the row (and its gate row), 2 = the values of `pre`, 3 = both
+// PARTS: 1 = the row (and its gate row), 2 = the values of `pre` if there is one, 4 = of a `pre` that is known to be there
+// (no branch between the loads)
 template <int K, int NT, bool ALWAYS = false, bool GATE = false, int PARTS = 3>
 __device__ __forceinline__ void row_load(const __half *__restrict__ x, const float *__restrict__ pre, const int t,
                                          RowLoad<K, NT> &ld, const __half *__restrict__ gate = nullptr)
@@ -338,7 +339,7 @@ __device__ __forceinline__ void row_load(const __half *__restrict__ x, const flo
     for (int i = 0; i < RowLoad<K, NT>::NG; ++i) {
         int g = t + i * NT;
         if (ALWAYS) g = g < K / 16 ? g : 0;
-        if (g < K / 16) {
+        if (K / 16 % NT == 0 || g < K / 16) {
             if constexpr (PARTS & 1) {
                 ld.u[i][0] = *reinterpret_cast<const uint4 *>(x + 16 * g);
                 ld.u[i][1] = *reinterpret_cast<const uint4 *>(x + 16 * g + 8);
@@ -347,8 +348,8 @@ __device__ __forceinline__ void row_load(const __half *__restrict__ x, const flo
                     ld.gu[i][1] = *reinterpret_cast<const uint4 *>(gate + 16 * g + 8);
                 }
             }
-            if constexpr (PARTS & 2) {
-                if (pre) {
+            if constexpr (PARTS & 6) {
+                if ((PARTS & 4) || pre) {
 #pragma unroll
                     for (int q = 0; q < 4; ++q) ld.p[i][q] = *reinterpret_cast<const float4 *>(pre + 16 * g + 4 * q);
                 }
@@ -357,12 +358,50 @@ __device__ __forceinline__ void row_load(const __half *__restrict__ x, const flo
     }
 }
 
+// The 16 loaded values of a thread, times silu(gate) and / or the factors, after the butterfly level of index bit 0.
+template <bool GATE>
+__device__ __forceinline__ void first_level16(const uint4 (&u)[2], const uint4 (&gu)[2], const float4 (&p)[4],
+                                              const bool has_pre, float (&v)[16])
+{
+    union { uint4 u[2]; half2v h[8]; } raw;
+    raw.u[0] = u[0];
+    raw.u[1] = u[1];
+    float f[16];                                       // per-element factor: silu(gate) and / or 1 / s
+    if constexpr (GATE) {
+        union { uint4 u[2]; half2v h[8]; } graw;
+        graw.u[0] = gu[0];
+        graw.u[1] = gu[1];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            // silu(g) = g / (1 + exp(-g)); exp(-g) = inf for very negative g gives g * 0 = 0
+            const _Float16 gh = graw.h[e >> 1][e & 1];
+            const float sig = __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(__builtin_fmaf((float)gh, -1.44269504088896341f, 0.f)));
+            f[e] = __builtin_fmaf((float)gh, sig, 0.f);
+        }
+    }
+    if (GATE || has_pre) {
+        if (has_pre) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float4 sc = p[q];
+                if constexpr (GATE) { f[4 * q] *= sc.x; f[4 * q + 1] *= sc.y; f[4 * q + 2] *= sc.z; f[4 * q + 3] *= sc.w; }
+                else { f[4 * q] = sc.x; f[4 * q + 1] = sc.y; f[4 * q + 2] = sc.z; f[4 * q + 3] = sc.w; }
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) pair_level(raw.h[e], f[2 * e], f[2 * e + 1], v[2 * e], v[2 * e + 1]);
+    } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) pair_level(raw.h[e], v[2 * e], v[2 * e + 1]);
+    }
+}
+
 // GATE: x = silu(gate) * x in fp32 before the smoothing factors (the down-projection input of a gated FFN,
 // paper Fig. 2: sigma(gate) (.) up, then 1/s, Hadamard, quantiser).
 struct NoHook { __device__ __forceinline__ void operator()() const {} };
 
-// after_pass1: called once the loaded values have been consumed (a caller that walks over several rows issues the
-// loads of its next row there, into the same RowLoad, so that they travel during the rest of this row's work).
+// after_pass1: called once the loaded values have been consumed (for loads that should travel during the rest of the
+// row's work).
 template <int K, int NT, bool GATE = false, typename Hook = NoHook>
 __device__ __forceinline__ float rotate_loaded_row_absmax(const RowLoad<K, NT> &ld, const float *__restrict__ pre,
                                                           float *row, float *red, const int t, Hook after_pass1 = Hook{})
@@ -376,39 +415,9 @@ __device__ __forceinline__ float rotate_loaded_row_absmax(const RowLoad<K, NT> &
 #pragma unroll
     for (int i = 0; i < RowLoad<K, NT>::NG; ++i) {
         const int g = t + i * NT;
-        if (g < K / 16) {
-            union { uint4 u[2]; half2v h[8]; } raw;
-            raw.u[0] = ld.u[i][0];
-            raw.u[1] = ld.u[i][1];
+        if (K / 16 % NT == 0 || g < K / 16) {
             float v[16];
-            float f[16];                                       // per-element factor: silu(gate) and / or 1 / s
-            if constexpr (GATE) {
-                union { uint4 u[2]; half2v h[8]; } graw;
-                graw.u[0] = ld.gu[i][0];
-                graw.u[1] = ld.gu[i][1];
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    // silu(g) = g / (1 + exp(-g)); exp(-g) = inf for very negative g gives g * 0 = 0
-                    const _Float16 gh = graw.h[e >> 1][e & 1];
-                    const float sig = __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(__builtin_fmaf((float)gh, -1.44269504088896341f, 0.f)));
-                    f[e] = __builtin_fmaf((float)gh, sig, 0.f);
-                }
-            }
-            if (GATE || pre) {
-                if (pre) {
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const float4 sc = ld.p[i][q];
-                        if constexpr (GATE) { f[4 * q] *= sc.x; f[4 * q + 1] *= sc.y; f[4 * q + 2] *= sc.z; f[4 * q + 3] *= sc.w; }
-                        else { f[4 * q] = sc.x; f[4 * q + 1] = sc.y; f[4 * q + 2] = sc.z; f[4 * q + 3] = sc.w; }
-                    }
-                }
-#pragma unroll
-                for (int e = 0; e < 8; ++e) pair_level(raw.h[e], f[2 * e], f[2 * e + 1], v[2 * e], v[2 * e + 1]);
-            } else {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) pair_level(raw.h[e], v[2 * e], v[2 * e + 1]);
-            }
+            first_level16<GATE>(ld.u[i], ld.gu[i], ld.p[i], pre != nullptr, v);
             butterflies_from<4, 2>(v);
             float *dst = row + pad(16 * g);
 #pragma unroll

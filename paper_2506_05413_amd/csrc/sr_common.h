@@ -111,6 +111,12 @@ hipError_t launch_fwht_quant(const void *X_f16, int64_t rows, int64_t K, int64_t
                              uint8_t *Q, float *scale_out, hipStream_t st, bool f6 = false,
                              const void *warm = nullptr, size_t warm_bytes = 0);
 
+// The same (gate: x = silu(gate) * X, row stride ldg, when set) for K = 2048, 4096, 8192 and 14336 by one workgroup per row
+// in two passes (see fwht_two_pass.hip); the hint is honoured from 256 workgroups on.
+hipError_t launch_fwht_two_pass(const void *X_f16, int64_t rows, int64_t K, int64_t ldx, const float *pre, float clip,
+                                float post_scale, uint8_t *Q, float *scale_out, const __half *gate, int64_t ldg,
+                                hipStream_t st, bool f6, const void *warm, size_t warm_bytes);
+
 // Optional extras of the row kernel (see fwht_quant.hip).
 constexpr int kMaxClipGrid = 32;
 struct RowExtras {
