@@ -61,13 +61,18 @@ constexpr int ROWB = 128;  // packed bytes per row per stage (256 codes = one 12
 // memory pipeline going across the tile boundary -- the first stage of the next tile is in flight while the
 // finished tile is dequantised, transposed and stored, and the stores (fire and forget) drain under the next
 // tile's MFMAs.  One launch of <= (CUs x workgroups per CU) workgroups instead of one workgroup per tile.
-template <int BM, int BN, int WGM, int WGN>
-__global__ __launch_bounds__(WGM * WGN * 64) void gemm_w4a4_kernel(
+//
+// KS = 2: two sets of waves share a tile, each multiplying half of every stage (the 64-code sub-steps 2 kw, 2 kw + 1),
+// and add their sums through LDS at the end, each finishing half of the channels.
+template <int BM, int BN, int WGM, int WGN, int KS = 1>
+__global__ __launch_bounds__(WGM * WGN * KS * 64) void gemm_w4a4_kernel(
     const uint8_t *__restrict__ Xq, const float *__restrict__ xs, const uint8_t *__restrict__ Wq,
     const float *__restrict__ ws, int M, int N, int K, void *__restrict__ Yv, int64_t ldy, int out_i32,
     int tiles_m, int tiles_n, int xcd_m)
 {
-    constexpr int NWAVE = WGM * WGN;                 // (two ring stages of LDS)
+    static_assert(KS == 1 || KS == 2, "waves per tile position");
+    constexpr int NWAVE = WGM * WGN * KS;
+    constexpr int SLOTS = KS == 2 ? 4 : 2;           // ring stages of LDS
     constexpr int WM = BM / WGM, WN = BN / WGN;      // wave tile
     constexpr int FM = WM / 32, FN = WN / 32;        // 32 x 32 MFMA tiles per wave
     constexpr int REGIONS = (BM + BN) / 8;           // 1 KB DMA regions (8 rows x 128 B) per stage
@@ -80,7 +85,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_w4a4_kernel(
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave % WGM, wn = wave / WGM;
+    const int wm = wave % WGM, wn = wave / WGM % WGN, kw = wave / (WGM * WGN);
     const int total = tiles_m * tiles_n;
 
     // workgroups are dealt round-robin to the 8 XCDs; with the XCD split on, the grid size is a multiple of 8,
@@ -210,13 +215,15 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_w4a4_kernel(
     constexpr std::integral_constant<int, 3> P3{};
 
     // epilogue staging: one piece = 32 tokens x WN channels of fp16 per wave, in ring slot 1
-    constexpr int PIECE = 32 * (WN * 2 + 16);
-    static_assert(NWAVE * PIECE <= STAGE_BYTES, "epilogue staging must fit one ring slot");
+    // (KS = 2: of WN / 2 channels, in the exchange area)
+    constexpr int EN = FN / KS;                      // 32-channel tiles a wave finishes
+    constexpr int PIECE = 32 * (EN * 64 + 16);
+    static_assert(FN % KS == 0 && NWAVE * PIECE <= STAGE_BYTES, "epilogue staging must fit one ring slot");
 
     // Token and channel scales of the tile's epilogue are fetched at the start of the tile (10 loads per lane for
     // a 64 x 64 wave tile) -- fetched at the tile boundary, their latency was exposed on every tile.
     float sx[FM];
-    float4 sw[FN][4];
+    float4 sw[EN][4];
     // (With the raw int32 output the host passes readable stand-ins for the two scale vectors, so the loads
     // need no branch -- a branch made the compiler wait for them at once; the values are then not used.)
     auto load_scales = [&](int m0, int n0) {
@@ -226,10 +233,10 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_w4a4_kernel(
             sx[j] = xs[m < M ? m : M - 1];
         }
 #pragma unroll
-        for (int i = 0; i < FN; ++i)
+        for (int i = 0; i < EN; ++i)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const int n = n0 + wn * WN + i * 32 + q * 8 + fg * 4;
+                const int n = n0 + wn * WN + (kw * EN + i) * 32 + q * 8 + fg * 4;
                 sw[i][q] = *reinterpret_cast<const float4 *>(ws + (n < N ? n : N - 4));
             }
     };
@@ -238,8 +245,8 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_w4a4_kernel(
     int m0, n0;
     tile_origin(v, m0, n0);
     set_sources(m0, n0);
-    issue(0, 0);
-    issue(ns > 1 ? 1 : 0, 1);
+#pragma unroll
+    for (int i = 0; i < SLOTS; ++i) issue(i < ns ? i : ns - 1, i);
     for (;;) {
 #pragma unroll
         for (int i = 0; i < FN; ++i)
@@ -252,18 +259,32 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_w4a4_kernel(
         // complete in order among themselves and the RPW loads of stage 1 are the youngest, so an unfinished
         // older load would leave more than RPW outstanding -- however many stores of the previous tile are
         // still on their way (stores and loads may overtake each other).
-        wait_vmcnt<RPW>();
+        // (KS = 2: the same with the three stages behind stage 0.)
+        wait_vmcnt<(SLOTS - 1) * RPW>();
         barrier_nofence();
         load_scales(m0, n0);                         // used after the K loop, whose first wait covers them
         Ops o0, o1;
         Frag fa, fb;                                 // fragments of even / odd sub-steps
-        load_frags(fa, 0, 0);
-        load_frags(fb, 0, 1);
+        load_frags(fa, 0, 2 * kw);
+        load_frags(fb, 0, 2 * kw + 1);
         widen_all(fa, o0);
         int slot = 0;
         // Every stage runs the same branch-free body.  Past the end of K the pipeline keeps reading (stale,
         // in-bounds) LDS and re-fetching the last stage; those fragments are widened but never multiplied.
-        for (int s = 0; s < ns; ++s) {
+        if constexpr (KS == 2) {
+            for (int s = 0; s < ns; ++s) {
+                const int nslot = (slot + 1) & (SLOTS - 1);
+                const int st4 = s + SLOTS < ns ? s + SLOTS : ns - 1;
+                // stage s + 1 has landed (at most the two behind it are on their way), and every wave's reads of stage s
+                // have returned: its slot takes stage s + 4
+                asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((SLOTS - 2) * RPW) : "memory");
+                barrier_nofence();
+                ssub(P0, o0, o1, fb, fa, nslot, 2 * kw, st4, slot);
+                ssub(P1, o1, o0, fa, fb, nslot, 2 * kw + 1, st4, slot);
+                slot = nslot;
+            }
+        }
+        for (int s = 0; KS == 1 && s < ns; ++s) {
             const int nslot = slot ^ 1;
             const int st2 = s + 2 < ns ? s + 2 : ns - 1;
             ssub(P2, o0, o1, fb, fa, slot, 2, st2, nslot);
@@ -286,7 +307,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_w4a4_kernel(
 #pragma unroll
         for (int j = 0; j < FM; ++j) asm volatile("" : "+v"(sx[j]));
 #pragma unroll
-        for (int i = 0; i < FN; ++i)
+        for (int i = 0; i < EN; ++i)
 #pragma unroll
             for (int q = 0; q < 4; ++q)
                 asm volatile("" : "+v"(sw[i][q].x), "+v"(sw[i][q].y), "+v"(sw[i][q].z), "+v"(sw[i][q].w));
@@ -296,15 +317,55 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_w4a4_kernel(
             tile_origin(vn, m1, n1);
             set_sources(m1, n1);
             issue(0, 0);
+            if constexpr (KS == 2) issue(ns > 1 ? 1 : 0, 1);
         }
 #pragma unroll
         for (int j = 0; j < FM; ++j) sx[j] *= 1.f / 256.f;      // both operands carried a factor 16
-        store_wave_tile<FM, FN>(acc, smem + STAGE_BYTES + wave * PIECE, lane, m0 + wm * WM, n0 + wn * WN, M, N, sx, sw,
-                                Yv, ldy, out_i32);
+        if constexpr (KS == 2) {
+            // the sums of the other half of the channels go to the wave that finishes them (ring slots 2 and 3)
+            constexpr int PART = EN * FM * 16 * 256;             // bytes a wave hands over
+            static_assert(NWAVE * PART <= 2 * STAGE_BYTES && PIECE <= PART, "exchange area");
+            uint8_t *mine = smem + 2 * STAGE_BYTES + wave * PART + lane * 16;
+            uint8_t *other = smem + 2 * STAGE_BYTES + (wave ^ (WGM * WGN)) * PART;
+            v16i fin[EN][FM];
+#pragma unroll
+            for (int i = 0; i < EN; ++i)
+#pragma unroll
+                for (int j = 0; j < FM; ++j) {
+                    v16i give;
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) {
+                        fin[i][j][e] = kw ? acc[EN + i][j][e] : acc[i][j][e];
+                        give[e] = kw ? acc[i][j][e] : acc[EN + i][j][e];
+                    }
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        *reinterpret_cast<v4i *>(mine + ((i * FM + j) * 4 + q) * 1024) = v4i{give[4 * q], give[4 * q + 1], give[4 * q + 2], give[4 * q + 3]};
+                }
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            barrier_nofence();
+#pragma unroll
+            for (int i = 0; i < EN; ++i)
+#pragma unroll
+                for (int j = 0; j < FM; ++j)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const v4i o = *reinterpret_cast<const v4i *>(other + lane * 16 + ((i * FM + j) * 4 + q) * 1024);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) fin[i][j][4 * q + e] += o[e];
+                    }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            // (only this wave reads `other`: its staging may follow there)
+            store_wave_tile<FM, EN>(fin, other, lane, m0 + wm * WM, n0 + wn * WN + kw * EN * 32, M, N, sx, sw, Yv, ldy, out_i32);
+        } else {
+            store_wave_tile<FM, EN>(acc, smem + STAGE_BYTES + wave * PIECE, lane, m0 + wm * WM, n0 + wn * WN, M, N, sx, sw,
+                                    Yv, ldy, out_i32);
+        }
         if (!more) break;
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         barrier_nofence();                           // every wave has read its staging back: slot 1 is free
-        issue(ns > 1 ? 1 : 0, 1);
+#pragma unroll
+        for (int i = SLOTS / 2; i < SLOTS; ++i) issue(i < ns ? i : ns - 1, i);
         v = vn;
         m0 = m1;
         n0 = n1;
@@ -312,12 +373,12 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_w4a4_kernel(
     wait_vmcnt<0>();
 }
 
-template <int BM, int BN, int WGM, int WGN, int WG_PER_CU>
+template <int BM, int BN, int WGM, int WGN, int WG_PER_CU, int KS = 1>
 hipError_t launch_tile(const uint8_t *Xq, const float *xs, const uint8_t *Wq, const float *ws, int64_t M, int64_t N,
                        int64_t K, void *Y, int64_t ldy, int out_i32, hipStream_t st)
 {
-    constexpr auto kern = gemm_w4a4_kernel<BM, BN, WGM, WGN>;
-    constexpr int lds = 2 * (BM + BN) * ROWB;
+    constexpr auto kern = gemm_w4a4_kernel<BM, BN, WGM, WGN, KS>;
+    constexpr int lds = 2 * KS * (BM + BN) * ROWB;
     static_assert(lds * WG_PER_CU <= 160 * 1024, "LDS");
     if (lds > 48 * 1024) {
         hipError_t e = allow_dynamic_lds<kern>(lds);
@@ -337,7 +398,7 @@ hipError_t launch_tile(const uint8_t *Xq, const float *xs, const uint8_t *Wq, co
         xs = reinterpret_cast<const float *>(Xq);
         ws = reinterpret_cast<const float *>(Wq);
     }
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(WGM * WGN * 64), lds, st, Xq, xs, Wq, ws,
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(WGM * WGN * KS * 64), lds, st, Xq, xs, Wq, ws,
                        (int)M, (int)N, (int)K, Y, ldy, out_i32, tiles_m, tiles_n, xcd_m);
     return hipGetLastError();
 }
@@ -514,25 +575,35 @@ hipError_t launch_gemm_prefill(const uint8_t *Xq, const float *xs, const uint8_t
     }
     // What a launch costs, by configuration: with t tiles on c compute units, r = ceil(t / c) rounds and n = K / 256
     // stages,   fixed + per_round r + n (stage_round r + stage_tile t / c)   microseconds,
-    // fitted to 150 shapes (M 17 .. 4900, N 1024 .. 16000, K 2048 .. 14336).  Between the two large tiles the cheaper
-    // schedule of whole rounds decides (ties to the larger tile); another configuration replaces that choice where it is
-    // predicted at least 5 % faster: mostly below 500 rows, where 128 x 128 tiles leave CUs idle (29 x 4096 x 14336
-    // 47.6 -> 12.2 us, 52 x 2208 x 8192 28.7 -> 9.7, 172 x 3968 x 4096 17.3 -> 10.2, 445 x 3088 x 4096 18.3 -> 14.4).
+    // fitted to 77 shapes (M 17 .. 4100, N 1024 .. 14336, K 2048 .. 14336, weights from HBM; mean error 3 - 5 % for the large
+    // tiles and 64 x 64, 6 - 12 % for the others).  Between the two large tiles the cheaper schedule of whole rounds
+    // decides (ties to the larger tile); another configuration replaces that choice where it is predicted at least 6 %
+    // faster: mostly below 500 rows, where 128 x 128 tiles leave CUs idle (29 x 4096 x 14336 47.6 -> 12.2 us, 52 x 2208 x
+    // 8192 28.7 -> 9.7, 172 x 3968 x 4096 17.3 -> 10.2, 445 x 3088 x 4096 18.3 -> 14.4), and where 128 x 128 tiles make
+    // one round, which two sets of waves run faster than one (below).
     struct Config { int id, bm, bn; float fixed, per_round, stage_round, stage_tile; };
     static constexpr Config configs[] = {
-        {14, 128, 128, 4.86f, .55f, .675f, .153f},    // four waves of 64 x 64, two workgroups per CU
-        {15, 256, 128, 1.62f, 4.18f, .964f, .456f},   // eight waves of 64 x 64: while one wave of a SIMD is held up issuing
+        {14, 128, 128, 7.48f, -3.82f, 0.940f, 0.129f},// four waves of 64 x 64, two workgroups per CU
+        {15, 256, 128, 1.15f, 3.34f, 1.178f, 0.327f}, // eight waves of 64 x 64: while one wave of a SIMD is held up issuing
                                                       // LDS or DMA instructions, the other can issue MFMAs
-        {17, 128, 64, 3.62f, .31f, .477f, .128f},     // eight waves of 32 x 32, two workgroups per CU
-        {18, 192, 128, 2.18f, 2.86f, .977f, .328f},   // eight waves of 96 x 32
-        {19, 64, 128, 3.99f, .03f, .527f, .074f},     // eight waves of 32 x 32, two workgroups per CU
+        {17, 128, 64, 5.60f, -1.93f, 0.633f, 0.101f}, // eight waves of 32 x 32, two workgroups per CU
+        {18, 192, 128, 1.19f, 3.19f, 1.078f, 0.253f}, // eight waves of 96 x 32
+        {19, 64, 128, 5.74f, -2.35f, 0.686f, 0.064f}, // eight waves of 32 x 32, two workgroups per CU
+        // Two sets of four waves of 64 x 64, each with half of every stage, one workgroup per CU: two waves per SIMD on
+        // one 128 x 128 tile without widening anything twice, and a ring of four stages instead of two, which weights
+        // from HBM need.  512 x 4096 x 14336 52 -> 42 us, 1345 x 1632 x 8192 36.6 -> 25.6, 142 x 12832 x 8192 39.5 ->
+        // 30.2, 643 x 3424 x 4096 20.9 -> 16.3, 600 x 6144 x 4096 21.0 -> 17.6; with several rounds the two workgroups per
+        // CU of 14 overlap their tile boundaries and win (2048 x 14336 x 4096: 105 against 118 us).
+        // (Tried: workgroups starting at different places of K, against all of them asking for the same lines of every row
+        // at a time -- no difference at K = 4096, 8192 and 14336.)
+        {20, 128, 128, 1.30f, 4.00f, 0.551f, 0.324f},
         // operands straight into registers, K split over eight waves (gemm_packed_stream.hip)
-        {64064, 64, 64, 1.26f, 2.32f, .370f, .114f},
-        {48064, 48, 64, 1.25f, 2.22f, .327f, .088f},
-        {48032, 48, 32, 1.26f, 2.57f, .172f, .068f},
-        {32064, 32, 64, 2.62f, 1.99f, .248f, .062f},
-        {32032, 32, 32, 2.71f, .96f, .155f, .038f},
-        {32016, 32, 16, 2.04f, 1.05f, .114f, .021f},
+        {64064, 64, 64, 1.62f, 2.36f, 0.390f, 0.095f},
+        {48064, 48, 64, 1.64f, 2.04f, 0.365f, 0.054f},
+        {48032, 48, 32, 2.48f, 2.73f, 0.110f, 0.126f},
+        {32064, 32, 64, 2.57f, 3.11f, 0.208f, 0.071f},
+        {32032, 32, 32, 3.43f, 1.51f, 0.108f, 0.059f},
+        {32016, 32, 16, 2.65f, 1.54f, 0.068f, 0.045f},
     };
     const int64_t cus = compute_units();
     auto tiles = [&](const Config &c) { return ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn); };
@@ -542,7 +613,7 @@ hipError_t launch_gemm_prefill(const uint8_t *Xq, const float *xs, const uint8_t
     };
     auto area = [&](const Config &c) { return (tiles(c) + cus - 1) / cus * c.bm * c.bn; };
     const Config *best = area(configs[1]) <= area(configs[0]) ? &configs[1] : &configs[0];
-    float best_cost = .95f * cost(*best);
+    float best_cost = .94f * cost(*best);
     for (const Config &c : configs)
         if (const float v = cost(c); v < best_cost) { best = &c; best_cost = v; }
     for (const Config &c : configs)
@@ -550,6 +621,7 @@ hipError_t launch_gemm_prefill(const uint8_t *Xq, const float *xs, const uint8_t
     switch (best->id) {
         case 14: return launch_tile<128, 128, 2, 2, 2>(Xq, xs, Wq, ws, M, N, K, Y, ldy, out_i32, st);
         case 15: return launch_tile<256, 128, 4, 2, 1>(Xq, xs, Wq, ws, M, N, K, Y, ldy, out_i32, st);
+        case 20: return launch_tile<128, 128, 2, 2, 1, 2>(Xq, xs, Wq, ws, M, N, K, Y, ldy, out_i32, st);
         case 17: return launch_tile<128, 64, 4, 2, 2>(Xq, xs, Wq, ws, M, N, K, Y, ldy, out_i32, st);
         case 18: return launch_tile<192, 128, 2, 4, 1>(Xq, xs, Wq, ws, M, N, K, Y, ldy, out_i32, st);
         case 19: return launch_tile<64, 128, 2, 4, 2>(Xq, xs, Wq, ws, M, N, K, Y, ldy, out_i32, st);

@@ -11,7 +11,7 @@ from parity import check_output
 
 pytestmark = pytest.mark.gpu
 
-CONFIGS = [14, 15, 17, 18, 19, 64064, 48064, 48032, 32064, 32032, 32016]
+CONFIGS = [14, 15, 17, 18, 19, 20, 64064, 48064, 48032, 32064, 32032, 32016]
 SHAPES = [(17, 16, 256), (33, 80, 2304), (49, 208, 4352), (65, 48, 768), (200, 1040, 2560), (40, 4112, 4608), (70, 96, 192)]
 
 
