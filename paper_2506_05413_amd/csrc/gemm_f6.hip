@@ -486,18 +486,23 @@ hipError_t launch_gemm_f6(const uint8_t *X6, const float *xs, const uint8_t *W6,
         {16016, 16, 16, 2.70f, .22f, .019f, .016f},
     };
     const int64_t cus = compute_units();
+    auto rounds = [&](const Config &c) { return (((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn) + cus - 1) / cus; };
     auto cost = [&](const Config &c) {
         const int64_t tiles = ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
-        const float r = (float)((tiles + cus - 1) / cus), n = (float)(K / 128);
+        const float r = (float)rounds(c), n = (float)(K / 128);
         return c.fixed + c.per_round * r + n * (c.stage_round * r + c.stage_tile * (float)tiles / (float)cus);
     };
-    const Config *best = &configs[0];
-    float best_cost = cost(configs[0]), cost65 = 0.f;
-    for (const Config &c : configs) {
-        const float v = cost(c);
-        if (v < best_cost) { best = &c; best_cost = v; }
-        if (c.id == 65) cost65 = v;
-    }
+    // Between 256 x 256 and 256 x 128 tiles the cheaper schedule of whole rounds decides (the small tile, which moves more
+    // LDS bytes per product, with a handicap of 15 %); another configuration has to be predicted 10 % faster.  With weights
+    // from HBM the large tiles run closer to each other than the fit has them, and without the margin it took 192- and
+    // 128-row tiles where 256 x 256 is ahead: 1944 x 5648 x 4096 37.9 against 34.3 us, 935 x 12528 x 4096 39.7 against
+    // 35.9, 315 x 11056 x 8192 44.4 against 40.1.
+    const Config *best = rounds(configs[0]) * 100 <= rounds(configs[2]) * 50 * 115 / 100 ? &configs[0] : &configs[2];
+    const float cost65 = cost(configs[2]);
+    float best_cost = .9f * cost(*best);
+    for (const Config &c : configs)
+        if (const float v = cost(c); v < best_cost) { best = &c; best_cost = v; }
+    best_cost = cost(*best);
     int id = best->id;
     // the hint is worth several microseconds to the next launch (44 MB read ahead save it 4 us of 67)
     if (warm && warm_bytes >= ((size_t)1 << 20) && cost65 <= 1.15f * best_cost) id = 65;
