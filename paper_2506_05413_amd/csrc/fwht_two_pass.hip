@@ -91,21 +91,27 @@ struct TwoPass {
     static constexpr int RPOS = RSTRIDE + RSTRIDE / 32 * 4 + (KRON ? (RSTRIDE >> XSH) * EXTRA : 0);
     // sign that the 16 values of set g = i >> 4 carry into the quantiser: the lane bits of pass 1 were g & 3, those of
     // pass 2 the index bits Q0 .. Q0 + Q - 1
-    __device__ static __forceinline__ bool flipped(int g)
+    // (bits that `mask` leaves out are not transformed and flip nothing)
+    __device__ static __forceinline__ bool flipped(int g, uint32_t mask = 0xFFFFFFFFu)
     {
-        return __builtin_popcount((g & 3) | (((g >> (Q0 - 4)) & ((1 << Q) - 1)) << 2)) & 1;
+        const int i = (int)((uint32_t)(16 * g) & mask);
+        return __builtin_popcount(((i >> 4) & 3) | (((i >> Q0) & ((1 << Q) - 1)) << 2)) & 1;
     }
 };
 
-template <int K, int THREADS, bool HAS_PRE, bool F6, bool GATE>
+// MASKED: head-wise transform -- only the index bits set in had_mask are butterflied (uniform branches; powers of two).
+template <int K, int THREADS, bool HAS_PRE, bool F6, bool GATE, bool MASKED>
 __global__ __launch_bounds__((TwoPass<K, THREADS>::NT)) void fwht_two_pass_kernel(const __half *__restrict__ X, int64_t ldx, int64_t rows,
                                                                       const float *__restrict__ pre, float clip, float post_scale,
                                                                       uint8_t *__restrict__ Q, float *__restrict__ scale_out,
                                                                       const __half *__restrict__ gate, int64_t ldg,
-                                                                      const uint32_t *__restrict__ warm, int64_t warm_lines)
+                                                                      const uint32_t *__restrict__ warm, int64_t warm_lines,
+                                                                      uint32_t had_mask)
 {
     using S = TwoPass<K, THREADS>;
+    static_assert(!MASKED || (!GATE && !S::KRON), "head-wise: powers of two without a gate row");
     constexpr int NT = S::NT, NW = NT / 64;
+    const uint32_t mask = MASKED ? had_mask : 0xFFFFFFFFu;
     extern __shared__ __attribute__((aligned(16))) float row[];
     __shared__ float red[NW];
     const int t = threadIdx.x, lane = t & 63;
@@ -130,10 +136,25 @@ __global__ __launch_bounds__((TwoPass<K, THREADS>::NT)) void fwht_two_pass_kerne
         const int g = t + i * NT;
         if (K / 16 % NT == 0 || g < K / 16) {            // whole waves (K / 16 is a multiple of 64)
             float v[16];
-            first_level16<GATE>(ld.u[i], ld.gu[i], ld.p[i], HAS_PRE, v);
-            butterflies_from<4, 2>(v);
-            lane_butterfly<0>(v, c0);
-            lane_butterfly<1>(v, c1);
+            if constexpr (MASKED) {
+                union { uint4 u[2]; half2v h[8]; } raw;
+                raw.u[0] = ld.u[i][0];
+                raw.u[1] = ld.u[i][1];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const float4 f = HAS_PRE ? ld.p[i][q] : make_float4(1.f, 1.f, 1.f, 1.f);
+                    v[4 * q] = __builtin_fmaf((float)raw.h[2 * q][0], f.x, 0.f);
+                    v[4 * q + 1] = __builtin_fmaf((float)raw.h[2 * q][1], f.y, 0.f);
+                    v[4 * q + 2] = __builtin_fmaf((float)raw.h[2 * q + 1][0], f.z, 0.f);
+                    v[4 * q + 3] = __builtin_fmaf((float)raw.h[2 * q + 1][1], f.w, 0.f);
+                }
+                butterflies_masked<4>(v, mask & 15u);
+            } else {
+                first_level16<GATE>(ld.u[i], ld.gu[i], ld.p[i], HAS_PRE, v);
+                butterflies_from<4, 2>(v);
+            }
+            if (mask & 16u) lane_butterfly<0>(v, c0);
+            if (mask & 32u) lane_butterfly<1>(v, c1);
             float *d = row + S::pos(16 * g);
 #pragma unroll
             for (int q = 0; q < 4; ++q) *reinterpret_cast<float4 *>(d + 4 * q) = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
@@ -162,15 +183,16 @@ __global__ __launch_bounds__((TwoPass<K, THREADS>::NT)) void fwht_two_pass_kerne
 #pragma unroll
         for (int r = 0; r < S::R; ++r) v[r] = col[S::RPOS * r];
         auto across_lanes = [&]() {
-            lane_butterfly<0>(v, (q & 1) ? -1.f : 1.f);
-            if constexpr (S::Q >= 2) lane_butterfly<1>(v, (q & 2) ? -1.f : 1.f);
-            if constexpr (S::Q >= 3) lane_butterfly<2>(v, (q & 4) ? -1.f : 1.f);
+            if (mask & (1u << S::Q0)) lane_butterfly<0>(v, (q & 1) ? -1.f : 1.f);
+            if constexpr (S::Q >= 2) if (mask & (2u << S::Q0)) lane_butterfly<1>(v, (q & 2) ? -1.f : 1.f);
+            if constexpr (S::Q >= 3) if (mask & (4u << S::Q0)) lane_butterfly<2>(v, (q & 4) ? -1.f : 1.f);
         };
         if constexpr (S::KRON) {
             across_lanes();
             h28_program(v, o);
         } else {
-            butterflies<4>(v);
+            if constexpr (MASKED) butterflies_masked<4>(v, (mask >> 6) & 15u);
+            else butterflies<4>(v);
             across_lanes();
 #pragma unroll
             for (int r = 0; r < S::R; ++r) o[r] = v[r];
@@ -195,7 +217,7 @@ __global__ __launch_bounds__((TwoPass<K, THREADS>::NT)) void fwht_two_pass_kerne
     // ---- quantise ----------------------------------------------------------------------------------
     if constexpr (F6) {
         if (t < K / 32) {
-            const float lo = S::flipped(2 * t) ? -inv_delta : inv_delta, hi = S::flipped(2 * t + 1) ? -inv_delta : inv_delta;
+            const float lo = S::flipped(2 * t, mask) ? -inv_delta : inv_delta, hi = S::flipped(2 * t + 1, mask) ? -inv_delta : inv_delta;
             quant_store_f6_piece(row + S::pos(32 * t), lo, hi, Q, (rows + 7) >> 3, m, t);
         }
     } else {
@@ -205,7 +227,7 @@ __global__ __launch_bounds__((TwoPass<K, THREADS>::NT)) void fwht_two_pass_kerne
             const int g = t + i * NT;
             if (K / 16 % NT == 0 || g < K / 16) {
                 const float *s16 = row + S::pos(16 * g);
-                const float sd = S::flipped(g) ? -inv_delta : inv_delta;
+                const float sd = S::flipped(g, mask) ? -inv_delta : inv_delta;
                 uint32_t w2[2];
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
@@ -221,20 +243,21 @@ __global__ __launch_bounds__((TwoPass<K, THREADS>::NT)) void fwht_two_pass_kerne
     asm volatile("" ::"v"(warm_acc));                    // keeps the warming loads; they returned long ago
 }
 
-template <int K, int THREADS, bool HAS_PRE, bool F6, bool GATE>
+template <int K, int THREADS, bool HAS_PRE, bool F6, bool GATE, bool MASKED = false>
 hipError_t launch(const __half *X, int64_t rows, int64_t ldx, const float *pre, float clip, float post_scale, uint8_t *Q,
-                  float *scale_out, const __half *gate, int64_t ldg, hipStream_t st, const void *warm, size_t warm_bytes)
+                  float *scale_out, const __half *gate, int64_t ldg, hipStream_t st, const void *warm, size_t warm_bytes,
+                  uint32_t had_mask = 0xFFFFFFFFu)
 {
     using S = TwoPass<K, THREADS>;
     constexpr size_t lds = S::LEN * sizeof(float);
-    constexpr auto kern = fwht_two_pass_kernel<K, THREADS, HAS_PRE, F6, GATE>;
+    constexpr auto kern = fwht_two_pass_kernel<K, THREADS, HAS_PRE, F6, GATE, MASKED>;
     if constexpr (lds > 40 * 1024)
         if (hipError_t e = allow_dynamic_lds<kern>((int)lds); e != hipSuccess) return e;
     const int64_t blocks = F6 ? (rows + 63) / 64 * 64 : rows;
     // the hint is honoured from 256 workgroups on (a launch of a few rows cannot move megabytes on the side)
     const bool warms = warm && warm_bytes >= 128 && blocks >= 256;
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(S::NT), lds, st, X, ldx, rows, pre, clip, post_scale, Q, scale_out, gate,
-                       ldg, warms ? static_cast<const uint32_t *>(warm) : nullptr, (int64_t)(warm_bytes / 128));
+                       ldg, warms ? static_cast<const uint32_t *>(warm) : nullptr, (int64_t)(warm_bytes / 128), had_mask);
     return hipGetLastError();
 }
 
@@ -251,7 +274,28 @@ hipError_t launch_k(const void *X, int64_t rows, int64_t ldx, const float *pre, 
 #undef SR_LAUNCH
 }
 
+template <int K>
+hipError_t launch_masked(const void *X, int64_t rows, int64_t ldx, const float *pre, float clip, float post_scale, uint8_t *Q,
+                         float *scale_out, uint32_t had_mask, hipStream_t st, bool f6)
+{
+    const __half *x = static_cast<const __half *>(X);
+#define SR_LAUNCH(P, F) launch<K, 0, P, F, false, true>(x, rows, ldx, pre, clip, post_scale, Q, scale_out, nullptr, 0, st, nullptr, 0, had_mask)
+    return pre ? (f6 ? SR_LAUNCH(true, true) : SR_LAUNCH(true, false)) : (f6 ? SR_LAUNCH(false, true) : SR_LAUNCH(false, false));
+#undef SR_LAUNCH
+}
+
 }  // namespace
+
+hipError_t launch_fwht_two_pass_heads(const void *X, int64_t rows, int64_t K, int64_t ldx, const float *pre, float clip,
+                                      float post_scale, uint8_t *Q, float *scale_out, uint32_t had_mask, hipStream_t st, bool f6)
+{
+    switch (K) {
+        case 2048: return launch_masked<2048>(X, rows, ldx, pre, clip, post_scale, Q, scale_out, had_mask, st, f6);
+        case 4096: return launch_masked<4096>(X, rows, ldx, pre, clip, post_scale, Q, scale_out, had_mask, st, f6);
+        case 8192: return launch_masked<8192>(X, rows, ldx, pre, clip, post_scale, Q, scale_out, had_mask, st, f6);
+        default: return hipErrorInvalidValue;
+    }
+}
 
 hipError_t launch_fwht_two_pass(const void *X, int64_t rows, int64_t K, int64_t ldx, const float *pre, float clip,
                                 float post_scale, uint8_t *Q, float *scale_out, const __half *gate, int64_t ldg,
