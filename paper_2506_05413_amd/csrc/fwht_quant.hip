@@ -336,12 +336,13 @@ __global__ __launch_bounds__(NT) void fwht_quant_ex_kernel(const __half *__restr
 // CU's vector-memory path, which every row load of the launch has to share.  The copies are inline assembly with a
 // hand-counted wait, so that the order (factors, then the row) and the wait (factors have landed while the row is
 // still in flight) are what is written here, not what the compiler's scheduler makes of them.
-template <bool HAS_PRE, bool F6, bool STAGED = false>
+// MASKED: head-wise transform -- only the index bits set in had_mask are butterflied (uniform branches).
+template <bool HAS_PRE, bool F6, bool STAGED = false, bool MASKED = false>
 __global__ __launch_bounds__(256) void fwht4096_wave_kernel(const __half *__restrict__ X, int64_t ldx, int64_t rows,
                                                             const float *__restrict__ pre, float clip, float post_scale,
                                                             uint8_t *__restrict__ Q, float *__restrict__ scale_out,
                                                             const uint32_t *__restrict__ warm,
-                                                            int64_t warm_lines)
+                                                            int64_t warm_lines, uint32_t had_mask)
 {
     constexpr int K = 4096, ROWF = F6 ? K + 576 : K + 64;   // floats per wave-private row incl. padding
     extern __shared__ __attribute__((aligned(16))) float smem_rows[];
@@ -353,7 +354,8 @@ __global__ __launch_bounds__(256) void fwht4096_wave_kernel(const __half *__rest
         const int64_t w = blockIdx.x, x = w & 7, a = w >> 3;
         m = 8 * (8 * (a >> 1) + x) + 4 * (a & 1) + wave;
     }
-    static_assert(!STAGED || HAS_PRE, "the staged variant is the plain transform with factors");
+    static_assert(!STAGED || (HAS_PRE && !MASKED), "the staged variant is the plain transform with factors");
+    static_assert(!MASKED || !F6, "head-wise rows are written as nibbles");
     if constexpr (!STAGED) {
         if (m >= rows) {                                 // no barrier below: waves are independent
             if constexpr (F6) zero_f6_padding_row<K, 64>(Q, (rows + 7) >> 3, m, lane);
@@ -439,11 +441,18 @@ __global__ __launch_bounds__(256) void fwht4096_wave_kernel(const __half *__rest
             f[0] = s0.x; f[1] = s0.y; f[2] = s0.z; f[3] = s0.w;
             f[4] = s1.x; f[5] = s1.y; f[6] = s1.z; f[7] = s1.w;
         }
-        // conversion, factor and index bit 0 in one go
+        if constexpr (MASKED) {                          // index bit 0 may be unselected: values as they are
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            if (HAS_PRE) pair_level(raw.h[e], f[2 * e], f[2 * e + 1], v[8 * j + 2 * e], v[8 * j + 2 * e + 1]);
-            else pair_level(raw.h[e], v[8 * j + 2 * e], v[8 * j + 2 * e + 1]);
+            for (int e = 0; e < 8; ++e) {
+                v[8 * j + e] = (float)raw.h[e >> 1][e & 1];
+                if (HAS_PRE) v[8 * j + e] *= f[e];
+            }
+        } else {                                         // conversion, factor and index bit 0 in one go
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if (HAS_PRE) pair_level(raw.h[e], f[2 * e], f[2 * e + 1], v[8 * j + 2 * e], v[8 * j + 2 * e + 1]);
+                else pair_level(raw.h[e], v[8 * j + 2 * e], v[8 * j + 2 * e + 1]);
+            }
         }
         // (STAGED: keeps the arithmetic of chunk j between the waits for chunks j and j + 1 -- the compiler
         // otherwise gathers the eight waits in front of all of it)
@@ -458,7 +467,9 @@ __global__ __launch_bounds__(256) void fwht4096_wave_kernel(const __half *__rest
             }
         }
     }
-    if constexpr (STAGED) butterflies_from<6, 8>(v);   // bits 1, 2 were done chunk by chunk
+    // register bits = index bits 0, 1, 2, 9, 10, 11
+    if constexpr (MASKED) butterflies_masked<6>(v, (had_mask & 7u) | (((had_mask >> 9) & 7u) << 3));
+    else if constexpr (STAGED) butterflies_from<6, 8>(v);   // bits 1, 2 were done chunk by chunk
     else butterflies_from<6, 2>(v);
     // Warming the memory-side cache for the kernel that follows (its weights): the waves of the launch share the
     // 128-byte lines of [warm, warm + 128 warm_lines) and read one word of each -- with ordinary loads, so that the
@@ -480,7 +491,8 @@ __global__ __launch_bounds__(256) void fwht4096_wave_kernel(const __half *__rest
     const float *src = buf + 520 * (lane >> 3) + (lane & 7);
 #pragma unroll
     for (int r = 0; r < 64; ++r) v[r] = src[8 * r];
-    butterflies<6>(v);
+    if constexpr (MASKED) butterflies_masked<6>(v, (had_mask >> 3) & 63u);      // index bits 3..8
+    else butterflies<6>(v);
     float amax = 0.f;
 #pragma unroll
     for (int r = 0; r < 64; r += 2) amax = fmaxf(fmaxf(amax, fabsf(v[r])), fabsf(v[r + 1]));
@@ -628,19 +640,19 @@ hipError_t launch_one_ex(const void *X, int64_t rows, int64_t ldx, const float *
 constexpr int64_t kWaveKernelMinRows = 1024;   // measured: 3.3 - 4.8 us against 4.2 - 5.9 us up to 512 rows, equal at 1024
 constexpr int64_t kTwoPassMaxRows4096 = 3072;  // the two-pass workgroup-per-row kernel up to here (see launch_fwht_quant)
 
-template <bool HAS_PRE, bool F6, bool STAGED = false>
+template <bool HAS_PRE, bool F6, bool STAGED = false, bool MASKED = false>
 hipError_t launch_wave4096(const void *X, int64_t rows, int64_t ldx, const float *pre, float clip, float post_scale,
                            uint8_t *Q, float *scale_out, hipStream_t st,
-                           const void *warm = nullptr, size_t warm_bytes = 0)
+                           const void *warm = nullptr, size_t warm_bytes = 0, uint32_t had_mask = 0xFFFFFFFFu)
 {
     constexpr size_t lds = 4 * (4096 + (F6 ? 576 : 64)) * sizeof(float);
     const unsigned blocks = F6 ? (unsigned)((rows + 63) / 64 * 16) : (unsigned)((rows + 3) / 4);
-    constexpr auto kern = fwht4096_wave_kernel<HAS_PRE, F6, STAGED>;
+    constexpr auto kern = fwht4096_wave_kernel<HAS_PRE, F6, STAGED, MASKED>;
     hipError_t e = allow_dynamic_lds<kern>((int)lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), lds, st, static_cast<const __half *>(X), ldx, rows, pre, clip,
                        post_scale, Q, scale_out, warm_bytes >= 128 ? static_cast<const uint32_t *>(warm) : nullptr,
-                       (int64_t)(warm_bytes / 128));
+                       (int64_t)(warm_bytes / 128), had_mask);
     return hipGetLastError();
 }
 
@@ -690,15 +702,20 @@ hipError_t launch_fwht_quant_ex(const void *X, int64_t rows, int64_t K, int64_t 
                                 float clip, float post_scale, uint8_t *Q, float *scale_out,
                                 const RowExtras &ex, hipStream_t st, bool f6)
 {
-    // head-wise transform: two passes with the unselected butterflies skipped, at every row count (32 heads, across / within:
-    // K = 4096 2048 rows 9.6 / 10.0 -> 9.0 / 9.4 us against the wave-per-row kernel, 8000 rows across 26.2 -> 21.8; 817
-    // rows of 8192 12.9 / 11.5 -> 9.3 / 10.0 us against the general kernel, 1500 rows of 2048 9.8 -> 6.4)
+    // head-wise transform: two passes with the unselected butterflies skipped (817 rows of 8192, 32 heads, across / within:
+    // 12.9 / 11.5 -> 9.3 / 10.0 us against the general kernel, 1500 rows of 2048 9.8 -> 6.4); more than 1024 rows of 4096
+    // by a wave per row.  There two passes would be faster too (2048 rows 9.6 / 10.0 -> 9.0 / 9.4 us, 8000 rows across
+    // 26.2 -> 21.8), but add the values in another order (index bits 0..11 in turn; a wave per row does 0, 1, 2, 9, 10, 11
+    // before 3..8): about one code in a million, on a rounding boundary, comes out one off.
     if (!ex.gate && ex.n_grid == 0 && (K == 2048 || K == 4096 || K == 8192)) {
         // no search: the ratio "chosen" for every row is the fixed one (the kernel does not report it)
         if (ex.ratio_out) {
             hipLaunchKernelGGL(fill_f32_kernel, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, st, ex.ratio_out, rows, clip);
             if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
         }
+        if (K == 4096 && rows > kWaveKernelMinRows)
+            return pre ? launch_wave4096<true, false, false, true>(X, rows, ldx, pre, clip, post_scale, Q, scale_out, st, nullptr, 0, ex.had_mask)
+                       : launch_wave4096<false, false, false, true>(X, rows, ldx, pre, clip, post_scale, Q, scale_out, st, nullptr, 0, ex.had_mask);
         return launch_fwht_two_pass_heads(X, rows, K, ldx, pre, clip, post_scale, Q, scale_out, ex.had_mask, st, f6);
     }
     // the gate alone (the FFN down-projection input) goes through the plain kernels: fewer passes over the row
