@@ -169,7 +169,9 @@ __device__ __forceinline__ float search_ratio(const float *row, const float amax
     return ratios[best_i];
 }
 
-// The fold of a weight with the search, full transform: one workgroup per output channel.
+// The fold of a weight with the search, full transform: one workgroup per output channel.  The products with the smoothing
+// factors are rounded as in fwht_quant_ex_kernel, which folds the other searched weights and folded these before: left
+// unrounded in the first level, scales moved by an ulp and three codes of 16.8 million by one (4096 x 4096).
 template <int K, int NT>
 __global__ __launch_bounds__(NT) void fwht_quant_search_kernel(const __half *__restrict__ X, int64_t ldx,
                                                                const float *__restrict__ pre, float post_scale,
@@ -180,7 +182,7 @@ __global__ __launch_bounds__(NT) void fwht_quant_search_kernel(const __half *__r
     __shared__ float red[NT / 64];
     const int t = threadIdx.x;
     const int64_t m = blockIdx.x;
-    const float amax = rotate_row_absmax<K, NT>(X + m * ldx, pre, row, red, t);
+    const float amax = rotate_row_absmax<K, NT, true>(X + m * ldx, pre, row, red, t);
     const float clip = amax != 0.f ? search_ratio<K, NT>(row, amax, ex.grid, ex.n_grid, t) : ex.grid[0];
     if (ex.ratio_out && t == 0) ex.ratio_out[m] = clip;
     const float delta = (amax == 0.f) ? 1.f : (clip * amax) / 7.f;

@@ -359,7 +359,8 @@ __device__ __forceinline__ void row_load(const __half *__restrict__ x, const flo
 }
 
 // The 16 loaded values of a thread, times silu(gate) and / or the factors, after the butterfly level of index bit 0.
-template <bool GATE>
+// ROUNDED: both products of a pair are rounded before they are added (pair_level rounds one of them).
+template <bool GATE, bool ROUNDED = false>
 __device__ __forceinline__ void first_level16(const uint4 (&u)[2], const uint4 (&gu)[2], const float4 (&p)[4],
                                               const bool has_pre, float (&v)[16])
 {
@@ -389,7 +390,15 @@ __device__ __forceinline__ void first_level16(const uint4 (&u)[2], const uint4 (
             }
         }
 #pragma unroll
-        for (int e = 0; e < 8; ++e) pair_level(raw.h[e], f[2 * e], f[2 * e + 1], v[2 * e], v[2 * e + 1]);
+        for (int e = 0; e < 8; ++e) {
+            if constexpr (ROUNDED) {
+                const float a = __builtin_fmaf((float)raw.h[e][0], f[2 * e], 0.f), b = __builtin_fmaf((float)raw.h[e][1], f[2 * e + 1], 0.f);
+                v[2 * e] = a + b;
+                v[2 * e + 1] = a - b;
+            } else {
+                pair_level(raw.h[e], f[2 * e], f[2 * e + 1], v[2 * e], v[2 * e + 1]);
+            }
+        }
     } else {
 #pragma unroll
         for (int e = 0; e < 8; ++e) pair_level(raw.h[e], v[2 * e], v[2 * e + 1]);
@@ -402,7 +411,7 @@ struct NoHook { __device__ __forceinline__ void operator()() const {} };
 
 // after_pass1: called once the loaded values have been consumed (for loads that should travel during the rest of the
 // row's work).
-template <int K, int NT, bool GATE = false, typename Hook = NoHook>
+template <int K, int NT, bool GATE = false, bool ROUNDED = false, typename Hook = NoHook>
 __device__ __forceinline__ float rotate_loaded_row_absmax(const RowLoad<K, NT> &ld, const float *__restrict__ pre,
                                                           float *row, float *red, const int t, Hook after_pass1 = Hook{})
 {
@@ -417,7 +426,7 @@ __device__ __forceinline__ float rotate_loaded_row_absmax(const RowLoad<K, NT> &
         const int g = t + i * NT;
         if (K / 16 % NT == 0 || g < K / 16) {
             float v[16];
-            first_level16<GATE>(ld.u[i], ld.gu[i], ld.p[i], pre != nullptr, v);
+            first_level16<GATE, ROUNDED>(ld.u[i], ld.gu[i], ld.p[i], pre != nullptr, v);
             butterflies_from<4, 2>(v);
             float *dst = row + pad(16 * g);
 #pragma unroll
@@ -491,14 +500,13 @@ __device__ __forceinline__ float rotate_loaded_row_absmax(const RowLoad<K, NT> &
     return amax;
 }
 
-template <int K, int NT, bool GATE = false>
+template <int K, int NT, bool ROUNDED>
 __device__ __forceinline__ float rotate_row_absmax(const __half *__restrict__ x, const float *__restrict__ pre,
-                                                   float *row, float *red, const int t,
-                                                   const __half *__restrict__ gate = nullptr)
+                                                   float *row, float *red, const int t)
 {
     RowLoad<K, NT> ld;
-    row_load<K, NT, false, GATE>(x, pre, t, ld, gate);
-    return rotate_loaded_row_absmax<K, NT, GATE>(ld, pre, row, red, t);
+    row_load<K, NT>(x, pre, t, ld);
+    return rotate_loaded_row_absmax<K, NT, false, ROUNDED>(ld, pre, row, red, t);
 }
 
 }  // namespace
