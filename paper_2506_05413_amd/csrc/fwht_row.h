@@ -291,7 +291,9 @@ __device__ __forceinline__ void zero_f6_padding_row(uint8_t *__restrict__ T6, in
     for (int p = t; p < K / 32; p += NT) store_f6_piece(v6u{0u, 0u, 0u, 0u, 0u, 0u}, T6, row_blocks, m, p);
 }
 // (inv_lo for the first 16 values, inv_hi for the last 16: callers whose values carry a sign per group of 16
-// pass +-1/Delta; the others the same factor twice)
+// pass +-1/Delta; the others the same factor twice.  PLUS_ZERO: a value that is exactly zero gets the field 0 although its
+// factor is negative: + 0 inside the multiply-add turns -0 into +0.)
+template <bool PLUS_ZERO = false>
 __device__ __forceinline__ void quant_store_f6_piece(const float *s32, float inv_lo, float inv_hi, uint8_t *__restrict__ T6,
                                                      int64_t row_blocks, int64_t m, int p)
 {
@@ -300,10 +302,11 @@ __device__ __forceinline__ void quant_store_f6_piece(const float *s32, float inv
     for (int k = 0; k < 8; ++k) {
         const float4 q = *reinterpret_cast<const float4 *>(s32 + 4 * k);
         const float inv_delta = k < 4 ? inv_lo : inv_hi;
-        ev[2 * k] = __builtin_amdgcn_fmed3f(q.x * inv_delta, -8.f, 7.f);
-        od[2 * k] = __builtin_amdgcn_fmed3f(q.y * inv_delta, -8.f, 7.f);
-        ev[2 * k + 1] = __builtin_amdgcn_fmed3f(q.z * inv_delta, -8.f, 7.f);
-        od[2 * k + 1] = __builtin_amdgcn_fmed3f(q.w * inv_delta, -8.f, 7.f);
+        auto scaled = [&](float y) { return __builtin_amdgcn_fmed3f(PLUS_ZERO ? __builtin_fmaf(y, inv_delta, 0.f) : y * inv_delta, -8.f, 7.f); };
+        ev[2 * k] = scaled(q.x);
+        od[2 * k] = scaled(q.y);
+        ev[2 * k + 1] = scaled(q.z);
+        od[2 * k + 1] = scaled(q.w);
     }
     store_f6_piece(__builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(ev, od, 8.f), T6, row_blocks, m, p);
 }

@@ -17,7 +17,10 @@
 // 193;  8192 gated, factors 4.9 / 6.2 / 25.3 / 164 -> 4.2 / 5.4 / 21.6 / 150;  8192 4.6 / 5.7 / 21.0 / 133 -> 3.8 / 4.9 /
 // 17.2 / 112;  2048 3.3 / 3.6 / 6.9 / 33.5 -> 3.0 / 3.2 / 6.2 / 30.2;  4096 gated 3.8 / 4.9 / 13.9 / 82.3 -> 3.5 / 4.5 /
 // 12.9 / 80.5.  Nibble output gains the same or a little more.  Every level is the same addition of the same two values as
-// there (index bits in rising order), so the outputs did not change.
+// there (index bits in rising order), so codes and scales did not change.  Tiles show the sign of a zero (field 32 is -0):
+// a value that is exactly zero gets the field 0, as without flips; only where all of a row is zero with negative zeros among
+// them, and for the zeros that H_28 negates (K = 14336), the general kernel wrote 32.  (Ending the flips in front of H_28
+// keeps those too: 16384 gated rows 256 -> 261 us, for the same numbers; dropped.)
 // Measured and dropped for 14336: 896 threads with two rows per CU (14 waves each: 1024 rows 21.1 -> 27.4 us); workgroups
 // that walk over rows, the next row requested after pass 1 (it helped the three-pass kernel: 264 -> 243 us; here 193 against
 // 192 us without a gate, spills and 375 against 258 us with one); for 4096 two, four or eight rows per workgroup one after
@@ -218,7 +221,9 @@ __global__ __launch_bounds__((TwoPass<K, THREADS>::NT)) void fwht_two_pass_kerne
     if constexpr (F6) {
         if (t < K / 32) {
             const float lo = S::flipped(2 * t, mask) ? -inv_delta : inv_delta, hi = S::flipped(2 * t + 1, mask) ? -inv_delta : inv_delta;
-            quant_store_f6_piece(row + S::pos(32 * t), lo, hi, Q, (rows + 7) >> 3, m, t);
+            // exact zeros become the field 0 (plain rows of 4096, which have always come from this kernel, write 32 where the
+            // sign is flipped)
+            quant_store_f6_piece<GATE || K != 4096>(row + S::pos(32 * t), lo, hi, Q, (rows + 7) >> 3, m, t);
         }
     } else {
         uint32_t *q = reinterpret_cast<uint32_t *>(Q + m * (int64_t)(K / 2));
