@@ -56,7 +56,11 @@ const at::Tensor &matrix(PyObject *o, at::ScalarType type, const char *name)
     return t;
 }
 
+// Addresses are taken before the lock is released: data_ptr() throws for a tensor without memory of its own (inside vmap, ..).
 void *pointer(PyObject *o, const char *name) { return o == Py_None ? nullptr : tensor(o, name).data_ptr(); }
+float *floats(PyObject *o, const char *name) { return static_cast<float *>(pointer(o, name)); }
+float *floats(const at::Tensor &t) { return static_cast<float *>(t.data_ptr()); }
+uint8_t *bytes(const at::Tensor &t) { return static_cast<uint8_t *>(t.data_ptr()); }
 int64_t integer(PyObject *o)
 {
     const int64_t v = PyLong_AsLongLong(o);
@@ -90,7 +94,7 @@ void *stream() { return c10::hip::getCurrentHIPStream().stream(); }
 
 PyObject *pair(const at::Tensor &a, const at::Tensor &b) { return Py_BuildValue("(NN)", THPVariable_Wrap(a), THPVariable_Wrap(b)); }
 
-// calls into the library without holding the interpreter's lock
+// calls into the library without holding the interpreter's lock (the library does not throw)
 template <typename F> int released(F f)
 {
     int status;
@@ -122,12 +126,13 @@ PyObject *fwht_quant_act(PyObject *const *a)
     const int64_t M = X.size(0), K = X.size(1);
     const at::Tensor Xq = output(a[3], "Xq", {M, K / 2}, at::kByte, X), xs = output(a[4], "x_scale", {M}, at::kFloat, X);
     const float clip = real(a[2]);
-    const float *inv = static_cast<const float *>(pointer(a[1], "inv_s"));
+    const float *inv = floats(a[1], "inv_s");
+    const void *x = X.data_ptr();
+    uint8_t *q = bytes(Xq);
+    float *scale = floats(xs);
+    const int64_t ldx = row_stride(X);
     void *st = stream();
-    const int status = released([&] {
-        return sr_fwht_quant_act(X.data_ptr(), M, K, row_stride(X), inv, clip, static_cast<uint8_t *>(Xq.data_ptr()),
-                                 static_cast<float *>(xs.data_ptr()), st);
-    });
+    const int status = released([&] { return sr_fwht_quant_act(x, M, K, ldx, inv, clip, q, scale, st); });
     return status ? PyLong_FromLong(status) : pair(Xq, xs);
 }
 
@@ -139,25 +144,26 @@ PyObject *fwht_quant_act_heads(PyObject *const *a)
     const int across = truth(a[2]);
     const at::Tensor Xq = output(a[5], "Xq", {M, K / 2}, at::kByte, X), xs = output(a[6], "x_scale", {M}, at::kFloat, X);
     const float clip = real(a[4]);
-    const float *inv = static_cast<const float *>(pointer(a[3], "inv_s"));
+    const float *inv = floats(a[3], "inv_s");
+    const void *x = X.data_ptr();
+    uint8_t *q = bytes(Xq);
+    float *scale = floats(xs);
+    const int64_t ldx = row_stride(X);
     void *st = stream();
-    const int status = released([&] {
-        return sr_fwht_quant_act_heads(X.data_ptr(), M, K, row_stride(X), heads, across, inv, clip,
-                                       static_cast<uint8_t *>(Xq.data_ptr()), static_cast<float *>(xs.data_ptr()), st);
-    });
+    const int status = released([&] { return sr_fwht_quant_act_heads(x, M, K, ldx, heads, across, inv, clip, q, scale, st); });
     return status ? PyLong_FromLong(status) : pair(Xq, xs);
 }
 
 // a buffer whose bytes the library may read as the next operand: (address, bytes)
-void warm_region(PyObject *o, const void *&p, size_t &bytes)
+void warm_region(PyObject *o, const void *&p, size_t &size)
 {
     p = nullptr;
-    bytes = 0;
+    size = 0;
     if (o == Py_None) return;
     const at::Tensor &t = tensor(o, "warm");
     if (!t.is_cuda() || !t.is_contiguous()) value_error("%s must be a contiguous device tensor", "warm");
     p = t.data_ptr();
-    bytes = t.nbytes();
+    size = t.nbytes();
 }
 
 int64_t tile_bytes(int64_t M, int64_t K)
@@ -173,15 +179,16 @@ PyObject *fwht_quant_act_f6(PyObject *const *a)
     const int64_t M = X.size(0), K = X.size(1);
     const at::Tensor X6 = output(a[3], "X6", {tile_bytes(M, K)}, at::kByte, X), xs = output(a[4], "x_scale", {M}, at::kFloat, X);
     const float clip = real(a[2]);
-    const float *inv = static_cast<const float *>(pointer(a[1], "inv_s"));
+    const float *inv = floats(a[1], "inv_s");
     const void *warm;
     size_t warm_bytes;
     warm_region(a[5], warm, warm_bytes);
+    const void *x = X.data_ptr();
+    uint8_t *q = bytes(X6);
+    float *scale = floats(xs);
+    const int64_t ldx = row_stride(X);
     void *st = stream();
-    const int status = released([&] {
-        return sr_fwht_quant_act_f6_warm(X.data_ptr(), M, K, row_stride(X), inv, clip, static_cast<uint8_t *>(X6.data_ptr()),
-                                         static_cast<float *>(xs.data_ptr()), warm, warm_bytes, st);
-    });
+    const int status = released([&] { return sr_fwht_quant_act_f6_warm(x, M, K, ldx, inv, clip, q, scale, warm, warm_bytes, st); });
     return status ? PyLong_FromLong(status) : pair(X6, xs);
 }
 
@@ -195,13 +202,14 @@ PyObject *swiglu_fwht_quant_act(PyObject *const *a)
     const at::Tensor Q = tiles ? output(a[4], "X6", {tile_bytes(M, K)}, at::kByte, U) : output(a[4], "Xq", {M, K / 2}, at::kByte, U);
     const at::Tensor xs = output(a[5], "x_scale", {M}, at::kFloat, U);
     const float clip = real(a[3]);
-    const float *inv = static_cast<const float *>(pointer(a[2], "inv_s"));
+    const float *inv = floats(a[2], "inv_s");
+    const void *g = G.data_ptr(), *u = U.data_ptr();
+    uint8_t *q = bytes(Q);
+    float *scale = floats(xs);
+    const int64_t ldg = row_stride(G), ldu = row_stride(U);
     void *st = stream();
     const auto f = tiles ? sr_swiglu_fwht_quant_act_f6 : sr_swiglu_fwht_quant_act;
-    const int status = released([&] {
-        return f(G.data_ptr(), U.data_ptr(), M, K, row_stride(G), row_stride(U), inv, clip,
-                 static_cast<uint8_t *>(Q.data_ptr()), static_cast<float *>(xs.data_ptr()), st);
-    });
+    const int status = released([&] { return f(g, u, M, K, ldg, ldu, inv, clip, q, scale, st); });
     return status ? PyLong_FromLong(status) : pair(Q, xs);
 }
 
@@ -213,17 +221,15 @@ PyObject *w4a4_gemm(PyObject *const *a)
     if (Wq.size(1) != Kb) value_error("%s disagree on K", "Xq and Wq");
     const int type = (int)integer(a[4]);
     const at::Tensor Y = output(a[5], "Y", {M, N}, type == SR_F16 ? at::kHalf : at::kInt, Xq);
-    const float *xs = static_cast<const float *>(pointer(a[1], "x_scale")), *ws = static_cast<const float *>(pointer(a[3], "w_scale"));
+    const float *xs = floats(a[1], "x_scale"), *ws = floats(a[3], "w_scale");
     at::Tensor work;
     if (a[6] != Py_None) work = tensor(a[6], "workspace");
     else if (const size_t need = sr_gemm_workspace_bytes(M, N, 2 * Kb)) work = empty({(int64_t)need}, at::kByte, Xq);
     const int64_t ldy = M > 1 ? Y.stride(0) : N;
-    void *st = stream();
-    const int status = released([&] {
-        return sr_w4a4_gemm(static_cast<const uint8_t *>(Xq.data_ptr()), xs, static_cast<const uint8_t *>(Wq.data_ptr()), ws,
-                            M, N, 2 * Kb, Y.data_ptr(), ldy, type, work.defined() ? work.data_ptr() : nullptr,
-                            work.defined() ? (size_t)work.numel() : 0, st);
-    });
+    const uint8_t *x = bytes(Xq), *w = bytes(Wq);
+    void *y = Y.data_ptr(), *scratch = work.defined() ? work.data_ptr() : nullptr, *st = stream();
+    const size_t scratch_bytes = work.defined() ? (size_t)work.numel() : 0;
+    const int status = released([&] { return sr_w4a4_gemm(x, xs, w, ws, M, N, 2 * Kb, y, ldy, type, scratch, scratch_bytes, st); });
     return status ? PyLong_FromLong(status) : THPVariable_Wrap(Y);
 }
 
@@ -236,16 +242,14 @@ PyObject *w4a4_gemm_f6(PyObject *const *a)
         value_error("%s are smaller than sr_f6_tiles_bytes says", "tile buffers");
     const int type = (int)integer(a[7]);
     const at::Tensor Y = output(a[8], "Y", {M, N}, type == SR_F16 ? at::kHalf : at::kInt, X6);
-    const float *xs = static_cast<const float *>(pointer(a[1], "x_scale")), *ws = static_cast<const float *>(pointer(a[3], "w_scale"));
+    const float *xs = floats(a[1], "x_scale"), *ws = floats(a[3], "w_scale");
     const void *warm;
     size_t warm_bytes;
     warm_region(a[9], warm, warm_bytes);
     const int64_t ldy = M > 1 ? Y.stride(0) : N;
-    void *st = stream();
-    const int status = released([&] {
-        return sr_w4a4_gemm_f6_warm(static_cast<const uint8_t *>(X6.data_ptr()), xs, static_cast<const uint8_t *>(W6.data_ptr()), ws,
-                                    M, N, K, Y.data_ptr(), ldy, type, warm, warm_bytes, nullptr, 0, st);
-    });
+    const uint8_t *x = bytes(X6), *w = bytes(W6);
+    void *y = Y.data_ptr(), *st = stream();
+    const int status = released([&] { return sr_w4a4_gemm_f6_warm(x, xs, w, ws, M, N, K, y, ldy, type, warm, warm_bytes, nullptr, 0, st); });
     return status ? PyLong_FromLong(status) : THPVariable_Wrap(Y);
 }
 
@@ -256,19 +260,20 @@ PyObject *w4a4_linear_decode(PyObject *const *a)
     const int64_t M = X.size(0), K = X.size(1), N = Wq.size(0);
     if (Wq.size(1) * 2 != K) value_error("%s disagree on K", "X and Wq");
     const at::Tensor Y = output(a[5], "Y", {M, N}, at::kHalf, X);
-    const float *inv = static_cast<const float *>(pointer(a[1], "inv_s")), *ws = static_cast<const float *>(pointer(a[3], "w_scale"));
+    const float *inv = floats(a[1], "inv_s"), *ws = floats(a[3], "w_scale");
     uint8_t *xq = static_cast<uint8_t *>(pointer(a[6], "Xq_out"));
-    float *xs = static_cast<float *>(pointer(a[7], "x_scale_out"));
+    float *xs = floats(a[7], "x_scale_out");
     const float clip = real(a[4]);
     at::Tensor work;
     if (a[8] != Py_None) work = tensor(a[8], "workspace");
     else if (const size_t need = sr_linear_decode_workspace_bytes(M, K)) work = empty({(int64_t)need}, at::kByte, X);
-    const int64_t ldy = M > 1 ? Y.stride(0) : N;
-    void *st = stream();
+    const int64_t ldx = row_stride(X), ldy = M > 1 ? Y.stride(0) : N;
+    const void *x = X.data_ptr();
+    const uint8_t *w = bytes(Wq);
+    void *y = Y.data_ptr(), *scratch = work.defined() ? work.data_ptr() : nullptr, *st = stream();
+    const size_t scratch_bytes = work.defined() ? (size_t)work.numel() : 0;
     const int status = released([&] {
-        return sr_w4a4_linear_decode(X.data_ptr(), M, K, row_stride(X), inv, clip, static_cast<const uint8_t *>(Wq.data_ptr()), ws,
-                                     N, Y.data_ptr(), ldy, xq, xs, work.defined() ? work.data_ptr() : nullptr,
-                                     work.defined() ? (size_t)work.numel() : 0, st);
+        return sr_w4a4_linear_decode(x, M, K, ldx, inv, clip, w, ws, N, y, ldy, xq, xs, scratch, scratch_bytes, st);
     });
     return status ? PyLong_FromLong(status) : THPVariable_Wrap(Y);
 }
@@ -283,11 +288,12 @@ PyObject *kv_quant_asym(PyObject *const *a)
     const at::Tensor Q = output(a[3], "Q", {rows, D / 2}, at::kByte, X), scale = output(a[4], "scale", {rows, groups}, at::kFloat, X),
                      zero = output(a[5], "zero", {rows, groups}, at::kFloat, X);
     const float clip = real(a[2]);
+    const void *x = X.data_ptr();
+    uint8_t *q = bytes(Q);
+    float *scales = floats(scale), *zeros = floats(zero);
+    const int64_t ldx = row_stride(X);
     void *st = stream();
-    const int status = released([&] {
-        return sr_kv_quant_asym(X.data_ptr(), rows, D, row_stride(X), group, clip, static_cast<uint8_t *>(Q.data_ptr()),
-                                static_cast<float *>(scale.data_ptr()), static_cast<float *>(zero.data_ptr()), st);
-    });
+    const int status = released([&] { return sr_kv_quant_asym(x, rows, D, ldx, group, clip, q, scales, zeros, st); });
     return status ? PyLong_FromLong(status)
                   : Py_BuildValue("(NNN)", THPVariable_Wrap(Q), THPVariable_Wrap(scale), THPVariable_Wrap(zero));
 }
