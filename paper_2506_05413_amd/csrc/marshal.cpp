@@ -14,11 +14,12 @@
 #include <ATen/ATen.h>
 #include <ATen/hip/EmptyTensor.h>
 #include <c10/hip/HIPStream.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include "../../include/smoothrot.h"
 
-#include <stdexcept>
+#include <exception>
 
 namespace {
 
@@ -113,8 +114,8 @@ template <PyObject *(*F)(PyObject *const *), int N> PyObject *entry(PyObject *, 
     try {
         return F(args);
     } catch (const Raised &) {
-    } catch (const std::exception &e) {                  // c10::Error, out of memory, ..
-        PyErr_SetString(PyExc_RuntimeError, e.what());
+    } catch (...) {                                      // as torch raises them: out of memory, bad index, ..
+        torch::translate_exception_to_python(std::current_exception());
     }
     return nullptr;
 }

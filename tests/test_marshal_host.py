@@ -42,3 +42,23 @@ def test_tensor_without_memory_inside_vmap(name):
         batch = torch.empty((3, 4, 128), dtype=torch.float16, device="cuda")
     with pytest.raises(RuntimeError, match="(?i)storage|data pointer"):
         torch.func.vmap(call)(batch)
+
+
+@pytest.mark.filterwarnings("ignore:Accessing the data pointer")
+def test_torch_exceptions_keep_their_type():
+    t = device_tensors()
+    with FakeTensorMode():
+        scalar = torch.empty((), dtype=torch.float16, device="cuda")
+    with pytest.raises(IndexError):
+        sr.sr_w4a4_gemm(t["q"], t["s"], t["W"], t["ws"], Y=scalar)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("call", [lambda x: sr.sr_fwht_quant_act(x, None), lambda x: sr.sr_kv_quant_asym(x, 64)])
+def test_out_of_memory_is_torchs(gpu, call):
+    """The outputs of 2^37 rows of 64 values do not fit: torch.OutOfMemoryError, which a server catches to shed load."""
+    x = torch.zeros((1, 64), dtype=torch.float16, device="cuda").expand(1 << 37, 64)
+    with pytest.raises(torch.OutOfMemoryError):
+        call(x)
+    q, s = gpu.sr_fwht_quant_act(x[:2].contiguous(), None)
+    assert bool((s == 1).all()) and not bool(q.any())
