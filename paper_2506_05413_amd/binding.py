@@ -3,8 +3,9 @@
 Function names and argument order follow include/smoothrot.h.  torch supplies
 device memory and the current stream; every step of the computation runs in the
 library's HIP kernels.  The per-token calls marshal their tensors in native code
-(csrc/marshal.cpp), the offline ones through ctypes.  There is no fallback: if a
-shared library is missing or a call fails, an exception is raised.
+(csrc/marshal.cpp), which is built for one Python and one torch; the offline ones
+through ctypes, with any torch.  There is no fallback: if a shared library is
+missing or a call fails, an exception is raised.
 """
 from __future__ import annotations
 
@@ -97,8 +98,11 @@ def _marshal():
         try:
             from . import _marshal as module
         except ImportError as e:
-            raise ImportError("_marshal.so is not built: run `python -m paper_2506_05413_amd.build` "
+            raise ImportError("_marshal is not built for this Python and torch: run `python -m paper_2506_05413_amd.build` "
                               "(there is no fallback path)") from e
+        if module.torch_version != torch.__version__:
+            raise ImportError("_marshal was built against torch %s, this is torch %s: run `python -m paper_2506_05413_amd.build`"
+                              % (module.torch_version, torch.__version__))
         _native = module
     return _native
 
@@ -108,7 +112,7 @@ def _ptr(t):
 
 
 def _stream():
-    return (_native or _marshal()).current_stream()
+    return _native.current_stream() if _native else torch.cuda.current_stream().cuda_stream
 
 
 def _refused(status: int, where: str):

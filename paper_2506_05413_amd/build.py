@@ -1,4 +1,7 @@
-"""Builds libsmoothrot.so (HIP, gfx950 only) with hipcc and _marshal.so (the binding's native half) with g++, in-tree.
+"""Builds libsmoothrot.so (HIP, gfx950 only) with hipcc and _marshal (the binding's native half) with g++, in-tree.
+
+_marshal is an extension module for the Python and the torch that run the build; its file name carries the Python ABI, and it
+holds the torch version it was compiled against.
 
     python -m paper_2506_05413_amd.build
 """
@@ -14,7 +17,7 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libsmoothrot.so")
-MARSHAL = os.path.join(PKG, "_marshal.so")
+MARSHAL = os.path.join(PKG, "_marshal" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 SOURCES = ["sr_api.hip", "fwht_quant.hip", "fwht_two_pass.hip", "calib_fold.hip", "gemm_prefill.hip", "gemm_packed_stream.hip", "gemm_f6.hip", "gemm_f6_stream.hip", "gemm_decode.hip", "kv_quant.hip", "linear_decode.hip", "ceilings.hip"]
 
@@ -63,7 +66,7 @@ def _compile_marshal() -> str:
     root = os.path.dirname(torch.__file__)
     obj = os.path.join(OBJ, "marshal.o")
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-fvisibility=hidden", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
-           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI]
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, '-DSR_TORCH_VERSION="%s"' % torch.__version__]
     cmd += [f for d in ("include", "include/torch/csrc/api/include") for f in ("-isystem", os.path.join(root, d))]
     cmd += ["-isystem", "/opt/rocm/include", "-isystem", sysconfig.get_paths()["include"]]
     r = subprocess.run(cmd + ["-c", os.path.join(CSRC, "marshal.cpp"), "-o", obj], capture_output=True, text=True)
@@ -73,30 +76,30 @@ def _compile_marshal() -> str:
 
 
 def _link_marshal(obj: str) -> None:
-    """_marshal.so; torch's libraries are in the process when it is imported, libsmoothrot.so lies beside it."""
+    """_marshal; torch's libraries are in the process when it is imported, libsmoothrot.so lies beside it."""
     import torch
     libs = os.path.join(os.path.dirname(torch.__file__), "lib")
     cmd = ["g++", "-shared", "-o", MARSHAL, obj, "-L", PKG, "-lsmoothrot", "-L", libs, "-ltorch_python", "-ltorch_hip", "-ltorch_cpu",
            "-lc10_hip", "-lc10", "-Wl,-rpath,$ORIGIN"]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
-        raise RuntimeError("link of _marshal.so failed:\n" + r.stderr)
+        raise RuntimeError("link of _marshal failed:\n" + r.stderr)
 
 
 def build(verbose: bool = True) -> str:
-    """Compile every source and link both shared libraries; returns the path of libsmoothrot.so."""
+    """Compile every source and link both shared libraries; returns the path of libsmoothrot.so (linked first: it needs neither
+    torch nor Python)."""
     os.makedirs(OBJ, exist_ok=True)
     with ThreadPoolExecutor(max_workers=8) as ex:
         marshal = ex.submit(_compile_marshal)
         check = ex.submit(_check_asm_loads)
         objs = list(ex.map(_compile, SOURCES))
         check.result()
-        marshal_obj = marshal.result()
     cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("link failed:\n" + r.stderr)
-    _link_marshal(marshal_obj)
+    _link_marshal(marshal.result())
     if verbose:
         print("built", LIB)
     return LIB

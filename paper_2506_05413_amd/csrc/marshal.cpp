@@ -309,4 +309,12 @@ PyModuleDef module_def = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, method
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__marshal(void) { return PyModule_Create(&module_def); }
+PyMODINIT_FUNC PyInit__marshal(void)
+{
+    PyObject *m = PyModule_Create(&module_def);
+    if (m && PyModule_AddStringConstant(m, "torch_version", SR_TORCH_VERSION) < 0) {
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
+}

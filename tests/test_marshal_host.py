@@ -5,6 +5,7 @@ import torch
 from torch._subclasses.fake_tensor import FakeTensorMode
 
 import paper_2506_05413_amd as sr
+from paper_2506_05413_amd import binding
 
 
 def device_tensors(M=4, K=128, N=32):
@@ -51,6 +52,34 @@ def test_torch_exceptions_keep_their_type():
         scalar = torch.empty((), dtype=torch.float16, device="cuda")
     with pytest.raises(IndexError):
         sr.sr_w4a4_gemm(t["q"], t["s"], t["W"], t["ws"], Y=scalar)
+
+
+@pytest.mark.filterwarnings("ignore:Accessing the data pointer")
+def test_offline_calls_do_without_the_native_half(monkeypatch):
+    """Calibration, fold and repacking marshal through ctypes and need no module that is tied to one torch."""
+    class Stream:
+        cuda_stream = 0
+
+    def unavailable():
+        raise ImportError("not built for this torch")
+
+    monkeypatch.setattr(binding, "_native", None)
+    monkeypatch.setattr(binding, "_marshal", unavailable)
+    monkeypatch.setattr(torch.cuda, "current_stream", Stream)
+    t = device_tensors()
+    with FakeTensorMode():
+        W, f = torch.empty((128, 32), dtype=torch.float16, device="cuda"), torch.empty(128, device="cuda")
+        for call in (lambda: sr.sr_calib_absmax(t["X"], f), lambda: sr.sr_pack_f6_tiles(t["W"], t["W6"]),
+                     lambda: sr.sr_fold_smooth_rotate_quant(W, f, 0.5)):
+            with pytest.raises(sr.SmoothRotError):       # the library is reached and refuses the missing memory
+                call()
+
+
+def test_native_half_of_another_torch_is_refused(monkeypatch):
+    monkeypatch.setattr(binding, "_native", None)
+    monkeypatch.setattr(torch, "__version__", "0.0.1")
+    with pytest.raises(ImportError, match="0.0.1"):
+        sr.sr_fwht_quant_act(None, None)
 
 
 @pytest.mark.gpu
