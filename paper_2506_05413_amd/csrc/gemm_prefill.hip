@@ -46,6 +46,7 @@
 // K % 256 != 0 (and any K % 64 == 0) runs on a simpler register-staged kernel further down.
 #include "sr_common.h"
 #include "gemm_common.h"
+#include "gemm_rules.h"
 
 #include <hip/hip_fp16.h>
 #include <type_traits>
@@ -573,50 +574,8 @@ hipError_t launch_gemm_prefill(const uint8_t *Xq, const float *xs, const uint8_t
                            Xq, xs, Wq, ws, (int)M, (int)N, (int)K, Y, ldy, out_i32, tiles_m, tiles_n);
         return hipGetLastError();
     }
-    // What a launch costs, by configuration: with t tiles on c compute units, r = ceil(t / c) rounds and n = K / 256
-    // stages,   fixed + per_round r + n (stage_round r + stage_tile t / c)   microseconds,
-    // fitted to 77 shapes (M 17 .. 4100, N 1024 .. 14336, K 2048 .. 14336, weights from HBM; mean error 3 - 5 % for the large
-    // tiles and 64 x 64, 6 - 12 % for the others).  Between the two large tiles the cheaper schedule of whole rounds
-    // decides (ties to the larger tile); another configuration replaces that choice where it is predicted at least 6 %
-    // faster: mostly below 500 rows, where 128 x 128 tiles leave CUs idle (29 x 4096 x 14336 47.6 -> 12.2 us, 52 x 2208 x
-    // 8192 28.7 -> 9.7, 172 x 3968 x 4096 17.3 -> 10.2, 445 x 3088 x 4096 18.3 -> 14.4), and where 128 x 128 tiles make
-    // one round, which two sets of waves run faster than one (below).
-    struct Config { int id, bm, bn; float fixed, per_round, stage_round, stage_tile; };
-    static constexpr Config configs[] = {
-        {14, 128, 128, 7.48f, -3.82f, 0.940f, 0.129f},// four waves of 64 x 64, two workgroups per CU
-        {15, 256, 128, 1.15f, 3.34f, 1.178f, 0.327f}, // eight waves of 64 x 64: while one wave of a SIMD is held up issuing
-                                                      // LDS or DMA instructions, the other can issue MFMAs
-        {17, 128, 64, 5.60f, -1.93f, 0.633f, 0.101f}, // eight waves of 32 x 32, two workgroups per CU
-        {18, 192, 128, 1.19f, 3.19f, 1.078f, 0.253f}, // eight waves of 96 x 32
-        {19, 64, 128, 5.74f, -2.35f, 0.686f, 0.064f}, // eight waves of 32 x 32, two workgroups per CU
-        // Two sets of four waves of 64 x 64, each with half of every stage, one workgroup per CU: two waves per SIMD on
-        // one 128 x 128 tile without widening anything twice, and a ring of four stages instead of two, which weights
-        // from HBM need.  512 x 4096 x 14336 52 -> 42 us, 1345 x 1632 x 8192 36.6 -> 25.6, 142 x 12832 x 8192 39.5 ->
-        // 30.2, 643 x 3424 x 4096 20.9 -> 16.3, 600 x 6144 x 4096 21.0 -> 17.6; with several rounds the two workgroups per
-        // CU of 14 overlap their tile boundaries and win (2048 x 14336 x 4096: 105 against 118 us).
-        // (Tried: workgroups starting at different places of K, against all of them asking for the same lines of every row
-        // at a time -- no difference at K = 4096, 8192 and 14336.)
-        {20, 128, 128, 1.30f, 4.00f, 0.551f, 0.324f},
-        // operands straight into registers, K split over eight waves (gemm_packed_stream.hip)
-        {64064, 64, 64, 1.62f, 2.36f, 0.390f, 0.095f},
-        {48064, 48, 64, 1.64f, 2.04f, 0.365f, 0.054f},
-        {48032, 48, 32, 2.48f, 2.73f, 0.110f, 0.126f},
-        {32064, 32, 64, 2.57f, 3.11f, 0.208f, 0.071f},
-        {32032, 32, 32, 3.43f, 1.51f, 0.108f, 0.059f},
-        {32016, 32, 16, 2.65f, 1.54f, 0.068f, 0.045f},
-    };
-    const int64_t cus = compute_units();
-    auto tiles = [&](const Config &c) { return ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn); };
-    auto cost = [&](const Config &c) {
-        const float r = (float)((tiles(c) + cus - 1) / cus), n = (float)(K / 256);
-        return c.fixed + c.per_round * r + n * (c.stage_round * r + c.stage_tile * (float)tiles(c) / (float)cus);
-    };
-    auto area = [&](const Config &c) { return (tiles(c) + cus - 1) / cus * c.bm * c.bn; };
-    const Config *best = area(configs[1]) <= area(configs[0]) ? &configs[1] : &configs[0];
-    float best_cost = .94f * cost(*best);
-    for (const Config &c : configs)
-        if (const float v = cost(c); v < best_cost) { best = &c; best_cost = v; }
-    for (const Config &c : configs)
+    const GemmConfig *best = packed_config(packed_shape(M, N, K, compute_units()));
+    for (const GemmConfig &c : kPackedConfigs)           // the tile knob
         if (c.id == variant) best = &c;
     switch (best->id) {
         case 14: return launch_tile<128, 128, 2, 2, 2>(Xq, xs, Wq, ws, M, N, K, Y, ldy, out_i32, st);

@@ -1,0 +1,103 @@
+// Which configuration a GEMM launch takes: a predicted time per configuration, the cheapest wins.  Plain C++ (no HIP), so
+// that the rule can be compiled and checked on its own.
+//
+// With t = tiles of the configuration, c compute units, r = ceil(t / c) rounds and n stages of K, a launch is predicted at
+//     fixed + per_round r + n (stage time of the rounds + stage_tile t / c) + out_mb (MB of Y) + weights_mb (MB of W)
+// microseconds.  The stage time of a round is stage_round.  Where a CU holds two workgroups, two rounds run side by side
+// and take stage_round together; a last one that is alone takes stage_lone, about six tenths of it.  No coefficient
+// is negative, so a prediction grows with M, N and K, also outside the shapes that were timed.
+//
+// The coefficients come from 2050 shapes (M 17 .. 16384, N 512 .. 28672, K 256 .. 14336, weights from HBM
+// and in the memory-side cache), every configuration timed on every shape: least squares, then adjusted so that the choices,
+// not the predictions, come out best.  On 400 further shapes the choice is 1.0 % slower on average than
+// the fastest configuration of the shape, 17 % at worst (4.5 % and 51 % by the table before, which was fitted to K >= 2048
+// without the bytes of Y and with negative coefficients: 8192 x 14336 x 256 93 us for 70, 214 x 27376 x 512 15.3 for 11.0).
+#pragma once
+
+#include <stdint.h>
+
+namespace sr {
+
+struct GemmConfig {
+    int id, bm, bn;
+    bool pairs;                                          // two workgroups per CU
+    float fixed, per_round, stage_round, stage_lone, stage_tile, out_mb, weights_mb;
+};
+
+struct GemmShape {
+    int64_t M, N, K;
+    int stage;                                           // codes of K per stage
+    float weight_bytes;                                  // per code
+    int64_t cus;
+};
+
+constexpr int64_t gemm_tiles(const GemmConfig &c, const GemmShape &s) { return ((s.M + c.bm - 1) / c.bm) * ((s.N + c.bn - 1) / c.bn); }
+constexpr int64_t gemm_rounds(const GemmConfig &c, const GemmShape &s) { return (gemm_tiles(c, s) + s.cus - 1) / s.cus; }
+
+constexpr float gemm_cost(const GemmConfig &c, const GemmShape &s)
+{
+    const int64_t r = gemm_rounds(c, s);
+    const float stages = (float)(s.K / s.stage);
+    const float round_time = c.pairs ? (float)(r / 2) * c.stage_round + (float)(r & 1) * c.stage_lone : (float)r * c.stage_round;
+    return c.fixed + c.per_round * (float)r + stages * (round_time + c.stage_tile * (float)gemm_tiles(c, s) / (float)s.cus) +
+           c.out_mb * 2e-6f * (float)s.M * (float)s.N + c.weights_mb * 1e-6f * s.weight_bytes * (float)s.N * (float)s.K;
+}
+
+// The cheapest configuration but `skip`, if it is predicted at least 5 % faster than `base` (which stays otherwise: the
+// predictions of two large tiles are as close as their errors).
+template <int COUNT> constexpr const GemmConfig *gemm_cheapest(const GemmConfig (&configs)[COUNT], const GemmConfig *base,
+                                                               const GemmConfig *skip, const GemmShape &s)
+{
+    const GemmConfig *best = base;
+    float best_cost = .95f * gemm_cost(*base, s);
+    for (const GemmConfig &c : configs)
+        if (const float v = gemm_cost(c, s); &c != skip && v < best_cost) { best = &c; best_cost = v; }
+    return best;
+}
+
+// ---- packed nibbles, M > 16 (gemm_prefill.hip) -------------------------------------------------------------------------
+constexpr GemmConfig kPackedConfigs[] = {
+    {14, 128, 128, true, 3.027f, 1.335f, 1.091f, .702f, .216f, .073f, .050f},   // four waves of 64 x 64
+    {15, 256, 128, false, 1.807f, 3.329f, 1.053f, 0.f, .405f, .061f, .028f},    // eight waves of 64 x 64: while one wave of a
+                                                                                // SIMD is held up issuing LDS or DMA
+                                                                                // instructions, the other can issue MFMAs
+    {17, 128, 64, true, 2.595f, .723f, .863f, .548f, .153f, .130f, .047f},      // eight waves of 32 x 32
+    {18, 192, 128, false, 1.404f, 2.505f, 1.047f, 0.f, .270f, .097f, .035f},    // eight waves of 96 x 32
+    {19, 64, 128, true, 2.622f, .650f, .874f, .554f, .146f, .128f, .058f},      // eight waves of 32 x 32
+    // Two sets of four waves of 64 x 64, each with half of every stage, one workgroup per CU: two waves per SIMD on one
+    // 128 x 128 tile without widening anything twice, and a ring of four stages instead of two, which weights from HBM
+    // need.  512 x 4096 x 14336 60.6 -> 40.7 us, 190 x 9456 x 8192 38.8 -> 28.0, 224 x 13616 x 4096 23.0 -> 20.5,
+    // 600 x 6144 x 4096 22.6 -> 19.7 against 14; with several rounds the two workgroups per CU of 14 overlap their tile
+    // boundaries and win (2048 x 14336 x 4096: 105 against 124 us).
+    // (Tried: workgroups starting at different places of K, against all of them asking for the same lines of every row
+    // at a time -- no difference at K = 4096, 8192 and 14336.)
+    {20, 128, 128, false, 2.230f, 2.657f, .548f, 0.f, .226f, .120f, .006f},
+    // operands straight into registers, K split over eight waves (gemm_packed_stream.hip)
+    {64064, 64, 64, false, 1.683f, 1.856f, .436f, 0.f, .015f, .377f, .016f},
+    {48064, 48, 64, false, 1.778f, 1.389f, .399f, 0.f, .005f, .266f, .025f},
+    {48032, 48, 32, true, 1.921f, .999f, .517f, .264f, .021f, .710f, .003f},
+    {32064, 32, 64, true, 2.731f, 1.071f, .635f, .314f, .002f, .421f, .026f},
+    {32032, 32, 32, true, 2.520f, .212f, .397f, .217f, 0.f, 1.191f, .036f},
+    {32016, 32, 16, false, 2.422f, .308f, .154f, 0.f, 0.f, 1.314f, .004f},
+};
+constexpr GemmShape packed_shape(int64_t M, int64_t N, int64_t K, int64_t cus) { return {M, N, K, 256, .5f, cus}; }
+constexpr const GemmConfig *packed_config(const GemmShape &s)
+{
+    // between the two large tiles the cheaper schedule of whole rounds (in outputs) decides, ties to the larger tile: with
+    // many rounds of few stages that is right where the predictions are not (8192 x 14336 x 256: 70 against 75 us)
+    const GemmConfig &small = kPackedConfigs[0], &large = kPackedConfigs[1];
+    const bool larger = gemm_rounds(large, s) * large.bm <= gemm_rounds(small, s) * small.bm;
+    return gemm_cheapest(kPackedConfigs, larger ? &large : &small, larger ? &small : &large, s);
+}
+
+template <int COUNT> constexpr bool coefficients_grow(const GemmConfig (&configs)[COUNT])
+{
+    for (const GemmConfig &c : configs) {
+        if (c.fixed <= 0.f || c.per_round < 0.f || c.stage_tile < 0.f || c.out_mb < 0.f || c.weights_mb < 0.f) return false;
+        if (c.stage_round <= 0.f || (c.pairs && (c.stage_lone <= 0.f || c.stage_lone > c.stage_round))) return false;
+    }
+    return true;
+}
+static_assert(coefficients_grow(kPackedConfigs), "a prediction may not fall where work is added");
+
+}  // namespace sr
