@@ -44,6 +44,7 @@
 // kernel; scales of a tile fetched by LDS-DMA at the start of the tile.
 #include "sr_common.h"
 #include "gemm_common.h"
+#include "gemm_rules.h"
 
 #include <type_traits>
 
@@ -460,55 +461,14 @@ hipError_t launch_pack_f6(const uint8_t *Q4, int64_t rows, int64_t K, uint8_t *T
 hipError_t launch_gemm_f6(const uint8_t *X6, const float *xs, const uint8_t *W6, const float *ws, int64_t M, int64_t N,
                           int64_t K, void *Y, int64_t ldy, int out_i32, hipStream_t st, const void *warm, size_t warm_bytes)
 {
-    // What a launch costs, by configuration: with t tiles on c compute units, r = ceil(t / c) rounds and n = K / 128
-    // stages,   fixed + per_round r + n (stage_round r + stage_tile t / c)   microseconds,
-    // fitted to 240 shapes (M 8 .. 5000, N 1024 .. 28672, K 2048 .. 14336; weights rotating over three copies).  On
-    // shapes left out of the fit the cheapest configuration by this rule is 0.9 % slower on average (29 % at worst)
-    // than the fastest one of all; the rule that knew 256 x 256 and 256 x 128 tiles only was 1.7 times slower, mostly
-    // below ~1000 rows, where those tiles leave CUs idle (37 x 6144 x 4096: 15.8 -> 6.1 us, 128 x 4096 x 14336:
-    // 40.8 -> 14.8 us, 521 x 4096 x 14336: 44.7 -> 35.4 us, 2869 x 8192 x 8192: 110 -> 88 us).  A stage costs what the
-    // vector-memory path of a CU takes for its operands, 80 - 120 GB/s whatever the shape of the tile.
-    struct Config { int id, bm, bn; float fixed, per_round, stage_round, stage_tile; };
-    static constexpr Config configs[] = {
-        {61, 256, 256, 0.f, 5.71f, .419f, .435f},     // eight waves of 128 x 64
-        {72, 192, 256, .62f, 4.11f, .385f, .320f},    // eight waves of 96 x 64
-        {65, 256, 128, .97f, 3.29f, .316f, .225f},    // eight waves of 64 x 64, a ninth for the cache-warming hint
-        {68, 128, 256, 1.93f, 2.62f, .332f, .240f},   // eight waves of 64 x 64
-        {67, 128, 128, 4.24f, 0.f, .250f, .099f},     // four waves of 64 x 64, two workgroups per CU
-        {69, 128, 64, 3.90f, 0.f, .182f, .062f},      // four waves of 64 x 32, two workgroups per CU
-        // operands straight into registers, K split over eight waves (gemm_f6_stream.hip)
-        {64064, 64, 64, 2.24f, 1.61f, .099f, .069f},
-        {48064, 48, 64, 2.00f, 1.46f, .101f, .042f},
-        {48032, 48, 32, 2.80f, 0.f, .069f, .027f},
-        {32064, 32, 64, 2.97f, 0.f, .090f, .027f},
-        {32032, 32, 32, 2.89f, 0.f, .053f, .024f},
-        {16032, 16, 32, 2.80f, 0.f, .040f, .018f},
-        {16016, 16, 16, 2.70f, .22f, .019f, .016f},
-    };
-    const int64_t cus = compute_units();
-    auto rounds = [&](const Config &c) { return (((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn) + cus - 1) / cus; };
-    auto cost = [&](const Config &c) {
-        const int64_t tiles = ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
-        const float r = (float)rounds(c), n = (float)(K / 128);
-        return c.fixed + c.per_round * r + n * (c.stage_round * r + c.stage_tile * (float)tiles / (float)cus);
-    };
-    // Between 256 x 256 and 256 x 128 tiles the cheaper schedule of whole rounds decides (the small tile, which moves more
-    // LDS bytes per product, with a handicap of 15 %); another configuration has to be predicted 10 % faster.  With weights
-    // from HBM the large tiles run closer to each other than the fit has them, and without the margin it took 192- and
-    // 128-row tiles where 256 x 256 is ahead: 1944 x 5648 x 4096 37.9 against 34.3 us, 935 x 12528 x 4096 39.7 against
-    // 35.9, 315 x 11056 x 8192 44.4 against 40.1.
-    const Config *best = rounds(configs[0]) * 100 <= rounds(configs[2]) * 50 * 115 / 100 ? &configs[0] : &configs[2];
-    const float cost65 = cost(configs[2]);
-    float best_cost = .9f * cost(*best);
-    for (const Config &c : configs)
-        if (const float v = cost(c); v < best_cost) { best = &c; best_cost = v; }
-    best_cost = cost(*best);
+    const GemmShape shape = f6_shape(M, N, K, compute_units());
+    const GemmConfig *best = f6_config(shape), *hinted = &kF6Configs[2];
     int id = best->id;
     // the hint is worth several microseconds to the next launch (44 MB read ahead save it 4 us of 67)
-    if (warm && warm_bytes >= ((size_t)1 << 20) && cost65 <= 1.15f * best_cost) id = 65;
+    if (warm && warm_bytes >= ((size_t)1 << 20) && gemm_cost(*hinted, shape) <= 1.15f * gemm_cost(*best, shape)) id = hinted->id;
     // the tile knob selects a configuration by number; not set or unknown = the rule above
     if (int64_t t; tuned(kTuneGemmTile, t)) {
-        for (const Config &c : configs)
+        for (const GemmConfig &c : kF6Configs)
             if (c.id == t) id = (int)t;
     }
     switch (id) {

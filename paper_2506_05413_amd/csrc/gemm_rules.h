@@ -7,11 +7,12 @@
 // and take stage_round together; a last one that is alone takes stage_lone, about six tenths of it.  No coefficient
 // is negative, so a prediction grows with M, N and K, also outside the shapes that were timed.
 //
-// The coefficients come from 2050 shapes (M 17 .. 16384, N 512 .. 28672, K 256 .. 14336, weights from HBM
+// The coefficients come from 2050 shapes per GEMM (M 8 or 17 .. 16384, N 512 .. 28672, K 128 or 256 .. 14336, weights from HBM
 // and in the memory-side cache), every configuration timed on every shape: least squares, then adjusted so that the choices,
-// not the predictions, come out best.  On 400 further shapes the choice is 1.0 % slower on average than
+// not the predictions, come out best.  On 400 further shapes the choice for packed nibbles is 1.0 % slower on average than
 // the fastest configuration of the shape, 17 % at worst (4.5 % and 51 % by the table before, which was fitted to K >= 2048
-// without the bytes of Y and with negative coefficients: 8192 x 14336 x 256 93 us for 70, 214 x 27376 x 512 15.3 for 11.0).
+// without the bytes of Y and with negative coefficients: 8192 x 14336 x 256 93 us for 70, 214 x 27376 x 512 15.3 for 11.0);
+// for FP6 1.1 % and 30 % (3.8 % and 72 %; 1062 x 8576 x 128 18.4 us for 6.9, 7448 x 24416 x 512 160 for 111).
 #pragma once
 
 #include <stdint.h>
@@ -53,6 +54,32 @@ template <int COUNT> constexpr const GemmConfig *gemm_cheapest(const GemmConfig 
     for (const GemmConfig &c : configs)
         if (const float v = gemm_cost(c, s); &c != skip && v < best_cost) { best = &c; best_cost = v; }
     return best;
+}
+
+// ---- FP6 pipe (gemm_f6.hip) ------------------------------------------------------------------------------------------
+constexpr GemmConfig kF6Configs[] = {
+    {61, 256, 256, false, .544f, 5.021f, .458f, 0.f, .388f, .085f, .027f},      // eight waves of 128 x 64
+    {72, 192, 256, false, 1.089f, 3.895f, .400f, 0.f, .335f, .089f, .065f},     // eight waves of 96 x 64
+    {65, 256, 128, false, 2.117f, 2.326f, .337f, 0.f, .264f, .185f, .001f},       // eight waves of 64 x 64, a ninth for the hint
+    {68, 128, 256, false, 2.153f, 2.385f, .336f, 0.f, .236f, .125f, .091f},     // eight waves of 64 x 64
+    {67, 128, 128, true, 2.743f, .715f, .474f, .260f, .129f, .077f, .047f},     // four waves of 64 x 64
+    {69, 128, 64, true, 2.658f, .645f, .402f, .214f, .049f, .138f, .066f},      // four waves of 64 x 32
+    // operands straight into registers, K split over eight waves (gemm_f6_stream.hip)
+    {64064, 64, 64, false, 1.536f, 1.934f, .122f, 0.f, .006f, .294f, .105f},
+    {48064, 48, 64, false, 1.537f, 1.601f, .111f, 0.f, .001f, .431f, .093f},
+    {48032, 48, 32, true, 2.048f, .349f, .144f, .085f, .012f, .505f, .088f},
+    {32064, 32, 64, true, 2.191f, .319f, .185f, .090f, .005f, .434f, .108f},
+    {32032, 32, 32, true, 2.086f, .239f, .117f, .069f, .008f, .542f, .095f},
+    {16032, 16, 32, true, 1.952f, .151f, .080f, .048f, .007f, .941f, .124f},
+    {16016, 16, 16, false, 2.192f, .298f, .030f, 0.f, .001f, .868f, .114f},
+};
+constexpr GemmShape f6_shape(int64_t M, int64_t N, int64_t K, int64_t cus) { return {M, N, K, 128, .75f, cus}; }
+constexpr const GemmConfig *f6_config(const GemmShape &s)
+{
+    // between 256 x 256 and 256 x 128 tiles the cheaper schedule of whole rounds decides first (the small tile, which moves
+    // more LDS bytes per product, with a handicap of 15 %)
+    const GemmConfig *base = gemm_rounds(kF6Configs[0], s) * 100 <= gemm_rounds(kF6Configs[2], s) * 50 * 115 / 100 ? &kF6Configs[0] : &kF6Configs[2];
+    return gemm_cheapest(kF6Configs, base, nullptr, s);
 }
 
 // ---- packed nibbles, M > 16 (gemm_prefill.hip) -------------------------------------------------------------------------
@@ -98,6 +125,6 @@ template <int COUNT> constexpr bool coefficients_grow(const GemmConfig (&configs
     }
     return true;
 }
-static_assert(coefficients_grow(kPackedConfigs), "a prediction may not fall where work is added");
+static_assert(coefficients_grow(kF6Configs) && coefficients_grow(kPackedConfigs), "a prediction may not fall where work is added");
 
 }  // namespace sr

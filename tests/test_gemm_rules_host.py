@@ -1,4 +1,4 @@
-"""The launch rule of the packed GEMM (csrc/gemm_rules.h), compiled on their own: what they predict is possible and grows with
+"""The launch rules of the two GEMMs (csrc/gemm_rules.h), compiled on their own: what they predict is possible and grows with
 the work, and what they choose is no slower than the two large tiles they started from."""
 import os
 import subprocess
@@ -15,10 +15,12 @@ int main()
     char kind[16];
     long long M, N, K;
     while (std::scanf("%15s %lld %lld %lld", kind, &M, &N, &K) == 4) {
-        const sr::GemmShape s = sr::packed_shape(M, N, K, 256);
-        const sr::GemmConfig *c = sr::packed_config(s);
+        const bool f6 = !std::strcmp(kind, "f6");
+        const sr::GemmShape s = f6 ? sr::f6_shape(M, N, K, 256) : sr::packed_shape(M, N, K, 256);
+        const sr::GemmConfig *c = f6 ? sr::f6_config(s) : sr::packed_config(s);
         std::printf("%d %.6f", c->id, sr::gemm_cost(*c, s));
-        for (const sr::GemmConfig &d : sr::kPackedConfigs) std::printf(" %.6f", sr::gemm_cost(d, s));
+        if (f6) for (const sr::GemmConfig &d : sr::kF6Configs) std::printf(" %.6f", sr::gemm_cost(d, s));
+        else for (const sr::GemmConfig &d : sr::kPackedConfigs) std::printf(" %.6f", sr::gemm_cost(d, s));
         std::printf("\n");
     }
 }
@@ -45,7 +47,7 @@ KS = {"packed": [256, 512, 768, 1024, 2048, 4096, 8192, 14336, 28672], "f6": [12
 OPS = {"packed": 3.7e15, "f6": 6.2e15}                           # the most the bare matrix loops reach
 
 
-@pytest.mark.parametrize("kind", ["packed"])
+@pytest.mark.parametrize("kind", ["packed", "f6"])
 def test_predictions_grow_with_the_work(rule, kind):
     for axis, values in enumerate((MS, NS, KS[kind])):
         shapes = [(m, n, k) for m in MS for n in NS for k in KS[kind]]
@@ -58,7 +60,7 @@ def test_predictions_grow_with_the_work(rule, kind):
                 assert all(a <= b * (1 + 1e-6) for a, b in zip(at[s][2], at[tuple(t)][2])), (s, t)
 
 
-@pytest.mark.parametrize("kind", ["packed"])
+@pytest.mark.parametrize("kind", ["packed", "f6"])
 def test_no_prediction_beats_the_matrix_pipe(rule, kind):
     shapes = [(m, n, k) for m in MS for n in NS for k in KS[kind]]
     for s, (choice, us, every) in zip(shapes, rule(kind, shapes)):
@@ -75,6 +77,10 @@ MEASURED = {
                (4096, 14336, 256): {14: 40.01, 15: 37.31, 17: 50.06, 18: 41.43, 19: 47.20, 20: 56.23},
                (8192, 14336, 256): {14: 74.83, 15: 70.40, 17: 99.36, 18: 77.69, 19: 94.73, 20: 109.30},
                (16384, 4096, 1024): {14: 83.17, 15: 78.29, 17: 111.15, 18: 91.37, 19: 107.38, 20: 103.50}},
+    "f6": {(947, 24592, 2048): {61: 51.65, 72: 50.01, 65: 61.70, 68: 64.84, 67: 58.79},      # (45.5 and 49.0 in other runs)
+           (1050, 7776, 2048): {61: 16.73, 72: 17.73, 65: 27.94, 68: 29.25, 67: 26.56},
+           (1062, 8576, 128): {61: 6.94, 72: 6.93, 65: 8.70, 68: 9.12, 67: 7.54, 32064: 18.40},
+           (7448, 24416, 512): {61: 111.37, 72: 148.21, 65: 165.56, 68: 142.00, 67: 160.73}},
 }
 
 
