@@ -41,6 +41,27 @@ def rule(tmp_path_factory):
     return run
 
 
+def test_gpu_tests_force_every_configuration(rule, tmp_path):
+    """A number that no rule knows would silently run the automatic choice."""
+    import test_gpu_f6_configs as f6
+    import test_gpu_gemm_configs as packed
+    (tmp_path / "ids.cpp").write_text("""
+#include "gemm_rules.h"
+#include <cstdio>
+int main()
+{
+    for (const sr::GemmConfig &c : sr::kPackedConfigs) std::printf("packed %d %d %d\\n", c.id, c.bm, c.bn);
+    for (const sr::GemmConfig &c : sr::kF6Configs) std::printf("f6 %d %d %d\\n", c.id, c.bm, c.bn);
+}
+""")
+    subprocess.run(["g++", "-std=c++17", "-I", CSRC, "-o", str(tmp_path / "ids"), str(tmp_path / "ids.cpp")], check=True)
+    out = subprocess.run([str(tmp_path / "ids")], capture_output=True, text=True, check=True).stdout
+    for kind, module in (("packed", packed), ("f6", f6)):
+        tiles = {int(i): (int(m), int(n)) for k, i, m, n in (l.split() for l in out.splitlines()) if k == kind}
+        assert sorted(tiles) == sorted(module.CONFIGS)
+        assert {i: t for i, t in tiles.items() if i < 1000} == module.TILES
+
+
 MS = [17, 31, 64, 129, 200, 333, 513, 777, 1024, 2048, 3000, 4096, 8192, 16384, 65536]
 NS = [16, 512, 1040, 2784, 4096, 6144, 14336, 28672]
 KS = {"packed": [256, 512, 768, 1024, 2048, 4096, 8192, 14336, 28672], "f6": [128, 256, 512, 1024, 2048, 4096, 8192, 14336, 28672]}

@@ -76,10 +76,10 @@ def test_seeded_random_shapes(gpu):
         assert np.array_equal(got.astype(np.int64), o.gemm_i32_c(cx, cw)), (M, N, K)
 
 
-@pytest.mark.parametrize("tile", ["61", "63", "64", "65", "66"])
-def test_every_tile_configuration(gpu, tile, tune):
-    """The launch heuristic picks one configuration per shape; each of them is checked on a shape with
-    ragged edges and more tiles than workgroups can hold at once is covered by the full-size test below."""
+@pytest.mark.parametrize("tile", ["61", "65"])
+def test_large_tile_configurations(gpu, tile, tune):
+    """The two large tiles the launch rule starts from, on a shape with ragged edges (every configuration:
+    test_gpu_f6_configs.py)."""
     tune(gpu.SR_TUNE_GEMM_TILE, tile)
     M, N, K = 700, 1040, 640
     cx, cw = wl.random_codes(1, M, K), wl.random_codes(2, N, K)
@@ -336,38 +336,46 @@ def test_gemm_cache_warming_changes_nothing(gpu, tune, M, N, K, grid):
 
 
 @pytest.mark.parametrize("M", [700, 1100])
-def test_row_kernel_walking_over_rows(gpu, tune, M):
-    """K = 14336 with many rows: as many workgroups as the chip holds, each walking over several rows and
-    fetching its next row while it works (forced here at a row count that leaves workgroups with one, two or
-    three rows and a ragged last tile block).  Same arithmetic as one workgroup per row: every output must
-    equal that launch's bit for bit, and the oracle's under the boundary rule."""
+def test_threads_per_row_of_14336(gpu, tune, M):
+    """K = 14336 by workgroups of 896 threads (the choice while every row has a CU to itself) and of 512 (beyond), each
+    forced at row counts where the launch takes the other, with a ragged last tile block; with and without a gate row.
+    Same arithmetic: the outputs must equal each other bit for bit, and the oracle's under the boundary rule."""
     K = 14336
     X = wl.gauss_acts(31 + M, M, K, 3, 300.0)
     inv_s = np.random.default_rng(M).uniform(0.5, 2.0, K).astype(np.float32)
-    Xd, inv = torch.from_numpy(X).cuda(), torch.from_numpy(inv_s).cuda()
+    G = wl.gate_up(57 + M, M, K, 3, 1.0)[0]
+    Xd, Gd, inv = torch.from_numpy(X).cuda(), torch.from_numpy(G).cuda(), torch.from_numpy(inv_s).cuda()
 
     def run_all():
         outs = []
         for pre in (inv, None):
             outs += list(gpu.sr_fwht_quant_act_f6(Xd, pre, 0.9))
             outs += list(gpu.sr_fwht_quant_act(Xd, pre, 0.9))
+        for pre in (inv, None):
+            outs += list(gpu.sr_swiglu_fwht_quant_act_f6(Gd, Xd, pre, 0.9))
+            outs += list(gpu.sr_swiglu_fwht_quant_act(Gd, Xd, pre, 0.9))
         torch.cuda.synchronize()
         return [t.cpu().numpy() for t in outs]
 
     tune(gpu.SR_TUNE_FWHT_STREAM, 0)
-    one = run_all()
+    narrow = run_all()
     tune(gpu.SR_TUNE_FWHT_STREAM, 1)
-    walk = run_all()
-    for a, b in zip(one, walk):
+    wide = run_all()
+    assert len(narrow) == len(wide) == 16
+    for a, b in zip(narrow, wide):
         assert np.array_equal(a, b)
     ref = o.fwht_quant_act(X, inv_s, 0.9)
-    check_scales(walk[1], ref["x_scale"])
-    check_codes(fc.f6_codes(fc.f6_tiles_unpack(walk[0], M, K)), ref["codes"], ref["t"])
-    check_codes(o.unpack_int4(walk[2]), ref["codes"], ref["t"])
+    check_scales(wide[1], ref["x_scale"])
+    check_codes(fc.f6_codes(fc.f6_tiles_unpack(wide[0], M, K)), ref["codes"], ref["t"])
+    check_codes(o.unpack_int4(wide[2]), ref["codes"], ref["t"])
     ref = o.fwht_quant_act(X, None, 0.9)
-    check_scales(walk[5], ref["x_scale"])
-    check_codes(fc.f6_codes(fc.f6_tiles_unpack(walk[4], M, K)), ref["codes"], ref["t"])
-    check_codes(o.unpack_int4(walk[6]), ref["codes"], ref["t"])
+    check_scales(wide[5], ref["x_scale"])
+    check_codes(fc.f6_codes(fc.f6_tiles_unpack(wide[4], M, K)), ref["codes"], ref["t"])
+    check_codes(o.unpack_int4(wide[6]), ref["codes"], ref["t"])
+    ref = o.fwht_quant_swiglu(G, X, inv_s, 0.9)
+    check_scales(wide[9], ref["x_scale"])
+    check_codes(fc.f6_codes(fc.f6_tiles_unpack(wide[8], M, K)), ref["codes"], ref["t"])
+    check_codes(o.unpack_int4(wide[10]), ref["codes"], ref["t"])
 
 
 @pytest.mark.parametrize("M,K", [(5, 896), (24, 14336), (9, 4096)])

@@ -1,6 +1,8 @@
 """Every configuration of the FP6-pipe GEMM the launch rule can pick, forced where its indexing can go wrong: fewer K
-chunks than waves, K remainders of the wave split and of the ring, one block of rows, ragged last tiles on both sides,
-more tiles than workgroups.  INT32 accumulators are integers in fp32 and must equal the oracle's bit for bit."""
+chunks than waves, K remainders of the wave split and of the ring, one block of rows, ragged last tiles on both sides; and
+the persistent ones with a grid of eight workgroups, so that each walks over several tiles, with fewer K stages than the ring
+has slots and with K that leaves the ring at another slot than it began.  INT32 accumulators are integers in fp32 and must
+equal the oracle's bit for bit."""
 import numpy as np
 import pytest
 import torch
@@ -11,15 +13,12 @@ from parity import check_output
 
 pytestmark = pytest.mark.gpu
 
-CONFIGS = [67, 68, 69, 72, 64064, 48064, 48032, 32064, 32032, 16032, 16016]
+CONFIGS = [61, 65, 67, 68, 69, 72, 64064, 48064, 48032, 32064, 32032, 16032, 16016]
+TILES = {61: (256, 256), 65: (256, 128), 67: (128, 128), 68: (128, 256), 69: (128, 64), 72: (192, 256)}      # persistent workgroups
 SHAPES = [(1, 16, 128), (9, 48, 1152), (17, 80, 2176), (65, 208, 384), (200, 1040, 3200), (40, 4112, 2304)]
 
 
-@pytest.mark.parametrize("config", CONFIGS)
-@pytest.mark.parametrize("M,N,K", SHAPES)
-def test_forced_configuration(gpu, tune, config, M, N, K):
-    print("case", config, M, N, K, flush=True)
-    tune(gpu.SR_TUNE_GEMM_TILE, config)
+def compare(gpu, M, N, K):
     cx, cw = wl.random_codes(M + K, M, K), wl.random_codes(N + 3 * K, N, K)
     X6, W6 = (gpu.sr_pack_f6_tiles(torch.from_numpy(o.pack_int4(c)).cuda()) for c in (cx, cw))
     want = o.gemm_i32_c(cx, cw)
@@ -34,3 +33,22 @@ def test_forced_configuration(gpu, tune, config, M, N, K):
     assert bool((full[:, N:] == -7).all())
     assert np.array_equal(full[:, :N].cpu().numpy().astype(np.int64), want)
     check_output(Y.cpu().numpy(), o.dequant_out(want, xs[1:].astype(np.float64), ws[1:].astype(np.float64)))
+
+
+@pytest.mark.parametrize("config", CONFIGS)
+@pytest.mark.parametrize("M,N,K", SHAPES)
+def test_forced_configuration(gpu, tune, config, M, N, K):
+    print("case", config, M, N, K, flush=True)
+    tune(gpu.SR_TUNE_GEMM_TILE, config)
+    compare(gpu, M, N, K)
+
+
+@pytest.mark.parametrize("config", TILES)
+@pytest.mark.parametrize("M,N,K", [(1100, 1040, 128), (1030, 784, 384), (777, 1168, 640), (1100, 1040, 1152)])
+def test_several_tiles_per_workgroup(gpu, tune, config, M, N, K):
+    print("case", config, M, N, K, flush=True)
+    bm, bn = TILES[config]
+    assert -(-M // bm) * -(-N // bn) > 2 * 8             # every workgroup has two tiles, some three or more
+    tune(gpu.SR_TUNE_GEMM_TILE, config)
+    tune(gpu.SR_TUNE_GEMM_GRID, 8)
+    compare(gpu, M, N, K)

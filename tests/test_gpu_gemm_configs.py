@@ -1,6 +1,8 @@
 """Every configuration of the packed-nibble GEMM (M > 16) the launch rule can pick, forced where its indexing can go
-wrong: fewer K chunks than waves, K remainders of the wave split, ragged last tiles on both sides, more tiles than
-workgroups, K that only the generic kernel takes.  INT32 accumulators must equal the oracle's bit for bit."""
+wrong: fewer K chunks than waves, K remainders of the wave split, ragged last tiles on both sides, K that only the generic
+kernel takes; and the persistent ones with a grid of eight workgroups, so that each walks over several tiles, with fewer K
+stages than the ring has slots and with K that leaves the ring at another slot than it began.  INT32 accumulators must equal
+the oracle's bit for bit."""
 import numpy as np
 import pytest
 import torch
@@ -12,14 +14,11 @@ from parity import check_output
 pytestmark = pytest.mark.gpu
 
 CONFIGS = [14, 15, 17, 18, 19, 20, 64064, 48064, 48032, 32064, 32032, 32016]
+TILES = {14: (128, 128), 15: (256, 128), 17: (128, 64), 18: (192, 128), 19: (64, 128), 20: (128, 128)}      # persistent workgroups
 SHAPES = [(17, 16, 256), (33, 80, 2304), (49, 208, 4352), (65, 48, 768), (200, 1040, 2560), (40, 4112, 4608), (70, 96, 192)]
 
 
-@pytest.mark.parametrize("config", CONFIGS)
-@pytest.mark.parametrize("M,N,K", SHAPES)
-def test_forced_configuration(gpu, tune, config, M, N, K):
-    print("case", config, M, N, K, flush=True)
-    tune(gpu.SR_TUNE_GEMM_TILE, config)
+def compare(gpu, M, N, K):
     cx, cw = wl.random_codes(M + K, M, K), wl.random_codes(N + 3 * K, N, K)
     Xq, Wq = (torch.from_numpy(o.pack_int4(c)).cuda() for c in (cx, cw))
     want = o.gemm_i32_c(cx, cw)
@@ -32,3 +31,22 @@ def test_forced_configuration(gpu, tune, config, M, N, K):
     assert bool((full[:, N:] == -7).all())
     assert np.array_equal(full[:, :N].cpu().numpy().astype(np.int64), want)
     check_output(Y.cpu().numpy(), o.dequant_out(want, xs.astype(np.float64), ws.astype(np.float64)))
+
+
+@pytest.mark.parametrize("config", CONFIGS)
+@pytest.mark.parametrize("M,N,K", SHAPES)
+def test_forced_configuration(gpu, tune, config, M, N, K):
+    print("case", config, M, N, K, flush=True)
+    tune(gpu.SR_TUNE_GEMM_TILE, config)
+    compare(gpu, M, N, K)
+
+
+@pytest.mark.parametrize("config", TILES)
+@pytest.mark.parametrize("M,N,K", [(1100, 1040, 256), (1030, 784, 768), (777, 1168, 1280), (1100, 1040, 2304)])
+def test_several_tiles_per_workgroup(gpu, tune, config, M, N, K):
+    print("case", config, M, N, K, flush=True)
+    bm, bn = TILES[config]
+    assert -(-M // bm) * -(-N // bn) > 2 * 8             # every workgroup has two tiles, some three or more
+    tune(gpu.SR_TUNE_GEMM_TILE, config)
+    tune(gpu.SR_TUNE_GEMM_GRID, 8)
+    compare(gpu, M, N, K)

@@ -42,8 +42,9 @@ def test_swiglu_orders(gpu, K):
 
 @pytest.mark.parametrize("K,M", [(14336, 300), (14336, 100), (14336, 3), (7168, 600), (7168, 4), (8192, 5), (16384, 3), (28672, 2), (2048, 9), (1024, 3)])
 def test_swiglu_thread_counts(gpu, K, M):
-    """The gated prologue on the plain row kernel, with every number of threads per row its launcher picks
-    (K = 14336 above 256 rows and K = 7168 above 512 rows: 256 threads; fewer rows, and the longer rows: 512 or 1024)."""
+    """The gated prologue without the general kernel, with every number of threads per row its launchers pick (K = 14336 in
+    two passes: 512 threads above as many rows as there are CUs, 896 up to there; K = 7168: 256 above 512 rows, 512 up to
+    there; 16384 and 28672: 1024)."""
     G, U = wl.gate_up(21 + M, M, K, 3, 500.0)
     inv_s = np.exp(np.random.default_rng(K + M).standard_normal(K) * 0.5).astype(np.float32)
     compare_swiglu(gpu, G, U, inv_s, 0.9, "K=%d M=%d" % (K, M))
