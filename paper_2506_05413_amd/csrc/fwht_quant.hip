@@ -637,10 +637,9 @@ hipError_t launch_one_ex(const void *X, int64_t rows, int64_t ldx, const float *
 
 }  // namespace
 
-// K = 4096: below this many rows the wave-per-row kernel leaves most of the chip idle (4 rows per workgroup)
-// and the workgroup-per-row kernel has the shorter critical path.
-constexpr int64_t kWaveKernelMinRows = 1024;   // measured: 3.3 - 4.8 us against 4.2 - 5.9 us up to 512 rows, equal at 1024
-constexpr int64_t kTwoPassMaxRows4096 = 3072;  // the two-pass workgroup-per-row kernel up to here (see launch_fwht_quant)
+// K = 4096: the two-pass workgroup-per-row kernel up to here, a wave per row beyond (see launch_fwht_quant)
+constexpr int64_t kTwoPassMaxRows4096 = 3072;
+constexpr int64_t kTwoPassMaxRows4096Heads = 1024;       // head-wise transform (see launch_fwht_quant_ex)
 
 template <bool HAS_PRE, bool F6, bool STAGED = false, bool MASKED = false>
 hipError_t launch_wave4096(const void *X, int64_t rows, int64_t ldx, const float *pre, float clip, float post_scale,
@@ -670,7 +669,7 @@ hipError_t launch_fwht_quant(const void *X, int64_t rows, int64_t K, int64_t ldx
     // kernel and 4.4 / 5.4 / 6.3 / 7.2 / 9.4 / 14.0 for a wave per row); a wave per row beyond (16384 rows: 52 against 57 us)
     if (K == 2048 || K == 8192 || K == 14336 || (K == 4096 && (pick == 5 || (pick == 0 && rows <= kTwoPassMaxRows4096))))
         return launch_fwht_two_pass(X, rows, K, ldx, pre, clip, post_scale, Q, scale_out, nullptr, 0, st, f6, warm, warm_bytes);
-    if (K == 4096 && (pick == 1 || pick == 3 || pick == 4 || (pick == 0 && rows > kWaveKernelMinRows))) {
+    if (K == 4096 && (pick == 0 || pick == 1 || pick == 3 || pick == 4)) {
         // factors through LDS (one copy per workgroup) unless the knob asks for per-wave vector loads (4)
         if (pre && pick != 4 && (reinterpret_cast<uintptr_t>(pre) & 15u) == 0 && ldx * 2 * rows < (int64_t)1 << 40)
             return f6 ? launch_wave4096<true, true, true>(X, rows, ldx, pre, clip, post_scale, Q, scale_out, st, warm, warm_bytes)
@@ -709,16 +708,16 @@ hipError_t launch_fwht_quant_ex(const void *X, int64_t rows, int64_t K, int64_t 
     // by a wave per row.  There two passes would be faster too (2048 rows 9.6 / 10.0 -> 9.0 / 9.4 us, 8000 rows across
     // 26.2 -> 21.8), but add the values in another order (index bits 0..11 in turn; a wave per row does 0, 1, 2, 9, 10, 11
     // before 3..8): about one code in a million, on a rounding boundary, comes out one off.
-    if (!ex.gate && ex.n_grid == 0 && (K == 2048 || K == 4096 || K == 8192)) {
+    if (!ex.gate && !f6 && ex.n_grid == 0 && (K == 2048 || K == 4096 || K == 8192)) {
         // no search: the ratio "chosen" for every row is the fixed one (the kernel does not report it)
         if (ex.ratio_out) {
             hipLaunchKernelGGL(fill_f32_kernel, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, st, ex.ratio_out, rows, clip);
             if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
         }
-        if (K == 4096 && rows > kWaveKernelMinRows)
+        if (K == 4096 && rows > kTwoPassMaxRows4096Heads)
             return pre ? launch_wave4096<true, false, false, true>(X, rows, ldx, pre, clip, post_scale, Q, scale_out, st, nullptr, 0, ex.had_mask)
                        : launch_wave4096<false, false, false, true>(X, rows, ldx, pre, clip, post_scale, Q, scale_out, st, nullptr, 0, ex.had_mask);
-        return launch_fwht_two_pass_heads(X, rows, K, ldx, pre, clip, post_scale, Q, scale_out, ex.had_mask, st, f6);
+        return launch_fwht_two_pass_heads(X, rows, K, ldx, pre, clip, post_scale, Q, scale_out, ex.had_mask, st);
     }
     // the gate alone (the FFN down-projection input) goes through the plain kernels: fewer passes over the row
     // than the general kernel below (K = 14336, 2048 rows: 38 against 68 us)
@@ -736,13 +735,11 @@ hipError_t launch_fwht_quant_ex(const void *X, int64_t rows, int64_t K, int64_t 
         }
 #undef SR_CASE
     }
-    if (f6 && ex.n_grid > 0) return hipErrorInvalidValue;
-    if (f6) {
+    if (f6) {                                            // a gate row of the other K; nothing else asks for tiles
+        if (!ex.gate || ex.n_grid > 0) return hipErrorInvalidValue;
 #define SR_CASE(KK) case KK: return launch_one_ex<KK, true>(X, rows, ldx, pre, clip, post_scale, Q, scale_out, ex, st);
         switch (K) {                                    // K % 128 == 0
-            SR_CASE(128) SR_CASE(256) SR_CASE(512) SR_CASE(1024) SR_CASE(2048)
-            SR_CASE(4096) SR_CASE(8192) SR_CASE(16384) SR_CASE(32768)
-            SR_CASE(896) SR_CASE(1792) SR_CASE(3584) SR_CASE(7168) SR_CASE(14336) SR_CASE(28672)
+            SR_CASE(128) SR_CASE(256) SR_CASE(512) SR_CASE(32768) SR_CASE(896) SR_CASE(1792)
             default: return hipErrorInvalidValue;
         }
 #undef SR_CASE

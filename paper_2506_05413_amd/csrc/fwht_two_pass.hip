@@ -112,7 +112,7 @@ __global__ __launch_bounds__((TwoPass<K, THREADS>::NT)) void fwht_two_pass_kerne
                                                                       uint32_t had_mask)
 {
     using S = TwoPass<K, THREADS>;
-    static_assert(!MASKED || (!GATE && !S::KRON), "head-wise: powers of two without a gate row");
+    static_assert(!MASKED || (!GATE && !F6 && !S::KRON), "head-wise: powers of two without a gate row, nibbles");
     constexpr int NT = S::NT, NW = NT / 64;
     const uint32_t mask = MASKED ? had_mask : 0xFFFFFFFFu;
     extern __shared__ __attribute__((aligned(16))) float row[];
@@ -281,23 +281,23 @@ hipError_t launch_k(const void *X, int64_t rows, int64_t ldx, const float *pre, 
 
 template <int K>
 hipError_t launch_masked(const void *X, int64_t rows, int64_t ldx, const float *pre, float clip, float post_scale, uint8_t *Q,
-                         float *scale_out, uint32_t had_mask, hipStream_t st, bool f6)
+                         float *scale_out, uint32_t had_mask, hipStream_t st)
 {
     const __half *x = static_cast<const __half *>(X);
-#define SR_LAUNCH(P, F) launch<K, 0, P, F, false, true>(x, rows, ldx, pre, clip, post_scale, Q, scale_out, nullptr, 0, st, nullptr, 0, had_mask)
-    return pre ? (f6 ? SR_LAUNCH(true, true) : SR_LAUNCH(true, false)) : (f6 ? SR_LAUNCH(false, true) : SR_LAUNCH(false, false));
+#define SR_LAUNCH(P) launch<K, 0, P, false, false, true>(x, rows, ldx, pre, clip, post_scale, Q, scale_out, nullptr, 0, st, nullptr, 0, had_mask)
+    return pre ? SR_LAUNCH(true) : SR_LAUNCH(false);
 #undef SR_LAUNCH
 }
 
 }  // namespace
 
 hipError_t launch_fwht_two_pass_heads(const void *X, int64_t rows, int64_t K, int64_t ldx, const float *pre, float clip,
-                                      float post_scale, uint8_t *Q, float *scale_out, uint32_t had_mask, hipStream_t st, bool f6)
+                                      float post_scale, uint8_t *Q, float *scale_out, uint32_t had_mask, hipStream_t st)
 {
     switch (K) {
-        case 2048: return launch_masked<2048>(X, rows, ldx, pre, clip, post_scale, Q, scale_out, had_mask, st, f6);
-        case 4096: return launch_masked<4096>(X, rows, ldx, pre, clip, post_scale, Q, scale_out, had_mask, st, f6);
-        case 8192: return launch_masked<8192>(X, rows, ldx, pre, clip, post_scale, Q, scale_out, had_mask, st, f6);
+        case 2048: return launch_masked<2048>(X, rows, ldx, pre, clip, post_scale, Q, scale_out, had_mask, st);
+        case 4096: return launch_masked<4096>(X, rows, ldx, pre, clip, post_scale, Q, scale_out, had_mask, st);
+        case 8192: return launch_masked<8192>(X, rows, ldx, pre, clip, post_scale, Q, scale_out, had_mask, st);
         default: return hipErrorInvalidValue;
     }
 }

@@ -117,9 +117,9 @@ hipError_t launch_fwht_two_pass(const void *X_f16, int64_t rows, int64_t K, int6
                                 float post_scale, uint8_t *Q, float *scale_out, const __half *gate, int64_t ldg,
                                 hipStream_t st, bool f6, const void *warm, size_t warm_bytes);
 
-// The same with only the index bits of had_mask transformed (head-wise), K = 2048, 4096 and 8192.
+// The same with only the index bits of had_mask transformed (head-wise), K = 2048, 4096 and 8192, packed nibbles.
 hipError_t launch_fwht_two_pass_heads(const void *X_f16, int64_t rows, int64_t K, int64_t ldx, const float *pre, float clip,
-                                      float post_scale, uint8_t *Q, float *scale_out, uint32_t had_mask, hipStream_t st, bool f6);
+                                      float post_scale, uint8_t *Q, float *scale_out, uint32_t had_mask, hipStream_t st);
 
 // Optional extras of the row kernel (see fwht_quant.hip).
 constexpr int kMaxClipGrid = 32;
