@@ -16,7 +16,8 @@
  *  - Every data pointer is DEVICE memory owned by the caller.  The library never
  *    allocates, frees or keeps a pointer and is re-entrant.  Its only process-wide
  *    state: the tuning knobs of sr_tune_set (all "auto" unless a caller sets one), a
- *    cached compute-unit count per device, and the device-resident scratch array of
+ *    cached compute-unit count per device, a flag per kernel and device that its LDS
+ *    limit has been raised, and the device-resident scratch array of
  *    sr_fold_smooth_rotate_quant_noalloc.  No environment variable is read.
  *  - `stream` is a hipStream_t passed as void* (NULL = the default stream).  Calls
  *    only enqueue work and return; they never synchronise.
@@ -299,7 +300,8 @@ SR_API int sr_w4a4_linear_decode(const void *X_f16, int64_t M, int64_t K, int64_
  * matrix instruction reads without any unpacking:
  *
  *   a code matrix [rows, K] (K % 128 == 0; rows padded to a multiple of 8 -- the padding rows may hold
- *   anything: sr_pack_f6_tiles and the activation quantisers write zero codes there, and
+ *   anything: sr_pack_f6_tiles and the activation quantisers write zero codes there (and a code 0 may be
+ *   the field 0 or 32 = -0 anywhere: a negative value that rounds to 0 is stored as 32), and
  *   the GEMM multiplies them but never stores their outputs; every 6-bit pattern is a finite number) is
  *   cut into blocks of 8 rows x 128 codes; block (R, C) is 768 bytes at ((C * rows/8) + R) * 768
  *   (all row blocks of one 128-code chunk are contiguous);
@@ -345,9 +347,8 @@ SR_API int sr_fwht_quant_act_f6(const void *X_f16, int64_t M, int64_t K, int64_t
  *   next_operand   device memory, readable for next_bytes bytes, 16-byte aligned; NULL with next_bytes = 0
  *                  gives sr_fwht_quant_act_f6
  *   next_bytes     the last next_bytes % 128 bytes are not touched
- * A hint: honoured where the launch is large enough to move megabytes on the side (K = 4096 with more than 1024
- * rows; K = 14336 and the other orders served by the default workgroup-per-row launch from 256 rows on), ignored
- * otherwise.  Errors as sr_fwht_quant_act_f6, plus SR_ERR_NULL / SR_ERR_ALIGN for the hint.
+ * A hint: honoured where the launch is large enough to move megabytes on the side (K = 2048, 4096, 8192, 14336 and
+ * the other orders served by the default workgroup-per-row launch, from 256 rows on), ignored otherwise.  Errors as sr_fwht_quant_act_f6, plus SR_ERR_NULL / SR_ERR_ALIGN for the hint.
  */
 SR_API int sr_fwht_quant_act_f6_warm(const void *X_f16, int64_t M, int64_t K, int64_t ldx,
                               const float *inv_s, float clip, uint8_t *X6, float *x_scale,

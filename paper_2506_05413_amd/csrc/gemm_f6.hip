@@ -16,7 +16,7 @@
 // the all -8 worst case) and issues at 5.4 - 6.2 POP/s where the int8 MFMA reaches 3.3 - 3.7.
 //
 // The operands arrive already packed as 6-bit fields in the layout the MFMA wants ("f6 tiles",
-// written by pack_f6.hip and by the activation quantiser), so the main loop has no vector-ALU
+// written by sr_pack_f6_tiles and by the activation quantiser), so the main loop has no vector-ALU
 // work at all: LDS-DMA loads, LDS reads, MFMAs.
 //
 // f6 tiles of a code matrix [rows, K], K % 128 == 0, rows padded to a multiple of 8:

@@ -12,7 +12,7 @@
 // waves split K: wave w takes the 128-code chunks w, w + NW, ..  Every wave reads each byte of its chunks once, so
 // nothing is shared through LDS and the loop has no barrier; the waves' sums (exact in fp32, any order) meet in
 // LDS at the end.  What bounds it: the ~90 GB/s at which a CU takes operands from L2 (64 x 64 outputs, K = 14336:
-// 0.13 us per 12 KB stage), so near-square tiles win once N / 16 column tiles fill the chip (launch_gemm_f6 picks).
+// 0.13 us per 12 KB stage), so near-square tiles win once N / 16 column tiles fill the chip (gemm_rules.h picks).
 // Measured against the 256 x 128 tile kernel, weights in the memory-side cache: 37 x 6144 x 4096 15.8 -> 6.1 us,
 // 37 x 4096 x 14336 40.5 -> 10.4, 128 x 4096 x 14336 40.8 -> 14.8, 256 x 4096 x 4096 17.2 -> 8.6; the 18.9 MB of the
 // first take 3.6 us to read.  Non-temporal loads of W: 5 % faster from HBM, 5 - 20 % slower out of that cache; dropped.

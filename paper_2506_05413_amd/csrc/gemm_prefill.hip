@@ -31,8 +31,9 @@
 //    whole 128-byte lines (256 codes per row per stage) -- half-line fetches were re-fetched
 //    from L2 each time, an int8 copy of X doubled its traffic and was slower.
 //  * Global -> LDS copies use the LDS-DMA form of the global load (no staging registers) into a
-//    ring of two stages of 256 codes; one barrier per stage; per 64 codes a register-level
-//    software pipeline (LDS reads for t+2, widening for t+1, MFMAs for t).
+//    ring of stages of 256 codes (two; four where two sets of waves share a tile, KS = 2); one
+//    barrier per stage; per 64 codes a register-level software pipeline (LDS reads for t+2,
+//    widening for t+1, MFMAs for t).
 //  * The epilogue transposes each wave tile through the idle LDS ring and stores whole rows:
 //    8-byte stores scattered over 32 rows per instruction cost 14 us per tile, this costs ~5.
 //  * LDS rows are XOR-swizzled in 16-byte chunks (applied on the global side of the DMA,
@@ -40,8 +41,8 @@
 //    (240 B/clk/CU measured with eight waves; one wave alone reaches 33 B/clk).
 //  * MFMA operand roles are swapped (A = weight rows, B = token rows): a lane then owns 4
 //    consecutive output channels of one token per accumulator quad = one 8-byte store.
-//  * Tried and dropped: deeper DMA prefetch (three ring slots: DMA latency is already hidden),
-//    dedicated DMA-issuing waves (1, 2 or 4 per workgroup: slower, a wave issues DMA too slowly).
+//  * Tried and dropped: three ring slots for 256 x 128 tiles and for two workgroups of 128 x 128
+//    per CU (weights in the memory-side cache: their latency is hidden by two slots), dedicated DMA-issuing waves (1, 2 or 4 per workgroup: slower, a wave issues DMA too slowly).
 //
 // K % 256 != 0 (and any K % 64 == 0) runs on a simpler register-staged kernel further down.
 #include "sr_common.h"
@@ -61,7 +62,7 @@ constexpr int ROWB = 128;  // packed bytes per row per stage (256 codes = one 12
 // Persistent workgroups: a workgroup walks over tiles v = blockIdx.x, blockIdx.x + gridDim.x, ... and keeps the
 // memory pipeline going across the tile boundary -- the first stage of the next tile is in flight while the
 // finished tile is dequantised, transposed and stored, and the stores (fire and forget) drain under the next
-// tile's MFMAs.  One launch of <= (CUs x workgroups per CU) workgroups instead of one workgroup per tile.
+// tile's MFMAs (KS = 2: the first two stages, while slots 2 and 3 hold the sums that change hands).  One launch of <= (CUs x workgroups per CU) workgroups instead of one workgroup per tile.
 //
 // KS = 2: two sets of waves share a tile, each multiplying half of every stage (the 64-code sub-steps 2 kw, 2 kw + 1),
 // and add their sums through LDS at the end, each finishing half of the channels.
@@ -364,7 +365,7 @@ __global__ __launch_bounds__(WGM * WGN * KS * 64) void gemm_w4a4_kernel(
         }
         if (!more) break;
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        barrier_nofence();                           // every wave has read its staging back: slot 1 is free
+        barrier_nofence();                           // every wave has read its staging back: slot 1 (KS = 2: 2, 3) is free
 #pragma unroll
         for (int i = SLOTS / 2; i < SLOTS; ++i) issue(i < ns ? i : ns - 1, i);
         v = vn;

@@ -7,7 +7,7 @@
 // and take stage_round together; a last one that is alone takes stage_lone, about six tenths of it.  No coefficient
 // is negative, so a prediction grows with M, N and K, also outside the shapes that were timed.
 //
-// The coefficients come from 2050 shapes per GEMM (M 8 or 17 .. 16384, N 512 .. 28672, K 128 or 256 .. 14336, weights from HBM
+// The coefficients come from 2050 shapes (FP6: 2550, N from 16; M 8 or 17 .. 16384, N .. 28672, K 128 or 256 .. 14336, weights from HBM
 // and in the memory-side cache), every configuration timed on every shape: least squares, then adjusted so that the choices,
 // not the predictions, come out best.  On 400 further shapes the choice for packed nibbles is 1.0 % slower on average than
 // the fastest configuration of the shape, 17 % at worst (4.5 % and 51 % by the table before, which was fitted to K >= 2048
