@@ -103,11 +103,13 @@ __global__ __launch_bounds__(NT) void fwht_quant_kernel(const __half *__restrict
 // Eight terms are summed in fp32, those sums in fp64.  4096 x 14336, 21 ratios, whole kernel: 288 -> 190 us (five
 // instructions of 4.6 cycles per value and a six-step lane reduction per ratio before).
 // ------------------------------------------------------------------------------------------
+constexpr int search_subsets(int NT) { return NT <= 256 ? 8 : 4; }
+constexpr int search_scratch_bytes(int NT) { return NT / 64 * search_subsets(NT) * kMaxClipGrid * 8; }
 template <int K, int NT>
-__device__ __forceinline__ float search_ratio(const float *row, const float amax, const float *grid, const int n, const int t)
+__device__ __forceinline__ float search_ratio(const float *row, const float amax, const float *grid, const int n, const int t,
+                                              double (*err_w)[kMaxClipGrid])
 {
-    constexpr int NW = NT / 64, G = K / 8, MAX_SUB = NW <= 4 ? 8 : 4;
-    __shared__ double err_w[NW * MAX_SUB][kMaxClipGrid];
+    constexpr int NW = NT / 64, G = K / 8, MAX_SUB = search_subsets(NT);
     __shared__ float ratios[kMaxClipGrid];
     if (t == 0) {
 #pragma unroll
@@ -169,32 +171,177 @@ __device__ __forceinline__ float search_ratio(const float *row, const float amax
     return ratios[best_i];
 }
 
+// ------------------------------------------------------------------------------------------
+// The same choice from ONE pass over the row, for ratios that are multiples of 1 / q (21 ratios from 1 to 0.5: q = 40).
+// With u = |y| / amax, Delta_i = a_i / (7 q) and c the magnitude of the code,
+//     err_i = sum u^2 - 2 Delta_i sum u c + Delta_i^2 sum c^2,
+//     sum u c = sum over j of the sum of u above the j-th rounding boundary,  sum c^2 = sum over j of (2 j - 1) times their number,
+// j = 1 .. 7 (8 where y < 0), and the j-th boundary of ratio i is (2 j - 1) a_i / (14 q): a multiple of 1 / (14 q) whatever
+// the row.  So the values are counted and summed in cells of width 1 / (14 q), one 64-bit LDS atomic per value (number in the
+// upper 16 bits, sum of u * 2^30 in the lower 48: integers, exact in any order), negative and positive ones apart, a prefix
+// sum over the cells gives every boundary's number and sum, and err_i without the common first term is 8 terms in fp64.
+//
+// The result is that of search_ratio, ratio for ratio: its errors carry roundings of up to about 1.2e-5 of themselves
+// (fp32 terms; a boundary moved by 1e-6 code units where values sit on it), err_0 is at most K / 196 (no value is further
+// from its code than half a step of 1 / 7), and so is the smallest.  Where only one ratio is within 2^-16 K / 196 of the
+// smallest error it is search_ratio's as well; else (about 2 % of normal rows) the caller runs search_ratio.
+//
+// Bound by the LDS atomics (a wave's 64 cells fall on random banks); search_ratio needs 105 vector instructions per value for
+// 21 ratios, this 9.  4096 x 14336, 21 ratios, whole kernel: 190 -> 92 us.
+// ------------------------------------------------------------------------------------------
+constexpr int kMaxClipDenominator = 100;
+// the smallest q <= kMaxClipDenominator of which every ratio is a multiple of 1 / q, to the last bit of a float; 0: none
+int clip_grid_denominator(const float *grid, int n)
+{
+    for (int q = 1; q <= kMaxClipDenominator; ++q) {
+        bool all = true;
+        for (int i = 0; i < n && all; ++i) {
+            const double a = (double)grid[i] * q, r = (double)(int64_t)(a + 0.5);
+            all = r >= 1.0 && a - r <= q * 0x1p-24 && r - a <= q * 0x1p-24;
+        }
+        if (all) return q;
+    }
+    return 0;
+}
+// cells per thread: 14 q + 1 for either sign, dealt to the threads in runs
+constexpr int histogram_run(int NT, int q) { return (2 * (14 * q + 1) + NT - 1) / NT; }
+
+template <int CTRL, int ROW_MASK> __device__ __forceinline__ uint64_t add_shifted(uint64_t v)   // v + the permuted lane's v (0 where there is none)
+{
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, CTRL, ROW_MASK, 0xF, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), CTRL, ROW_MASK, 0xF, false);
+    return v + ((uint64_t)hi << 32 | lo);
+}
+template <int CTRL> __device__ __forceinline__ double add_partner(double v)
+{
+    const uint64_t b = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)lane_perm<CTRL>((int)(uint32_t)b), hi = (uint32_t)lane_perm<CTRL>((int)(uint32_t)(b >> 32));
+    return v + __longlong_as_double((int64_t)((uint64_t)hi << 32 | lo));
+}
+
+// `cells`: histogram_run(NT, q) * NT words, all zero and visible to the workgroup.  Returns the index of the ratio, or -1
+// where more than one comes into question, to every thread.  t >= 0 < NT, NT >= 256.
+template <int K, int NT>
+__device__ __forceinline__ int histogram_ratio(const float *row, const float amax, const float *grid, const int n, const int q,
+                                               uint64_t *cells, const int t)
+{
+    constexpr int NW = NT / 64;
+    static_assert(NT >= 8 * kMaxClipGrid && K <= 32768, "a thread per boundary; 16 bits of number and 48 of sum");
+    __shared__ uint64_t wave_sum[NW];
+    __shared__ double err[kMaxClipGrid];
+    __shared__ int choice;
+    const int lane = t & 63, top = 14 * q;
+
+    // ---- cell c of the negative values is word top - c, of the others word 2 top + 1 - c: descending, so that a prefix
+    // sum up to a cell is the sum of what lies above its lower boundary.  |y| <= amax: c <= top.
+    {
+        const float to_cell = (float)top / amax, to_fixed = 1073741824.f / amax;
+#pragma unroll
+        for (int i = 0; i < (K / 4 + NT - 1) / NT; ++i) {
+            const int c = t + i * NT;
+            if (K / 4 % NT != 0 && c >= K / 4) break;
+            const float4 v = *reinterpret_cast<const float4 *>(row + pad(4 * c));
+            const float y[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int cell = (int)(uint32_t)(fabsf(y[e]) * to_cell);
+                const uint64_t one = (uint64_t)1 << 48 | (uint32_t)(fabsf(y[e]) * to_fixed);
+                __hip_atomic_fetch_add(cells + (y[e] < 0.f ? top : 2 * top + 1) - cell, one, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
+        }
+    }
+    __syncthreads();
+
+    // ---- inclusive prefix sums over all words
+    const int run = histogram_run(NT, q);
+    uint64_t sum = 0;
+    for (int e = 0; e < run; ++e) sum += cells[t * run + e];
+    uint64_t upto = add_shifted<0x111, 0xF>(sum);        // row_shr 1, 2, 4, 8, then the rows before
+    upto = add_shifted<0x112, 0xF>(upto);
+    upto = add_shifted<0x114, 0xF>(upto);
+    upto = add_shifted<0x118, 0xF>(upto);
+    upto = add_shifted<0x142, 0xA>(upto);
+    upto = add_shifted<0x143, 0xC>(upto);
+    if (lane == 63) wave_sum[t >> 6] = upto;
+    __syncthreads();
+    {
+        uint64_t acc = upto - sum;
+        for (int w = 0; w < NW; ++w) acc += w < (t >> 6) ? wave_sum[w] : 0;
+        for (int e = 0; e < run; ++e) {
+            acc += cells[t * run + e];
+            cells[t * run + e] = acc;
+        }
+    }
+    __syncthreads();
+
+    // ---- one lane per ratio and boundary
+    {
+        const int i = t >> 3, j = (t & 7) + 1;
+        if (i < n) {
+            const int a = (int)(grid[i] * (float)q + 0.5f), c = (2 * j - 1) * a;
+            uint64_t above = 0;
+            if (c <= top) above = cells[top - c] + (j < 8 ? cells[2 * top + 1 - c] - cells[top] : 0);
+            const double d = (double)a / (7.0 * q), s = (double)(above & (((uint64_t)1 << 48) - 1)) * 0x1p-30;
+            double e = d * (d * (double)((2 * j - 1) * (int)(above >> 48)) - 2.0 * s);
+            e = add_partner<0xB1>(e);
+            e = add_partner<0x4E>(e);
+            e = add_partner<0x141>(e);
+            if (j == 1) err[i] = e;
+        }
+    }
+    __syncthreads();
+    if (t < 64) {
+        const double e = err[lane < n ? lane : 0];
+        double best = e;
+        for (int h = 16; h >= 1; h >>= 1) best = fmin(best, __shfl_xor(best, h));   // the ratios are in lanes 0 .. 31
+        const uint64_t near = __ballot(lane < n && e <= best + K * (0x1p-16 / 196.0));
+        if (t == 0) choice = __popcll(near) == 1 ? __builtin_ctzll(near) : -1;
+    }
+    __syncthreads();
+    return choice;
+}
+
 // The fold of a weight with the search, full transform: one workgroup per output channel.  The products with the smoothing
 // factors are rounded as in fwht_quant_ex_kernel, which folds the other searched weights and folded these before: left
 // unrounded in the first level, scales moved by an ulp and three codes of 16.8 million by one (4096 x 4096).
-template <int K, int NT>
+// HIST: the ratio from one pass over the row where that decides it (q: see histogram_ratio).
+template <int K, int NT, bool HIST>
 __global__ __launch_bounds__(NT) void fwht_quant_search_kernel(const __half *__restrict__ X, int64_t ldx,
                                                                const float *__restrict__ pre, float post_scale,
                                                                uint8_t *__restrict__ Q, float *__restrict__ scale_out,
-                                                               const RowExtras ex)
+                                                               const RowExtras ex, const int q)
 {
     extern __shared__ __attribute__((aligned(16))) float row[];
     __shared__ float red[NT / 64];
+    void *const scratch = row + padded_len(K);           // cells of histogram_ratio, or partial errors of search_ratio
     const int t = threadIdx.x;
     const int64_t m = blockIdx.x;
+    if constexpr (HIST) {                                // visible after the rotation's barriers
+        uint64_t *const cells = static_cast<uint64_t *>(scratch);
+        for (int e = 0; e < histogram_run(NT, q); ++e) cells[t + e * NT] = 0;
+    }
     const float amax = rotate_row_absmax<K, NT, true>(X + m * ldx, pre, row, red, t);
-    const float clip = amax != 0.f ? search_ratio<K, NT>(row, amax, ex.grid, ex.n_grid, t) : ex.grid[0];
+    float clip = ex.grid[0];
+    if (amax != 0.f) {
+        int i = -1;
+        if constexpr (HIST) {
+            // (beyond this range the scaled values would not stay inside fp32; the largest being finite, all values are)
+            if (amax > 0x1p-90f && amax < 0x1p90f) i = histogram_ratio<K, NT>(row, amax, ex.grid, ex.n_grid, q, static_cast<uint64_t *>(scratch), t);
+        }
+        if (i >= 0) clip = ex.grid[i];
+        else clip = search_ratio<K, NT>(row, amax, ex.grid, ex.n_grid, t, static_cast<double (*)[kMaxClipGrid]>(scratch));
+    }
     if (ex.ratio_out && t == 0) ex.ratio_out[m] = clip;
     const float delta = (amax == 0.f) ? 1.f : (clip * amax) / 7.f;
     const float inv_delta = 1.f / delta;
     if (t == 0) scale_out[m] = (amax == 0.f) ? 1.f : delta * post_scale;
-    uint32_t *q = reinterpret_cast<uint32_t *>(Q + m * (int64_t)(K / 2));
+    uint32_t *out = reinterpret_cast<uint32_t *>(Q + m * (int64_t)(K / 2));
     for (int c = t; c < K / 8; c += NT) {
         const float *src = row + pad(8 * c);
         const float4 a = *reinterpret_cast<const float4 *>(src);
         const float4 b = *reinterpret_cast<const float4 *>(src + 4);
         const float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-        q[c] = quant_pack8(v, inv_delta);
+        out[c] = quant_pack8(v, inv_delta);
     }
 }
 
@@ -300,7 +447,8 @@ __global__ __launch_bounds__(NT) void fwht_quant_ex_kernel(const __half *__restr
     for (int w = 1; w < NW; ++w) amax = fmaxf(amax, red[w]);
 
     if constexpr (!F6) {                                 // (the search belongs to the weight fold, which writes nibbles)
-        if (ex.n_grid > 0) clip = amax != 0.f ? search_ratio<K, NT>(row, amax, ex.grid, ex.n_grid, t) : ex.grid[0];
+        __shared__ double err_w[search_scratch_bytes(NT) / (8 * kMaxClipGrid)][kMaxClipGrid];
+        if (ex.n_grid > 0) clip = amax != 0.f ? search_ratio<K, NT>(row, amax, ex.grid, ex.n_grid, t, err_w) : ex.grid[0];
     }
     if (ex.ratio_out && t == 0) ex.ratio_out[m] = clip;
 
@@ -602,6 +750,24 @@ hipError_t launch_one_gated(const void *X, int64_t rows, int64_t ldx, const floa
     return launch_row_kernel<K, NT, F6, true>(X, rows, ldx, pre, clip, post_scale, Q, scale_out, gate, ldg, st);
 }
 
+template <int K, int NT, bool HIST>
+hipError_t launch_search(const void *X, int64_t rows, int64_t ldx, const float *pre, float post_scale, uint8_t *Q, float *scale_out,
+                         const RowExtras &ex, int q, hipStream_t st)
+{
+    constexpr auto kern = fwht_quant_search_kernel<K, NT, HIST>;
+    constexpr int row_bytes = (int)sizeof(float) * padded_len(K), most = HIST ? histogram_run(NT, kMaxClipDenominator) * NT * 8 : 0;
+    constexpr int lds_most = row_bytes + (most > search_scratch_bytes(NT) ? most : search_scratch_bytes(NT));
+    static_assert(lds_most + 1024 <= 160 * 1024, "LDS");
+    const int cells = HIST ? histogram_run(NT, q) * NT * 8 : 0;
+    if (lds_most > 40 * 1024) {
+        hipError_t e = allow_dynamic_lds<kern>(lds_most);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(kern, dim3((unsigned)rows), dim3(NT), row_bytes + (cells > search_scratch_bytes(NT) ? cells : search_scratch_bytes(NT)), st,
+                       static_cast<const __half *>(X), ldx, pre, post_scale, Q, scale_out, ex, q);
+    return hipGetLastError();
+}
+
 template <int K, bool F6 = false>
 hipError_t launch_one_ex(const void *X, int64_t rows, int64_t ldx, const float *pre, float clip,
                          float post_scale, uint8_t *Q, float *scale_out, const RowExtras &ex, hipStream_t st)
@@ -614,14 +780,12 @@ hipError_t launch_one_ex(const void *X, int64_t rows, int64_t ldx, const float *
             // threads per row as in launch_one (many rows); K = 2048 x 4096 channels, 21 ratios: 34 us with 256 threads
             // against 39 with 128 (1024: 24 against 19 with 64, 512: 17 against 13)
             constexpr int NTS = K == 8192 ? 512 : (K == 16384 || K == 28672 || K == 32768) ? 1024 : K == 2048 ? 256 : NT;
-            constexpr auto kern = fwht_quant_search_kernel<K, NTS>;
-            if (lds > 40 * 1024) {
-                hipError_t e = allow_dynamic_lds<kern>((int)lds);
-                if (e != hipSuccess) return e;
+            // one pass over the row where there are threads for every boundary and LDS beside the row (K = 32768: none left)
+            if constexpr (NTS >= 8 * kMaxClipGrid && K <= 28672) {
+                if (const int q = clip_grid_denominator(ex.grid, ex.n_grid); q > 0)
+                    return launch_search<K, NTS, true>(X, rows, ldx, pre, post_scale, Q, scale_out, ex, q, st);
             }
-            hipLaunchKernelGGL(kern, dim3((unsigned)rows), dim3(NTS), lds, st, static_cast<const __half *>(X), ldx, pre,
-                               post_scale, Q, scale_out, ex);
-            return hipGetLastError();
+            return launch_search<K, NTS, false>(X, rows, ldx, pre, post_scale, Q, scale_out, ex, 0, st);
         }
     }
     constexpr auto kern = fwht_quant_ex_kernel<K, NT, F6>;
