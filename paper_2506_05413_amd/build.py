@@ -19,7 +19,7 @@ OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libsmoothrot.so")
 MARSHAL = os.path.join(PKG, "_marshal" + sysconfig.get_config_var("EXT_SUFFIX"))
 
-SOURCES = ["sr_api.hip", "fwht_quant.hip", "fwht_two_pass.hip", "calib_fold.hip", "gemm_prefill.hip", "gemm_packed_stream.hip", "gemm_f6.hip", "gemm_f6_stream.hip", "gemm_decode.hip", "kv_quant.hip", "linear_decode.hip", "ceilings.hip"]
+SOURCES = ["sr_api.hip", "fwht_quant.hip", "fwht_two_pass.hip", "fold_search.hip", "calib_fold.hip", "gemm_prefill.hip", "gemm_packed_stream.hip", "gemm_f6.hip", "gemm_f6_stream.hip", "gemm_decode.hip", "kv_quant.hip", "linear_decode.hip", "ceilings.hip"]
 
 # packed-fp32 instructions are switched off on purpose (device code only)
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden",

@@ -1,0 +1,109 @@
+// Weight fold with clip search for rows of 2048, 4096, 8192 and 14336 values, full transform, ratios that are multiples of a
+// common 1 / q: one workgroup per output channel, rotation in two passes (two_pass_row.h), the ratio from one pass over the
+// values (clip_search.h), quantiser.  (Paper, section "Methodology": weights rotated offline; Eq. (1).)
+//
+// The values of pass 2 are counted straight from the registers that hold them.  Against the general rotation with the values
+// read back from LDS (4096 x 14336, 21 ratios): 92 -> 85 us.  The products with the smoothing factors are rounded as in
+// fwht_quant_ex_kernel, so codes, scales and ratios are bit for bit those of the other searched folds.
+#include "two_pass_row.h"
+#include "clip_search.h"
+
+namespace sr {
+namespace {
+
+template <int K>
+__global__ __launch_bounds__((TwoPass<K>::NT)) void fold_search_kernel(const __half *__restrict__ Wt, int64_t ldw,
+                                                                       const float *__restrict__ s, float post_scale,
+                                                                       uint8_t *__restrict__ Q, float *__restrict__ scale_out,
+                                                                       const RowExtras ex, const int q)
+{
+    using S = TwoPass<K>;
+    constexpr int NT = S::NT;
+    constexpr uint32_t ALL = 0xFFFFFFFFu;
+    extern __shared__ __attribute__((aligned(16))) float row[];
+    __shared__ float red[NT / 64];
+    void *const scratch = row + S::LEN;                  // the cells, or partial errors of search_ratio
+    uint64_t *const cells = static_cast<uint64_t *>(scratch);
+    const int t = threadIdx.x;
+    const int64_t m = blockIdx.x;
+    RowLoad<K, NT> ld;
+    row_load<K, NT, false, false, 5>(Wt + m * ldw, s, t, ld);
+    for (int e = 0; e < histogram_run(NT, q); ++e) cells[t + e * NT] = 0;      // visible after the rotation's barriers
+    float o[S::R];
+    const float amax = two_pass_rotate<S, K, true, false, false, true>(ld, row, red, t, ALL, o, NoHook{});
+    if (!(amax > 0.f && amax < __builtin_inff())) {
+        // nothing to search: zeros, or infinities and NaNs, whose signs (code 7 or -8) depend on the signs that values carry
+        // on the way -- rotated again as the other kernels do
+        __syncthreads();
+        const float a = rotate_row_absmax<K, NT, true>(Wt + m * ldw, s, row, red, t);
+        const float delta = a == 0.f ? 1.f : (ex.grid[0] * a) / 7.f;
+        if (ex.ratio_out && t == 0) ex.ratio_out[m] = ex.grid[0];
+        if (t == 0) scale_out[m] = a == 0.f ? 1.f : delta * post_scale;
+        quantise_padded_row_nibbles<K, NT>(row, 1.f / delta, Q + m * (int64_t)(K / 2), t);
+        return;
+    }
+    int i = -1;
+    // (beyond this range the scaled values would not stay inside fp32)
+    if (amax > 0x1p-90f && amax < 0x1p90f) {
+        if (NT == S::COLS || t < S::COLS) {
+            const CellScale scale(q, amax);
+            const bool f = S::flipped(S::first(t) >> 4);               // the same for all values of a thread
+            const int neg = f ? 28 * q + 1 : 14 * q, pos = f ? 14 * q : 28 * q + 1;
+#pragma unroll
+            for (int r = 0; r < S::R; ++r) count_value(cells, scale, neg, pos, o[r]);
+        }
+        __syncthreads();
+        i = ratio_of_cells<K, NT>(ex.grid, ex.n_grid, q, cells, t);
+    }
+    auto read8 = [&](int g, float4 &a, float4 &b) {
+        const float *src = row + S::pos(8 * g);
+        a = *reinterpret_cast<const float4 *>(src);
+        b = *reinterpret_cast<const float4 *>(src + 4);
+        if (S::flipped(g >> 1)) {
+            a = make_float4(-a.x, -a.y, -a.z, -a.w);
+            b = make_float4(-b.x, -b.y, -b.z, -b.w);
+        }
+    };
+    const float clip = i >= 0 ? ex.grid[i]
+                              : search_ratio<K, NT>(read8, amax, ex.grid, ex.n_grid, t, static_cast<double (*)[kMaxClipGrid]>(scratch));
+    if (ex.ratio_out && t == 0) ex.ratio_out[m] = clip;
+    const float delta = (clip * amax) / 7.f;
+    if (t == 0) scale_out[m] = delta * post_scale;
+    quantise_row_nibbles<S, K>(row, 1.f / delta, ALL, Q + m * (int64_t)(K / 2), t);
+}
+
+template <int K>
+hipError_t launch(const void *Wt, int64_t rows, int64_t ldw, const float *s, float post_scale, uint8_t *Q, float *scale_out,
+                  const RowExtras &ex, int q, hipStream_t st)
+{
+    using S = TwoPass<K>;
+    constexpr auto kern = fold_search_kernel<K>;
+    constexpr int row_bytes = S::LEN * (int)sizeof(float), search = search_scratch_bytes(S::NT);
+    constexpr int most = histogram_run(S::NT, kMaxClipDenominator) * S::NT * 8;
+    static_assert(most >= search && row_bytes + most + 1024 <= 160 * 1024, "LDS");
+    if constexpr (row_bytes + most > 40 * 1024)
+        if (hipError_t e = allow_dynamic_lds<kern>(row_bytes + most); e != hipSuccess) return e;
+    const int cells = histogram_run(S::NT, q) * S::NT * 8;
+    hipLaunchKernelGGL(kern, dim3((unsigned)rows), dim3(S::NT), row_bytes + (cells > search ? cells : search), st,
+                       static_cast<const __half *>(Wt), ldw, s, post_scale, Q, scale_out, ex, q);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_fold_search(const void *Wt, int64_t rows, int64_t K, int64_t ldw, const float *s, float post_scale,
+                              uint8_t *Q, float *scale_out, const RowExtras &ex, hipStream_t st, bool &taken)
+{
+    const int q = clip_grid_denominator(ex.grid, ex.n_grid);
+    taken = q > 0 && s;
+    if (!taken) return hipSuccess;
+    switch (K) {
+        case 2048: return launch<2048>(Wt, rows, ldw, s, post_scale, Q, scale_out, ex, q, st);
+        case 4096: return launch<4096>(Wt, rows, ldw, s, post_scale, Q, scale_out, ex, q, st);
+        case 8192: return launch<8192>(Wt, rows, ldw, s, post_scale, Q, scale_out, ex, q, st);
+        case 14336: return launch<14336>(Wt, rows, ldw, s, post_scale, Q, scale_out, ex, q, st);
+        default: taken = false; return hipSuccess;
+    }
+}
+
+}  // namespace sr

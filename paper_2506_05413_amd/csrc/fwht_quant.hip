@@ -15,6 +15,7 @@
 // The LDS row is padded by 4 floats per 64 so that every access pattern above is
 // bank-conflict free for K = 4096.
 #include "fwht_row.h"
+#include "clip_search.h"
 #include "gemm_common.h"      // LDS-DMA load, hand-placed waits, fence-free barrier
 
 namespace sr {
@@ -85,226 +86,21 @@ __global__ __launch_bounds__(NT) void fwht_quant_kernel(const __half *__restrict
     asm volatile("" ::"v"(warm_acc));                    // keeps the warming loads; they returned long ago
 }
 
-// ------------------------------------------------------------------------------------------
-// Clipping-ratio search over a rotated row in LDS (`row`, maximum `amax` > 0), by a workgroup of NT threads:
-//     err_i = sum_j (y_j - Delta_i * code_i(y_j))^2,   Delta_i = grid[i] * amax / 7
-// for every ratio; returns the ratio with the smallest error (first minimum in grid order) to every thread.
-//
-// Bound by vector-ALU issue: what counts is the number and kind of instructions per value and ratio.  On this chip
-// fp32 add / mul / fma with VGPR operands issue in ~2.7 cycles, rint / min / max / med3, conversions, and anything with
-// an SGPR or DPP operand in ~4.6 (measured per instruction).  So
-//  * a LANE owns a ratio (Delta_i, 1/Delta_i in its registers) and the values come by broadcast LDS reads: no scalar
-//    operands, and no reduction over lanes per ratio.  64 / n subsets of lanes take different groups of 8 values
-//    (21 ratios: 3 subsets, 63 lanes at work);
-//  * a value costs five of the cheap instructions: clamp to [0, 1] of (y / Delta + 8) / 15 (the clamp is an output
-//    modifier of the fma), times 15 plus 1.5 * 2^23 (rounds to an integer), minus 1.5 * 2^23 + 8 (the code), residual,
-//    square-accumulate.  The scaling by 15 moves a rounding boundary by less than 1e-6 code units, where both codes
-//    give the same error; the codes themselves are taken from the chosen ratio by the usual quantiser.
-// Eight terms are summed in fp32, those sums in fp64.  4096 x 14336, 21 ratios, whole kernel: 288 -> 190 us (five
-// instructions of 4.6 cycles per value and a six-step lane reduction per ratio before).
-// ------------------------------------------------------------------------------------------
-constexpr int search_subsets(int NT) { return NT <= 256 ? 8 : 4; }
-constexpr int search_scratch_bytes(int NT) { return NT / 64 * search_subsets(NT) * kMaxClipGrid * 8; }
-template <int K, int NT>
-__device__ __forceinline__ float search_ratio(const float *row, const float amax, const float *grid, const int n, const int t,
-                                              double (*err_w)[kMaxClipGrid])
-{
-    constexpr int NW = NT / 64, G = K / 8, MAX_SUB = search_subsets(NT);
-    __shared__ float ratios[kMaxClipGrid];
-    if (t == 0) {
-#pragma unroll
-        for (int i = 0; i < kMaxClipGrid; ++i) ratios[i] = grid[i];
-    }
-    __syncthreads();
-    const int lane = t & 63, subs = 64 / n < MAX_SUB ? 64 / n : MAX_SUB;
-    const int sub = lane / n, i = lane - sub * n;        // lanes of subset `subs` and above idle along with subset 0
-    const int units = NW * subs, unit = (t >> 6) * subs + (sub < subs ? sub : 0);
-    const float d = (ratios[i] * amax) / 7.f, inv15 = 1.f / (15.f * d);
-    constexpr float magic = 12582912.f;                  // 1.5 * 2^23
-    double acc = 0.0;
-    auto add_group = [&](const float4 &a, const float4 &b) {
-        const float y[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-        float u[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) u[e] = __builtin_amdgcn_fmed3f(fmaf(y[e], inv15, 8.f / 15.f), 0.f, 1.f);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) u[e] = fmaf(u[e], 15.f, magic);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) u[e] = fmaf(-d, u[e] - (magic + 8.f), y[e]);
-        float even = 0.f, odd = 0.f;
-#pragma unroll
-        for (int e = 0; e < 8; e += 2) {
-            even = fmaf(u[e], u[e], even);
-            odd = fmaf(u[e + 1], u[e + 1], odd);
-        }
-        acc += (double)(even + odd);
-    };
-    auto read = [&](int g, float4 &a, float4 &b) {
+// search_ratio's view of a row in the padded layout
+struct RowRead8 {
+    const float *row;
+    __device__ __forceinline__ void operator()(int g, float4 &a, float4 &b) const
+    {
         const float *src = row + pad(8 * g);
         a = *reinterpret_cast<const float4 *>(src);
         b = *reinterpret_cast<const float4 *>(src + 4);
-    };
-    float4 a0, b0, a1, b1;
-    int g = unit;                                        // a unit's groups: unit, unit + units, ..
-    read(g < G ? g : 0, a0, b0);
-    for (; g + units < G; g += 2 * units) {              // the group after the one at work is on its way
-        read(g + units, a1, b1);
-        add_group(a0, b0);
-        read(g + 2 * units < G ? g + 2 * units : 0, a0, b0);
-        add_group(a1, b1);
     }
-    if (g < G) add_group(a0, b0);
-    if (sub < subs) err_w[unit][i] = acc;
-    __syncthreads();
-    if (t < n) {
-        double e = err_w[0][t];
-        for (int u = 1; u < units; ++u) e += err_w[u][t];
-        err_w[0][t] = e;
-    }
-    __syncthreads();
-    double best = err_w[0][0];
-    int best_i = 0;
-    for (int k = 1; k < n; ++k) {                        // every thread takes the same decision
-        const double e = err_w[0][k];
-        if (e < best) { best = e; best_i = k; }
-    }
-    return ratios[best_i];
-}
-
-// ------------------------------------------------------------------------------------------
-// The same choice from ONE pass over the row, for ratios that are multiples of 1 / q (21 ratios from 1 to 0.5: q = 40).
-// With u = |y| / amax, Delta_i = a_i / (7 q) and c the magnitude of the code,
-//     err_i = sum u^2 - 2 Delta_i sum u c + Delta_i^2 sum c^2,
-//     sum u c = sum over j of the sum of u above the j-th rounding boundary,  sum c^2 = sum over j of (2 j - 1) times their number,
-// j = 1 .. 7 (8 where y < 0), and the j-th boundary of ratio i is (2 j - 1) a_i / (14 q): a multiple of 1 / (14 q) whatever
-// the row.  So the values are counted and summed in cells of width 1 / (14 q), one 64-bit LDS atomic per value (number in the
-// upper 16 bits, sum of u * 2^30 in the lower 48: integers, exact in any order), negative and positive ones apart, a prefix
-// sum over the cells gives every boundary's number and sum, and err_i without the common first term is 8 terms in fp64.
-//
-// The result is that of search_ratio, ratio for ratio: its errors carry roundings of up to about 1.2e-5 of themselves
-// (fp32 terms; a boundary moved by 1e-6 code units where values sit on it), err_0 is at most K / 196 (no value is further
-// from its code than half a step of 1 / 7), and so is the smallest.  Where only one ratio is within 2^-16 K / 196 of the
-// smallest error it is search_ratio's as well; else (about 2 % of normal rows) the caller runs search_ratio.
-//
-// Bound by the LDS atomics (a wave's 64 cells fall on random banks); search_ratio needs 105 vector instructions per value for
-// 21 ratios, this 9.  4096 x 14336, 21 ratios, whole kernel: 190 -> 92 us.
-// ------------------------------------------------------------------------------------------
-constexpr int kMaxClipDenominator = 100;
-// the smallest q <= kMaxClipDenominator of which every ratio is a multiple of 1 / q, to the last bit of a float; 0: none
-int clip_grid_denominator(const float *grid, int n)
-{
-    for (int q = 1; q <= kMaxClipDenominator; ++q) {
-        bool all = true;
-        for (int i = 0; i < n && all; ++i) {
-            const double a = (double)grid[i] * q, r = (double)(int64_t)(a + 0.5);
-            all = r >= 1.0 && a - r <= q * 0x1p-24 && r - a <= q * 0x1p-24;
-        }
-        if (all) return q;
-    }
-    return 0;
-}
-// cells per thread: 14 q + 1 for either sign, dealt to the threads in runs
-constexpr int histogram_run(int NT, int q) { return (2 * (14 * q + 1) + NT - 1) / NT; }
-
-template <int CTRL, int ROW_MASK> __device__ __forceinline__ uint64_t add_shifted(uint64_t v)   // v + the permuted lane's v (0 where there is none)
-{
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, CTRL, ROW_MASK, 0xF, false);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), CTRL, ROW_MASK, 0xF, false);
-    return v + ((uint64_t)hi << 32 | lo);
-}
-template <int CTRL> __device__ __forceinline__ double add_partner(double v)
-{
-    const uint64_t b = (uint64_t)__double_as_longlong(v);
-    const uint32_t lo = (uint32_t)lane_perm<CTRL>((int)(uint32_t)b), hi = (uint32_t)lane_perm<CTRL>((int)(uint32_t)(b >> 32));
-    return v + __longlong_as_double((int64_t)((uint64_t)hi << 32 | lo));
-}
-
-// `cells`: histogram_run(NT, q) * NT words, all zero and visible to the workgroup.  Returns the index of the ratio, or -1
-// where more than one comes into question, to every thread.  t >= 0 < NT, NT >= 256.
-template <int K, int NT>
-__device__ __forceinline__ int histogram_ratio(const float *row, const float amax, const float *grid, const int n, const int q,
-                                               uint64_t *cells, const int t)
-{
-    constexpr int NW = NT / 64;
-    static_assert(NT >= 8 * kMaxClipGrid && K <= 32768, "a thread per boundary; 16 bits of number and 48 of sum");
-    __shared__ uint64_t wave_sum[NW];
-    __shared__ double err[kMaxClipGrid];
-    __shared__ int choice;
-    const int lane = t & 63, top = 14 * q;
-
-    // ---- cell c of the negative values is word top - c, of the others word 2 top + 1 - c: descending, so that a prefix
-    // sum up to a cell is the sum of what lies above its lower boundary.  |y| <= amax: c <= top.
-    {
-        const float to_cell = (float)top / amax, to_fixed = 1073741824.f / amax;
-#pragma unroll
-        for (int i = 0; i < (K / 4 + NT - 1) / NT; ++i) {
-            const int c = t + i * NT;
-            if (K / 4 % NT != 0 && c >= K / 4) break;
-            const float4 v = *reinterpret_cast<const float4 *>(row + pad(4 * c));
-            const float y[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int cell = (int)(uint32_t)(fabsf(y[e]) * to_cell);
-                const uint64_t one = (uint64_t)1 << 48 | (uint32_t)(fabsf(y[e]) * to_fixed);
-                __hip_atomic_fetch_add(cells + (y[e] < 0.f ? top : 2 * top + 1) - cell, one, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            }
-        }
-    }
-    __syncthreads();
-
-    // ---- inclusive prefix sums over all words
-    const int run = histogram_run(NT, q);
-    uint64_t sum = 0;
-    for (int e = 0; e < run; ++e) sum += cells[t * run + e];
-    uint64_t upto = add_shifted<0x111, 0xF>(sum);        // row_shr 1, 2, 4, 8, then the rows before
-    upto = add_shifted<0x112, 0xF>(upto);
-    upto = add_shifted<0x114, 0xF>(upto);
-    upto = add_shifted<0x118, 0xF>(upto);
-    upto = add_shifted<0x142, 0xA>(upto);
-    upto = add_shifted<0x143, 0xC>(upto);
-    if (lane == 63) wave_sum[t >> 6] = upto;
-    __syncthreads();
-    {
-        uint64_t acc = upto - sum;
-        for (int w = 0; w < NW; ++w) acc += w < (t >> 6) ? wave_sum[w] : 0;
-        for (int e = 0; e < run; ++e) {
-            acc += cells[t * run + e];
-            cells[t * run + e] = acc;
-        }
-    }
-    __syncthreads();
-
-    // ---- one lane per ratio and boundary
-    {
-        const int i = t >> 3, j = (t & 7) + 1;
-        if (i < n) {
-            const int a = (int)(grid[i] * (float)q + 0.5f), c = (2 * j - 1) * a;
-            uint64_t above = 0;
-            if (c <= top) above = cells[top - c] + (j < 8 ? cells[2 * top + 1 - c] - cells[top] : 0);
-            const double d = (double)a / (7.0 * q), s = (double)(above & (((uint64_t)1 << 48) - 1)) * 0x1p-30;
-            double e = d * (d * (double)((2 * j - 1) * (int)(above >> 48)) - 2.0 * s);
-            e = add_partner<0xB1>(e);
-            e = add_partner<0x4E>(e);
-            e = add_partner<0x141>(e);
-            if (j == 1) err[i] = e;
-        }
-    }
-    __syncthreads();
-    if (t < 64) {
-        const double e = err[lane < n ? lane : 0];
-        double best = e;
-        for (int h = 16; h >= 1; h >>= 1) best = fmin(best, __shfl_xor(best, h));   // the ratios are in lanes 0 .. 31
-        const uint64_t near = __ballot(lane < n && e <= best + K * (0x1p-16 / 196.0));
-        if (t == 0) choice = __popcll(near) == 1 ? __builtin_ctzll(near) : -1;
-    }
-    __syncthreads();
-    return choice;
-}
+};
 
 // The fold of a weight with the search, full transform: one workgroup per output channel.  The products with the smoothing
 // factors are rounded as in fwht_quant_ex_kernel, which folds the other searched weights and folded these before: left
 // unrounded in the first level, scales moved by an ulp and three codes of 16.8 million by one (4096 x 4096).
-// HIST: the ratio from one pass over the row where that decides it (q: see histogram_ratio).
+// HIST: the ratio from one pass over the row where that decides it (q: see ratio_of_cells).
 template <int K, int NT, bool HIST>
 __global__ __launch_bounds__(NT) void fwht_quant_search_kernel(const __half *__restrict__ X, int64_t ldx,
                                                                const float *__restrict__ pre, float post_scale,
@@ -313,7 +109,7 @@ __global__ __launch_bounds__(NT) void fwht_quant_search_kernel(const __half *__r
 {
     extern __shared__ __attribute__((aligned(16))) float row[];
     __shared__ float red[NT / 64];
-    void *const scratch = row + padded_len(K);           // cells of histogram_ratio, or partial errors of search_ratio
+    void *const scratch = row + padded_len(K);           // the cells, or partial errors of search_ratio
     const int t = threadIdx.x;
     const int64_t m = blockIdx.x;
     if constexpr (HIST) {                                // visible after the rotation's barriers
@@ -321,28 +117,34 @@ __global__ __launch_bounds__(NT) void fwht_quant_search_kernel(const __half *__r
         for (int e = 0; e < histogram_run(NT, q); ++e) cells[t + e * NT] = 0;
     }
     const float amax = rotate_row_absmax<K, NT, true>(X + m * ldx, pre, row, red, t);
+    const RowRead8 read8{row};
     float clip = ex.grid[0];
     if (amax != 0.f) {
         int i = -1;
         if constexpr (HIST) {
             // (beyond this range the scaled values would not stay inside fp32; the largest being finite, all values are)
-            if (amax > 0x1p-90f && amax < 0x1p90f) i = histogram_ratio<K, NT>(row, amax, ex.grid, ex.n_grid, q, static_cast<uint64_t *>(scratch), t);
+            if (amax > 0x1p-90f && amax < 0x1p90f) {
+                uint64_t *const cells = static_cast<uint64_t *>(scratch);
+                const CellScale scale(q, amax);
+                for (int c = t; c < K / 4; c += NT) {
+                    const float4 v = *reinterpret_cast<const float4 *>(row + pad(4 * c));
+                    count_value(cells, scale, 14 * q, 28 * q + 1, v.x);
+                    count_value(cells, scale, 14 * q, 28 * q + 1, v.y);
+                    count_value(cells, scale, 14 * q, 28 * q + 1, v.z);
+                    count_value(cells, scale, 14 * q, 28 * q + 1, v.w);
+                }
+                __syncthreads();
+                i = ratio_of_cells<K, NT>(ex.grid, ex.n_grid, q, cells, t);
+            }
         }
         if (i >= 0) clip = ex.grid[i];
-        else clip = search_ratio<K, NT>(row, amax, ex.grid, ex.n_grid, t, static_cast<double (*)[kMaxClipGrid]>(scratch));
+        else clip = search_ratio<K, NT>(read8, amax, ex.grid, ex.n_grid, t, static_cast<double (*)[kMaxClipGrid]>(scratch));
     }
     if (ex.ratio_out && t == 0) ex.ratio_out[m] = clip;
     const float delta = (amax == 0.f) ? 1.f : (clip * amax) / 7.f;
     const float inv_delta = 1.f / delta;
     if (t == 0) scale_out[m] = (amax == 0.f) ? 1.f : delta * post_scale;
-    uint32_t *out = reinterpret_cast<uint32_t *>(Q + m * (int64_t)(K / 2));
-    for (int c = t; c < K / 8; c += NT) {
-        const float *src = row + pad(8 * c);
-        const float4 a = *reinterpret_cast<const float4 *>(src);
-        const float4 b = *reinterpret_cast<const float4 *>(src + 4);
-        const float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-        out[c] = quant_pack8(v, inv_delta);
-    }
+    quantise_padded_row_nibbles<K, NT>(row, inv_delta, Q + m * (int64_t)(K / 2), t);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -448,7 +250,7 @@ __global__ __launch_bounds__(NT) void fwht_quant_ex_kernel(const __half *__restr
 
     if constexpr (!F6) {                                 // (the search belongs to the weight fold, which writes nibbles)
         __shared__ double err_w[search_scratch_bytes(NT) / (8 * kMaxClipGrid)][kMaxClipGrid];
-        if (ex.n_grid > 0) clip = amax != 0.f ? search_ratio<K, NT>(row, amax, ex.grid, ex.n_grid, t, err_w) : ex.grid[0];
+        if (ex.n_grid > 0) clip = amax != 0.f ? search_ratio<K, NT>(RowRead8{row}, amax, ex.grid, ex.n_grid, t, err_w) : ex.grid[0];
     }
     if (ex.ratio_out && t == 0) ex.ratio_out[m] = clip;
 
@@ -780,8 +582,8 @@ hipError_t launch_one_ex(const void *X, int64_t rows, int64_t ldx, const float *
             // threads per row as in launch_one (many rows); K = 2048 x 4096 channels, 21 ratios: 34 us with 256 threads
             // against 39 with 128 (1024: 24 against 19 with 64, 512: 17 against 13)
             constexpr int NTS = K == 8192 ? 512 : (K == 16384 || K == 28672 || K == 32768) ? 1024 : K == 2048 ? 256 : NT;
-            // one pass over the row where there are threads for every boundary and LDS beside the row (K = 32768: none left)
-            if constexpr (NTS >= 8 * kMaxClipGrid && K <= 28672) {
+            // 2048, 4096, 8192 and 14336 have a kernel of their own (fold_search.hip); K = 32768 leaves no LDS beside the row
+            if constexpr (K == 16384 || K == 28672) {
                 if (const int q = clip_grid_denominator(ex.grid, ex.n_grid); q > 0)
                     return launch_search<K, NTS, true>(X, rows, ldx, pre, post_scale, Q, scale_out, ex, q, st);
             }
@@ -882,6 +684,11 @@ hipError_t launch_fwht_quant_ex(const void *X, int64_t rows, int64_t K, int64_t 
             return pre ? launch_wave4096<true, false, false, true>(X, rows, ldx, pre, clip, post_scale, Q, scale_out, st, nullptr, 0, ex.had_mask)
                        : launch_wave4096<false, false, false, true>(X, rows, ldx, pre, clip, post_scale, Q, scale_out, st, nullptr, 0, ex.had_mask);
         return launch_fwht_two_pass_heads(X, rows, K, ldx, pre, clip, post_scale, Q, scale_out, ex.had_mask, st);
+    }
+    if (ex.n_grid > 0 && !ex.gate && !f6 && (ex.had_mask == 0xFFFFFFFFu || !is_pow2(K))) {
+        bool taken = false;
+        const hipError_t e = launch_fold_search(X, rows, K, ldx, pre, post_scale, Q, scale_out, ex, st, taken);
+        if (taken || e != hipSuccess) return e;
     }
     // the gate alone (the FFN down-projection input) goes through the plain kernels: fewer passes over the row
     // than the general kernel below (K = 14336, 2048 rows: 38 against 68 us)

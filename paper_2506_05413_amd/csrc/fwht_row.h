@@ -261,6 +261,20 @@ __device__ __forceinline__ uint32_t quant_pack8(const float (&y)[8], float inv_d
     return (word - pack_bias()) ^ 0x88888888u;
 }
 
+// a rotated row in the padded layout -> packed nibbles at `out`
+template <int K, int NT>
+__device__ __forceinline__ void quantise_padded_row_nibbles(const float *row, const float inv_delta, uint8_t *out, const int t)
+{
+    uint32_t *q = reinterpret_cast<uint32_t *>(out);
+    for (int c = t; c < K / 8; c += NT) {
+        const float *src = row + pad(8 * c);
+        const float4 a = *reinterpret_cast<const float4 *>(src);
+        const float4 b = *reinterpret_cast<const float4 *>(src + 4);
+        const float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+        q[c] = quant_pack8(v, inv_delta);
+    }
+}
+
 // ---- the same quantiser writing "f6 tiles" (operand layout of the FP6-MFMA GEMM, see gemm_f6.hip) ----------
 // A code c becomes the 6-bit sign-magnitude field (c < 0 ? 32 : 0) | |c| (the E2M3 pattern of c / 8).  The E2M3
 // grid is uniform (steps of 1/8) up to 1.875, so the hardware conversion of (y / Delta) / 8, which rounds to

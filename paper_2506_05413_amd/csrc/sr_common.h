@@ -136,6 +136,11 @@ hipError_t launch_fwht_quant_ex(const void *X_f16, int64_t rows, int64_t K, int6
                                 const float *pre, float clip, float post_scale,
                                 uint8_t *Q, float *scale_out, const RowExtras &ex, hipStream_t st, bool f6 = false);
 
+// The fold with ex.grid searched, full transform, for K = 2048, 4096, 8192 and 14336 where the ratios are multiples of a common
+// fraction (see clip_search.h); taken = false and nothing launched otherwise.
+hipError_t launch_fold_search(const void *Wt_f16, int64_t rows, int64_t K, int64_t ldw, const float *s, float post_scale,
+                              uint8_t *Q, float *scale_out, const RowExtras &ex, hipStream_t st, bool &taken);
+
 hipError_t launch_calib_absmax(const void *X_f16, int64_t T, int64_t K, int64_t ldx,
                                float *absmax_io, hipStream_t st);
 
