@@ -80,6 +80,7 @@ SR_API const char *sr_status_str(int status);
  *   SR_TUNE_GEMM_GRID      persistent workgroups of the prefill GEMMs (rounded down to a multiple of 8)
  *   SR_TUNE_GEMM_XCDM      split of the tile grid over the 8 XCDs in m: 0 (none), 1, 2, 4, 8
  *   SR_TUNE_DECODE_KERNEL  M <= 16 GEMM: 1 dot product (M <= 2), 2 MFMA per 16 channels, 3 streaming MFMA
+ *                          (sr_w4a4_linear_decode of 2 .. 4 tokens: two launches with any of these; 4: one where there is one)
  *   SR_TUNE_FWHT4096       K = 4096 rotation: 1 wave per row (factors staged in LDS), 4 wave per row (factors
  *                          loaded per lane), 2 general workgroup-per-row kernel, 5 workgroup per row in two passes
  *   SR_TUNE_FWHT_STREAM    K = 14336 rotation: 1 workgroups of 896 threads, 0 of 512 (the name is that of a variant
@@ -267,10 +268,10 @@ SR_API int sr_kv_quant_asym(const void *X_f16, int64_t rows, int64_t D, int64_t 
  * "Methodology", Eq. (1); Fig. 2 puts it in front of the down-projection, K = 14336 for an 8B model).
  * Codes and scales are the ones the two calls would produce, up to the rounding-order freedom of the
  * fp32 rotation (a code may sit on the other side of a rounding boundary).
- * One token with K = 2048 or 4096 runs as a SINGLE launch (rotation, quantiser and GEMM in one kernel, every
- * workgroup rotating the row while its weights travel): 8.0 us against 9.6 - 10.0 us for 4096 -> 14336.  Every
- * other shape runs the two kernels back to back inside the call -- measured, no single launch beats that pair
- * there (see csrc/linear_decode.hip) -- so the call is never slower than the two calls and saves their host side.
+ * With K = 2048 or 4096 one token, and two to four tokens up to the channel counts at which that wins, run as a
+ * SINGLE launch (rotation, quantiser and GEMM in one kernel, every workgroup rotating the rows while its weights
+ * travel; 4096 -> 14336: 6.7 us for one token, 8.6 against 9.5 us for four).  Every other shape runs the two kernels
+ * back to back inside the call -- measured, no single launch beats that pair there (see csrc/linear_decode.hip).
  *
  *   X_f16   fp16 [M, K], 1 <= M <= 16 (M = 0 is a no-op), row stride ldx
  *   K       2048, 4096, 8192 or 14336 (SR_ERR_UNSUPPORTED_K otherwise: use the two calls)
@@ -279,7 +280,7 @@ SR_API int sr_kv_quant_asym(const void *X_f16, int64_t rows, int64_t D, int64_t 
  *   Xq_out  out, optional (may be NULL): uint8 [M, K/2], the activation codes that were used
  *   x_scale_out  out, optional (may be NULL): fp32 [M]
  *   workspace    sr_linear_decode_workspace_bytes(M, K) bytes, 256-byte aligned: the codes and scales between the
- *                two kernels (may be NULL where that is 0: the single-launch shapes).  Contents need no
+ *                two kernels (may be NULL where that is 0: one token of K <= 4096).  Contents need no
  *                initialisation; calls that share a workspace must not overlap.
  */
 SR_API size_t sr_linear_decode_workspace_bytes(int64_t M, int64_t K);

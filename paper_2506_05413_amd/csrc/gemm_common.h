@@ -34,6 +34,16 @@ __device__ __forceinline__ void dma16(const uint8_t *base, uint32_t lane_off, ui
                  : "memory", "m0");
 }
 
+// 32 packed codes -> the operands of two 16x16x64 int8 products
+__device__ __forceinline__ void unpack16(const u32x4 w, v4i &a0, v4i &a1)
+{
+    constexpr unsigned HM = 0xF0F0F0F0u;     // nibble kept in the high half of its byte = code * 16
+    a0[0] = (int)((w.x << 4) & HM); a0[1] = (int)(w.x & HM);
+    a0[2] = (int)((w.y << 4) & HM); a0[3] = (int)(w.y & HM);
+    a1[0] = (int)((w.z << 4) & HM); a1[1] = (int)(w.z & HM);
+    a1[2] = (int)((w.w << 4) & HM); a1[3] = (int)(w.w & HM);
+}
+
 // ------------------------------------------------------------------------------------------
 // Epilogue for 32 x 32 MFMA tiles: dequantise, then transpose the wave's WM x WN tile through LDS,
 // 32 tokens at a time, so that global memory is written in whole rows of the tile (16 bytes per

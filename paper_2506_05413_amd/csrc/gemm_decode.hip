@@ -31,15 +31,6 @@
 namespace sr {
 namespace {
 
-__device__ __forceinline__ void unpack16(const u32x4 w, v4i &a0, v4i &a1)
-{
-    constexpr unsigned HM = 0xF0F0F0F0u;     // nibble kept in the high half of its byte = code * 16
-    a0[0] = (int)((w.x << 4) & HM); a0[1] = (int)(w.x & HM);
-    a0[2] = (int)((w.y << 4) & HM); a0[3] = (int)(w.y & HM);
-    a1[0] = (int)((w.z << 4) & HM); a1[1] = (int)(w.z & HM);
-    a1[2] = (int)((w.w << 4) & HM); a1[3] = (int)(w.w & HM);
-}
-
 constexpr int SLAB = 128;    // packed bytes per row per slab (256 codes)
 
 // ------------------------------------------------------------------------------------------
@@ -476,6 +467,19 @@ hipError_t launch_stream_any(const uint8_t *Xq, const float *xs, const uint8_t *
 
 }  // namespace
 
+// Which kernel takes M <= 16 tokens, M > 2
+// The streaming kernel wins where every one of its 16 waves has a slab of K (K >= 4096) and a wave can keep
+// its whole share of K in registers (K <= 8192), except with few tokens and so many channels that a workgroup
+// per 16 channels fills the chip several times over (4096 -> 14336: 6.7 against 7.7 us for M <= 8; at 16
+// tokens 8.2 against 7.9 us the other way round).  Shorter rows leave waves idle (1024 -> 14336 at 16 tokens:
+// 6.0 against 4.5 us).
+bool gemm_decode_streams(int64_t M, int64_t N, int64_t K)
+{
+    const int nslab = (int)((K / 2 + SLAB - 1) / SLAB);
+    const bool few_tokens_many_channels = M <= 8 && nslab <= 16 && N >= 8192;
+    return M > 2 && nslab >= 16 && nslab <= 32 && !few_tokens_many_channels;
+}
+
 hipError_t launch_gemm_decode(const uint8_t *Xq, const float *xs, const uint8_t *Wq, const float *ws,
                               int64_t M, int64_t N, int64_t K, void *Y, int64_t ldy, int out_i32, hipStream_t st)
 {
@@ -491,13 +495,7 @@ hipError_t launch_gemm_decode(const uint8_t *Xq, const float *xs, const uint8_t 
         if (M <= 1) return launch_dot<1, 4, 1>(Xq, xs, Wq, ws, M, N, K, Y, ldy, out_i32, st);
         return launch_dot<2, 4, 2>(Xq, xs, Wq, ws, M, N, K, Y, ldy, out_i32, st);
     }
-    // The streaming kernel wins where every one of its 16 waves has a slab of K (K >= 4096) and a wave can keep
-    // its whole share of K in registers (K <= 8192), except with few tokens and so many channels that a workgroup
-    // per 16 channels fills the chip several times over (4096 -> 14336: 6.7 against 7.7 us for M <= 8; at 16
-    // tokens 8.2 against 7.9 us the other way round).  Shorter rows leave waves idle (1024 -> 14336 at 16 tokens:
-    // 6.0 against 4.5 us).
-    const bool few_tokens_many_channels = M <= 8 && nslab <= 16 && N >= 8192;
-    if (force == 3 || (force == 0 && nslab >= 16 && nslab <= 32 && !few_tokens_many_channels))
+    if (force == 3 || (force == 0 && gemm_decode_streams(M, N, K)))
         return launch_stream_any(Xq, xs, Wq, ws, M, N, K, Y, ldy, out_i32, st);
 
     const unsigned blocks = (unsigned)(N / 16);

@@ -185,6 +185,8 @@ hipError_t launch_gemm_f6(const uint8_t *X6, const float *xs, const uint8_t *W6,
 hipError_t launch_gemm_f6_stream(const uint8_t *X6, const float *xs, const uint8_t *W6, const float *ws, int64_t M,
                                  int64_t N, int64_t K, void *Y, int64_t ldy, int out_i32, hipStream_t st, int bm, int bn);
 
+// whether the streaming kernel takes these M <= 16 tokens (the outputs of the two others are rounded to fp16 once)
+bool gemm_decode_streams(int64_t M, int64_t N, int64_t K);
 hipError_t launch_gemm_decode(const uint8_t *Xq, const float *xs, const uint8_t *Wq, const float *ws,
                               int64_t M, int64_t N, int64_t K, void *Y, int64_t ldy, int out_i32,
                               hipStream_t st);
