@@ -3,6 +3,7 @@
 #pragma once
 
 #include "sr_common.h"
+#include "gemm_rules.h"
 
 #include <hip/hip_fp16.h>
 
@@ -118,47 +119,6 @@ __device__ __forceinline__ void store_wave_tile(const V16 (&acc)[FN][FM], uint8_
             }
         }
     }
-}
-
-// Split of the tile grid over the 8 XCDs (each with its own L2): XCD x = v & 7 gets the rectangle
-// (x % xcd_m, x / xcd_m) of an xcd_m x (8 / xcd_m) split and walks it m fastest.  Measured (FETCH_SIZE,
-// M = 2048, K = 4096, int8 kernel): two halves in m by four blocks in n reads 112 MB through the fabric at
-// N = 14336 where one run of tiles per XCD read 223 MB (half of X then stays in an XCD's 4 MB L2); it was
-// also the fastest split at K = 14336.  Otherwise: the split whose rectangles need the fewest operand rows.
-// 0 = no remapping.
-inline int choose_xcd_split(int tiles_m, int tiles_n, int BM, int BN)
-{
-    if (tiles_m % 2 == 0 && tiles_n % 4 == 0) return 2;
-    int xcd_m = 0;
-    int64_t best = 0;
-    for (int sm = 1; sm <= 8; sm *= 2) {
-        if (tiles_m % sm != 0 || tiles_n % (8 / sm) != 0) continue;
-        const int64_t rows = (int64_t)(tiles_m / sm) * BM + (int64_t)(tiles_n / (8 / sm)) * BN;
-        if (xcd_m == 0 || rows < best) { xcd_m = sm; best = rows; }
-    }
-    return xcd_m;
-}
-
-// virtual workgroup index -> tile origin under that split
-__device__ __forceinline__ void tile_origin(int v, int tiles_m, int tiles_n, int xcd_m, int BM, int BN, int &m0, int &n0)
-{
-    int tm, tn;
-    if (xcd_m > 0) {
-        const int x = v & 7, l = v >> 3;
-        const int rm = tiles_m / xcd_m, rn = tiles_n / (8 / xcd_m);      // rectangle size in tiles
-        // walk: mw tiles in m fastest, then across the rectangle in n, then the next mw rows of tiles -- the ~32
-        // tiles an XCD works on at a time then form a block of 8 x 4 tiles instead of a 32 x 1 column
-        // (M = 16384, N = 4096, K = 4096 on the FP6 kernel: 148.6 -> 139.5 us)
-        const int mw = (rm > 8 && rm % 8 == 0) ? 8 : rm;
-        const int a = l % mw, b = (l / mw) % rn, c = l / (mw * rn);
-        tm = (x % xcd_m) * rm + c * mw + a;
-        tn = (x / xcd_m) * rn + b;
-    } else {
-        tm = v % tiles_m;
-        tn = v / tiles_m;
-    }
-    m0 = tm * BM;
-    n0 = tn * BN;
 }
 
 }  // namespace

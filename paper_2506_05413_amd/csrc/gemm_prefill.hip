@@ -88,7 +88,6 @@ __global__ __launch_bounds__(WGM * WGN * KS * 64) void gemm_w4a4_kernel(
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave % WGM, wn = wave / WGM % WGN, kw = wave / (WGM * WGN);
-    const int total = tiles_m * tiles_n;
 
     // workgroups are dealt round-robin to the 8 XCDs; with the XCD split on, the grid size is a multiple of 8,
     // so a workgroup's later tiles stay in its XCD's rectangle
@@ -245,6 +244,7 @@ __global__ __launch_bounds__(WGM * WGN * KS * 64) void gemm_w4a4_kernel(
 
     int v = blockIdx.x;
     int m0, n0;
+    if (!tile_exists(v, tiles_m, tiles_n, xcd_m)) return;      // the whole workgroup
     tile_origin(v, m0, n0);
     set_sources(m0, n0);
 #pragma unroll
@@ -302,7 +302,7 @@ __global__ __launch_bounds__(WGM * WGN * KS * 64) void gemm_w4a4_kernel(
 
         // ---- tile boundary
         const int vn = v + (int)gridDim.x;
-        const bool more = vn < total;
+        const bool more = tile_exists(vn, tiles_m, tiles_n, xcd_m);
         wait_vmcnt<0>();                             // no LDS-DMA write is in flight any more ...
         // (the scales arrived long ago; naming them here keeps the compiler's own wait for them at this point
         // and not behind the loads issued next)
@@ -392,8 +392,7 @@ hipError_t launch_tile(const uint8_t *Xq, const float *xs, const uint8_t *Wq, co
     int64_t grid = (int64_t)compute_units() * WG_PER_CU;
     if (int64_t g; tuned(kTuneGemmGrid, g) && g > 0) grid = g / 8 * 8;
     if (grid < 8) grid = 8;
-    const int64_t total = (int64_t)tiles_m * tiles_n;
-    if (grid > total) grid = total;
+    grid = tile_workgroups(grid, (int64_t)tiles_m * tiles_n, xcd_m);
     // the raw int32 output takes no scales (they may be NULL): the kernel still fetches M and N floats it
     // then ignores, from the start of the code arrays (M * K / 2 >= 4 M bytes, 16-byte aligned)
     if (out_i32) {

@@ -1,5 +1,5 @@
-// Which configuration a GEMM launch takes: a predicted time per configuration, the cheapest wins.  Plain C++ (no HIP), so
-// that the rule can be compiled and checked on its own.
+// Which configuration a GEMM launch takes (a predicted time per configuration, the cheapest wins) and which workgroup takes
+// which tile.  Plain C++ (no HIP), so that both can be compiled and checked on their own.
 //
 // With t = tiles of the configuration, c compute units, r = ceil(t / c) rounds and n stages of K, a launch is predicted at
 //     fixed + per_round r + n (stage time of the rounds + stage_tile t / c) + out_mb (MB of Y) + weights_mb (MB of W)
@@ -126,5 +126,73 @@ template <int COUNT> constexpr bool coefficients_grow(const GemmConfig (&configs
     return true;
 }
 static_assert(coefficients_grow(kF6Configs) && coefficients_grow(kPackedConfigs), "a prediction may not fall where work is added");
+
+// ---- tiles and workgroups (device code too: constexpr) ------------------------------------------------------------------
+// Split of the tile grid over the 8 XCDs (each with its own L2): XCD x = v & 7 gets the rectangle
+// (x % xcd_m, x / xcd_m) of an xcd_m x (8 / xcd_m) split and walks it m fastest.  Measured (FETCH_SIZE,
+// M = 2048, K = 4096, int8 kernel): two halves in m by four blocks in n reads 112 MB through the fabric at
+// N = 14336 where one run of tiles per XCD read 223 MB (half of X then stays in an XCD's 4 MB L2); it was
+// also the fastest split at K = 14336.  Otherwise: the split whose rectangles need the fewest operand rows.
+// A grid that does not divide into rectangles (kXcdRuns): bands of 8 rows of tiles, walked m fastest, cut into 8 runs of
+// equal length, one per XCD: without it every XCD asks for nearly all of both operands (FP6, M 100 .. 6000, 72 ragged grids:
+// 6.8 % faster on average; 762 x 24288 x 8192 143 -> 119 us, 390 x 7792 x 4096 18.4 -> 15.0, 5713 x 6512 x 4096 120 -> 105; packed
+// nibbles, 74 grids: 3.2 %; 2871 x 9392 x 2048 62.5 -> 57.9).
+// 0 = tile v is tile v of the grid, m fastest (by the knob only).
+constexpr int kXcdRuns = -1;
+constexpr int choose_xcd_split(int tiles_m, int tiles_n, int BM, int BN)
+{
+    if (tiles_m % 2 == 0 && tiles_n % 4 == 0) return 2;
+    int xcd_m = kXcdRuns;
+    int64_t best = 0;
+    for (int sm = 1; sm <= 8; sm *= 2) {
+        if (tiles_m % sm != 0 || tiles_n % (8 / sm) != 0) continue;
+        const int64_t rows = (int64_t)(tiles_m / sm) * BM + (int64_t)(tiles_n / (8 / sm)) * BN;
+        if (xcd_m < 0 || rows < best) { xcd_m = sm; best = rows; }
+    }
+    return xcd_m;
+}
+
+// workgroups of a launch that holds `most` at a time (kXcdRuns: a multiple of 8, so that a workgroup's tiles stay in its XCD)
+constexpr int64_t tile_workgroups(int64_t most, int64_t tiles, int xcd_m)
+{
+    if (xcd_m == kXcdRuns) tiles = (tiles + 7) / 8 * 8;
+    return most < tiles ? most : tiles;
+}
+
+// whether virtual workgroup v has a tile (if not, nor has v + any multiple of the grid); without divisions: it is asked between
+// the last product and the stores of a tile
+constexpr bool tile_exists(int v, int tiles_m, int tiles_n, int xcd_m)
+{
+    const int64_t total = (int64_t)tiles_m * tiles_n, x = v & 7;
+    return xcd_m == kXcdRuns ? (x * total >> 3) + (v >> 3) < ((x + 1) * total >> 3) : v < total;
+}
+
+// its origin under that split
+constexpr void tile_origin(int v, int tiles_m, int tiles_n, int xcd_m, int BM, int BN, int &m0, int &n0)
+{
+    int tm = 0, tn = 0;
+    if (xcd_m > 0) {
+        const int x = v & 7, l = v >> 3;
+        const int rm = tiles_m / xcd_m, rn = tiles_n / (8 / xcd_m);      // rectangle size in tiles
+        // walk: mw tiles in m fastest, then across the rectangle in n, then the next mw rows of tiles -- the ~32
+        // tiles an XCD works on at a time then form a block of 8 x 4 tiles instead of a 32 x 1 column
+        // (M = 16384, N = 4096, K = 4096 on the FP6 kernel: 148.6 -> 139.5 us)
+        const int mw = (rm > 8 && rm % 8 == 0) ? 8 : rm;
+        const int a = l % mw, b = (l / mw) % rn, c = l / (mw * rn);
+        tm = (x % xcd_m) * rm + c * mw + a;
+        tn = (x / xcd_m) * rn + b;
+    } else if (xcd_m == kXcdRuns) {
+        const int idx = (int)((int64_t)(v & 7) * tiles_m * tiles_n >> 3) + (v >> 3);
+        const int band = idx / (8 * tiles_n), r = idx - band * 8 * tiles_n;
+        const int h = tiles_m - 8 * band < 8 ? tiles_m - 8 * band : 8;
+        tm = 8 * band + r % h;
+        tn = r / h;
+    } else {
+        tm = v % tiles_m;
+        tn = v / tiles_m;
+    }
+    m0 = tm * BM;
+    n0 = tn * BN;
+}
 
 }  // namespace sr

@@ -1,0 +1,44 @@
+"""Which workgroup takes which tile (csrc/gemm_rules.h), compiled on its own: every tile of a grid exactly once, whatever the
+grid's shape, the split over the XCDs and the number of workgroups; and no valid tile behind an invalid one."""
+import os
+import subprocess
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2506_05413_amd", "csrc")
+PROGRAM = r"""
+#include "gemm_rules.h"
+#include <cstdio>
+#include <vector>
+int main()
+{
+    long checked = 0;
+    for (int tm = 1; tm <= 41; ++tm)
+        for (int tn = 1; tn <= 61; tn += tm > 20 ? 3 : 1)
+            for (int split : {sr::choose_xcd_split(tm, tn, 256, 128), sr::kXcdRuns, 0})
+                for (int most : {8, 16, 248, 252, 256, 512}) {
+                    if (split > 0 && most % 8) continue;             // rectangles are asked for with multiples of 8 only
+                    const int grid = (int)sr::tile_workgroups(most, (long)tm * tn, split);
+                    std::vector<int> seen(tm * tn, 0);
+                    for (int v0 = 0; v0 < grid; ++v0) {
+                        int m = -1, n = -1, v = v0;
+                        for (; sr::tile_exists(v, tm, tn, split); v += grid) {
+                            sr::tile_origin(v, tm, tn, split, 256, 128, m, n);
+                            if (m % 256 || n % 128 || m / 256 >= tm || n / 128 >= tn || m < 0 || n < 0) return std::printf("outside %d %d %d %d\n", tm, tn, split, v), 1;
+                            ++seen[m / 256 * tn + n / 128];
+                        }
+                        for (int k = 0; k < 4; ++k, v += grid)
+                            if (sr::tile_exists(v, tm, tn, split)) return std::printf("behind %d %d %d %d\n", tm, tn, split, v), 1;
+                    }
+                    for (int c : seen)
+                        if (c != 1) return std::printf("%d times: %d x %d, split %d, %d workgroups\n", c, tm, tn, split, grid), 1;
+                    ++checked;
+                }
+    std::printf("%ld\n", checked);
+}
+"""
+
+
+def test_every_tile_once(tmp_path):
+    (tmp_path / "tiles.cpp").write_text(PROGRAM)
+    subprocess.run(["g++", "-std=c++17", "-O2", "-Wall", "-Werror", "-I", CSRC, "-o", str(tmp_path / "tiles"), str(tmp_path / "tiles.cpp")], check=True)
+    r = subprocess.run([str(tmp_path / "tiles")], capture_output=True, text=True)
+    assert r.returncode == 0 and int(r.stdout) > 10000, r.stdout
