@@ -395,14 +395,23 @@ hipError_t launch_rows_units(const void *X, int64_t M, int64_t ldx, const float 
 
 // Whether the call goes through linear_decode_rows_kernel: 2 .. 4 tokens, as many channels as its registers hold at once -- for
 // two tokens fewer, because the dot-product kernel behind the token quantiser is ahead there (24576 channels 12.1 against
-// 12.5 us; 20480 the same).  Not where an output overlaps the token rows, which other workgroups may still be reading.
-bool rows_path(const void *X, int64_t M, int64_t K, int64_t ldx, int64_t N, const void *Y, int64_t ldy, const void *Xq_out, const void *xs_out)
+// 12.5 us; 20480 the same).  Captured calls, which cost the host nothing when they run, with two tokens or K = 2048 only from 40 M
+// weights on: below, the GPU is done sooner with two small launches (graph of calls, 2 / 4 tokens: 2048 x 6144 5.4 / 5.7 against
+// 6.1 / 6.1 us, 4096 x 4096 6.5 / 6.6 against 6.9 / 6.6; but 2048 x 28672 8.9 / 9.3 against 8.2 / 8.1, 4096 x 14336 9.6 / 9.6
+// against 9.3 / 9.1; the linears of a layer, 4 tokens, 54.5 against 54.2).  Not where
+// an output overlaps the token rows, which other workgroups may still be reading.
+bool rows_path(const void *X, int64_t M, int64_t K, int64_t ldx, int64_t N, const void *Y, int64_t ldy, const void *Xq_out, const void *xs_out,
+               hipStream_t st)
 {
-    if (M < 2 || M > 4) return false;
-    if (int64_t f; tuned(kTuneDecodeKernel, f) && f != 4) return false;
-    if (K != 2048 && K != 4096) return false;
+    if (M < 2 || M > 4 || (K != 2048 && K != 4096)) return false;
     const int64_t units = K == 2048 ? rows_units<2048>(N) : rows_units<4096>(N);
     if (units > (K == 2048 ? kMaxUnits2048 : M == 2 ? kMaxUnits4096TwoTokens : kMaxUnits4096)) return false;
+    if (int64_t f; tuned(kTuneDecodeKernel, f)) {
+        if (f != 4) return false;
+    } else if ((M == 2 || K == 2048) && N * K < 40000000 && st) {
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(st, &capture) == hipSuccess && capture != hipStreamCaptureStatusNone) return false;
+    }
     const uintptr_t x = reinterpret_cast<uintptr_t>(X), x_end = x + (size_t)((M - 1) * ldx + K) * 2;
     auto overlaps = [&](const void *p, int64_t bytes) { const uintptr_t a = reinterpret_cast<uintptr_t>(p); return p && a < x_end && x < a + (size_t)bytes; };
     return !overlaps(Y, ((M - 1) * ldy + N) * 2) && !overlaps(Xq_out, M * (K / 2)) && !overlaps(xs_out, M * 4);
@@ -455,7 +464,7 @@ hipError_t launch_linear_decode(const void *X, int64_t M, int64_t K, int64_t ldx
         return hipErrorInvalidValue;
 #undef SR_LD
     }
-    if (rows_path(X, M, K, ldx, N, Y, ldy, Xq_out, xs_out)) {
+    if (rows_path(X, M, K, ldx, N, Y, ldy, Xq_out, xs_out, st)) {
         if (K == 2048) return launch_rows_units<2048>(X, M, ldx, pre, clip, Wq, ws, N, Y, ldy, Xq_out, xs_out, st);
         return launch_rows_units<4096>(X, M, ldx, pre, clip, Wq, ws, N, Y, ldy, Xq_out, xs_out, st);
     }

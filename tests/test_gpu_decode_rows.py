@@ -47,3 +47,26 @@ def test_output_over_the_token_rows(gpu):
         Y = X.clone()
         gpu.sr_w4a4_linear_decode(Y, None, Wq, ws, 0.9, Y=Y)
         assert torch.equal(Y, want)
+
+
+@pytest.mark.parametrize("M,K,N", [(3, 2048, 6144), (3, 2048, 28672), (2, 4096, 4096), (4, 4096, 4096), (2, 4096, 14336)])
+def test_captured_calls(gpu, M, K, N):
+    """Captured calls take two launches where the GPU is done sooner with them: the same outputs as eager ones, on every replay."""
+    print("case captured decode rows", M, K, N, flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N)
+    Wq = torch.randint(0, 256, (N, K // 2), generator=g, dtype=torch.uint8, device="cuda")
+    ws = 1e-3 + 1e-3 * torch.rand(N, generator=g, device="cuda")
+    X = torch.randn((M, K), generator=g, device="cuda").half()
+    x, Y = X.clone(), torch.empty((M, N), dtype=torch.float16, device="cuda")
+    work = torch.empty(gpu.sr_linear_decode_workspace_bytes(M, K), dtype=torch.uint8, device="cuda")
+    gpu.sr_w4a4_linear_decode(x, None, Wq, ws, 0.9, Y=Y, workspace=work)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        gpu.sr_w4a4_linear_decode(x, None, Wq, ws, 0.9, Y=Y, workspace=work)
+    for i in range(4):
+        x.copy_(X * (1 + i))
+        Y.zero_()
+        graph.replay()
+        assert torch.equal(Y, gpu.sr_w4a4_linear_decode(x, None, Wq, ws, 0.9)) and bool(Y.any())
