@@ -73,16 +73,18 @@ __device__ __forceinline__ void dma4(const void *base, uint32_t lane_off, uint32
 // (Also built and measured for the 256 x 256 configuration, which has no registers for a ninth wave: the
 // workgroups that run out of tiles before the last round reading the region instead.  With the 12.6 MB of the
 // benchmark's N = 4096 weights behind its N = 14336 launch the step got 2 % slower, not faster; dropped.)
-template <int BM, int BN, int WGM, int WGN, int SLOTS, int CG, bool WARM = false>
+// LIVE < BM / WGM / 32 or SPLIT: a tile has only its first row_step <= BM rows (a multiple of 16), and this wave multiplies only
+// LIVE of its fragments of 32 rows (see gemm_f6_rows_kernel).
+template <int BM, int BN, int WGM, int WGN, int SLOTS, int CG, bool WARM = false, bool SPLIT = false, int LIVE = BM / WGM / 32>
 __device__ __forceinline__ void f6_tiles(
     const uint8_t *__restrict__ X6, const float *__restrict__ xs, const uint8_t *__restrict__ W6,
     const float *__restrict__ ws, const int M, const int N, const int K, void *__restrict__ Yv, const int64_t ldy,
     const int out_i32, const int tiles_m, const int tiles_n, const int xcd_m, const int v0,
-    const int vstep, const uint32_t *__restrict__ warm = nullptr, const int64_t warm_lines = 0)
+    const int vstep, const int row_step, const uint32_t *__restrict__ warm = nullptr, const int64_t warm_lines = 0)
 {
     constexpr int NWAVE = WGM * WGN;
     constexpr int WM = BM / WGM, WN = BN / WGN;      // wave tile
-    constexpr int FM = WM / 32, FN = WN / 32;        // 32 x 32 MFMA tiles per wave
+    constexpr int FM = LIVE, FN = WN / 32;           // 32 x 32 MFMA tiles per wave
     constexpr int X_BYTES = BM / 8 * BLK, STAGE_BYTES = (BM + BN) / 8 * BLK;
     // 1 KB LDS-DMA instructions per stage: NXI for the X run, NWI for the W run; every wave issues XI + WI of
     // them -- where the count does not divide by the waves, the last ones wrap around and copy a KB a second
@@ -99,7 +101,8 @@ __device__ __forceinline__ void f6_tiles(
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave % WGM, wn = wave / WGM;
+    // SPLIT: the two waves of a SIMD (w, w + 4) share its row of fewer fragments
+    const int wm = SPLIT ? wave / WGN : wave % WGM, wn = SPLIT ? wave % WGN : wave / WGM;
     const int nc = K >> 7;                           // 128-code chunks per row = stages
     if constexpr (WARM) {
         if (wave == NWAVE) {
@@ -243,7 +246,7 @@ __device__ __forceinline__ void f6_tiles(
     int v = v0;
     int m0, n0;
     if (!tile_exists(v, tiles_m, tiles_n, xcd_m)) return;      // the whole workgroup
-    tile_origin(v, tiles_m, tiles_n, xcd_m, BM, BN, m0, n0);
+    tile_origin(v, tiles_m, tiles_n, xcd_m, SPLIT ? row_step : BM, BN, m0, n0);
     set_sources(m0, n0);
     // order of a wave's loads at the start of every tile: stage 0, scales, stages 1 .. SLOTS-2, first part of
     // stage SLOTS-1 (its second part is issued by the first step of the loop)
@@ -295,7 +298,7 @@ __device__ __forceinline__ void f6_tiles(
         barrier_nofence();                           // ... and all waves are done reading fragments
         int m1 = 0, n1 = 0;
         if (more) {                                  // the next tile's first stages fly during the epilogue
-            tile_origin(vn, tiles_m, tiles_n, xcd_m, BM, BN, m1, n1);
+            tile_origin(vn, tiles_m, tiles_n, xcd_m, SPLIT ? row_step : BM, BN, m1, n1);
             set_sources(m1, n1);
             issue(0, 0);
             issue_scales(m1, n1, area ^ 1);
@@ -313,8 +316,10 @@ __device__ __forceinline__ void f6_tiles(
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
                     sw[i][q] = *reinterpret_cast<const float4 *>(sc + BM + wn * WN + i * 32 + q * 8 + fg * 4);
+            // (rows past row_step belong to the next tile)
+            const int end = SPLIT && m0 + row_step < M ? m0 + row_step : M;
             store_wave_tile<FM, FN, CG>(acc, smem + (SLOTS - 1) * STAGE_BYTES + wave * PIECE, lane, m0 + wm * WM, n0 + wn * WN,
-                                    M, N, sx, sw, Yv, ldy, out_i32);
+                                    end, N, sx, sw, Yv, ldy, out_i32);
         }
         if (!more) break;
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -344,7 +349,7 @@ __global__ __launch_bounds__(WGM * WGN * 64, WGM * WGN * WG_PER_CU / 4) void gem
     int tiles_m, int tiles_n, int xcd_m)
 {
     f6_tiles<BM, BN, WGM, WGN, SLOTS, f6_staged_columns(BM, BN, WGM * WGN, WGN)>(X6, xs, W6, ws, M, N, K, Yv, ldy, out_i32, tiles_m, tiles_n, xcd_m,
-                                                     (int)blockIdx.x, (int)gridDim.x);
+                                                     (int)blockIdx.x, (int)gridDim.x, BM);
 }
 
 // The same with a ninth wave that warms the memory-side cache (one workgroup per CU: three waves then share the
@@ -356,7 +361,34 @@ __global__ __launch_bounds__((WGM * WGN + 1) * 64) void gemm_f6_warm_kernel(
     int tiles_m, int tiles_n, int xcd_m, const uint32_t *__restrict__ warm, int64_t warm_lines)
 {
     f6_tiles<BM, BN, WGM, WGN, SLOTS, BN / WGN / 32, true>(X6, xs, W6, ws, M, N, K, Yv, ldy, out_i32, tiles_m, tiles_n, xcd_m,
-                                                           (int)blockIdx.x, (int)gridDim.x, warm, warm_lines);
+                                                           (int)blockIdx.x, (int)gridDim.x, BM, warm, warm_lines);
+}
+
+// The same for row counts that leave the last row of tiles short: all rows of tiles get row_step rows, and the second row of
+// waves multiplies the fragments of 32 rows that are there (LIVE, one copy of the loop per count; the barriers are the same).
+// Its waves share their SIMDs with those of the first row, so every SIMD has the fewer products, and the LDS delivers fewer
+// fragments (a stage of 256 x 256 tiles moves 196 KB through it: with 128 B per clock that bounds a launch of one round).
+// Against padding the last row of tiles: 520 x 14336 x 4096 (six of eight fragments) 24.9 -> 22.9 us, 777 x 14336 x 4096 (seven)
+// 30.3 -> 29.3, 616 x 26992 x 4096 58.1 -> 54.2.
+template <int BM, int BN, int WGN, int SLOTS>
+__global__ __launch_bounds__(2 * WGN * 64, WGN / 2) void gemm_f6_rows_kernel(
+    const uint8_t *__restrict__ X6, const float *__restrict__ xs, const uint8_t *__restrict__ W6,
+    const float *__restrict__ ws, int M, int N, int K, void *__restrict__ Yv, int64_t ldy, int out_i32,
+    int tiles_m, int tiles_n, int xcd_m, int row_step)
+{
+    static_assert(WGN == 4, "waves w and w + 4 share a SIMD");
+    constexpr int WM = BM / 2, CG = f6_staged_columns(BM, BN, 2 * WGN, WGN);
+#define SR_ROWS(L)                                                                                                            \
+    f6_tiles<BM, BN, 2, WGN, SLOTS, CG, false, true, L>(X6, xs, W6, ws, M, N, K, Yv, ldy, out_i32, tiles_m, tiles_n, xcd_m,    \
+                                                        (int)blockIdx.x, (int)gridDim.x, row_step)
+    constexpr int FULL = WM / 32, THREE = FULL < 3 ? FULL : 3, TWO = FULL < 2 ? FULL : 2;
+    const bool second = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) >= WGN;
+    const int live = second ? (row_step - WM + 31) / 32 : FULL;
+    if (live >= FULL) SR_ROWS(FULL);
+    else if (live == THREE) SR_ROWS(THREE);
+    else if (live == TWO) SR_ROWS(TWO);
+    else SR_ROWS(1);
+#undef SR_ROWS
 }
 
 template <int BM, int BN, int WGM, int WGN, int SLOTS, int WG_PER_CU, bool CAN_WARM = false>
@@ -382,7 +414,8 @@ hipError_t launch_f6(const uint8_t *X6, const float *xs, const uint8_t *W6, cons
         }
     }
     const int tiles_m = (int)((M + BM - 1) / BM), tiles_n = (int)((N + BN - 1) / BN);
-    int xcd_m = choose_xcd_split(tiles_m, tiles_n, BM, BN);
+    const int row_step = WGM == 2 && WGN == 4 ? f6_row_step(M, BM) : BM;
+    int xcd_m = choose_xcd_split(tiles_m, tiles_n, row_step, BN);
     // (128 x 64 tiles: the plain order is 2 - 5 % ahead of the runs, 749 x 1984 x 8192 18.0 against 18.5 us)
     if (BN == 64 && xcd_m == kXcdRuns) xcd_m = 0;
     if (int64_t f; tuned(kTuneGemmXcdM, f)) {                         // force the split (0 = none)
@@ -403,6 +436,16 @@ hipError_t launch_f6(const uint8_t *X6, const float *xs, const uint8_t *W6, cons
             hipLaunchKernelGGL((gemm_f6_warm_kernel<BM, BN, WGM, WGN, SLOTS>), dim3((unsigned)grid), dim3((WGM * WGN + 1) * 64),
                                lds, st, X6, xs, W6, ws, (int)M, (int)N, (int)K, Y, ldy, out_i32, tiles_m, tiles_n, xcd_m,
                                static_cast<const uint32_t *>(warm), (int64_t)(warm_bytes / 128));
+            return hipGetLastError();
+        }
+    }
+    if constexpr (WGM == 2 && WGN == 4) {
+        if (row_step < BM) {
+            static_assert(lds > 48 * 1024 && WG_PER_CU == 1);
+            hipError_t e = allow_dynamic_lds<gemm_f6_rows_kernel<BM, BN, WGN, SLOTS>>(lds);
+            if (e != hipSuccess) return e;
+            hipLaunchKernelGGL((gemm_f6_rows_kernel<BM, BN, WGN, SLOTS>), dim3((unsigned)grid), dim3(2 * WGN * 64), lds, st, X6, xs,
+                               W6, ws, (int)M, (int)N, (int)K, Y, ldy, out_i32, tiles_m, tiles_n, xcd_m, row_step);
             return hipGetLastError();
         }
     }

@@ -159,6 +159,14 @@ constexpr int64_t tile_workgroups(int64_t most, int64_t tiles, int xcd_m)
     return most < tiles ? most : tiles;
 }
 
+// Rows per tile of the FP6 kernel with two rows of waves: bm, or fewer where the rows of tiles, made equally high, leave whole
+// fragments of 32 rows out (a multiple of 16 and more than bm / 2: the second row of waves has a fragment at least).
+constexpr int f6_row_step(int64_t M, int bm)
+{
+    const int64_t tiles = (M + bm - 1) / bm, step = ((M + tiles - 1) / tiles + 15) / 16 * 16;
+    return (step + 31) / 32 * 32 < bm && step > bm / 2 ? (int)step : bm;
+}
+
 // whether virtual workgroup v has a tile (if not, nor has v + any multiple of the grid); without divisions: it is asked between
 // the last product and the stores of a tile
 constexpr bool tile_exists(int v, int tiles_m, int tiles_n, int xcd_m)

@@ -7,6 +7,7 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 PROGRAM = r"""
 #include "gemm_rules.h"
 #include <cstdio>
+#include <initializer_list>
 #include <vector>
 int main()
 {
@@ -42,3 +43,27 @@ def test_every_tile_once(tmp_path):
     subprocess.run(["g++", "-std=c++17", "-O2", "-Wall", "-Werror", "-I", CSRC, "-o", str(tmp_path / "tiles"), str(tmp_path / "tiles.cpp")], check=True)
     r = subprocess.run([str(tmp_path / "tiles")], capture_output=True, text=True)
     assert r.returncode == 0 and int(r.stdout) > 10000, r.stdout
+
+
+def test_rows_per_tile(tmp_path):
+    """The rows of an FP6 tile: a multiple of 16 above half of it, no row left out, no empty row of tiles."""
+    (tmp_path / "rows.cpp").write_text(r"""
+#include "gemm_rules.h"
+#include <cstdio>
+#include <initializer_list>
+int main()
+{
+    int fewer = 0;
+    for (int bm : {128, 192, 256})
+        for (long M = 1; M <= 20000; ++M) {
+            const long step = sr::f6_row_step(M, bm), tiles = (M + bm - 1) / bm;
+            if (step > bm || step * tiles < M || step * (tiles - 1) >= M) return std::printf("%ld rows, %d: %ld\n", M, bm, step), 1;
+            if (step < bm && (step % 16 || step <= bm / 2 || (step + 31) / 32 >= bm / 32)) return std::printf("%ld rows, %d: %ld\n", M, bm, step), 1;
+            fewer += step < bm;
+        }
+    std::printf("%d\n", fewer);
+}
+""")
+    subprocess.run(["g++", "-std=c++17", "-O2", "-Wall", "-Werror", "-I", CSRC, "-o", str(tmp_path / "rows"), str(tmp_path / "rows.cpp")], check=True)
+    r = subprocess.run([str(tmp_path / "rows")], capture_output=True, text=True)
+    assert r.returncode == 0 and int(r.stdout) > 500, r.stdout
