@@ -7,13 +7,16 @@
 // kernel of gemm_prefill.hip, whose header explains the widening to code * 16.)
 //
 // A workgroup owns FM * 16 rows x FN * 16 channels and its NW waves split K in chunks of 256 codes -- one 128-byte line
-// of every row, which a wave fetches with two loads per 16-row fragment: lane (i = l & 15, g = l >> 4) takes bytes
-// 16 g .. + 15 and 64 + 16 g .. + 15 of row i.  Each 16-byte piece widens to the operands of two
-// v_mfma_i32_16x16x64_i8 (the order of k inside a dot product is free and X and W are widened alike).  No LDS and no
-// barrier until the waves' partial sums meet at the end.  What bounds it: the rate at which a CU takes operands from L2
-// plus the widening (each workgroup widens its activations again).  Measured against the 128 x 128 tile kernel, weights
-// in the memory-side cache: 20 x 4096 x 4096 16.4 -> 4.6 us, 29 x 4096 x 14336 47.6 -> 12.2, 123 x 8192 x 4096
-// 17.0 -> 11.7 us.
+// of every row, which eight neighbouring lanes fetch whole.  A wave brings each 16-row fragment into operand order through
+// two small buffers of its own LDS (no barrier: a wave's LDS accesses execute in order); each 16-byte piece then widens to
+// the operands of two v_mfma_i32_16x16x64_i8 (the order of k inside a dot product is free and X and W are widened alike).
+// No barrier until the waves' partial sums meet at the end.
+//
+// Loading the operand order directly (neighbouring lanes on 16 different rows) cost a lookup of the L1 per lane, 60 for a
+// load of 1 KB where whole lines take 16 (TCP_TOTAL_CACHE_ACCESSES): that bounded the kernel.  Weights in the memory-side
+// cache, us: 60 x 4096 x 4096 6.2 -> 4.8, 29 x 4096 x 14336 11.6 -> 8.1, 128 x 4096 x 8192 13.9 -> 10.1, 353 x 2096 x 8192
+// 19.0 -> 12.2 (from HBM 18.9 -> 12.6).  What bounds it now: the L1 still (16 KB per chunk of 64 x 64 outputs at 64 B per
+// clock), the widening and its matrix instructions, which do not overlap, and the trip through LDS, about equally.
 #include "sr_common.h"
 #include "gemm_common.h"
 
@@ -47,7 +50,9 @@ __global__ __launch_bounds__(NW * 64) void gemm_w4a4_stream_kernel(
     int tiles_m, int tiles_n)
 {
     constexpr int TILES = FM * FN, TPP = TILES <= 8 ? TILES : TILES % 8 == 0 ? 8 : 6;
-    __shared__ __attribute__((aligned(16))) v4i red[NW][TPP][64];
+    // a wave's partial sums; before that, two fragments on their way from load order to operand order
+    constexpr int ROW = 144, FRAG = 16 * ROW, OWN = TPP * 1024 > 2 * FRAG ? TPP * 1024 : 2 * FRAG;
+    __shared__ __attribute__((aligned(16))) uint8_t lds[NW][OWN];
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -60,32 +65,50 @@ __global__ __launch_bounds__(NW * 64) void gemm_w4a4_stream_kernel(
     const int m0 = tm * FM * 16, n0 = tn * FN * 16;
     const int nc = K >> 8, Kb = K >> 1, q = lane >> 4;
 
-    uint32_t xo[FM], wo[FN];                             // byte offset of the lane's row; rows past the end re-read the last
+    // Load order: eight neighbouring lanes fetch a 128-byte line, load j of a fragment its rows 8 j .. 8 j + 7.  Rows past the
+    // end re-read the last.
+    uint32_t xo[FM][2], wo[FN][2];
 #pragma unroll
-    for (int f = 0; f < FM; ++f) {
-        const int m = m0 + 16 * f + (lane & 15);
-        xo[f] = (uint32_t)(m < M ? m : M - 1) * (uint32_t)Kb + 16 * q;
-    }
+    for (int f = 0; f < FM; ++f)
 #pragma unroll
-    for (int f = 0; f < FN; ++f) {
-        const int n = n0 + 16 * f + (lane & 15);
-        wo[f] = (uint32_t)(n < N ? n : N - 1) * (uint32_t)Kb + 16 * q;
-    }
+        for (int j = 0; j < 2; ++j) {
+            const int m = m0 + 16 * f + 8 * j + (lane >> 3);
+            xo[f][j] = (uint32_t)(m < M ? m : M - 1) * (uint32_t)Kb + 16 * (lane & 7);
+        }
+#pragma unroll
+    for (int f = 0; f < FN; ++f)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int n = n0 + 16 * f + 8 * j + (lane >> 3);
+            wo[f][j] = (uint32_t)(n < N ? n : N - 1) * (uint32_t)Kb + 16 * (lane & 7);
+        }
 
-    u32x4 x[D][FM][2], w[D][FN][2];                      // chunk d in flight: both halves of the line of every row
+    u32x4 x[D][FM][2], w[D][FN][2];                      // chunk d in flight, in load order
     auto load = [&](auto DC, int s) {
         constexpr int d = decltype(DC)::value;
         const uint8_t *wp = Wq + (int64_t)s * 128, *xp = Xq + (int64_t)s * 128;
 #pragma unroll
-        for (int f = 0; f < FN; ++f) {
-            w[d][f][0] = *reinterpret_cast<const u32x4 *>(wp + wo[f]);
-            w[d][f][1] = *reinterpret_cast<const u32x4 *>(wp + wo[f] + 64);
-        }
+        for (int f = 0; f < FN; ++f)
 #pragma unroll
-        for (int f = 0; f < FM; ++f) {
-            x[d][f][0] = *reinterpret_cast<const u32x4 *>(xp + xo[f]);
-            x[d][f][1] = *reinterpret_cast<const u32x4 *>(xp + xo[f] + 64);
-        }
+            for (int j = 0; j < 2; ++j) w[d][f][j] = *reinterpret_cast<const u32x4 *>(wp + wo[f][j]);
+#pragma unroll
+        for (int f = 0; f < FM; ++f)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) x[d][f][j] = *reinterpret_cast<const u32x4 *>(xp + xo[f][j]);
+    };
+    // Load order -> operand order (lane (i = l & 15, g = l >> 4): bytes 16 g .. + 15 and 64 + 16 g .. + 15 of row i) through the
+    // wave's own LDS; its accesses execute in order.  Rows 144 bytes apart: free of bank conflicts both ways.
+    uint8_t *const put = &lds[wave][0] + (lane >> 3) * ROW + (lane & 7) * 16;
+    const uint8_t *const get = &lds[wave][0] + (lane & 15) * ROW + q * 16;
+    auto operands = [&](const u32x4 (&p)[2], int buffer, u32x4 (&h)[2]) {
+        *reinterpret_cast<u32x4 *>(put + buffer * FRAG) = p[0];
+        *reinterpret_cast<u32x4 *>(put + buffer * FRAG + 8 * ROW) = p[1];
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        h[0] = *reinterpret_cast<const u32x4 *>(get + buffer * FRAG);
+        h[1] = *reinterpret_cast<const u32x4 *>(get + buffer * FRAG + 64);
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
     };
     // Output o of pass k of the reduction = lane o & 63 of tile k TPP + (o >> 6): four channels of one token.  Its
     // dequantisation factors are fetched ahead of the operands and used last (see gemm_f6_stream.hip).
@@ -109,19 +132,26 @@ __global__ __launch_bounds__(NW * 64) void gemm_w4a4_stream_kernel(
         for (int f = 0; f < FM; ++f) acc[i][f] = v4i{0, 0, 0, 0};
     auto multiply = [&](auto DC) {
         constexpr int d = decltype(DC)::value;
+        v4i xa[FM][2][2];
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            v4i xa[FM][2];
+        for (int f = 0; f < FM; ++f) {
+            u32x4 h[2];
+            operands(x[d][f], f & 1, h);
+            widen(h[0], xa[f][0][0], xa[f][0][1]);
+            widen(h[1], xa[f][1][0], xa[f][1][1]);
+        }
 #pragma unroll
-            for (int f = 0; f < FM; ++f) widen(x[d][f][h], xa[f][0], xa[f][1]);
+        for (int i = 0; i < FN; ++i) {
+            u32x4 h[2];
+            operands(w[d][i], (FM + i) & 1, h);
 #pragma unroll
-            for (int i = 0; i < FN; ++i) {
+            for (int k = 0; k < 2; ++k) {
                 v4i wa[2];
-                widen(w[d][i][h], wa[0], wa[1]);
+                widen(h[k], wa[0], wa[1]);
 #pragma unroll
                 for (int f = 0; f < FM; ++f) {
-                    acc[i][f] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wa[0], xa[f][0], acc[i][f], 0, 0, 0);
-                    acc[i][f] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wa[1], xa[f][1], acc[i][f], 0, 0, 0);
+                    acc[i][f] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wa[0], xa[f][k][0], acc[i][f], 0, 0, 0);
+                    acc[i][f] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wa[1], xa[f][k][1], acc[i][f], 0, 0, 0);
                 }
             }
         }
@@ -153,16 +183,17 @@ __global__ __launch_bounds__(NW * 64) void gemm_w4a4_stream_kernel(
     }
 
     // ---- the waves' sums, TPP tiles at a time: lane l of tile (i, f) holds token l & 15, channels 4 (l >> 4) .. + 3
+    auto sums = [&](int from, int tile) -> v4i & { return *reinterpret_cast<v4i *>(&lds[from][(tile * 64 + lane) * 16]); };
 #pragma unroll
     for (int k = 0; k < PASSES; ++k) {
         if (k) __syncthreads();
 #pragma unroll
-        for (int p = 0; p < TPP; ++p) red[wave][p][lane] = acc[(k * TPP + p) / FM][(k * TPP + p) % FM];
+        for (int p = 0; p < TPP; ++p) sums(wave, p) = acc[(k * TPP + p) / FM][(k * TPP + p) % FM];
         __syncthreads();
         if (wave < TPP && om[k] < M && on[k] < N) {
-            v4i s = red[0][wave][lane];
+            v4i s = sums(0, wave);
 #pragma unroll
-            for (int u = 1; u < NW; ++u) s += red[u][wave][lane];
+            for (int u = 1; u < NW; ++u) s += sums(u, wave);
             s >>= 8;                                        // both operands carried a factor 16
             if (out_i32) {
                 *reinterpret_cast<v4i *>(static_cast<int32_t *>(Yv) + (int64_t)om[k] * ldy + on[k]) = s;

@@ -99,13 +99,15 @@ constexpr GemmConfig kPackedConfigs[] = {
     // (Tried: workgroups starting at different places of K, against all of them asking for the same lines of every row
     // at a time -- no difference at K = 4096, 8192 and 14336.)
     {20, 128, 128, false, 2.230f, 2.657f, .548f, 0.f, .226f, .120f, .006f},
-    // operands straight into registers, K split over eight waves (gemm_packed_stream.hip)
-    {64064, 64, 64, false, 1.683f, 1.856f, .436f, 0.f, .015f, .377f, .016f},
-    {48064, 48, 64, false, 1.778f, 1.389f, .399f, 0.f, .005f, .266f, .025f},
-    {48032, 48, 32, true, 1.921f, .999f, .517f, .264f, .021f, .710f, .003f},
-    {32064, 32, 64, true, 2.731f, 1.071f, .635f, .314f, .002f, .421f, .026f},
-    {32032, 32, 32, true, 2.520f, .212f, .397f, .217f, 0.f, 1.191f, .036f},
-    {32016, 32, 16, false, 2.422f, .308f, .154f, 0.f, 0.f, 1.314f, .004f},
+    // operands line by line into registers, K split over eight waves (gemm_packed_stream.hip).  Fitted to 675 shapes of M 17 ..
+    // 16384, weights in the memory-side cache, after its loads became whole lines: on 500 others the choice is 0.5 % behind the
+    // fastest configuration (14 % at worst), with the coefficients before 1.6 % (28 %).
+    {64064, 64, 64, false, 1.579f, 1.873f, .225f, 0.f, .042f, .187f, .021f},
+    {48064, 48, 64, false, 1.594f, 1.735f, .179f, 0.f, .035f, .209f, .039f},
+    {48032, 48, 32, true, 1.462f, 1.272f, .259f, .128f, .012f, .403f, .059f},
+    {32064, 32, 64, true, 1.335f, 1.672f, .289f, .153f, .023f, .293f, .060f},
+    {32032, 32, 32, true, 1.795f, .826f, .197f, .097f, .005f, .389f, .057f},
+    {32016, 32, 16, false, 2.145f, .414f, .055f, 0.f, 0.f, .545f, .055f},
 };
 constexpr GemmShape packed_shape(int64_t M, int64_t N, int64_t K, int64_t cus) { return {M, N, K, 256, .5f, cus}; }
 constexpr const GemmConfig *packed_config(const GemmShape &s)
