@@ -19,7 +19,8 @@
 //
 // A fragment of v_mfma_scale_f32_16x16x128_f8f6f4 wants lane l to hold the 32 codes 32 q .. 32 q + 31 (q = l >> 4)
 // of row l & 15: exactly piece (r = l & 7, t = q >> 1, g = q & 1) of block l >> 3 & 1 of two neighbouring 768-byte
-// blocks.  The 16-byte heads of a fragment are two runs of 512 contiguous bytes, its 8-byte tails two of 256.
+// blocks.  The 16-byte heads of a fragment are two runs of 512 contiguous bytes, its 8-byte tails two of 256 (fetched for
+// two fragments at a time where that pays, see launch_st).
 #include "sr_common.h"
 #include "gemm_common.h"
 
@@ -44,7 +45,7 @@ template <int N, typename F> __device__ __forceinline__ void static_for(F f)
 }
 
 // D = chunks a wave keeps in flight; TPP = 16 x 16 tiles whose partial sums are in LDS at a time.
-template <int FM, int FN, int NW, int D>
+template <int FM, int FN, int NW, int D, bool PAIRS>
 __global__ __launch_bounds__(NW * 64) void gemm_f6_stream_kernel(
     const uint8_t *__restrict__ X6, const float *__restrict__ xs, const uint8_t *__restrict__ W6,
     const float *__restrict__ ws, int M, int N, int K, void *__restrict__ Yv, int64_t ldy, int out_i32,
@@ -84,21 +85,52 @@ __global__ __launch_bounds__(NW * 64) void gemm_f6_stream_kernel(
         wo[f] = (b < wb ? b : wb - 1) * BLK;
     }
 
+    // Tails: the two steps of a (row, k half) share a 16-byte slot, so lanes 0 .. 31 fetch the slots of one fragment and lanes
+    // 32 .. 63 those of the next (lane bits: row, block, k half), whole lines; exchanging the halves of the wave then leaves
+    // every lane the 8 bytes of its step for either fragment.  (8 bytes per lane and fragment look every 64-byte piece up twice:
+    // 16 of the 64 lookups of two fragments less.)
+    // An odd last fragment, and all of them without PAIRS, are fetched 8 bytes a lane.
+    constexpr int XP = PAIRS ? FM / 2 : 0, WP = PAIRS ? FN / 2 : 0;
+    constexpr int XL = FM - 2 * XP, WL = FN - 2 * WP;
+    const uint32_t slot = 512 + 128 * ((q & 1) ^ half) + 16 * (lane & 7);
+    uint32_t xp[XP + 1], wp[WP + 1];
+#pragma unroll
+    for (int f = 0; f < XP; ++f) {
+        const uint32_t b = (uint32_t)(m0 >> 3) + 4 * f + 2 * (lane >> 5) + half;
+        xp[f] = (b < xb ? b : xb - 1) * BLK + slot;
+    }
+#pragma unroll
+    for (int f = 0; f < WP; ++f) {
+        const uint32_t b = (uint32_t)(n0 >> 3) + 4 * f + 2 * (lane >> 5) + half;
+        wp[f] = (b < wb ? b : wb - 1) * BLK + slot;
+    }
+
     u32x4 xh[D][FM], wh[D][FN];                          // chunk d in flight: heads and tails of its fragments
-    u32x2 xt[D][FM], wt[D][FN];
+    u32x4 xt[D][XP + 1], wt[D][WP + 1];
+    u32x2 xl[D][XL + 1], wl[D][WL + 1];
     auto load = [&](auto DC, int s) {
         constexpr int d = decltype(DC)::value;
         const uint8_t *w = W6 + (int64_t)s * cw_bytes, *x = X6 + (int64_t)s * cx_bytes;
 #pragma unroll
         for (int f = 0; f < FN; ++f) {
             wh[d][f] = *reinterpret_cast<const u32x4 *>(w + wo[f] + head);
-            wt[d][f] = *reinterpret_cast<const u32x2 *>(w + wo[f] + tail);
+            if (f >= 2 * WP) wl[d][f - 2 * WP] = *reinterpret_cast<const u32x2 *>(w + wo[f] + tail);
         }
+#pragma unroll
+        for (int f = 0; f < WP; ++f) wt[d][f] = *reinterpret_cast<const u32x4 *>(w + wp[f]);
 #pragma unroll
         for (int f = 0; f < FM; ++f) {
             xh[d][f] = *reinterpret_cast<const u32x4 *>(x + xo[f] + head);
-            xt[d][f] = *reinterpret_cast<const u32x2 *>(x + xo[f] + tail);
+            if (f >= 2 * XP) xl[d][f - 2 * XP] = *reinterpret_cast<const u32x2 *>(x + xo[f] + tail);
         }
+#pragma unroll
+        for (int f = 0; f < XP; ++f) xt[d][f] = *reinterpret_cast<const u32x4 *>(x + xp[f]);
+    };
+    // the tails of fragments 2 f and 2 f + 1 from the slots of both
+    auto split_tails = [](const u32x4 t, u32x2 &a, u32x2 &b) {
+        const auto lo = __builtin_amdgcn_permlane32_swap(t.x, t.z, false, false), hi = __builtin_amdgcn_permlane32_swap(t.y, t.w, false, false);
+        a = u32x2{lo[0], hi[0]};
+        b = u32x2{lo[1], hi[1]};
     };
     // Output o of pass p0 / TPP of the reduction = lane o & 63 of tile p0 + (o >> 6): four channels of one token.  Its
     // dequantisation factors are fetched ahead of the operands and used last (fetched after the reduction, their
@@ -123,12 +155,21 @@ __global__ __launch_bounds__(NW * 64) void gemm_f6_stream_kernel(
         for (int f = 0; f < FM; ++f) acc[i][f] = v4f{0.f, 0.f, 0.f, 0.f};
     auto multiply = [&](auto DC) {
         constexpr int d = decltype(DC)::value;
+        u32x2 xe[FM], we[FN];
+#pragma unroll
+        for (int f = 0; f < XP; ++f) split_tails(xt[d][f], xe[2 * f], xe[2 * f + 1]);
+#pragma unroll
+        for (int f = 0; f < XL; ++f) xe[2 * XP + f] = xl[d][f];
+#pragma unroll
+        for (int f = 0; f < WP; ++f) split_tails(wt[d][f], we[2 * f], we[2 * f + 1]);
+#pragma unroll
+        for (int f = 0; f < WL; ++f) we[2 * WP + f] = wl[d][f];
 #pragma unroll
         for (int i = 0; i < FN; ++i) {
-            const v8i w = {(int)wh[d][i].x, (int)wh[d][i].y, (int)wh[d][i].z, (int)wh[d][i].w, (int)wt[d][i].x, (int)wt[d][i].y, 0, 0};
+            const v8i w = {(int)wh[d][i].x, (int)wh[d][i].y, (int)wh[d][i].z, (int)wh[d][i].w, (int)we[i].x, (int)we[i].y, 0, 0};
 #pragma unroll
             for (int f = 0; f < FM; ++f) {
-                const v8i x = {(int)xh[d][f].x, (int)xh[d][f].y, (int)xh[d][f].z, (int)xh[d][f].w, (int)xt[d][f].x, (int)xt[d][f].y, 0, 0};
+                const v8i x = {(int)xh[d][f].x, (int)xh[d][f].y, (int)xh[d][f].z, (int)xh[d][f].w, (int)xe[f].x, (int)xe[f].y, 0, 0};
                 acc[i][f] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(w, x, acc[i][f], 2, 2, 0, 0, 0, 0);
             }
         }
@@ -191,7 +232,15 @@ hipError_t launch_st(const uint8_t *X6, const float *xs, const uint8_t *W6, cons
                      int64_t K, void *Y, int64_t ldy, int out_i32, hipStream_t st)
 {
     const int tiles_m = (int)((M + FM * 16 - 1) / (FM * 16)), tiles_n = (int)((N + FN * 16 - 1) / (FN * 16));
-    hipLaunchKernelGGL((gemm_f6_stream_kernel<FM, FN, NW, D>), dim3((unsigned)((tiles_m * tiles_n + 7) / 8 * 8)), dim3(NW * 64), 0, st,
+    // Paired tails take L1 lookups away, and a few registers.  They gain where several rows of tiles read the same weights
+    // (240 shapes, M 17 .. 334: 1 .. 5 % per tile, up to 12 %); with one row, or two of the wide tiles, memory bounds the launch
+    // (63 x 11040 x 2048, from HBM, 7.9 -> 8.5 us with pairs; 70 x 8048 x 8192 11.9 -> 12.4).  32 x 64 grows from 128 registers to 155, so one workgroup
+    // fits a CU instead of two: there only while every workgroup has a CU to itself (84 x 10464 x 2048, 492 of them, 6.9 ->
+    // 8.1; 128 x 4096 x 14336, 256 of them, 14.5 -> 14.2, weights from HBM 19.9 -> 18.6).
+    constexpr bool CAN_PAIR = FM > 1 || FN > 1;
+    const bool pairs = CAN_PAIR && 2 * tiles_m > FN && (FM * FN != 8 || tiles_m * tiles_n <= 256);
+    const auto kern = pairs ? gemm_f6_stream_kernel<FM, FN, NW, D, CAN_PAIR> : gemm_f6_stream_kernel<FM, FN, NW, D, false>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)((tiles_m * tiles_n + 7) / 8 * 8)), dim3(NW * 64), 0, st,
                        X6, xs, W6, ws, (int)M, (int)N, (int)K, Y, ldy, out_i32, tiles_m, tiles_n);
     return hipGetLastError();
 }

@@ -52,3 +52,11 @@ def test_several_tiles_per_workgroup(gpu, tune, config, M, N, K):
     tune(gpu.SR_TUNE_GEMM_TILE, config)
     tune(gpu.SR_TUNE_GEMM_GRID, 8)
     compare(gpu, M, N, K)
+
+
+# 32 x 64 fetches its 8-byte tails for two fragments at a time up to 256 tiles in several rows, else each by itself
+@pytest.mark.parametrize("M,N,K", [(130, 3312, 384), (130, 3216, 1152), (33, 8176, 2176), (32, 8176, 2176)])
+def test_paired_tails_and_single_ones(gpu, tune, M, N, K):
+    print("case", M, N, K, flush=True)
+    tune(gpu.SR_TUNE_GEMM_TILE, 32064)
+    compare(gpu, M, N, K)
