@@ -66,12 +66,17 @@ constexpr int ROWB = 128;  // packed bytes per row per stage (256 codes = one 12
 //
 // KS = 2: two sets of waves share a tile, each multiplying half of every stage (the 64-code sub-steps 2 kw, 2 kw + 1),
 // and add their sums through LDS at the end, each finishing half of the channels.
-template <int BM, int BN, int WGM, int WGN, int KS = 1>
+//
+// RUNS: the grid of tiles is cut into runs (kXcdRuns), of which the kernel for grids that divide knows nothing: one kernel for
+// both took registers and start-up from the latter (600 x 6144 x 4096 18.0 -> 18.2 us).
+template <int BM, int BN, int WGM, int WGN, int KS, bool RUNS>
 __global__ __launch_bounds__(WGM * WGN * KS * 64) void gemm_w4a4_kernel(
     const uint8_t *__restrict__ Xq, const float *__restrict__ xs, const uint8_t *__restrict__ Wq,
     const float *__restrict__ ws, int M, int N, int K, void *__restrict__ Yv, int64_t ldy, int out_i32,
-    int tiles_m, int tiles_n, int xcd_m)
+    int tiles_m, int tiles_n, int xcd_split)
 {
+    const int xcd_m = RUNS ? kXcdRuns : xcd_split;
+    if constexpr (!RUNS) __builtin_assume(xcd_m != kXcdRuns);
     static_assert(KS == 1 || KS == 2, "waves per tile position");
     constexpr int NWAVE = WGM * WGN * KS;
     constexpr int SLOTS = KS == 2 ? 4 : 2;           // ring stages of LDS
@@ -379,15 +384,16 @@ template <int BM, int BN, int WGM, int WGN, int WG_PER_CU, int KS = 1>
 hipError_t launch_tile(const uint8_t *Xq, const float *xs, const uint8_t *Wq, const float *ws, int64_t M, int64_t N,
                        int64_t K, void *Y, int64_t ldy, int out_i32, hipStream_t st)
 {
-    constexpr auto kern = gemm_w4a4_kernel<BM, BN, WGM, WGN, KS>;
+    constexpr auto divided = gemm_w4a4_kernel<BM, BN, WGM, WGN, KS, false>, runs = gemm_w4a4_kernel<BM, BN, WGM, WGN, KS, true>;
     constexpr int lds = 2 * KS * (BM + BN) * ROWB;
     static_assert(lds * WG_PER_CU <= 160 * 1024, "LDS");
-    if (lds > 48 * 1024) {
-        hipError_t e = allow_dynamic_lds<kern>(lds);
-        if (e != hipSuccess) return e;
-    }
     const int tiles_m = (int)((M + BM - 1) / BM), tiles_n = (int)((N + BN - 1) / BN);
     const int xcd_m = choose_xcd_split(tiles_m, tiles_n, BM, BN);
+    const auto kern = xcd_m == kXcdRuns ? runs : divided;
+    if (lds > 48 * 1024) {
+        hipError_t e = xcd_m == kXcdRuns ? allow_dynamic_lds<runs>(lds) : allow_dynamic_lds<divided>(lds);
+        if (e != hipSuccess) return e;
+    }
     // persistent grid: as many workgroups as the chip holds at once (a multiple of 8, as the XCD map needs)
     int64_t grid = (int64_t)compute_units() * WG_PER_CU;
     if (int64_t g; tuned(kTuneGemmGrid, g) && g > 0) grid = g / 8 * 8;
