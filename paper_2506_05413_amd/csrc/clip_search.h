@@ -105,8 +105,7 @@ __device__ __forceinline__ float search_ratio(Read8 read, const float amax, cons
 // smallest error it is search_ratio's as well; else (about 2 % of normal rows) the caller runs search_ratio.
 //
 // Bound by the LDS atomics (a wave's 64 cells fall on random banks); search_ratio needs 105 vector instructions per value for
-// 21 ratios, this 9.  4096 x 14336, 21 ratios, whole kernel: 190 -> 92 us (85 with the rotation of
-// fold_search.hip).
+// 21 ratios, this 9.  4096 x 14336, 21 ratios, whole kernel: 190 -> 92 us (85 with the rotation of fold_search.hip).
 // ------------------------------------------------------------------------------------------
 constexpr int kMaxClipDenominator = 100;
 // the smallest q <= kMaxClipDenominator of which every ratio is a multiple of 1 / q, to the last bit of a float; 0: none

@@ -5,8 +5,8 @@
 // projection, section "Methodology" and Eq. (1); this is the decode step, where a launch and a
 // round trip through memory cost as much as the arithmetic.)
 //
-// One token (several: see linear_decode_rows_kernel): a workgroup owns 8 G output channels over all of K.  It first ISSUES the loads of its token row
-// and smoothing factors, then of all its weights (they stay in flight in registers), then rotates
+// One token (several: see linear_decode_rows_kernel): a workgroup owns 8 G output channels over
+// all of K.  It first ISSUES the loads of its token row and smoothing factors, then of all its weights (they stay in flight in registers), then rotates
 // and quantises the row in LDS while the weights travel, and finally multiplies packed codes with
 // v_dot8_i32_i4 straight from the registers against the codes in LDS.  Every workgroup repeats
 // the rotation, so the grid is kept near one workgroup per CU; and only power-of-two K up to 8192
