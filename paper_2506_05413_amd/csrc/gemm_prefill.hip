@@ -93,6 +93,7 @@ __global__ __launch_bounds__(WGM * WGN * KS * 64) void gemm_w4a4_kernel(
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave % WGM, wn = wave / WGM % WGN, kw = wave / (WGM * WGN);
+    const int total = tiles_m * tiles_n;
 
     // workgroups are dealt round-robin to the 8 XCDs; with the XCD split on, the grid size is a multiple of 8,
     // so a workgroup's later tiles stay in its XCD's rectangle
@@ -249,7 +250,8 @@ __global__ __launch_bounds__(WGM * WGN * KS * 64) void gemm_w4a4_kernel(
 
     int v = blockIdx.x;
     int m0, n0;
-    if (!tile_exists(v, tiles_m, tiles_n, xcd_m)) return;      // the whole workgroup
+    if constexpr (RUNS)                              // (a divided grid has a tile for every workgroup)
+        if (!tile_exists(v, tiles_m, tiles_n, xcd_m)) return;      // the whole workgroup
     tile_origin(v, m0, n0);
     set_sources(m0, n0);
 #pragma unroll
@@ -307,7 +309,7 @@ __global__ __launch_bounds__(WGM * WGN * KS * 64) void gemm_w4a4_kernel(
 
         // ---- tile boundary
         const int vn = v + (int)gridDim.x;
-        const bool more = tile_exists(vn, tiles_m, tiles_n, xcd_m);
+        const bool more = RUNS ? tile_exists(vn, tiles_m, tiles_n, xcd_m) : vn < total;
         wait_vmcnt<0>();                             // no LDS-DMA write is in flight any more ...
         // (the scales arrived long ago; naming them here keeps the compiler's own wait for them at this point
         // and not behind the loads issued next)
