@@ -151,6 +151,44 @@ __device__ __forceinline__ void count_value(uint64_t *cells, const CellScale &s,
     __hip_atomic_fetch_add(cells + (y < 0.f ? neg : pos) - cell, one, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
+// One large value among small ones (weights of one sign, of equal size, ..): at most half of the waves have a value of amax / 19
+// (red: their maxima).  Where the large value does not decide between the ratios, hardly another does: nearly every such row
+// needs search_ratio behind the count, and its small values meet in a few cells, so it goes to search_ratio at once.  4096
+// channels of weights between -0.05 and 0, 21 ratios, us a call, K = 2048, 4096, 8192, 14336: 75, 103, 192, 358 with the count in
+// front, 59, 79, 143, 257 without (50, 70, 131, 256 in fwht_quant_search_kernel, which has the whole LDS for its rows).
+// The line: rows of one value among normally distributed ones, 21 ratios 0.025 apart, leave two ratios or more up to a standard
+// deviation of 0.014 .. 0.016 amax, where a wave's largest value is 0.048 .. 0.055 amax, and one ratio beyond.
+template <int NT> __device__ __forceinline__ bool spiked(const float *red, const float amax)
+{
+    int reach = 0;
+#pragma unroll
+    for (int w = 0; w < NT / 64; ++w) reach += red[w] >= amax * (1.f / 19.f);
+    return 2 * reach <= NT / 64;
+}
+// The signs of the large value (1: positive, 2: negative) with which it does not decide: the errors it has itself (code 7 at
+// most, -8 at least), more than one of them within the margin of ratio_of_cells.
+int undecided_signs(const float *grid, int n, int K)
+{
+    int signs = 0;
+    for (int negative = 0; negative < 2; ++negative) {
+        double err[kMaxClipGrid], best = 1.0;
+        for (int i = 0; i < n; ++i) {
+            const double step = grid[i] / 7.0, code = (double)(int)(1.0 / step + 0.5), most = 7 + negative;
+            const double r = 1.0 - step * (code < most ? code : most);
+            err[i] = r * r;
+            if (err[i] < best) best = err[i];
+        }
+        int near = 0;
+        for (int i = 0; i < n; ++i) near += err[i] <= best + K * (0x1p-16 / 196.0);
+        signs |= (near > 1) << negative;
+    }
+    return signs;
+}
+__device__ __forceinline__ void note_sign(int *signs, float y, float amax, bool flipped)
+{
+    if (fabsf(y) == amax) __hip_atomic_fetch_or(signs, (y < 0.f) != flipped ? 2 : 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
 // `cells`: histogram_run(NT, q) * NT words in which a row of K values has been counted (visible to the workgroup).  Returns
 // the index of the ratio, or -1 where more than one comes into question, to every thread.
 template <int K, int NT>

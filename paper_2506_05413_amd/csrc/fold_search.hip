@@ -15,13 +15,15 @@ template <int K>
 __global__ __launch_bounds__((TwoPass<K>::NT)) void fold_search_kernel(const __half *__restrict__ Wt, int64_t ldw,
                                                                        const float *__restrict__ s, float post_scale,
                                                                        uint8_t *__restrict__ Q, float *__restrict__ scale_out,
-                                                                       const RowExtras ex, const int q)
+                                                                       const RowExtras ex, const int q, const int undecided)
 {
     using S = TwoPass<K>;
     constexpr int NT = S::NT;
     constexpr uint32_t ALL = 0xFFFFFFFFu;
+    static_assert(NT == S::COLS, "every thread holds values after the rotation");
     extern __shared__ __attribute__((aligned(16))) float row[];
     __shared__ float red[NT / 64];
+    __shared__ int signs;                                // of the values of magnitude amax
     void *const scratch = row + S::LEN;                  // the cells, or partial errors of search_ratio
     uint64_t *const cells = static_cast<uint64_t *>(scratch);
     const int t = threadIdx.x;
@@ -29,6 +31,7 @@ __global__ __launch_bounds__((TwoPass<K>::NT)) void fold_search_kernel(const __h
     RowLoad<K, NT> ld;
     row_load<K, NT, false, false, 5>(Wt + m * ldw, s, t, ld);
     for (int e = 0; e < histogram_run(NT, q); ++e) cells[t + e * NT] = 0;      // visible after the rotation's barriers
+    if (t == 0) signs = 0;
     float o[S::R];
     const float amax = two_pass_rotate<S, K, true, false, false, true>(ld, row, red, t, ALL, o, NoHook{});
     if (!(amax > 0.f && amax < __builtin_inff())) {
@@ -42,34 +45,54 @@ __global__ __launch_bounds__((TwoPass<K>::NT)) void fold_search_kernel(const __h
         quantise_padded_row_nibbles<K, NT>(row, 1.f / delta, Q + m * (int64_t)(K / 2), t);
         return;
     }
-    int i = -1;
+    const bool f = S::flipped(S::first(t) >> 4);         // the sign that all values of a thread carry
     // (beyond this range the scaled values would not stay inside fp32)
-    if (amax > 0x1p-90f && amax < 0x1p90f) {
-        if (NT == S::COLS || t < S::COLS) {
-            const CellScale scale(q, amax);
-            const bool f = S::flipped(S::first(t) >> 4);               // the same for all values of a thread
-            const int neg = f ? 28 * q + 1 : 14 * q, pos = f ? 14 * q : 28 * q + 1;
+    bool count = amax > 0x1p-90f && amax < 0x1p90f;
+    if (count && undecided && spiked<NT>(red, amax)) {
+        if (undecided != 3) {
 #pragma unroll
-            for (int r = 0; r < S::R; ++r) count_value(cells, scale, neg, pos, o[r]);
+            for (int r = 0; r < S::R; ++r) note_sign(&signs, o[r], amax, f);
+            __syncthreads();
         }
+        count = undecided != 3 && (signs & undecided) == 0;
+    }
+    int i = -1;
+    if (count) {
+        const CellScale scale(q, amax);
+        const int neg = f ? 28 * q + 1 : 14 * q, pos = f ? 14 * q : 28 * q + 1;
+#pragma unroll
+        for (int r = 0; r < S::R; ++r) count_value(cells, scale, neg, pos, o[r]);
         __syncthreads();
         i = ratio_of_cells<K, NT>(ex.grid, ex.n_grid, q, cells, t);
     }
-    auto read8 = [&](int g, float4 &a, float4 &b) {
-        const float *src = row + S::pos(8 * g);
-        a = *reinterpret_cast<const float4 *>(src);
-        b = *reinterpret_cast<const float4 *>(src + 4);
-        if (S::flipped(g >> 1)) {
-            a = make_float4(-a.x, -a.y, -a.z, -a.w);
-            b = make_float4(-b.x, -b.y, -b.z, -b.w);
+    float clip;
+    uint32_t flips = ALL;
+    if (i >= 0) {
+        clip = ex.grid[i];
+    } else {
+        // the signs are put right once (undone at every read they cost the search a quarter more instructions)
+#pragma unroll
+        for (int e = 0; e < S::NG; ++e) {
+            const int g = t + e * NT;
+            if ((K / 16 % NT == 0 || g < K / 16) && S::flipped(g)) {
+                float4 *v = reinterpret_cast<float4 *>(row + S::pos(16 * g));
+#pragma unroll
+                for (int c = 0; c < 4; ++c) v[c] = make_float4(-v[c].x, -v[c].y, -v[c].z, -v[c].w);
+            }
         }
-    };
-    const float clip = i >= 0 ? ex.grid[i]
-                              : search_ratio<K, NT>(read8, amax, ex.grid, ex.n_grid, t, static_cast<double (*)[kMaxClipGrid]>(scratch));
+        flips = 0;
+        __syncthreads();
+        auto read8 = [&](int g, float4 &a, float4 &b) {
+            const float *src = row + S::pos(8 * g);
+            a = *reinterpret_cast<const float4 *>(src);
+            b = *reinterpret_cast<const float4 *>(src + 4);
+        };
+        clip = search_ratio<K, NT>(read8, amax, ex.grid, ex.n_grid, t, static_cast<double (*)[kMaxClipGrid]>(scratch));
+    }
     if (ex.ratio_out && t == 0) ex.ratio_out[m] = clip;
     const float delta = (clip * amax) / 7.f;
     if (t == 0) scale_out[m] = delta * post_scale;
-    quantise_row_nibbles<S, K>(row, 1.f / delta, ALL, Q + m * (int64_t)(K / 2), t);
+    quantise_row_nibbles<S, K>(row, 1.f / delta, flips, Q + m * (int64_t)(K / 2), t);
 }
 
 template <int K>
@@ -85,7 +108,7 @@ hipError_t launch(const void *Wt, int64_t rows, int64_t ldw, const float *s, flo
         if (hipError_t e = allow_dynamic_lds<kern>(row_bytes + most); e != hipSuccess) return e;
     const int cells = histogram_run(S::NT, q) * S::NT * 8;
     hipLaunchKernelGGL(kern, dim3((unsigned)rows), dim3(S::NT), row_bytes + (cells > search ? cells : search), st,
-                       static_cast<const __half *>(Wt), ldw, s, post_scale, Q, scale_out, ex, q);
+                       static_cast<const __half *>(Wt), ldw, s, post_scale, Q, scale_out, ex, q, undecided_signs(ex.grid, ex.n_grid, K));
     return hipGetLastError();
 }
 

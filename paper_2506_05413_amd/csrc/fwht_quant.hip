@@ -105,16 +105,18 @@ template <int K, int NT, bool HIST>
 __global__ __launch_bounds__(NT) void fwht_quant_search_kernel(const __half *__restrict__ X, int64_t ldx,
                                                                const float *__restrict__ pre, float post_scale,
                                                                uint8_t *__restrict__ Q, float *__restrict__ scale_out,
-                                                               const RowExtras ex, const int q)
+                                                               const RowExtras ex, const int q, const int undecided)
 {
     extern __shared__ __attribute__((aligned(16))) float row[];
     __shared__ float red[NT / 64];
+    __shared__ int signs;                                // of the values of magnitude amax
     void *const scratch = row + padded_len(K);           // the cells, or partial errors of search_ratio
     const int t = threadIdx.x;
     const int64_t m = blockIdx.x;
     if constexpr (HIST) {                                // visible after the rotation's barriers
         uint64_t *const cells = static_cast<uint64_t *>(scratch);
         for (int e = 0; e < histogram_run(NT, q); ++e) cells[t + e * NT] = 0;
+        if (t == 0) signs = 0;
     }
     const float amax = rotate_row_absmax<K, NT, true>(X + m * ldx, pre, row, red, t);
     const RowRead8 read8{row};
@@ -123,7 +125,15 @@ __global__ __launch_bounds__(NT) void fwht_quant_search_kernel(const __half *__r
         int i = -1;
         if constexpr (HIST) {
             // (beyond this range the scaled values would not stay inside fp32; the largest being finite, all values are)
-            if (amax > 0x1p-90f && amax < 0x1p90f) {
+            bool count = amax > 0x1p-90f && amax < 0x1p90f;
+            if (count && undecided && spiked<NT>(red, amax)) {
+                if (undecided != 3) {
+                    for (int c = t; c < K; c += NT) note_sign(&signs, row[pad(c)], amax, false);
+                    __syncthreads();
+                }
+                count = undecided != 3 && (signs & undecided) == 0;
+            }
+            if (count) {
                 uint64_t *const cells = static_cast<uint64_t *>(scratch);
                 const CellScale scale(q, amax);
                 for (int c = t; c < K / 4; c += NT) {
@@ -566,7 +576,7 @@ hipError_t launch_search(const void *X, int64_t rows, int64_t ldx, const float *
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL(kern, dim3((unsigned)rows), dim3(NT), row_bytes + (cells > search_scratch_bytes(NT) ? cells : search_scratch_bytes(NT)), st,
-                       static_cast<const __half *>(X), ldx, pre, post_scale, Q, scale_out, ex, q);
+                       static_cast<const __half *>(X), ldx, pre, post_scale, Q, scale_out, ex, q, HIST ? undecided_signs(ex.grid, ex.n_grid, K) : 0);
     return hipGetLastError();
 }
 

@@ -1,0 +1,60 @@
+"""Searched folds of weights whose rotated rows hold one large value and many small ones (all weights of one sign, or equal):
+hardly any value decides between the ratios, so nearly every row needs a sum per ratio, and counting its values first would be
+in vain.  Same ratios, codes and scales as from the sums alone, and not much dearer than those."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+def weights(kind, K, N):
+    rng = np.random.default_rng(K + N)
+    if kind == "equal":
+        W = np.full((K, N), 0.02)
+    elif kind == "noise":
+        W = 0.02 + 2e-4 * rng.standard_normal((K, N))
+    else:
+        W = 0.05 * rng.random((K, N))
+    W[:, 1::2] *= -1
+    return torch.from_numpy(wl.to_f16_sat(W.astype(np.float32))).cuda()
+
+
+def microseconds(f):
+    f()
+    runs = []
+    for _ in range(7):
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        a.record()
+        for _ in range(4):
+            f()
+        b.record()
+        torch.cuda.synchronize()
+        runs.append(a.elapsed_time(b) * 250)
+    return float(np.median(runs))
+
+
+# 21 ratios 0.025 apart share a fraction; with 0.499 as the last they do not, and every row takes a sum per ratio.  With the count
+# in front of the sums these calls took 1.34 .. 1.8 times as long; without it 1.0 .. 1.2 (the other kernel's rotation and LDS).
+@pytest.mark.parametrize("kind", ["equal", "noise", "uniform"])
+@pytest.mark.parametrize("K,N", [(2048, 4096), (4096, 4096), (8192, 4096), (14336, 2048), (16384, 2048), (28672, 2048)])
+def test_time(gpu, K, N, kind):
+    W = weights(kind, K, N)
+    work = torch.empty(gpu.sr_fold_workspace_bytes(K, N), dtype=torch.uint8, device="cuda")
+    both, sums = (microseconds(lambda lo=lo: gpu.sr_fold_smooth_rotate_quant_ex(W, None, 0.5, 0, False, 21, lo, workspace=work)) for lo in (0.5, 0.499))
+    print("case clustered", K, N, kind, "%.1f %.1f us" % (both, sums), flush=True)
+    assert both < 1.28 * sums
+
+
+@pytest.mark.parametrize("kind", ["equal", "noise", "uniform"])
+@pytest.mark.parametrize("K,N", [(2048, 32), (4096, 32), (8192, 32), (16384, 16)])
+def test_bits(gpu, K, N, kind):
+    print("case clustered bits", K, N, kind, flush=True)
+    W = weights(kind, K, N)
+    for steps, lo in ((21, 0.5), (32, 0.69), (2, 0.9)):
+        full = gpu.sr_fold_smooth_rotate_quant_ex(W, None, 0.5, 0, False, steps, lo)
+        head = gpu.sr_fold_smooth_rotate_quant_ex(W, None, 0.5, 1, False, steps, lo)
+        for name, x, y in zip(("codes", "scales", "1/s", "ratios"), full, head):
+            assert torch.equal(x, y), name
