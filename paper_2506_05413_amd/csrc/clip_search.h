@@ -107,20 +107,6 @@ __device__ __forceinline__ float search_ratio(Read8 read, const float amax, cons
 // Bound by the LDS atomics (a wave's 64 cells fall on random banks); search_ratio needs 105 vector instructions per value for
 // 21 ratios, this 9.  4096 x 14336, 21 ratios, whole kernel: 190 -> 92 us (85 with the rotation of fold_search.hip).
 // ------------------------------------------------------------------------------------------
-constexpr int kMaxClipDenominator = 100;
-// the smallest q <= kMaxClipDenominator of which every ratio is a multiple of 1 / q, to the last bit of a float; 0: none
-int clip_grid_denominator(const float *grid, int n)
-{
-    for (int q = 1; q <= kMaxClipDenominator; ++q) {
-        bool all = true;
-        for (int i = 0; i < n && all; ++i) {
-            const double a = (double)grid[i] * q, r = (double)(int64_t)(a + 0.5);
-            all = r >= 1.0 && a - r <= q * 0x1p-24 && r - a <= q * 0x1p-24;
-        }
-        if (all) return q;
-    }
-    return 0;
-}
 // cells per thread: 14 q + 1 for either sign, dealt to the threads in runs
 constexpr int histogram_run(int NT, int q) { return (2 * (14 * q + 1) + NT - 1) / NT; }
 
@@ -165,25 +151,7 @@ template <int NT> __device__ __forceinline__ bool spiked(const float *red, const
     for (int w = 0; w < NT / 64; ++w) reach += red[w] >= amax * (1.f / 19.f);
     return 2 * reach <= NT / 64;
 }
-// The signs of the large value (1: positive, 2: negative) with which it does not decide: the errors it has itself (code 7 at
-// most, -8 at least), more than one of them within the margin of ratio_of_cells.
-int undecided_signs(const float *grid, int n, int K)
-{
-    int signs = 0;
-    for (int negative = 0; negative < 2; ++negative) {
-        double err[kMaxClipGrid], best = 1.0;
-        for (int i = 0; i < n; ++i) {
-            const double step = grid[i] / 7.0, code = (double)(int)(1.0 / step + 0.5), most = 7 + negative;
-            const double r = 1.0 - step * (code < most ? code : most);
-            err[i] = r * r;
-            if (err[i] < best) best = err[i];
-        }
-        int near = 0;
-        for (int i = 0; i < n; ++i) near += err[i] <= best + K * (0x1p-16 / 196.0);
-        signs |= (near > 1) << negative;
-    }
-    return signs;
-}
+// note_sign: 1 for a positive, 2 for a negative value of magnitude amax (see undecided_signs).
 __device__ __forceinline__ void note_sign(int *signs, float y, float amax, bool flipped)
 {
     if (fabsf(y) == amax) __hip_atomic_fetch_or(signs, (y < 0.f) != flipped ? 2 : 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);

@@ -8,6 +8,8 @@
 #include <stddef.h>
 #include <atomic>
 
+#include "clip_grid.h"
+
 namespace sr {
 
 // ---- Hadamard order helpers (host) ------------------------------------------------
@@ -122,7 +124,6 @@ hipError_t launch_fwht_two_pass_heads(const void *X_f16, int64_t rows, int64_t K
                                       float post_scale, uint8_t *Q, float *scale_out, uint32_t had_mask, hipStream_t st);
 
 // Optional extras of the row kernel (see fwht_quant.hip).
-constexpr int kMaxClipGrid = 32;
 struct RowExtras {
     const __half *gate = nullptr;   // x = silu(gate) * X when set; row stride ldg elements
     int64_t ldg = 0;

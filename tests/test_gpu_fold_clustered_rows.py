@@ -53,7 +53,7 @@ def test_time(gpu, K, N, kind):
 def test_bits(gpu, K, N, kind):
     print("case clustered bits", K, N, kind, flush=True)
     W = weights(kind, K, N)
-    for steps, lo in ((21, 0.5), (32, 0.69), (2, 0.9)):
+    for steps, lo in ((21, 0.5), (32, 0.69), (2, 0.9), (5, 1.0)):
         full = gpu.sr_fold_smooth_rotate_quant_ex(W, None, 0.5, 0, False, steps, lo)
         head = gpu.sr_fold_smooth_rotate_quant_ex(W, None, 0.5, 1, False, steps, lo)
         for name, x, y in zip(("codes", "scales", "1/s", "ratios"), full, head):
