@@ -107,8 +107,26 @@ __device__ __forceinline__ float search_ratio(Read8 read, const float amax, cons
 // Bound by the LDS atomics (a wave's 64 cells fall on random banks); search_ratio needs 105 vector instructions per value for
 // 21 ratios, this 9.  4096 x 14336, 21 ratios, whole kernel: 190 -> 92 us (85 with the rotation of fold_search.hip).
 // ------------------------------------------------------------------------------------------
-// cells per thread: 14 q + 1 for either sign, dealt to the threads in runs
-constexpr int histogram_run(int NT, int q) { return (2 * (14 * q + 1) + NT - 1) / NT; }
+// 14 q + 1 cells for either sign, dealt to the threads in runs.  LDS for them: whole runs, so that no thread need know where the
+// cells end, or (from 8192 on, where the rows leave little) the cells alone: 14336 values and q = 56 .. 70 then run in two
+// workgroups per CU instead of one, 174 us against 124.  Not runs of 8 or 16 cells, with which a wave's reads fall on one bank in 16
+// or 32 (6 ratios 1 / 70 apart: 4096 x 2048 73 -> 38 us a call, 4096 x 4096 59 -> 45), nor, from 8192 on, of any even number.
+constexpr int histogram_cells(int q) { return 2 * (14 * q + 1); }
+constexpr bool histogram_trimmed(int K) { return K >= 8192; }
+constexpr int histogram_run(int K, int NT, int q)
+{
+    const int run = (histogram_cells(q) + NT - 1) / NT;
+    return histogram_trimmed(K) ? run | 1 : run % 8 ? run : run + 1;
+}
+constexpr int histogram_words(int K, int NT, int q) { return histogram_trimmed(K) ? histogram_cells(q) : histogram_run(K, NT, q) * NT; }
+template <int K, int NT> __device__ __forceinline__ void clear_cells(uint64_t *cells, const int q, const int t)
+{
+    if constexpr (histogram_trimmed(K)) {
+        for (int c = t; c < histogram_cells(q); c += NT) cells[c] = 0;
+    } else {
+        for (int e = 0; e < histogram_run(K, NT, q); ++e) cells[t + e * NT] = 0;
+    }
+}
 
 template <int CTRL, int ROW_MASK> __device__ __forceinline__ uint64_t add_shifted(uint64_t v)   // v + the permuted lane's v (0 where there is none)
 {
@@ -157,7 +175,7 @@ __device__ __forceinline__ void note_sign(int *signs, float y, float amax, bool 
     if (fabsf(y) == amax) __hip_atomic_fetch_or(signs, (y < 0.f) != flipped ? 2 : 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// `cells`: histogram_run(NT, q) * NT words in which a row of K values has been counted (visible to the workgroup).  Returns
+// `cells`: histogram_words(K, NT, q) words in which a row of K values has been counted (visible to the workgroup).  Returns
 // the index of the ratio, or -1 where more than one comes into question, to every thread.
 template <int K, int NT>
 __device__ __forceinline__ int ratio_of_cells(const float *grid, const int n, const int q, uint64_t *cells, const int t)
@@ -170,9 +188,12 @@ __device__ __forceinline__ int ratio_of_cells(const float *grid, const int n, co
     const int lane = t & 63, top = 14 * q;
 
     // ---- inclusive prefix sums over all words
-    const int run = histogram_run(NT, q);
+    const int run = histogram_run(K, NT, q);
+    uint64_t *const own = cells + t * run;
+    int len = run;
+    if constexpr (histogram_trimmed(K)) len = t * run + run > histogram_cells(q) ? histogram_cells(q) - t * run : run;      // (none: < 1)
     uint64_t sum = 0;
-    for (int e = 0; e < run; ++e) sum += cells[t * run + e];
+    for (int e = 0; e < len; ++e) sum += own[e];
     uint64_t upto = add_shifted<0x111, 0xF>(sum);        // row_shr 1, 2, 4, 8, then the rows before
     upto = add_shifted<0x112, 0xF>(upto);
     upto = add_shifted<0x114, 0xF>(upto);
@@ -184,9 +205,9 @@ __device__ __forceinline__ int ratio_of_cells(const float *grid, const int n, co
     {
         uint64_t acc = upto - sum;
         for (int w = 0; w < NW; ++w) acc += w < (t >> 6) ? wave_sum[w] : 0;
-        for (int e = 0; e < run; ++e) {
-            acc += cells[t * run + e];
-            cells[t * run + e] = acc;
+        for (int e = 0; e < len; ++e) {
+            acc += own[e];
+            own[e] = acc;
         }
     }
     __syncthreads();

@@ -30,7 +30,7 @@ __global__ __launch_bounds__((TwoPass<K>::NT)) void fold_search_kernel(const __h
     const int64_t m = blockIdx.x;
     RowLoad<K, NT> ld;
     row_load<K, NT, false, false, 5>(Wt + m * ldw, s, t, ld);
-    for (int e = 0; e < histogram_run(NT, q); ++e) cells[t + e * NT] = 0;      // visible after the rotation's barriers
+    clear_cells<K, NT>(cells, q, t);                     // visible after the rotation's barriers
     if (t == 0) signs = 0;
     float o[S::R];
     const float amax = two_pass_rotate<S, K, true, false, false, true>(ld, row, red, t, ALL, o, NoHook{});
@@ -102,11 +102,11 @@ hipError_t launch(const void *Wt, int64_t rows, int64_t ldw, const float *s, flo
     using S = TwoPass<K>;
     constexpr auto kern = fold_search_kernel<K>;
     constexpr int row_bytes = S::LEN * (int)sizeof(float), search = search_scratch_bytes(S::NT);
-    constexpr int most = histogram_run(S::NT, kMaxClipDenominator) * S::NT * 8;
+    constexpr int most = histogram_words(K, S::NT, kMaxClipDenominator) * 8;
     static_assert(most >= search && row_bytes + most + 1024 <= 160 * 1024, "LDS");
     if constexpr (row_bytes + most > 40 * 1024)
         if (hipError_t e = allow_dynamic_lds<kern>(row_bytes + most); e != hipSuccess) return e;
-    const int cells = histogram_run(S::NT, q) * S::NT * 8;
+    const int cells = histogram_words(K, S::NT, q) * 8;
     hipLaunchKernelGGL(kern, dim3((unsigned)rows), dim3(S::NT), row_bytes + (cells > search ? cells : search), st,
                        static_cast<const __half *>(Wt), ldw, s, post_scale, Q, scale_out, ex, q, undecided_signs(ex.grid, ex.n_grid, K));
     return hipGetLastError();
@@ -118,7 +118,11 @@ hipError_t launch_fold_search(const void *Wt, int64_t rows, int64_t K, int64_t l
                               uint8_t *Q, float *scale_out, const RowExtras &ex, hipStream_t st, bool &taken)
 {
     const int q = clip_grid_denominator(ex.grid, ex.n_grid);
-    taken = q > 0 && s;
+    // Fine fractions: the cells take the LDS of other rows, and a sum for each of a few ratios is done sooner (us a call, 4096 channels,
+    // sums against counts: 2048, 11 ratios 0.01 apart 39 / 42, 16 42 / 42; 4096, 2 48 / 49; 14336, 2 165 / 177, 8 168 / 177, 10 184 /
+    // 177; but 8192, 2 113 / 84; q = 70: 2048, 6 36 / 36, 14336, 6 166 / 127)
+    const int sums_up_to = q <= 70 ? 0 : K == 2048 ? 11 : K == 4096 ? 3 : K == 14336 ? 8 : 0;
+    taken = q > 0 && s && ex.n_grid > sums_up_to;
     if (!taken) return hipSuccess;
     switch (K) {
         case 2048: return launch<2048>(Wt, rows, ldw, s, post_scale, Q, scale_out, ex, q, st);

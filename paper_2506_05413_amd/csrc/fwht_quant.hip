@@ -114,8 +114,7 @@ __global__ __launch_bounds__(NT) void fwht_quant_search_kernel(const __half *__r
     const int t = threadIdx.x;
     const int64_t m = blockIdx.x;
     if constexpr (HIST) {                                // visible after the rotation's barriers
-        uint64_t *const cells = static_cast<uint64_t *>(scratch);
-        for (int e = 0; e < histogram_run(NT, q); ++e) cells[t + e * NT] = 0;
+        clear_cells<K, NT>(static_cast<uint64_t *>(scratch), q, t);
         if (t == 0) signs = 0;
     }
     const float amax = rotate_row_absmax<K, NT, true>(X + m * ldx, pre, row, red, t);
@@ -567,10 +566,10 @@ hipError_t launch_search(const void *X, int64_t rows, int64_t ldx, const float *
                          const RowExtras &ex, int q, hipStream_t st)
 {
     constexpr auto kern = fwht_quant_search_kernel<K, NT, HIST>;
-    constexpr int row_bytes = (int)sizeof(float) * padded_len(K), most = HIST ? histogram_run(NT, kMaxClipDenominator) * NT * 8 : 0;
+    constexpr int row_bytes = (int)sizeof(float) * padded_len(K), most = HIST ? histogram_words(K, NT, kMaxClipDenominator) * 8 : 0;
     constexpr int lds_most = row_bytes + (most > search_scratch_bytes(NT) ? most : search_scratch_bytes(NT));
     static_assert(lds_most + 1024 <= 160 * 1024, "LDS");
-    const int cells = HIST ? histogram_run(NT, q) * NT * 8 : 0;
+    const int cells = HIST ? histogram_words(K, NT, q) * 8 : 0;
     if (lds_most > 40 * 1024) {
         hipError_t e = allow_dynamic_lds<kern>(lds_most);
         if (e != hipSuccess) return e;

@@ -1,6 +1,7 @@
-"""Searched folds of weights whose rotated rows hold one large value and many small ones (all weights of one sign, or equal):
+"""Searched folds that count in vain or at a loss.  Weights whose rotated rows hold one large value and many small ones (all weights of one sign, or equal):
 hardly any value decides between the ratios, so nearly every row needs a sum per ratio, and counting its values first would be
-in vain.  Same ratios, codes and scales as from the sums alone, and not much dearer than those."""
+in vain.  Ratios that are multiples of a fine fraction only: many cells, some numbers of them at odds with the LDS banks.  Same
+ratios, codes and scales as from the sums alone, and not much dearer than those."""
 import numpy as np
 import pytest
 import torch
@@ -58,3 +59,26 @@ def test_bits(gpu, K, N, kind):
         head = gpu.sr_fold_smooth_rotate_quant_ex(W, None, 0.5, 1, False, steps, lo)
         for name, x, y in zip(("codes", "scales", "1/s", "ratios"), full, head):
             assert torch.equal(x, y), name
+
+
+# (of the counts that these grids need, the two at 1 / 70 and 1 / 64 took 2.0 and 1.2 times as long as the sums)
+@pytest.mark.parametrize("K,N,steps,q", [(2048, 4096, 6, 70), (4096, 4096, 6, 64), (8192, 4096, 6, 70), (14336, 2048, 6, 70), (16384, 2048, 6, 70),
+                                         (2048, 4096, 11, 100), (14336, 2048, 2, 100)])
+def test_time_of_fine_fractions(gpu, K, N, steps, q):
+    W = 0.02 * torch.randn((K, N), generator=torch.Generator(device="cuda").manual_seed(K), device="cuda")
+    W, lo = W.half(), 1 - (steps - 1) / q
+    work = torch.empty(gpu.sr_fold_workspace_bytes(K, N), dtype=torch.uint8, device="cuda")
+    both, sums = (microseconds(lambda lo=lo: gpu.sr_fold_smooth_rotate_quant_ex(W, None, 0.5, 0, False, steps, lo, workspace=work)) for lo in (lo, lo + 1.37e-4))
+    print("case fine fractions", K, N, steps, q, "%.1f %.1f us" % (both, sums), flush=True)
+    assert both < 1.15 * sums
+
+
+@pytest.mark.parametrize("steps,q", [(2, 100), (3, 71), (4, 100), (6, 56), (6, 64), (6, 70), (8, 98), (9, 75), (11, 100), (12, 100), (32, 62), (32, 99)])
+@pytest.mark.parametrize("K,N", [(2048, 48), (4096, 32), (8192, 32), (16384, 16)])
+def test_bits_of_fine_fractions(gpu, K, N, steps, q):
+    print("case fine fractions bits", K, N, steps, q, flush=True)
+    W = torch.from_numpy(wl.to_f16_sat(np.random.default_rng(K + q).standard_t(4, (K, N)).astype(np.float32) * 0.02)).cuda()
+    full = gpu.sr_fold_smooth_rotate_quant_ex(W, None, 0.5, 0, False, steps, 1 - (steps - 1) / q)
+    head = gpu.sr_fold_smooth_rotate_quant_ex(W, None, 0.5, 1, False, steps, 1 - (steps - 1) / q)
+    for name, x, y in zip(("codes", "scales", "1/s", "ratios"), full, head):
+        assert torch.equal(x, y), name
