@@ -17,22 +17,21 @@ namespace {
 // fp32 add / mul / fma with VGPR operands issue in ~2.7 cycles, rint / min / max / med3, conversions, and anything with
 // an SGPR or DPP operand in ~4.6 (measured per instruction).  So
 //  * a LANE owns a ratio (Delta_i, 1/Delta_i in its registers) and the values come by broadcast LDS reads: no scalar
-//    operands, and no reduction over lanes per ratio.  64 / n subsets of lanes take different groups of 8 values
-//    (21 ratios: 3 subsets, 63 lanes at work);
+//    operands, and no reduction over lanes per ratio.  64 / n subsets of lanes (8 at most) take different groups of 8
+//    values (21 ratios: 3 subsets, 63 lanes at work);
 //  * a value costs five of the cheap instructions: clamp to [0, 1] of (y / Delta + 8) / 15 (the clamp is an output
 //    modifier of the fma), times 15 plus 1.5 * 2^23 (rounds to an integer), minus 1.5 * 2^23 + 8 (the code), residual,
 //    square-accumulate.  The scaling by 15 moves a rounding boundary by less than 1e-6 code units, where both codes
 //    give the same error; the codes themselves are taken from the chosen ratio by the usual quantiser.
 // Eight terms are summed in fp32, those sums in fp64.  4096 x 14336, 21 ratios, whole kernel: 288 -> 190 us (five
-// instructions of 4.6 cycles per value and a six-step lane reduction per ratio before).
+// instructions of 4.6 cycles per value and a six-step lane reduction per ratio before).  `err_w` is as small as it can be, so that two
+// rows of 16384 fit a CU (4 subsets of 32 ratios each: 2048 channels, 21 ratios, 121 us a call against 95).
 // ------------------------------------------------------------------------------------------
-constexpr int search_subsets(int NT) { return NT <= 256 ? 8 : 4; }
-constexpr int search_scratch_bytes(int NT) { return NT / 64 * search_subsets(NT) * kMaxClipGrid * 8; }
+constexpr int search_scratch(int NT) { return NT; }      // doubles of err_w: one per unit and ratio, at most one per lane
 template <int K, int NT, typename Read8>
-__device__ __forceinline__ float search_ratio(Read8 read, const float amax, const float *grid, const int n, const int t,
-                                              double (*err_w)[kMaxClipGrid])
+__device__ __forceinline__ float search_ratio(Read8 read, const float amax, const float *grid, const int n, const int t, double *err_w)
 {
-    constexpr int NW = NT / 64, G = K / 8, MAX_SUB = search_subsets(NT);
+    constexpr int NW = NT / 64, G = K / 8, MAX_SUB = 8;
     __shared__ float ratios[kMaxClipGrid];
     if (t == 0) {
 #pragma unroll
@@ -72,18 +71,18 @@ __device__ __forceinline__ float search_ratio(Read8 read, const float amax, cons
         add_group(a1, b1);
     }
     if (g < G) add_group(a0, b0);
-    if (sub < subs) err_w[unit][i] = acc;
+    if (sub < subs) err_w[unit * n + i] = acc;
     __syncthreads();
     if (t < n) {
-        double e = err_w[0][t];
-        for (int u = 1; u < units; ++u) e += err_w[u][t];
-        err_w[0][t] = e;
+        double e = err_w[t];
+        for (int u = 1; u < units; ++u) e += err_w[u * n + t];
+        err_w[t] = e;
     }
     __syncthreads();
-    double best = err_w[0][0];
+    double best = err_w[0];
     int best_i = 0;
     for (int k = 1; k < n; ++k) {                        // every thread takes the same decision
-        const double e = err_w[0][k];
+        const double e = err_w[k];
         if (e < best) { best = e; best_i = k; }
     }
     return ratios[best_i];
@@ -147,19 +146,24 @@ struct CellScale {
     float to_cell, to_fixed;
     __device__ __forceinline__ CellScale(int q, float amax) : to_cell((float)(14 * q) / amax), to_fixed(1073741824.f / amax) {}
 };
-// (neg, pos: words of cell 0 for the two signs, swapped by a caller whose value carries a flipped sign)
-__device__ __forceinline__ void count_value(uint64_t *cells, const CellScale &s, int neg, int pos, float y)
+// (neg, pos: words of cell 0 for the two signs, swapped by a caller whose value carries a flipped sign; LOWEST: cells below
+// `lowest` are left out)
+template <bool LOWEST> __device__ __forceinline__ void count_value(uint64_t *cells, const CellScale &s, int neg, int pos, float y, int lowest = 0)
 {
     const int cell = (int)(uint32_t)(fabsf(y) * s.to_cell);
+    if (LOWEST && cell < lowest) return;
     const uint64_t one = (uint64_t)1 << 48 | (uint32_t)(fabsf(y) * s.to_fixed);
     __hip_atomic_fetch_add(cells + (y < 0.f ? neg : pos) - cell, one, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// One large value among small ones (weights of one sign, of equal size, ..): at most half of the waves have a value of amax / 19
-// (red: their maxima).  Where the large value does not decide between the ratios, hardly another does: nearly every such row
-// needs search_ratio behind the count, and its small values meet in a few cells, so it goes to search_ratio at once.  4096
-// channels of weights between -0.05 and 0, 21 ratios, us a call, K = 2048, 4096, 8192, 14336: 75, 103, 192, 358 with the count in
-// front, 59, 79, 143, 257 without (50, 70, 131, 256 in fwht_quant_search_kernel, which has the whole LDS for its rows).
+// Few large values among small ones (weights of one sign, of equal size, ..): at most half of the waves have a value of amax / 19
+// (red: their maxima).  The small values meet in a few cells, and hardly one of them decides between the ratios.  So
+//  * values below every boundary of every ratio are not counted in such a row (in others the comparison is not worth it);
+//  * a row whose large value does not decide either (undecided_signs; any row of K = 28 2^p, where 28 large values come together)
+//    goes to search_ratio at once: the count would leave nearly every one open.
+// us a call, weights between -0.05 and 0, 21 ratios, 4096 channels of 2048, 4096, 8192, 14336: 75, 103, 192, 358 counted like other
+// rows, 59, 80, 146, 257 this way (50, 70, 131, 255 in fwht_quant_search_kernel, whose workgroups have no cells); 11 ratios: 36, 48, 91,
+// 192 -> 33, 39, 67, 198.
 // The line: rows of one value among normally distributed ones, 21 ratios 0.025 apart, leave two ratios or more up to a standard
 // deviation of 0.014 .. 0.016 amax, where a wave's largest value is 0.048 .. 0.055 amax, and one ratio beyond.
 template <int NT> __device__ __forceinline__ bool spiked(const float *red, const float amax)
@@ -170,6 +174,7 @@ template <int NT> __device__ __forceinline__ bool spiked(const float *red, const
     return 2 * reach <= NT / 64;
 }
 // note_sign: 1 for a positive, 2 for a negative value of magnitude amax (see undecided_signs).
+__device__ __forceinline__ int lowest_boundary(float smallest_ratio, int q) { return (int)(smallest_ratio * (float)q + 0.5f); }
 __device__ __forceinline__ void note_sign(int *signs, float y, float amax, bool flipped)
 {
     if (fabsf(y) == amax) __hip_atomic_fetch_or(signs, (y < 0.f) != flipped ? 2 : 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -189,11 +194,15 @@ __device__ __forceinline__ int ratio_of_cells(const float *grid, const int n, co
 
     // ---- inclusive prefix sums over all words
     const int run = histogram_run(K, NT, q);
-    uint64_t *const own = cells + t * run;
-    int len = run;
-    if constexpr (histogram_trimmed(K)) len = t * run + run > histogram_cells(q) ? histogram_cells(q) - t * run : run;      // (none: < 1)
+    int from = 0, to = run;                              // of its run: known to be the same for all threads where it is not trimmed
+    uint64_t *own = cells + t * run;
+    if constexpr (histogram_trimmed(K)) {
+        own = cells;
+        from = t * run;
+        to = from + run < histogram_cells(q) ? from + run : histogram_cells(q);
+    }
     uint64_t sum = 0;
-    for (int e = 0; e < len; ++e) sum += own[e];
+    for (int c = from; c < to; ++c) sum += own[c];
     uint64_t upto = add_shifted<0x111, 0xF>(sum);        // row_shr 1, 2, 4, 8, then the rows before
     upto = add_shifted<0x112, 0xF>(upto);
     upto = add_shifted<0x114, 0xF>(upto);
@@ -205,9 +214,9 @@ __device__ __forceinline__ int ratio_of_cells(const float *grid, const int n, co
     {
         uint64_t acc = upto - sum;
         for (int w = 0; w < NW; ++w) acc += w < (t >> 6) ? wave_sum[w] : 0;
-        for (int e = 0; e < len; ++e) {
-            acc += own[e];
-            own[e] = acc;
+        for (int c = from; c < to; ++c) {
+            acc += own[c];
+            own[c] = acc;
         }
     }
     __syncthreads();

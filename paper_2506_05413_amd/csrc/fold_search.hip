@@ -48,7 +48,10 @@ __global__ __launch_bounds__((TwoPass<K>::NT)) void fold_search_kernel(const __h
     const bool f = S::flipped(S::first(t) >> 4);         // the sign that all values of a thread carry
     // (beyond this range the scaled values would not stay inside fp32)
     bool count = amax > 0x1p-90f && amax < 0x1p90f;
-    if (count && undecided && spiked<NT>(red, amax)) {
+    const bool spikes = spiked<NT>(red, amax);
+    if constexpr (!is_pow2(K)) {
+        count = count && !spikes;
+    } else if (count && spikes && undecided) {
         if (undecided != 3) {
 #pragma unroll
             for (int r = 0; r < S::R; ++r) note_sign(&signs, o[r], amax, f);
@@ -60,8 +63,14 @@ __global__ __launch_bounds__((TwoPass<K>::NT)) void fold_search_kernel(const __h
     if (count) {
         const CellScale scale(q, amax);
         const int neg = f ? 28 * q + 1 : 14 * q, pos = f ? 14 * q : 28 * q + 1;
+        if (is_pow2(K) && spikes) {
+            const int lowest = lowest_boundary(ex.grid[ex.n_grid - 1], q);
 #pragma unroll
-        for (int r = 0; r < S::R; ++r) count_value(cells, scale, neg, pos, o[r]);
+            for (int r = 0; r < S::R; ++r) count_value<true>(cells, scale, neg, pos, o[r], lowest);
+        } else {
+#pragma unroll
+            for (int r = 0; r < S::R; ++r) count_value<false>(cells, scale, neg, pos, o[r]);
+        }
         __syncthreads();
         i = ratio_of_cells<K, NT>(ex.grid, ex.n_grid, q, cells, t);
     }
@@ -87,7 +96,7 @@ __global__ __launch_bounds__((TwoPass<K>::NT)) void fold_search_kernel(const __h
             a = *reinterpret_cast<const float4 *>(src);
             b = *reinterpret_cast<const float4 *>(src + 4);
         };
-        clip = search_ratio<K, NT>(read8, amax, ex.grid, ex.n_grid, t, static_cast<double (*)[kMaxClipGrid]>(scratch));
+        clip = search_ratio<K, NT>(read8, amax, ex.grid, ex.n_grid, t, static_cast<double *>(scratch));
     }
     if (ex.ratio_out && t == 0) ex.ratio_out[m] = clip;
     const float delta = (clip * amax) / 7.f;
@@ -101,7 +110,7 @@ hipError_t launch(const void *Wt, int64_t rows, int64_t ldw, const float *s, flo
 {
     using S = TwoPass<K>;
     constexpr auto kern = fold_search_kernel<K>;
-    constexpr int row_bytes = S::LEN * (int)sizeof(float), search = search_scratch_bytes(S::NT);
+    constexpr int row_bytes = S::LEN * (int)sizeof(float), search = search_scratch(S::NT) * 8;
     constexpr int most = histogram_words(K, S::NT, kMaxClipDenominator) * 8;
     static_assert(most >= search && row_bytes + most + 1024 <= 160 * 1024, "LDS");
     if constexpr (row_bytes + most > 40 * 1024)

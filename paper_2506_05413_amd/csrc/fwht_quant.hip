@@ -18,6 +18,8 @@
 #include "clip_search.h"
 #include "gemm_common.h"      // LDS-DMA load, hand-placed waits, fence-free barrier
 
+#include <type_traits>
+
 namespace sr {
 namespace {
 
@@ -125,7 +127,10 @@ __global__ __launch_bounds__(NT) void fwht_quant_search_kernel(const __half *__r
         if constexpr (HIST) {
             // (beyond this range the scaled values would not stay inside fp32; the largest being finite, all values are)
             bool count = amax > 0x1p-90f && amax < 0x1p90f;
-            if (count && undecided && spiked<NT>(red, amax)) {
+            const bool spikes = spiked<NT>(red, amax);
+            if constexpr (!is_pow2(K)) {
+                count = count && !spikes;
+            } else if (count && spikes && undecided) {
                 if (undecided != 3) {
                     for (int c = t; c < K; c += NT) note_sign(&signs, row[pad(c)], amax, false);
                     __syncthreads();
@@ -135,19 +140,23 @@ __global__ __launch_bounds__(NT) void fwht_quant_search_kernel(const __half *__r
             if (count) {
                 uint64_t *const cells = static_cast<uint64_t *>(scratch);
                 const CellScale scale(q, amax);
-                for (int c = t; c < K / 4; c += NT) {
-                    const float4 v = *reinterpret_cast<const float4 *>(row + pad(4 * c));
-                    count_value(cells, scale, 14 * q, 28 * q + 1, v.x);
-                    count_value(cells, scale, 14 * q, 28 * q + 1, v.y);
-                    count_value(cells, scale, 14 * q, 28 * q + 1, v.z);
-                    count_value(cells, scale, 14 * q, 28 * q + 1, v.w);
-                }
+                auto count_row = [&](auto some, int lowest) {
+                    for (int c = t; c < K / 4; c += NT) {
+                        const float4 v = *reinterpret_cast<const float4 *>(row + pad(4 * c));
+                        count_value<some.value>(cells, scale, 14 * q, 28 * q + 1, v.x, lowest);
+                        count_value<some.value>(cells, scale, 14 * q, 28 * q + 1, v.y, lowest);
+                        count_value<some.value>(cells, scale, 14 * q, 28 * q + 1, v.z, lowest);
+                        count_value<some.value>(cells, scale, 14 * q, 28 * q + 1, v.w, lowest);
+                    }
+                };
+                if (is_pow2(K) && spikes) count_row(std::true_type{}, lowest_boundary(ex.grid[ex.n_grid - 1], q));
+                else count_row(std::false_type{}, 0);
                 __syncthreads();
                 i = ratio_of_cells<K, NT>(ex.grid, ex.n_grid, q, cells, t);
             }
         }
         if (i >= 0) clip = ex.grid[i];
-        else clip = search_ratio<K, NT>(read8, amax, ex.grid, ex.n_grid, t, static_cast<double (*)[kMaxClipGrid]>(scratch));
+        else clip = search_ratio<K, NT>(read8, amax, ex.grid, ex.n_grid, t, static_cast<double *>(scratch));
     }
     if (ex.ratio_out && t == 0) ex.ratio_out[m] = clip;
     const float delta = (amax == 0.f) ? 1.f : (clip * amax) / 7.f;
@@ -258,7 +267,7 @@ __global__ __launch_bounds__(NT) void fwht_quant_ex_kernel(const __half *__restr
     for (int w = 1; w < NW; ++w) amax = fmaxf(amax, red[w]);
 
     if constexpr (!F6) {                                 // (the search belongs to the weight fold, which writes nibbles)
-        __shared__ double err_w[search_scratch_bytes(NT) / (8 * kMaxClipGrid)][kMaxClipGrid];
+        __shared__ double err_w[search_scratch(NT)];
         if (ex.n_grid > 0) clip = amax != 0.f ? search_ratio<K, NT>(RowRead8{row}, amax, ex.grid, ex.n_grid, t, err_w) : ex.grid[0];
     }
     if (ex.ratio_out && t == 0) ex.ratio_out[m] = clip;
@@ -567,14 +576,14 @@ hipError_t launch_search(const void *X, int64_t rows, int64_t ldx, const float *
 {
     constexpr auto kern = fwht_quant_search_kernel<K, NT, HIST>;
     constexpr int row_bytes = (int)sizeof(float) * padded_len(K), most = HIST ? histogram_words(K, NT, kMaxClipDenominator) * 8 : 0;
-    constexpr int lds_most = row_bytes + (most > search_scratch_bytes(NT) ? most : search_scratch_bytes(NT));
+    constexpr int scratch = search_scratch(NT) * 8, lds_most = row_bytes + (most > scratch ? most : scratch);
     static_assert(lds_most + 1024 <= 160 * 1024, "LDS");
     const int cells = HIST ? histogram_words(K, NT, q) * 8 : 0;
     if (lds_most > 40 * 1024) {
         hipError_t e = allow_dynamic_lds<kern>(lds_most);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(kern, dim3((unsigned)rows), dim3(NT), row_bytes + (cells > search_scratch_bytes(NT) ? cells : search_scratch_bytes(NT)), st,
+    hipLaunchKernelGGL(kern, dim3((unsigned)rows), dim3(NT), row_bytes + (cells > scratch ? cells : scratch), st,
                        static_cast<const __half *>(X), ldx, pre, post_scale, Q, scale_out, ex, q, HIST ? undecided_signs(ex.grid, ex.n_grid, K) : 0);
     return hipGetLastError();
 }
