@@ -600,8 +600,11 @@ hipError_t launch_one_ex(const void *X, int64_t rows, int64_t ldx, const float *
             // threads per row as in launch_one (many rows); K = 2048 x 4096 channels, 21 ratios: 34 us with 256 threads
             // against 39 with 128 (1024: 24 against 19 with 64, 512: 17 against 13)
             constexpr int NTS = K == 8192 ? 512 : (K == 16384 || K == 28672 || K == 32768) ? 1024 : K == 2048 ? 256 : NT;
-            // 2048, 4096, 8192 and 14336 have a kernel of their own (fold_search.hip); K = 32768 leaves no LDS beside the row
-            if constexpr (K == 16384 || K == 28672) {
+            // The one-pass search, us a call, 21 ratios, without / with it: 7168 x 4096 115 / 80 (2 ratios 0.01 apart 75 / 76, weights of
+            // one sign 112 / 125).  2048, 4096, 8192 and 14336 have a kernel of their own (fold_search.hip).  Not 3584, where few or
+            // fine ratios lose (72 / 54, but 2 ratios 0.01 apart 47 / 55), nor shorter rows, for which the cells are too many (1792 42 /
+            // 45, 1024 30 / 32, 512 34 / 38; 11 ratios 0.01 apart 35 / 54, 26 / 44, 29 / 63).  K = 32768 leaves no LDS beside the row.
+            if constexpr (K == 7168 || K == 16384 || K == 28672) {
                 if (const int q = clip_grid_denominator(ex.grid, ex.n_grid); q > 0)
                     return launch_search<K, NTS, true>(X, rows, ldx, pre, post_scale, Q, scale_out, ex, q, st);
             }

@@ -1,7 +1,8 @@
-"""Searched folds that count in vain or at a loss.  Weights whose rotated rows hold one large value and many small ones (all weights of one sign, or equal):
-hardly any value decides between the ratios, so nearly every row needs a sum per ratio, and counting its values first would be
-in vain.  Ratios that are multiples of a fine fraction only: many cells, some numbers of them at odds with the LDS banks.  Same
-ratios, codes and scales as from the sums alone, and not much dearer than those."""
+"""Searched folds that count in vain, at a loss or not at all.  Weights whose rotated rows hold one large value and many small
+ones (all weights of one sign, or equal): hardly any value decides between the ratios, so nearly every row needs a sum per ratio,
+and counting its values first would be in vain.  Ratios that are multiples of a fine fraction only: many cells, some numbers of
+them at odds with the LDS banks.  Row lengths that are to be counted.  Same ratios, codes and scales as from the sums alone, and
+not much dearer than those."""
 import numpy as np
 import pytest
 import torch
@@ -82,3 +83,13 @@ def test_bits_of_fine_fractions(gpu, K, N, steps, q):
     head = gpu.sr_fold_smooth_rotate_quant_ex(W, None, 0.5, 1, False, steps, 1 - (steps - 1) / q)
     for name, x, y in zip(("codes", "scales", "1/s", "ratios"), full, head):
         assert torch.equal(x, y), name
+
+
+# normal weights, 21 ratios: with the count 0.6 .. 0.82 of the time of the sums
+@pytest.mark.parametrize("K,N", [(2048, 4096), (4096, 4096), (7168, 4096), (8192, 4096), (14336, 2048), (16384, 2048), (28672, 2048)])
+def test_count_is_ahead(gpu, K, N):
+    W = (0.02 * torch.randn((K, N), generator=torch.Generator(device="cuda").manual_seed(K), device="cuda")).half()
+    work = torch.empty(gpu.sr_fold_workspace_bytes(K, N), dtype=torch.uint8, device="cuda")
+    count, sums = (microseconds(lambda lo=lo: gpu.sr_fold_smooth_rotate_quant_ex(W, None, 0.5, 0, False, 21, lo, workspace=work)) for lo in (0.5, 0.499))
+    print("case count ahead", K, N, "%.1f %.1f us" % (count, sums), flush=True)
+    assert count < 0.9 * sums
