@@ -486,7 +486,7 @@ hipError_t launch_gemm_decode(const uint8_t *Xq, const float *xs, const uint8_t 
     // the decode-kernel knob = 1 (dot, M <= 2 only), 2 (MFMA, workgroup per 16 channels) or 3 (streaming MFMA)
     // forces a kernel (tuning and test aid); not set = the choice measured below.
     int force = 0;
-    if (int64_t f; tuned(kTuneDecodeKernel, f)) force = (int)f;
+    if (int64_t f; tuned(kTuneDecodeKernel, f) && f <= 3) force = (int)f;            // (4 is about sr_w4a4_linear_decode only)
     const int nslab = (int)((K / 2 + SLAB - 1) / SLAB);
 
     // measured (4096 -> 14336): dot kernel 6.2 / 7.0 us for M = 1 / 2 (one more microsecond per further token),

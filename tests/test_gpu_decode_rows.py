@@ -70,3 +70,28 @@ def test_captured_calls(gpu, M, K, N):
         Y.zero_()
         graph.replay()
         assert torch.equal(Y, gpu.sr_w4a4_linear_decode(x, None, Wq, ws, 0.9)) and bool(Y.any())
+
+
+@pytest.mark.parametrize("M,K,N", [(1, 4096, 4096), (2, 4096, 4096), (3, 4096, 4096), (4, 2048, 6144), (4, 4096, 28688), (7, 4096, 2048), (16, 8192, 2048)])
+def test_one_launch_knob_leaves_the_gemm_alone(gpu, tune, M, K, N):
+    """The knob value for one launch where there is one: inside that range, outside it and in the GEMM on its own, the same bits."""
+    print("case decode knob 4", M, K, N, flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M + N)
+    Wq = torch.randint(0, 256, (N, K // 2), generator=g, dtype=torch.uint8, device="cuda")
+    ws = 1e-3 + 1e-3 * torch.rand(N, generator=g, device="cuda")
+    X = torch.randn((M, K), generator=g, device="cuda").half()
+    Xq, xs = gpu.sr_fwht_quant_act(X, None, 0.9)
+    work = torch.empty(max(gpu.sr_linear_decode_workspace_bytes(M, K), 16), dtype=torch.uint8, device="cuda")
+    Y = torch.empty((M, N), dtype=torch.float16, device="cuda")
+    want, gemm = gpu.sr_w4a4_linear_decode(X, None, Wq, ws, 0.9, workspace=work), gpu.sr_w4a4_gemm(Xq, xs, Wq, ws)
+    tune(gpu.SR_TUNE_DECODE_KERNEL, 4)
+    assert torch.equal(gpu.sr_w4a4_gemm(Xq, xs, Wq, ws), gemm)
+    assert torch.equal(gpu.sr_w4a4_linear_decode(X, None, Wq, ws, 0.9, workspace=work), want)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        gpu.sr_w4a4_linear_decode(X, None, Wq, ws, 0.9, Y=Y, workspace=work)
+    for _ in range(3):
+        Y.zero_()
+        graph.replay()
+        assert torch.equal(Y, want)
