@@ -45,6 +45,22 @@ __device__ __forceinline__ void unpack16(const u32x4 w, v4i &a0, v4i &a1)
     a1[2] = (int)((w.w << 4) & HM); a1[3] = (int)(w.w & HM);
 }
 
+// fp16 of a * b, rounded once, or to fp32 first.  Spelled out in the kernels for up to 16 tokens, because the calls in one launch
+// reproduce the outputs of the kernel that they replace bit for bit: from __float2half_rn(a * b) the compiler makes the first where
+// one value is stored at a time and the second where it converts pairs.
+__device__ __forceinline__ __half rounded_once(float a, float b)
+{
+    uint32_t h;
+    asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(h) : "v"(a), "v"(b));
+    return __ushort_as_half((unsigned short)h);
+}
+__device__ __forceinline__ __half rounded_twice(float a, float b)
+{
+    float p = a * b;
+    asm("" : "+v"(p));
+    return __float2half_rn(p);
+}
+
 // ------------------------------------------------------------------------------------------
 // Epilogue for 32 x 32 MFMA tiles: dequantise, then transpose the wave's WM x WN tile through LDS,
 // 32 tokens at a time, so that global memory is written in whole rows of the tile (16 bytes per

@@ -184,7 +184,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_decode_kernel(const uint8_t *__r
         for (int w = 0; w < NW; ++w) sum += red[w][0][a][b][r & 3][t + 8 * (r >> 2)] + red[w][1][a][b][r & 3][t + 8 * (r >> 2)];
         sum >>= 8;                                         // both operands carried the factor 16
         if (out_i32) static_cast<int32_t *>(Yv)[(int64_t)m * ldy + n] = sum;
-        else static_cast<__half *>(Yv)[(int64_t)m * ldy + n] = __float2half_rn((float)sum * fx[k] * fw[k]);
+        else static_cast<__half *>(Yv)[(int64_t)m * ldy + n] = rounded_once((float)sum * fx[k], fw[k]);
     }
 }
 
@@ -318,10 +318,10 @@ __global__ __launch_bounds__(1024) void gemm_decode_stream_kernel(const uint8_t 
                 *reinterpret_cast<v4i *>(static_cast<int32_t *>(Yv) + (int64_t)om * ldy + on) = sum;
             } else {
                 union { __half h[4]; uint2 u; } o;
-                o.h[0] = __float2half_rn((float)sum[0] * fx * fw.x);
-                o.h[1] = __float2half_rn((float)sum[1] * fx * fw.y);
-                o.h[2] = __float2half_rn((float)sum[2] * fx * fw.z);
-                o.h[3] = __float2half_rn((float)sum[3] * fx * fw.w);
+                o.h[0] = rounded_twice((float)sum[0] * fx, fw.x);
+                o.h[1] = rounded_twice((float)sum[1] * fx, fw.y);
+                o.h[2] = rounded_twice((float)sum[2] * fx, fw.z);
+                o.h[3] = rounded_twice((float)sum[3] * fx, fw.w);
                 *reinterpret_cast<uint2 *>(static_cast<__half *>(Yv) + (int64_t)om * ldy + on) = o.u;
             }
         }
@@ -410,7 +410,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_decode_dot_kernel(const uint8_t 
 #pragma unroll
             for (int w = 0; w < NW; ++w) sum += red[w][m][j];
             if (out_i32) static_cast<int32_t *>(Yv)[(int64_t)m * ldy + n] = sum;
-            else static_cast<__half *>(Yv)[(int64_t)m * ldy + n] = __float2half_rn((float)sum * fx * fw);
+            else static_cast<__half *>(Yv)[(int64_t)m * ldy + n] = rounded_once((float)sum * fx, fw);
         }
     }
 }

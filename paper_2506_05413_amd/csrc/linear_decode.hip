@@ -143,7 +143,7 @@ __global__ __launch_bounds__(LD_NT) void linear_decode_kernel(const __half *__re
         int sum = 0;
 #pragma unroll
         for (int wv = 0; wv < LD_NW; ++wv) sum += part[wv * LD_MT * (8 * G) + t];
-        Y[n0 + t] = __float2half_rn((float)sum * sx[0] * w_scale);
+        Y[n0 + t] = rounded_once((float)sum * sx[0], w_scale);
     }
 }
 
@@ -188,20 +188,6 @@ template <int LO, int HI, typename F> __device__ __forceinline__ void units_from
         f(std::integral_constant<int, LO>{});
         units_from_to<LO + 1, HI>(f);
     }
-}
-
-// fp16 of a * b, rounded once (v_fma_mixlo_f16: as the compiler has it in the kernels that store one value at a time) or to
-// fp32 first (where it converts pairs)
-__device__ __forceinline__ __half dequantised(float a, float b, bool once)
-{
-    if (once) {
-        uint32_t h;
-        asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(h) : "v"(a), "v"(b));
-        return __ushort_as_half((unsigned short)h);
-    }
-    float p = a * b;
-    asm("" : "+v"(p));
-    return __float2half_rn(p);
 }
 
 template <int K> struct DecodeRows {
@@ -342,10 +328,10 @@ __global__ __launch_bounds__(DecodeRows<K>::NW * 64, 4) void linear_decode_rows_
         for (int v = 1; v < NW; ++v) sum += sums[(v * PAIRS + wave) * 64 + lane];
         sum >>= 8;                                       // both operands carried the factor 16
         union { __half h[4]; uint2 u; } y;
-        y.h[0] = dequantised((float)sum[0] * fx, fw.x, once);
-        y.h[1] = dequantised((float)sum[1] * fx, fw.y, once);
-        y.h[2] = dequantised((float)sum[2] * fx, fw.z, once);
-        y.h[3] = dequantised((float)sum[3] * fx, fw.w, once);
+        y.h[0] = once ? rounded_once((float)sum[0] * fx, fw.x) : rounded_twice((float)sum[0] * fx, fw.x);
+        y.h[1] = once ? rounded_once((float)sum[1] * fx, fw.y) : rounded_twice((float)sum[1] * fx, fw.y);
+        y.h[2] = once ? rounded_once((float)sum[2] * fx, fw.z) : rounded_twice((float)sum[2] * fx, fw.z);
+        y.h[3] = once ? rounded_once((float)sum[3] * fx, fw.w) : rounded_twice((float)sum[3] * fx, fw.w);
         *reinterpret_cast<uint2 *>(Y + (int64_t)om * ldy + on) = y.u;
     }
 }
