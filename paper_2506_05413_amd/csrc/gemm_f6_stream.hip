@@ -232,13 +232,8 @@ hipError_t launch_st(const uint8_t *X6, const float *xs, const uint8_t *W6, cons
                      int64_t K, void *Y, int64_t ldy, int out_i32, hipStream_t st)
 {
     const int tiles_m = (int)((M + FM * 16 - 1) / (FM * 16)), tiles_n = (int)((N + FN * 16 - 1) / (FN * 16));
-    // Paired tails take L1 lookups away, and a few registers.  They gain where several rows of tiles read the same weights
-    // (240 shapes, M 17 .. 334: 1 .. 5 % per tile, up to 12 %); with one row, or two of the wide tiles, memory bounds the launch
-    // (63 x 11040 x 2048, from HBM, 7.9 -> 8.5 us with pairs; 70 x 8048 x 8192 11.9 -> 12.4).  32 x 64 grows from 128 registers to 155, so one workgroup
-    // fits a CU instead of two: there only while every workgroup has a CU to itself (84 x 10464 x 2048, 492 of them, 6.9 ->
-    // 8.1; 128 x 4096 x 14336, 256 of them, 14.5 -> 14.2, weights from HBM 19.9 -> 18.6).
     constexpr bool CAN_PAIR = FM > 1 || FN > 1;
-    const bool pairs = CAN_PAIR && 2 * tiles_m > FN && (FM * FN != 8 || tiles_m * tiles_n <= 256);
+    const bool pairs = CAN_PAIR && f6_pairs_tails(tiles_m, tiles_n, FM, FN, compute_units());
     const auto kern = pairs ? gemm_f6_stream_kernel<FM, FN, NW, D, CAN_PAIR> : gemm_f6_stream_kernel<FM, FN, NW, D, false>;
     hipLaunchKernelGGL(kern, dim3((unsigned)((tiles_m * tiles_n + 7) / 8 * 8)), dim3(NW * 64), 0, st,
                        X6, xs, W6, ws, (int)M, (int)N, (int)K, Y, ldy, out_i32, tiles_m, tiles_n);

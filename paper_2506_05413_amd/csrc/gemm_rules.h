@@ -129,6 +129,17 @@ template <int COUNT> constexpr bool coefficients_grow(const GemmConfig (&configs
 }
 static_assert(coefficients_grow(kF6Configs) && coefficients_grow(kPackedConfigs), "a prediction may not fall where work is added");
 
+// Whether the register kernel of the FP6 GEMM (tiles of 16 FM x 16 FN) fetches the 8-byte tails of two fragments at a time.  That
+// takes L1 lookups away, and a few registers.  It gains where several rows of tiles read the same weights (240 shapes, M 17 .. 334: 1
+// .. 5 % per tile, up to 12 %); with one row, or two of the wide tiles, memory bounds the launch (63 x 11040 x 2048, from HBM, 7.9 ->
+// 8.5 us with pairs; 70 x 8048 x 8192 11.9 -> 12.4).  32 x 64 grows from 128 registers to 155, so one workgroup fits a CU instead of
+// two: there only while every workgroup has a CU to itself (84 x 10464 x 2048, 492 of them on 256, 6.9 -> 8.1; 128 x 4096 x 14336, 256
+// of them, 14.5 -> 14.2, weights from HBM 19.9 -> 18.6).
+constexpr bool f6_pairs_tails(int64_t tiles_m, int64_t tiles_n, int fm, int fn, int64_t cus)
+{
+    return 2 * tiles_m > fn && (fm * fn != 8 || tiles_m * tiles_n <= cus);
+}
+
 // ---- tiles and workgroups (device code too: constexpr) ------------------------------------------------------------------
 // Split of the tile grid over the 8 XCDs (each with its own L2): XCD x = v & 7 gets the rectangle
 // (x % xcd_m, x / xcd_m) of an xcd_m x (8 / xcd_m) split and walks it m fastest.  Measured (FETCH_SIZE,

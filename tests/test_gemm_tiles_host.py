@@ -67,3 +67,27 @@ int main()
     subprocess.run(["g++", "-std=c++17", "-O2", "-Wall", "-Werror", "-I", CSRC, "-o", str(tmp_path / "rows"), str(tmp_path / "rows.cpp")], check=True)
     r = subprocess.run([str(tmp_path / "rows")], capture_output=True, text=True)
     assert r.returncode == 0 and int(r.stdout) > 500, r.stdout
+
+
+def test_paired_tails_follow_the_compute_units(tmp_path):
+    """Tiles of 32 x 64, whose paired kernel has room for one workgroup per compute unit, pair while there are no more tiles than those."""
+    (tmp_path / "pairs.cpp").write_text(r"""
+#include "gemm_rules.h"
+#include <cstdio>
+int main()
+{
+    int both = 0;
+    for (int cus = 32; cus <= 512; cus *= 2)
+        for (int tm = 1; tm <= 20; ++tm)
+            for (int tn = 1; tn <= 300; ++tn) {
+                const bool pairs = sr::f6_pairs_tails(tm, tn, 2, 4, cus);
+                if (pairs != (tm > 2 && tm * tn <= cus)) return std::printf("%d x %d tiles, %d units\n", tm, tn, cus), 1;
+                if (sr::f6_pairs_tails(tm, tn, 4, 4, cus) != (tm > 2)) return std::printf("64 x 64, %d x %d tiles\n", tm, tn), 1;
+                both += pairs;
+            }
+    std::printf("%d\n", both);
+}
+""")
+    subprocess.run(["g++", "-std=c++17", "-O2", "-Wall", "-Werror", "-I", CSRC, "-o", str(tmp_path / "pairs"), str(tmp_path / "pairs.cpp")], check=True)
+    r = subprocess.run([str(tmp_path / "pairs")], capture_output=True, text=True)
+    assert r.returncode == 0 and int(r.stdout) > 100, r.stdout
