@@ -7,6 +7,8 @@
 
 #include <hip/hip_fp16.h>
 
+#include <type_traits>
+
 namespace sr {
 namespace {
 
@@ -33,6 +35,15 @@ __device__ __forceinline__ void dma16(const uint8_t *base, uint32_t lane_off, ui
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(lane_off), "s"(base)
                  : "memory", "m0");
+}
+
+// f(0), .. f(N - 1) with constants
+template <int N, typename F> __device__ __forceinline__ void static_for(F f)
+{
+    if constexpr (N > 0) {
+        static_for<N - 1>(f);
+        f(std::integral_constant<int, N - 1>{});
+    }
 }
 
 // 32 packed codes -> the operands of two 16x16x64 int8 products

@@ -36,14 +36,6 @@ typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int BLK = 768;     // bytes of one block (8 rows x 128 codes x 6 bits)
 
-template <int N, typename F> __device__ __forceinline__ void static_for(F f)
-{
-    if constexpr (N > 0) {
-        static_for<N - 1>(f);
-        f(std::integral_constant<int, N - 1>{});
-    }
-}
-
 // D = chunks a wave keeps in flight; TPP = 16 x 16 tiles whose partial sums are in LDS at a time.
 template <int FM, int FN, int NW, int D, bool PAIRS>
 __global__ __launch_bounds__(NW * 64) void gemm_f6_stream_kernel(

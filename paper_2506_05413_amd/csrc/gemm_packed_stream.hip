@@ -27,21 +27,6 @@ namespace {
 
 typedef float v4f_dword __attribute__((ext_vector_type(4), aligned(4)));
 
-template <int N, typename F> __device__ __forceinline__ void static_for(F f)
-{
-    if constexpr (N > 0) {
-        static_for<N - 1>(f);
-        f(std::integral_constant<int, N - 1>{});
-    }
-}
-
-__device__ __forceinline__ void widen(const u32x4 w, v4i &a0, v4i &a1)
-{
-    constexpr unsigned HM = 0xF0F0F0F0u;     // nibble kept in the high half of its byte = code * 16
-    a0 = v4i{(int)((w.x << 4) & HM), (int)(w.x & HM), (int)((w.y << 4) & HM), (int)(w.y & HM)};
-    a1 = v4i{(int)((w.z << 4) & HM), (int)(w.z & HM), (int)((w.w << 4) & HM), (int)(w.w & HM)};
-}
-
 // D = chunks a wave keeps in flight; TPP = 16 x 16 tiles whose partial sums are in LDS at a time.
 template <int FM, int FN, int NW, int D>
 __global__ __launch_bounds__(NW * 64) void gemm_w4a4_stream_kernel(
@@ -137,8 +122,8 @@ __global__ __launch_bounds__(NW * 64) void gemm_w4a4_stream_kernel(
         for (int f = 0; f < FM; ++f) {
             u32x4 h[2];
             operands(x[d][f], f & 1, h);
-            widen(h[0], xa[f][0][0], xa[f][0][1]);
-            widen(h[1], xa[f][1][0], xa[f][1][1]);
+            unpack16(h[0], xa[f][0][0], xa[f][0][1]);
+            unpack16(h[1], xa[f][1][0], xa[f][1][1]);
         }
 #pragma unroll
         for (int i = 0; i < FN; ++i) {
@@ -147,7 +132,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_w4a4_stream_kernel(
 #pragma unroll
             for (int k = 0; k < 2; ++k) {
                 v4i wa[2];
-                widen(h[k], wa[0], wa[1]);
+                unpack16(h[k], wa[0], wa[1]);
 #pragma unroll
                 for (int f = 0; f < FM; ++f) {
                     acc[i][f] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wa[0], xa[f][k][0], acc[i][f], 0, 0, 0);
