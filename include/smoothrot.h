@@ -86,10 +86,12 @@ SR_API const char *sr_status_str(int status);
  *   SR_TUNE_FWHT_STREAM    K = 14336 rotation: 1 workgroups of 896 threads, 0 of 512 (the name is that of a variant
  *                          that walked over rows)
  *   SR_TUNE_GEMM_WARM      sr_w4a4_gemm_f6_warm: 0 = ignore the hint (the launch of sr_w4a4_gemm_f6)
+ *   SR_TUNE_CLIP_SEARCH    weight fold over several ratios: 1 = a sum per ratio whatever the ratios are
  * sr_tune_set returns SR_ERR_ARG for an unknown knob; sr_tune_get returns SR_TUNE_AUTO for one.
  */
 enum { SR_TUNE_GEMM_TILE = 0, SR_TUNE_GEMM_GRID = 1, SR_TUNE_GEMM_XCDM = 2, SR_TUNE_DECODE_KERNEL = 3,
-       SR_TUNE_FWHT4096 = 4, SR_TUNE_FWHT_STREAM = 5, SR_TUNE_GEMM_WARM = 6 };
+       SR_TUNE_FWHT4096 = 4, SR_TUNE_FWHT_STREAM = 5, SR_TUNE_GEMM_WARM = 6,
+       SR_TUNE_CLIP_SEARCH = 7 };
 #define SR_TUNE_AUTO INT64_MIN
 SR_API int sr_tune_set(int knob, int64_t value);
 SR_API int64_t sr_tune_get(int knob);

@@ -18,8 +18,8 @@ SR_OK, SR_ERR_NULL, SR_ERR_SHAPE, SR_ERR_UNSUPPORTED_K = 0, 1, 2, 3
 SR_ERR_ALIGN, SR_ERR_ARG, SR_ERR_WORKSPACE, SR_ERR_DEVICE = 4, 5, 6, 7
 SR_F16, SR_I32 = 0, 1
 SR_TUNE_GEMM_TILE, SR_TUNE_GEMM_GRID, SR_TUNE_GEMM_XCDM, SR_TUNE_DECODE_KERNEL = 0, 1, 2, 3
-SR_TUNE_FWHT4096, SR_TUNE_FWHT_STREAM, SR_TUNE_GEMM_WARM = 4, 5, 6
-SR_TUNE_KNOBS = 7
+SR_TUNE_FWHT4096, SR_TUNE_FWHT_STREAM, SR_TUNE_GEMM_WARM, SR_TUNE_CLIP_SEARCH = 4, 5, 6, 7
+SR_TUNE_KNOBS = 8
 SR_TUNE_AUTO = -(1 << 63)
 
 _PKG = os.path.dirname(os.path.abspath(__file__))

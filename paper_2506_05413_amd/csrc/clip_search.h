@@ -127,6 +127,13 @@ template <int K, int NT> __device__ __forceinline__ void clear_cells(uint64_t *c
     }
 }
 
+// q where the ratios of a fold may be taken from the count, 0 where not
+inline int counted_fraction(const RowExtras &ex)
+{
+    if (int64_t f; tuned(kTuneClipSearch, f) && f == 1) return 0;
+    return clip_grid_denominator(ex.grid, ex.n_grid);
+}
+
 template <int CTRL, int ROW_MASK> __device__ __forceinline__ uint64_t add_shifted(uint64_t v)   // v + the permuted lane's v (0 where there is none)
 {
     const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, CTRL, ROW_MASK, 0xF, false);

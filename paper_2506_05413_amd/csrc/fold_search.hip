@@ -126,7 +126,7 @@ hipError_t launch(const void *Wt, int64_t rows, int64_t ldw, const float *s, flo
 hipError_t launch_fold_search(const void *Wt, int64_t rows, int64_t K, int64_t ldw, const float *s, float post_scale,
                               uint8_t *Q, float *scale_out, const RowExtras &ex, hipStream_t st, bool &taken)
 {
-    const int q = clip_grid_denominator(ex.grid, ex.n_grid);
+    const int q = counted_fraction(ex);
     // Fine fractions: the cells take the LDS of other rows, and a sum for each of a few ratios is done sooner (us a call, 4096 channels,
     // sums against counts: 2048, 11 ratios 0.01 apart 39 / 42, 16 42 / 42; 4096, 2 48 / 49; 14336, 2 165 / 177, 8 168 / 177, 10 184 /
     // 177; but 8192, 2 113 / 84; q = 70: 2048, 6 36 / 36, 14336, 6 166 / 127)

@@ -605,7 +605,7 @@ hipError_t launch_one_ex(const void *X, int64_t rows, int64_t ldx, const float *
             // fine ratios lose (72 / 54, but 2 ratios 0.01 apart 47 / 55), nor shorter rows, for which the cells are too many (1792 42 /
             // 45, 1024 30 / 32, 512 34 / 38; 11 ratios 0.01 apart 35 / 54, 26 / 44, 29 / 63).  K = 32768 leaves no LDS beside the row.
             if constexpr (K == 7168 || K == 16384 || K == 28672) {
-                if (const int q = clip_grid_denominator(ex.grid, ex.n_grid); q > 0)
+                if (const int q = counted_fraction(ex); q > 0)
                     return launch_search<K, NTS, true>(X, rows, ldx, pre, post_scale, Q, scale_out, ex, q, st);
             }
             return launch_search<K, NTS, false>(X, rows, ldx, pre, post_scale, Q, scale_out, ex, 0, st);

@@ -8,8 +8,8 @@
 namespace sr {
 namespace {
 std::atomic<int64_t> g_tune[kTuneCount] = {
-    {kTuneAuto}, {kTuneAuto}, {kTuneAuto}, {kTuneAuto}, {kTuneAuto}, {kTuneAuto}, {kTuneAuto}};
-static_assert(kTuneCount == 7, "one initialiser per knob");
+    {kTuneAuto}, {kTuneAuto}, {kTuneAuto}, {kTuneAuto}, {kTuneAuto}, {kTuneAuto}, {kTuneAuto}, {kTuneAuto}};
+static_assert(kTuneCount == 8, "one initialiser per knob");
 }
 int64_t tune(int knob) { return g_tune[knob].load(std::memory_order_relaxed); }
 }  // namespace sr

@@ -67,7 +67,7 @@ __device__ __forceinline__ float max_of_wave(float v)
 // use them to run every kernel on every shape, tuning runs to compare variants inside one process.  A knob that
 // is not set (kTuneAuto) leaves the measured choice in place.  Relaxed atomics: a launch reads each knob once.
 enum { kTuneGemmTile = 0, kTuneGemmGrid, kTuneGemmXcdM, kTuneDecodeKernel, kTuneFwht4096, kTuneFwhtStream,
-       kTuneGemmWarm, kTuneCount };
+       kTuneGemmWarm, kTuneClipSearch, kTuneCount };
 constexpr int64_t kTuneAuto = INT64_MIN;
 int64_t tune(int knob);                                  // sr_api.hip
 inline bool tuned(int knob, int64_t &v) { v = tune(knob); return v != kTuneAuto; }
