@@ -50,3 +50,16 @@ def test_several_tiles_per_workgroup(gpu, tune, config, M, N, K):
     tune(gpu.SR_TUNE_GEMM_TILE, config)
     tune(gpu.SR_TUNE_GEMM_GRID, 8)
     compare(gpu, M, N, K)
+
+
+# the kernel for tile grids that divide among the XCDs is another than the one for grids cut into runs (all but one of those above)
+@pytest.mark.parametrize("config", TILES)
+@pytest.mark.parametrize("tiles_m,tiles_n,K", [(4, 8, 256), (8, 3, 768), (2, 12, 1280), (4, 8, 2304)])
+def test_several_tiles_per_workgroup_of_divided_grids(gpu, tune, config, tiles_m, tiles_n, K):
+    bm, bn = TILES[config]
+    assert (tiles_m % 2 == 0 and tiles_n % 4 == 0) or tiles_m % 8 == 0      # rectangles, and at least three tiles a workgroup
+    M, N = tiles_m * bm - 5, tiles_n * bn - 16
+    print("case divided", config, M, N, K, flush=True)
+    tune(gpu.SR_TUNE_GEMM_TILE, config)
+    tune(gpu.SR_TUNE_GEMM_GRID, 8)
+    compare(gpu, M, N, K)
