@@ -503,7 +503,7 @@ def main():
             extra["decode_M%d_4096x14336_whole_path" % Md] = {
                 "two_calls_us": round(t2 * 1e6, 2), "one_call_us": round(t1 * 1e6, 2), "GB/s": round(b / t1 / 1e9, 1),
                 "frac_hbm": round(b / t1 / 1e9 / PEAK_HBM_GBS, 4),
-                "launches_in_the_one_call": 1 if Md == 1 else 2}
+                "launches_in_the_one_call": 1 if Md <= 4 else 2}
         del copies
         # down-projection shape (config 3): K = 14336 = 28 * 512 -> N = 4096; rotation-only fold (s = 1)
         K3, N3 = 14336, 4096

@@ -23,7 +23,7 @@
  *    only enqueue work and return; they never synchronise.
  *  - Arguments are validated on the host before anything is launched.  On error a
  *    status is returned, nothing is launched and outputs are untouched.
- *  - Input and output buffers must not overlap.  Non-finite inputs give
+ *  - Input and output buffers must not overlap (one exception: sr_w4a4_linear_decode).  Non-finite inputs give
  *    unspecified values (never an out-of-bounds access).
  *  - X is [tokens, K] row-major fp16 (row = token, K = input channels);
  *    W is [K, N] row-major fp16 (N = output channels).
@@ -272,8 +272,12 @@ SR_API int sr_kv_quant_asym(const void *X_f16, int64_t rows, int64_t D, int64_t 
  * fp32 rotation (a code may sit on the other side of a rounding boundary).
  * With K = 2048 or 4096 one token, and two to four tokens up to the channel counts at which that wins, run as a
  * SINGLE launch (rotation, quantiser and GEMM in one kernel, every workgroup rotating the rows while its weights
- * travel; 4096 -> 14336: 6.7 us for one token, 8.6 against 9.5 us for four).  Every other shape runs the two kernels
+ * travel; 4096 -> 14336: 6.7 us for one token, 8.4 against 9.2 us for four with the weights in the memory-side cache;
+ * 7.3 against 9.0 and 8.6 against 9.8 us with the weights from HBM).  Every other shape runs the two kernels
  * back to back inside the call -- measured, no single launch beats that pair there (see csrc/linear_decode.hip).
+ * While a stream is being captured, two tokens, and K = 2048, take the single launch from 40 M weights on only: the
+ * GPU is done sooner with two small kernels and a replay costs the host nothing.  Either way the same outputs, bit
+ * for bit.
  *
  *   X_f16   fp16 [M, K], 1 <= M <= 16 (M = 0 is a no-op), row stride ldx
  *   K       2048, 4096, 8192 or 14336 (SR_ERR_UNSUPPORTED_K otherwise: use the two calls)
@@ -284,6 +288,8 @@ SR_API int sr_kv_quant_asym(const void *X_f16, int64_t rows, int64_t D, int64_t 
  *   workspace    sr_linear_decode_workspace_bytes(M, K) bytes, 256-byte aligned: the codes and scales between the
  *                two kernels (may be NULL where that is 0: one token of K <= 4096).  Contents need no
  *                initialisation; calls that share a workspace must not overlap.
+ * Y may lie over X for two tokens and more, and for any number with K = 8192 or 14336 (the row is read for good
+ * before the first output is written); not for one token with K = 2048 or 4096.
  */
 SR_API size_t sr_linear_decode_workspace_bytes(int64_t M, int64_t K);
 SR_API int sr_w4a4_linear_decode(const void *X_f16, int64_t M, int64_t K, int64_t ldx,

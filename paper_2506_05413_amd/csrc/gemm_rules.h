@@ -9,10 +9,10 @@
 //
 // The coefficients come from 2050 shapes (FP6: 2550, N from 16; M 8 or 17 .. 16384, N .. 28672, K 128 or 256 .. 14336, weights from HBM
 // and in the memory-side cache), every configuration timed on every shape: least squares, then adjusted so that the choices,
-// not the predictions, come out best.  On 400 further shapes the choice for packed nibbles is 1.0 % slower on average than
-// the fastest configuration of the shape, 17 % at worst (4.5 % and 51 % by the table before, which was fitted to K >= 2048
-// without the bytes of Y and with negative coefficients: 8192 x 14336 x 256 93 us for 70, 214 x 27376 x 512 15.3 for 11.0);
-// for FP6 1.1 % and 30 % (3.8 % and 72 %; 1062 x 8576 x 128 18.4 us for 6.9, 7448 x 24416 x 512 160 for 111).
+// not the predictions, come out best.  On 400 further shapes the choice for FP6 is 1.1 % slower on average than the fastest
+// configuration of the shape, 30 % at worst (3.8 % and 72 % by a table fitted to K >= 2048 without the bytes of Y and with negative
+// coefficients: 1062 x 8576 x 128 18.4 us for 6.9, 7448 x 24416 x 512 160 for 111).  The register kernels for packed nibbles were
+// fitted again later, to 675 shapes (below); on 500 others that table is 0.5 % behind the fastest, 14 % at worst.
 #pragma once
 
 #include <stdint.h>
@@ -150,7 +150,7 @@ constexpr bool f6_pairs_tails(int64_t tiles_m, int64_t tiles_n, int fm, int fn, 
 // equal length, one per XCD: without it every XCD asks for nearly all of both operands (FP6, M 100 .. 6000, 72 ragged grids:
 // 6.8 % faster on average; 762 x 24288 x 8192 143 -> 119 us, 390 x 7792 x 4096 18.4 -> 15.0, 5713 x 6512 x 4096 120 -> 105; packed
 // nibbles, 74 grids: 3.2 %; 2871 x 9392 x 2048 62.5 -> 57.9).
-// 0 = tile v is tile v of the grid, m fastest (by the knob only).
+// 0 = tile v is tile v of the grid, m fastest (by the knob, and for the 128 x 64 tiles of the FP6 kernel in place of runs).
 constexpr int kXcdRuns = -1;
 constexpr int choose_xcd_split(int tiles_m, int tiles_n, int BM, int BN)
 {

@@ -381,11 +381,20 @@ hipError_t launch_rows_units(const void *X, int64_t M, int64_t ldx, const float 
 
 // Whether the call goes through linear_decode_rows_kernel: 2 .. 4 tokens, as many channels as its registers hold at once -- for
 // two tokens fewer, because the dot-product kernel behind the token quantiser is ahead there (24576 channels 12.1 against
-// 12.5 us; 20480 the same).  Captured calls, which cost the host nothing when they run, with two tokens or K = 2048 only from 40 M
-// weights on: below, the GPU is done sooner with two small launches (graph of calls, 2 / 4 tokens: 2048 x 6144 5.4 / 5.7 against
-// 6.1 / 6.1 us, 4096 x 4096 6.5 / 6.6 against 6.9 / 6.6; but 2048 x 28672 8.9 / 9.3 against 8.2 / 8.1, 4096 x 14336 9.6 / 9.6
-// against 9.3 / 9.1; the linears of a layer, 4 tokens, 54.5 against 54.2).  Not where
-// an output overlaps the token rows, which other workgroups may still be reading.
+// 12.5 us; 20480 the same).
+//
+// Captured calls, which cost the host nothing when they run, with two tokens or K = 2048 only from 40 M weights on: below, the
+// GPU is done sooner with two small launches (graph of calls, 2 / 4 tokens: 2048 x 6144 5.4 / 5.7 against 6.1 / 6.1 us, 4096 x
+// 4096 6.5 / 6.6 against 6.9 / 6.6; but 2048 x 28672 8.9 / 9.3 against 8.2 / 8.1, 4096 x 14336 9.6 / 9.6 against 9.3 / 9.1; the
+// linears of a layer, 4 tokens, 54.5 against 54.2).
+// In a stream the launches follow each other as fast as the host makes them: 3.2 - 3.9 us a call with one, 4.9 - 6.5 with two from a
+// C program, 6 and 9 from Python.  So small calls wait for the host: 1024 .. 4096 channels of 2048, C 6.4 -> 5.5 .. 5.8 us a call for
+// two tokens, 6.6 -> 5.5 .. 5.8 for four, Python 8.7 -> 5.9; of 4096, C 6.5 .. 6.7 -> 6.0 .. 6.3 and 7.1 .. 7.4 -> 6.1 .. 6.4.  Behind
+// a stream that is never empty three and four tokens win or lose nothing (2048 x 4096, weights cached, 5.5 -> 5.7, from HBM 6.2 ->
+// 5.8; 4096 x 4096 6.9 -> 6.2 and 7.2 -> 6.7); two tokens lose with cached weights of up to 8192 channels of 2048 and 5120 of 4096
+// (5.2 -> 5.7 and 5.7 -> 6.2 at worst), with weights from HBM between -5 % (4096 x 3072) and + 8 %.
+//
+// Not where an output overlaps the token rows, which other workgroups may still be reading.
 bool rows_path(const void *X, int64_t M, int64_t K, int64_t ldx, int64_t N, const void *Y, int64_t ldy, const void *Xq_out, const void *xs_out,
                hipStream_t st)
 {
@@ -426,7 +435,7 @@ inline int pick_g(int64_t N, int gmax)
 bool linear_decode_supported(int64_t K) { return K == 2048 || K == 4096 || K == 8192 || K == 14336; }
 
 // one token and a power-of-two order up to 4096: ONE launch in which every workgroup rotates the row itself
-// (4096 -> 14336: 8.0 against 9.6 - 10.0 us for two launches; 4096 -> 4096: 5.0 against 6.5 us; K = 8192: 11.3 us
+// (4096 -> 14336, weights from HBM: 7.3 against 9.0 us for two launches; 4096 -> 4096: 5.0 against 6.5 us; K = 8192: 11.3 us
 // either way, so it takes the general path)
 static bool redundant_rotation_path(int64_t M, int64_t K) { return M == 1 && (K == 2048 || K == 4096); }
 

@@ -95,3 +95,17 @@ def test_one_launch_knob_leaves_the_gemm_alone(gpu, tune, M, K, N):
         Y.zero_()
         graph.replay()
         assert torch.equal(Y, want)
+
+
+@pytest.mark.parametrize("M,K", [(2, 2048), (3, 4096), (1, 8192), (4, 8192), (16, 4096)])
+def test_output_over_the_token_rows_of_other_calls(gpu, M, K):
+    """The same for the other calls that the header names: two tokens and more, any number of tokens of 8192."""
+    print("case decode over rows", M, K, flush=True)
+    X = torch.from_numpy(wl.cfg4_X(M, K)).cuda()
+    Wq = torch.from_numpy(np.random.default_rng(K).integers(0, 256, (K, K // 2), dtype=np.uint8)).cuda()
+    ws = torch.full((K,), 1e-3, device="cuda")
+    want = gpu.sr_w4a4_linear_decode(X, None, Wq, ws, 0.9)
+    for _ in range(10):
+        Y = X.clone()
+        gpu.sr_w4a4_linear_decode(Y, None, Wq, ws, 0.9, Y=Y)
+        assert torch.equal(Y, want)
