@@ -392,7 +392,7 @@ hipError_t launch_rows_units(const void *X, int64_t M, int64_t ldx, const float 
 // two tokens, 6.6 -> 5.5 .. 5.8 for four, Python 8.7 -> 5.9; of 4096, C 6.5 .. 6.7 -> 6.0 .. 6.3 and 7.1 .. 7.4 -> 6.1 .. 6.4.  Behind
 // a stream that is never empty three and four tokens win or lose nothing (2048 x 4096, weights cached, 5.5 -> 5.7, from HBM 6.2 ->
 // 5.8; 4096 x 4096 6.9 -> 6.2 and 7.2 -> 6.7); two tokens lose with cached weights of up to 8192 channels of 2048 and 5120 of 4096
-// (5.2 -> 5.7 and 5.7 -> 6.2 at worst), with weights from HBM between -5 % (4096 x 3072) and + 8 %.
+// (5.2 -> 5.7 and 5.7 -> 6.2 at worst); with weights from HBM they take from 5 % longer (4096 x 3072) to 11 % less.
 //
 // Not where an output overlaps the token rows, which other workgroups may still be reading.
 bool rows_path(const void *X, int64_t M, int64_t K, int64_t ldx, int64_t N, const void *Y, int64_t ldy, const void *Xq_out, const void *xs_out,
